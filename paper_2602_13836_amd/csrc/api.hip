@@ -53,6 +53,8 @@ hipError_t device_state(const DeviceState** out) {
             if (e != hipSuccess) return e;
             e = configure_union_lds();
             if (e != hipSuccess) return e;
+            e = configure_panel_lds();
+            if (e != hipSuccess) return e;
             void* p = nullptr;
             e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
             if (e != hipSuccess) return e;
@@ -119,7 +121,7 @@ SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) 
     w.total = w.radix_off + round256(sv::select_scratch_words(rows, V) * sizeof(uint32_t));
     w.bracket_off = w.s_off;
     if (sv::bracket_select_supported(dt, rows, V, k)) {
-        const size_t t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
+        const size_t t = w.bracket_off + round256(sv::bracket_scratch_words((int)(d_prime * esize_of(dt) / 16), rows, V) * sizeof(uint32_t));
         if (t > w.total) w.total = t;
     }
     return w;
@@ -268,6 +270,21 @@ int launch_down_projection(const void* h, int64_t rows, int64_t d, int64_t ldh, 
     return sv::launch_gemv(dt, g, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
+// the same product for the kernel that keeps the hidden rows in registers
+sv::PanelArgs panel_args(const sv::GemvArgs& g) {
+    sv::PanelArgs p{};
+    p.x = g.x;
+    p.x_row_bytes = g.x_row_bytes;
+    p.M = g.M;
+    p.m_row_bytes = g.m_row_bytes;
+    p.n_items = g.n_items;
+    p.chunks = g.chunks;
+    p.rows = g.rows;
+    p.out = g.out_f32;
+    p.out_row_stride = g.out_row_stride;
+    return p;
+}
+
 int check_select_shape(int64_t rows, int64_t d, int64_t V, int64_t k, int64_t d_prime, int dt) {
     if (!dtype_ok(dt)) return SV_ERR_DTYPE;
     if (rows < 1 || rows > kMaxRows || V < 1 || V > kMaxVocab || k < 1 || k > V) return SV_ERR_SHAPE;
@@ -290,6 +307,15 @@ int check_aux_shape(int64_t rows, int64_t d, int64_t V, int64_t d_prime, int dt)
     return SV_OK;
 }
 
+// Section 3.4 for a batch: the scores are made twice -- once for the rows' normalisers, once to be stored with them
+// subtracted -- instead of being written, read twice and written again.  Measured from 65 rows on, d' <= 256: 22 against
+// 24 us at 65 rows x 16384, 50 against 76 at 128 x 128256, 237 against 574 at 1024 x 151936.  Selectors of more than 256
+// elements run on panels of 256 hidden rows, which up to 128 rows leave half idle: 95 against 88 us at 100 rows x 128256
+// (the other way round from 256 rows on: 112 against 151).
+bool aux_twice(int dt, int chunks, int64_t rows, int64_t V) {
+    return sv::panel_supported(dt, chunks, rows, V) && (chunks <= 32 || rows > 128);
+}
+
 struct AuxWs {
     size_t hp_off, partial_off, total;
 };
@@ -297,7 +323,10 @@ AuxWs aux_ws(int64_t rows, int64_t V, int64_t d_prime, int dt) {
     AuxWs w;
     w.hp_off = 0;
     w.partial_off = round256((size_t)rows * (size_t)d_prime * (size_t)esize_of(dt));
-    w.total = w.partial_off + round256(sv::log_softmax_ws_floats(rows, V) * sizeof(float));
+    const int chunks = (int)(d_prime * esize_of(dt) / 16);
+    const size_t floats = aux_twice(dt, chunks, rows, V) ? sv::panel_log_softmax_ws_floats(chunks, rows, V)
+                                                                   : sv::log_softmax_ws_floats(rows, V);
+    w.total = w.partial_off + round256(floats * sizeof(float));
     return w;
 }
 
@@ -389,9 +418,13 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         uint32_t* bscratch = reinterpret_cast<uint32_t*>(base + w.bracket_off);
         int32_t* ids = nullptr;
         int64_t m = 0;
+        int log2_m = 0;
         float* samp = nullptr;
-        sv::bracket_sample(rows, V, bscratch, &ids, &m, &samp);
-        if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s, ids, m, V) != SV_OK)
+        const int chunks = (int)(d_prime * es / 16);
+        sv::bracket_sample(chunks, rows, V, bscratch, &ids, &m, &log2_m, &samp);
+        // (the kernel that keeps the hidden rows in registers works the sample's ids out itself)
+        const bool panel = sv::panel_supported(dt, chunks, rows, V);
+        if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s, ids, panel ? 0 : m, V) != SV_OK)
             return SV_ERR_HIP;
         sv::GemvArgs gs{};
         gs.x = hp;
@@ -400,16 +433,24 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         gs.m_row_bytes = d_prime * es;
         gs.idx = ids;
         gs.n_items = m;
-        gs.chunks = (int)(d_prime * es / 16);
+        gs.chunks = chunks;
         gs.rows = (int)rows;
         gs.out_f32 = samp;
         gs.out_row_stride = m;
-        const hipError_t e = rows > 64 ? sv::launch_tile_mfma(gs, s, true) : sv::launch_skinny_mfma(gs, s);
+        hipError_t e;
+        if (panel) {
+            sv::PanelArgs p = panel_args(gs);
+            p.spread_V = V;
+            p.spread_shift = log2_m;
+            e = sv::launch_panel_sample(p, s);
+        } else {
+            e = sv::launch_tile_mfma(gs, s, true);
+        }
         if (e != hipSuccess) return SV_ERR_HIP;
         sv::BracketArgs ba{};
         ba.hp = hp;
         ba.Wv = static_cast<const char*>(W_vocab);
-        ba.chunks = gs.chunks;
+        ba.chunks = chunks;
         ba.V = V;
         ba.rows = (int)rows;
         ba.k = k;
@@ -531,6 +572,8 @@ int specvocab_aux_log_softmax(const void* h, int64_t rows, int64_t d, int64_t ld
     g.rows = (int)rows;
     g.out_f32 = logq_out;
     g.out_row_stride = V;
+    if (aux_twice(dt, g.chunks, rows, V))
+        return sv::launch_panel_log_softmax(panel_args(g), partial, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
     st = launch_rows_product(dt, g, V, nullptr, 0, s);
     if (st != SV_OK) return st;
     if (sv::launch_log_softmax_rows(logq_out, V, (int)rows, partial, s) != hipSuccess) return SV_ERR_HIP;

@@ -1,0 +1,529 @@
+// Products with a SHORT reduction for many hidden rows (the selector's W_vocab h', Section 3.3 Step 1, for a batch,
+// and Section 3.4's distribution over the whole vocabulary):
+//     s[r, j] = < M[row(j), :], x[r, :] >      r < rows (more than 64), rows of M of at most 512 elements, bf16
+//
+// What bounds it.  With d' = 256 a 256 x 256 output tile is four 64-element slices of main loop: the tiled kernel spends
+// more time filling its pipeline, and in its epilogue, than multiplying (512 rows x 151936: 45 us of product of which
+// the matrix cores need 20, 85-97 us with the epilogue of the bracketed selection).  Here the hidden rows are STATIONARY:
+// a wavefront keeps the fragments of its 32 WM hidden rows for the whole reduction in registers (128 of them at
+// 64 rows x 256 elements), and a workgroup that owns a panel of TM = 32 WM GM hidden rows streams a long run of rows
+// of M past them, 64 (32) rows at a time, double buffered in LDS and requested two steps ahead.  A step is then
+// nothing but LDS reads of M's fragments (one per WM MFMAs), MFMAs and the epilogue; there is no prologue but the
+// first tile's, and one barrier per step.  The matrix is read once per panel (once in all up to 512 hidden rows).
+//
+// Where the epilogue reduces or selects along the rows of M (the two that store nothing), M is the MFMA's first operand:
+// a lane then holds 16 scores of ONE hidden row, whose bracket, running maximum and counters stay in its registers.
+// (Tried and not used: the two wavefronts of a SIMD half a step apart, so that one multiplies while the other is in its
+// epilogue, and a sub-tile's epilogue cut into pieces between the MFMAs of the next one: 103 and 92-95 us against 97 for
+// the sums of 1024 rows x 151936 -- the matrix cores alone take 65, at the clock their load leaves.)
+//
+// Measured (512 rows x 151936, d' = 256): the classifying product of the selection 97 us on the tiled kernel, 79 here --
+// of which 39 are the panel's start and MFMAs, 15 the comparisons, 5 the bit masks, 26 the candidates --, the whole
+// selection 166 -> 138; log-probabilities of 1024 rows x 151936 579 -> 237 us (sums 97, stored product 145 under a
+// profiler: 622 MB at 4.3 TB/s).
+//
+// The sums are the ones the tiled kernel makes (v_mfma_f32_32x32x16_bf16 over ascending k from zero), bit for bit.
+#include "sv_device.h"
+#include "sv_launch.h"
+
+#include <math.h>
+
+#include <type_traits>
+
+#include "tile_epilogue.h"
+
+namespace sv {
+
+namespace {
+
+constexpr int kXcds = 8;
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kGroups = 256;             // workgroups a launch is cut into (the CUs of the part)
+constexpr int kRunUnit = 64;             // a run is a multiple of this many rows of M
+
+// EPI_SAMPLE     row(j) = floor(j spread_V / 2^spread_shift), a sample of M's rows; the product is stored
+// EPI_LOGP       the product minus a value per hidden row (the normaliser of Section 3.4) is stored
+// EPI_LSE        only (maximum, sum of exponentials relative to it) per hidden row and run of rows of M
+// EPI_BRACKET    the bracketed selection's classification (see tile_mfma_kernels.hip)
+enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_BRACKET = 3 };
+
+template <int KS>
+constexpr int lds_row_bytes() { return KS * 32 + 16; }        // padded like the tiled kernel's rows: full read rate
+template <int KS>
+constexpr int step_items() { return KS > 16 ? 32 : 64; }      // rows of M per step
+template <int KS>
+constexpr size_t stage_bytes() { return (size_t)step_items<KS>() * lds_row_bytes<KS>(); }
+template <int KS>
+constexpr int fill_rows() { return KS > 16 ? 16 : 32; }       // hidden rows a wavefront fetches through LDS at a time
+template <int KS, int WM, int GM, int EPI>
+constexpr size_t panel_lds_bytes() {
+    size_t n = 2 * stage_bytes<KS>();
+    if (EPI == EPI_BRACKET) n += (size_t)kWaves * WM * 4096 + (size_t)32 * WM * GM * 4;      // a sub-tile's scores, counters
+    if (EPI == EPI_LOGP) n += (size_t)32 * WM * GM * 4;
+    const size_t fill = (size_t)kWaves * fill_rows<KS>() * lds_row_bytes<KS>();
+    return n > fill ? n : fill;
+}
+
+// KS 16-element steps of the reduction are held (rows of M of up to 16 KS elements), WM groups of 32 hidden rows per
+// wavefront, GM wavefronts along the panel; the other 8 / GM share the step's rows of M.
+template <int KS, int WM, int GM, int EPI>
+__global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a) {
+    constexpr int GI = kWaves / GM;                      // wavefronts along the rows of M
+    constexpr int kTI = step_items<KS>();
+    constexpr int SUB = kTI / (32 * GI);                 // 32-row sub-tiles per wavefront and step
+    constexpr int TM = 32 * WM * GM;
+    constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_BRACKET;               // M is the MFMA's first operand
+    constexpr int kRowB = lds_row_bytes<KS>();
+    constexpr int kUnits = 2 * KS;                       // 16-byte units of a staged row
+    constexpr int Q = kTI * kUnits / kThreads;           // ... per thread and step
+    static_assert(kTI * kUnits % kThreads == 0 && kTI % (32 * GI) == 0, "whole loader passes, whole sub-tiles");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [2][kTI][kRowB], then the epilogue's
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gm = wave % GM, gi = wave / GM;
+    const int C = a.chunks;
+    // block id -> (XCD, slot on that XCD); consecutive slots of one XCD: the panels of one run of rows of M
+    const int RT = (a.rows + TM - 1) / TM;
+    const int slot = (int)(blockIdx.x / kXcds);
+    const int panel = slot % RT;
+    const int run = slot / RT * kXcds + (int)(blockIdx.x % kXcds);
+    const int n_items = (int)a.n_items, run_items = (int)a.run_items;        // (below 2^22: panel_supported)
+    if (run >= (n_items + run_items - 1) / run_items) return;
+    const int i0 = run * run_items;
+    const int i1 = i0 + run_items < n_items ? i0 + run_items : n_items;
+    const int nt = (i1 - i0 + kTI - 1) / kTI;
+
+    // loader: consecutive threads on consecutive 16-byte units of a row (units past its end: the last one again,
+    // zeroed on the way into LDS; rows past the run: the run's last row again, never used)
+    // (branch-free, from one uniform address: a load inside a condition makes the compiler wait for everything in flight)
+    u32x4 stage[Q];
+    const char* m_base = EPI == EPI_SAMPLE ? a.M : a.M + (int64_t)i0 * a.m_row_bytes;
+    const uint32_t m_row_bytes = (uint32_t)a.m_row_bytes;                    // n_items * m_row_bytes < 2^32: panel_supported
+    auto request = [&](int t) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int p = q * kThreads + tid;
+            const int u = p % kUnits;
+            uint32_t row = (uint32_t)min(t * kTI + p / kUnits, i1 - i0 - 1);
+            if constexpr (EPI == EPI_SAMPLE) row = (uint32_t)(((uint64_t)(row + (uint32_t)i0) * (uint64_t)a.spread_V) >> a.spread_shift);
+            stage[q] = *reinterpret_cast<const u32x4*>(m_base + (row * m_row_bytes + (uint32_t)(u < C ? u : C - 1) * 16u));
+        }
+    };
+    auto put = [&](int t) {
+        unsigned char* base = smem + (size_t)(t & 1) * stage_bytes<KS>();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int p = q * kThreads + tid;
+            *reinterpret_cast<u32x4*>(base + (p / kUnits) * kRowB + (p % kUnits) * 16) = p % kUnits < C ? stage[q] : zero16();
+        }
+    };
+    request(0);
+
+    // This wavefront's hidden rows: lane = (row within a group of 32, k-group), like every operand of the MFMA.  They come
+    // through LDS (a part of all of it per wavefront, before the first stage is filled): whole rows per load instruction,
+    // where the operand's own shape, 32 bytes of 32 rows, took 15 us for the 256 KB of a panel.
+    const int row_w = panel * TM + gm * 32 * WM;         // first hidden row of the wavefront
+    bf16x8_t fx[WM][KS];
+    {
+        constexpr int kRows = fill_rows<KS>();           // rows per round
+        constexpr int kLoads = kRows * kUnits / 64;
+        unsigned char* s_fill = smem + (size_t)wave * kRows * kRowB;
+#pragma unroll
+        for (int m = 0; m < WM; ++m)
+#pragma unroll
+            for (int part = 0; part < 32 / kRows; ++part) {
+                u32x4 v[kLoads];
+#pragma unroll
+                for (int q = 0; q < kLoads; ++q) {
+                    const int p = q * 64 + lane, u = p % kUnits;
+                    const int row = min(row_w + 32 * m + kRows * part + p / kUnits, a.rows - 1);   // padding rows: never stored
+                    v[q] = reinterpret_cast<const u32x4*>(a.x + (int64_t)row * a.x_row_bytes)[u < C ? u : C - 1];
+                }
+#pragma unroll
+                for (int q = 0; q < kLoads; ++q) {
+                    const int p = q * 64 + lane, u = p % kUnits;
+                    *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kRowB + u * 16) = u < C ? v[q] : zero16();
+                }
+                // (a wavefront's own LDS accesses stay in order)
+                if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
+#pragma unroll
+                    for (int kk = 0; kk < KS; ++kk)
+                        fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
+                                                                     s_fill + ((lane & 31) % kRows) * kRowB + (lane >> 5) * 16 + kk * 32));
+                }
+            }
+        __syncthreads();                                 // the fill regions are the stages from here on
+    }
+
+    // ---- per-workgroup state of the epilogues, behind the two stages
+    unsigned char* s_epi = smem + 2 * stage_bytes<KS>();
+    [[maybe_unused]] f32x4_t* s_dump = reinterpret_cast<f32x4_t*>(s_epi) + (size_t)wave * (WM * 4 * 64);   // EPI_BRACKET: scores
+    [[maybe_unused]] float* s_sub = reinterpret_cast<float*>(s_epi);          // EPI_LOGP: [TM]
+    const int half = lane >> 5;
+    // EPI_BRACKET, of hidden row row_w + 32 m + lane % 32: the bracket, and how many candidates the run has so far
+    [[maybe_unused]] float thr_hi[WM], thr_lo[WM];
+    [[maybe_unused]] uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_epi + (size_t)kWaves * WM * 4096);
+    if constexpr (EPI == EPI_BRACKET) {
+        for (int t = tid; t < TM; t += kThreads) s_cnt[t] = 0u;
+#pragma unroll
+        for (int m = 0; m < WM; ++m) {
+            const int row = row_w + 32 * m + (lane & 31);
+            const float2 t = reinterpret_cast<const float2*>(a.bracket.thr)[min(row, a.rows - 1)];
+            // rows past the end: no score is above +inf, none compares with NaN
+            thr_hi[m] = row < a.rows ? t.x : INFINITY;
+            thr_lo[m] = row < a.rows ? t.y : __builtin_nanf("");
+        }
+    }
+    if constexpr (EPI == EPI_LOGP) {
+        for (int t = tid; t < TM; t += kThreads) s_sub[t] = panel * TM + t < a.rows ? a.row_sub[panel * TM + t] : 0.0f;
+    }
+    float run_max[WM], run_sum[WM];                      // EPI_LSE: of hidden row row_w + 32 m + lane % 32
+#pragma unroll
+    for (int m = 0; m < WM; ++m) {
+        run_max[m] = -INFINITY;
+        run_sum[m] = 0.0f;
+    }
+
+    f32x16_t acc[WM];
+    const int b_lane = (lane & 31) * kRowB + (lane >> 5) * 16;
+    auto multiply = [&](int t, int s) {
+        const unsigned char* sb = smem + (size_t)(t & 1) * stage_bytes<KS>() + (size_t)((gi * SUB + s) * 32) * kRowB + b_lane;
+#pragma unroll
+        for (int m = 0; m < WM; ++m)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[m][e] = 0.f;
+        // M's fragments are read four 16-element steps ahead of their MFMAs; the fence keeps the compiler from reading all
+        // of them first (registers)
+        constexpr int kAhead = 4;
+        static_assert(KS % kAhead == 0, "whole groups of steps");
+        bf16x8_t fb[2][kAhead];
+        auto read = [&](int g, bf16x8_t (&b)[kAhead]) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                b[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(sb + (g * kAhead + i) * 32));
+        };
+        read(0, fb[0]);
+#pragma unroll
+        for (int g = 0; g < KS / kAhead; ++g) {
+            if (g + 1 < KS / kAhead) read(g + 1, fb[(g + 1) & 1]);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int m = 0; m < WM; ++m) {
+                    const bf16x8_t b = fb[g & 1][i], x = fx[m][g * kAhead + i];
+                    if constexpr (kSwap) acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, x, acc[m], 0, 0, 0);
+                    else acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b, acc[m], 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // first row of M of the wavefront's sub-tile s of step t
+    auto item_of = [&](int t, int s) { return i0 + t * kTI + (gi * SUB + s) * 32; };
+
+    // EPI_BRACKET: the candidate lists of the lane's hidden rows, one per (row, run)
+    [[maybe_unused]] const uint32_t fcap = (uint32_t)a.bracket.first_cap;
+    [[maybe_unused]] const uint32_t lists = (uint32_t)a.bracket.item_tiles;
+    [[maybe_unused]] const uint32_t list0 = (uint32_t)(row_w + (lane & 31)) * lists + (uint32_t)run;
+    [[maybe_unused]] const uint32_t list_step = 32u * lists;
+    [[maybe_unused]] uint32_t word_even = 0u;            // the bits of the step's first sub-tile
+    auto epilogue = [&](int t, int s) {
+        const int j0 = item_of(t, s);
+        if constexpr (EPI == EPI_SAMPLE || EPI == EPI_LOGP) {
+            // element e: hidden row 8 (e / 4) + 4 (lane / 32) + e % 4, item lane % 32: two 128-byte runs per store, at a
+            // wavefront-uniform address plus a lane's offset that never changes
+            int64_t stride = a.out_row_stride;
+            asm volatile("" : "+s"(stride));             // the rows' addresses are made here, not kept in registers
+            const uint32_t lane_off = (uint32_t)(4 * half * (int)stride + (lane & 31)) * 4u;
+            auto store_all = [&](auto whole) {
+#pragma unroll
+                for (int m = 0; m < WM; ++m)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        f32x4_t sub = {0.f, 0.f, 0.f, 0.f};
+                        if constexpr (EPI == EPI_LOGP)
+                            sub = *reinterpret_cast<const f32x4_t*>(s_sub + gm * 32 * WM + 32 * m + 8 * q4 + 4 * half);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int r = row_w + 32 * m + 8 * q4 + e;
+                            char* o = reinterpret_cast<char*>(a.out + (int64_t)r * stride + j0) + lane_off;
+                            float v = acc[m][4 * q4 + e];
+                            if constexpr (EPI == EPI_LOGP) v -= sub[e];
+                            if (decltype(whole)::value || (j0 + (lane & 31) < i1 && r + 4 * half < a.rows)) *reinterpret_cast<float*>(o) = v;
+                        }
+                    }
+            };
+            if (row_w + 32 * WM <= a.rows && j0 + 32 <= i1) store_all(std::true_type{});     // uniform
+            else store_all(std::false_type{});
+        }
+        if constexpr (EPI == EPI_LSE) {
+            // element e of acc[m]: hidden row 32 m + lane % 32, item 8 (e / 4) + 4 (lane / 32) + e % 4
+            if (j0 + 32 > i1) {
+                int left = i1 - j0 - 4 * (lane >> 5);
+                asm volatile("" : "+v"(left));           // the comparisons stay inside this rare branch
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (8 * (e >> 2) + (e & 3) >= left) {
+#pragma unroll
+                        for (int m = 0; m < WM; ++m) acc[m][e] = -INFINITY;
+                    }
+            }
+#pragma unroll
+            for (int m = 0; m < WM; ++m) {
+                float mx = acc[m][0];
+#pragma unroll
+                for (int e = 1; e < 16; ++e) mx = fmaxf(mx, acc[m][e]);
+                mx = fmaxf(mx, run_max[m]);
+                const float ref = mx == -INFINITY ? 0.0f : mx;              // nothing seen yet
+                float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 16; ++e) p[e & 3] += __expf(acc[m][e] - ref);
+                run_sum[m] = run_sum[m] * __expf(run_max[m] - ref) + ((p[0] + p[1]) + (p[2] + p[3]));
+                run_max[m] = mx;
+            }
+        }
+        if constexpr (EPI == EPI_BRACKET) {
+            // element e of acc[m]: hidden row 32 m + lane % 32, item 8 (e / 4) + 4 (lane / 32) + e % 4.  Per score two
+            // comparisons, each shifted into a word per lane by an add whose carry-in is the comparison's mask.
+            static_assert(WM <= 2, "the band bits of a lane are one word");
+            if (j0 + 32 > i1) {                          // items past the run compare false with everything
+                int left = i1 - j0 - 4 * half;
+                asm volatile("" : "+v"(left));
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+#pragma unroll
+                    for (int m = 0; m < WM; ++m) acc[m][e] = 8 * (e >> 2) + (e & 3) >= left ? __builtin_nanf("") : acc[m][e];
+            }
+            uint32_t above[WM], inside = 0u;             // bit 15 - e: above hi; bit 31 - 16 m - e: inside the bracket
+#pragma unroll
+            for (int m = 0; m < WM; ++m) {
+                uint32_t up = 0u, in = 0u;
+#pragma unroll
+                for (int e = 15; e >= 0; --e) {          // (e = 15 first: it ends in the highest bit)
+                    up = 2u * up + (acc[m][e] > thr_hi[m] ? 1u : 0u);
+                    in = 2u * in + (acc[m][e] >= thr_lo[m] ? 1u : 0u);
+                }
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    s_dump[(m * 4 + q4) * 64 + lane] = f32x4_t{acc[m][4 * q4], acc[m][4 * q4 + 1], acc[m][4 * q4 + 2], acc[m][4 * q4 + 3]};
+                above[m] = up;                           // bit e
+                inside |= (in & ~up) << (16 * m);        // bit 16 m + e
+            }
+            // the lane's scores inside a bracket (about one) are taken out, up to four per round
+            while (__builtin_amdgcn_ballot_w64(inside != 0u)) {
+                constexpr int kPer = 4;
+                int q[kPer];
+                bool has[kPer];
+                float f[kPer];
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    has[u] = inside != 0u;
+                    q[u] = has[u] ? __ffs((int)inside) - 1 : 0;                  // 16 m + e
+                    inside &= inside - 1u;                                       // (0 stays 0)
+                    f[u] = reinterpret_cast<const float*>(s_dump)[((q[u] >> 2) * 64 + lane) * 4 + (q[u] & 3)];
+                }
+                uint32_t at[kPer];
+#pragma unroll
+                for (int u = 0; u < kPer; ++u)
+                    at[u] = has[u] ? atomicAdd(&s_cnt[gm * 32 * WM + 32 * (q[u] >> 4) + (lane & 31)], 1u) : 0u;   // < run_items
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    if (has[u]) {
+                        const int m = WM == 1 ? 0 : q[u] >> 4, e = q[u] & 15;
+                        const uint32_t list = list0 + (m == 0 ? 0u : list_step);
+                        const uint32_t item = (uint32_t)(j0 + 8 * (e >> 2) + 4 * half + (e & 3));
+                        uint64_t* dst = at[u] < fcap ? a.bracket.cand_first + ((uint64_t)list * fcap + at[u])
+                                                     : a.bracket.cand + ((uint64_t)list * (uint32_t)a.bracket.over_cap + (at[u] - fcap));
+                        *dst = ((uint64_t)f32_to_ord(f[u]) << 32) | (uint32_t)(~item);
+                    }
+                }
+            }
+            // The words of the bit masks: a lane has the bits of items 4 half + {0..3}, 8 + .., 16 + .., 24 + ..; spread to
+            // those places and joined with the other half's.  Lanes 0..31 then store the word of their first hidden row,
+            // lanes 32..63 that of the second, two sub-tiles at a time where a step has two.
+            uint32_t word = 0u;
+#pragma unroll
+            for (int m = 0; m < WM; ++m) {
+                uint32_t x = above[m];
+                x = (x | (x << 8)) & 0x00FF00FFu;
+                x = ((x | (x << 4)) & 0x0F0F0F0Fu) << (4 * half);
+                x |= (uint32_t)__shfl_xor((int)x, 32);
+                if (WM == 1 || m == half) word = x;
+            }
+            const int brow = row_w + (WM == 1 ? lane & 31 : lane);
+            const bool bok = brow < a.rows && (WM == 2 || half == 0);
+            if constexpr (SUB == 2) {
+                if (s == 0) word_even = word;
+                if (s == 1 && bok) {
+                    uint32_t* o = a.bracket.bits + (int64_t)brow * a.bracket.words_per_row + (j0 - 32) / 32;
+                    *reinterpret_cast<uint2*>(o) = uint2{word_even, word};
+                }
+            } else {
+                if (bok) a.bracket.bits[(int64_t)brow * a.bracket.words_per_row + j0 / 32] = word;
+            }
+        }
+    };
+
+    // LDS is complete, and the other stage free, at this barrier; loads and stores to memory stay in flight
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    put(0);
+    request(1);
+    barrier();
+    for (int t = 0; t < nt; ++t) {
+        // stage t + 1 (read last in step t - 1, before the barrier) is filled, then its registers are requested again:
+        // in flight for a whole step
+        put(t + 1);
+        request(t + 2);
+#pragma unroll 1
+        for (int s = 0; s < SUB; ++s) {
+            multiply(t, s);
+            epilogue(t, s);
+        }
+        barrier();
+    }
+
+    if constexpr (EPI == EPI_LSE) {
+        // lanes l and l + 32 hold the same hidden row; one pair per hidden row, run and wavefront along the rows of M
+#pragma unroll
+        for (int m = 0; m < WM; ++m) {
+            const float om = __shfl_xor(run_max[m], 32), os = __shfl_xor(run_sum[m], 32);
+            const float mx = fmaxf(run_max[m], om), ref = mx == -INFINITY ? 0.0f : mx;
+            const float sum = run_sum[m] * __expf(run_max[m] - ref) + os * __expf(om - ref);
+            const int row = row_w + 32 * m + lane;
+            if (lane < 32 && row < a.rows)
+                reinterpret_cast<float2*>(a.partial)[(int64_t)row * a.partial_stride + run * GI + gi] = float2{mx, sum};
+        }
+    }
+    if constexpr (EPI == EPI_BRACKET) {
+        // words past the last step (of the last run) name no item
+        const int tail0 = nt * (kTI / 32), tail = run_items / 32 - tail0;
+        for (int w = tid; w < tail * TM; w += kThreads) {
+            const int row = panel * TM + w / tail;
+            if (row < a.rows) a.bracket.bits[(int64_t)row * a.bracket.words_per_row + i0 / 32 + tail0 + w % tail] = 0u;
+        }
+        __syncthreads();                                 // all candidates of the run are counted
+        for (int t = tid; t < TM; t += kThreads)
+            if (panel * TM + t < a.rows) a.bracket.cnt[(int64_t)(panel * TM + t) * lists + run] = s_cnt[t];
+    }
+}
+
+// lse[r] = log of the sum of exponentials behind a row's `n` (maximum, sum) pairs: one wavefront per hidden row
+__global__ __launch_bounds__(256) void lse_fold_kernel(const float2* partial, int n, int rows, float* lse) {
+    const int lane = threadIdx.x & 63;
+    const int row = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (row >= rows) return;
+    const float2* p = partial + (int64_t)row * n;
+    float mx = -INFINITY;
+    for (int i = lane; i < n; i += 64) mx = fmaxf(mx, p[i].x);
+    mx = wave_max_f32(mx);
+    float sum = 0.0f;
+    for (int i = lane; i < n; i += 64) sum += p[i].y * __expf(p[i].x - mx);
+    sum = wave_sum(sum);
+    if (lane == 0) lse[row] = mx + logf(sum);
+}
+
+// The instance for a shape, as an index: hidden rows per panel and steps held.
+//   0  d' <= 256, panels of 512 (64 rows per wavefront)     1  ... of 256     2  ... of 128 (32 rows per wavefront)
+//   3  d' <= 512, panels of 256 (32 rows per wavefront)
+struct Shape { int panel, gi; };
+constexpr Shape kShapes[4] = {{512, 1}, {256, 2}, {128, 2}, {256, 1}};
+inline int shape_of(int chunks, int rows) {
+    if (chunks > 32) return 3;
+    if (rows <= 128) return 2;
+    const int pad256 = (rows + 255) / 256, pad512 = (rows + 511) / 512;
+    return 2 * pad512 == pad256 ? 0 : 1;                 // no panel half idle
+}
+template <int EPI, typename F>
+hipError_t with_shape(int shape, F&& f) {
+    switch (shape) {
+        case 0: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+        case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+        case 2: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+        default: return f(std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+    }
+}
+
+PanelRuns runs_of(int shape, int64_t rows, int64_t n_items) {
+    const int64_t panels = (rows + kShapes[shape].panel - 1) / kShapes[shape].panel;
+    const int64_t groups = panels < kGroups ? kGroups / panels : 1;
+    PanelRuns r;
+    r.items = ((n_items + groups - 1) / groups + kRunUnit - 1) / kRunUnit * kRunUnit;
+    r.runs = (n_items + r.items - 1) / r.items;
+    return r;
+}
+
+template <int EPI>
+hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
+    PanelArgs a = a0;
+    // A sample of a few thousand rows of M is over in one or two steps and costs what fetching the hidden rows costs:
+    // small panels (512 rows, 8192 of them: 10.8 us on panels of 128 against 14.0 on panels of 512).
+    const int shape = EPI == EPI_SAMPLE && a.chunks <= 32 ? 2 : shape_of(a.chunks, a.rows);
+    const PanelRuns pr = runs_of(shape, a.rows, a.n_items);
+    a.run_items = pr.items;
+    a.partial_stride = pr.runs * kShapes[shape].gi;
+    const int64_t RT = (a.rows + kShapes[shape].panel - 1) / kShapes[shape].panel;
+    const int64_t bx = (pr.runs + kXcds - 1) / kXcds * kXcds * RT;
+    if (bx > 0x7fffffffLL) return hipErrorInvalidValue;
+    return with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
+        constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
+        hipLaunchKernelGGL((panel_mfma_kernel<KS, WM, GM, EPI>), dim3((unsigned)bx), dim3(kThreads),
+                           (panel_lds_bytes<KS, WM, GM, EPI>()), stream, a);
+        return hipGetLastError();
+    });
+}
+
+template <int EPI>
+hipError_t opt_in_epi() {
+    for (int shape = 0; shape < 4; ++shape) {
+        const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
+            constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
+            static_assert(panel_lds_bytes<KS, WM, GM, EPI>() <= 160 * 1024, "one workgroup per CU");
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_mfma_kernel<KS, WM, GM, EPI>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)panel_lds_bytes<KS, WM, GM, EPI>());
+        });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t configure_panel_lds() {
+    hipError_t e = opt_in_epi<EPI_SAMPLE>();
+    if (e == hipSuccess) e = opt_in_epi<EPI_LOGP>();
+    if (e == hipSuccess) e = opt_in_epi<EPI_LSE>();
+    if (e == hipSuccess) e = opt_in_epi<EPI_BRACKET>();
+    return e;
+}
+
+bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
+    return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);
+}
+
+
+PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items) { return runs_of(shape_of(chunks, (int)rows), rows, n_items); }
+
+hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_SAMPLE>(a, stream); }
+hipError_t launch_panel_bracket(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_BRACKET>(a, stream); }
+
+size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V) {
+    const int64_t pairs = panel_runs(chunks, rows, V).runs * kShapes[shape_of(chunks, (int)rows)].gi;
+    return (size_t)rows * (size_t)(2 * pairs + 1);
+}
+
+hipError_t launch_panel_log_softmax(const PanelArgs& a0, float* ws, hipStream_t stream) {
+    PanelArgs a = a0;
+    const int64_t pairs = panel_runs(a.chunks, a.rows, a.n_items).runs * kShapes[shape_of(a.chunks, a.rows)].gi;
+    float* lse = ws + (size_t)a.rows * (size_t)pairs * 2;
+    a.partial = ws;
+    hipError_t e = launch_epi<EPI_LSE>(a, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(lse_fold_kernel, dim3((unsigned)((a.rows + 3) / 4)), dim3(256), 0, stream,
+                       reinterpret_cast<const float2*>(ws), (int)pairs, a.rows, lse);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.row_sub = lse;
+    return launch_epi<EPI_LOGP>(a, stream);
+}
+
+}  // namespace sv

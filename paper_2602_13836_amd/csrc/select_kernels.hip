@@ -770,20 +770,24 @@ __global__ __launch_bounds__(kRowThreads) void emit_rows_kernel(const float* s_a
 struct BracketLayout {
     int64_t V;
     int rows;
-    int tn;              // items per tile of the classify pass
+    int tn;              // items per tile (run) of the classify pass
+    int first;           // candidates of a (row, tile) that live in the compact array
     int64_t tiles;       // item tiles per row
     int64_t words;       // bit-mask words per row
     int64_t m;           // sample size
     int64_t nb;          // 4096-id vocabulary blocks (the redo path)
     // offsets in uint32 words from the scratch base (all multiples of 4: 16-byte aligned)
-    size_t ids, samp, thr, flag, bits, cnt, sure, boff, state, first, cand, total;
+    size_t ids, samp, thr, flag, bits, cnt, sure, boff, state, cand_first, cand, total;
 };
 __host__ __device__ inline size_t quad4(size_t n) { return (n + 3) & ~(size_t)3; }
+// (a bracket holds 3.2 % of a row's scores at k / V = 1/18 and at most 7 %: a compact list of a sixteenth of its items
+// and six more overflows for one list in thousands in the former case; the latter pays a second round trip)
 __host__ __device__ inline BracketLayout bracket_layout(int64_t V, int rows, int tn, int64_t m) {
     BracketLayout L;
     L.V = V;
     L.rows = rows;
     L.tn = tn;
+    L.first = (tn / 16 + 7) & ~1;
     L.tiles = (V + tn - 1) / tn;
     L.words = L.tiles * (tn / 32);
     L.m = m;
@@ -798,8 +802,8 @@ __host__ __device__ inline BracketLayout bracket_layout(int64_t V, int rows, int
     L.sure = o;   o += quad4((size_t)rows * L.nb);
     L.boff = o;   o += quad4((size_t)rows * L.nb);
     L.state = o;  o += (size_t)rows * 8;
-    L.first = o;  o += (size_t)rows * L.tiles * kCandFirst * 2;
-    L.cand = o;   o += (size_t)rows * L.tiles * tn * 2;
+    L.cand_first = o;  o += quad4((size_t)rows * L.tiles * L.first * 2);
+    L.cand = o;   o += (size_t)rows * L.tiles * tn * 2;      // (the redo of a row needs V slots)
     L.total = o;
     return L;
 }
@@ -987,18 +991,15 @@ __device__ __forceinline__ void redo_row(const char* hp_row, const char* Wv, int
 // One workgroup of 256 threads per row (small workgroups: several rows per CU overlap their memory round trips
 // and barriers are cheap): see the overview above.  The row's bit mask lives in LDS from the first step to
 // the last, so the selected candidates join it there and the ids are written from it.
-// Dynamic LDS: [words] bit mask | [cand_cap] candidates (8 bytes each).
+// Dynamic LDS: [words] bit mask | [tiles + 1] first place of every tile's candidates | [cand_cap] candidates (8 bytes each).
 // A row with at most cand_cap candidates packs them into LDS once and every later walk reads that dense list
-// (a few balanced iterations per thread); a row with more (ties by the thousand) walks the registers and the
-// memory regions instead.
-constexpr int kRbTiles = 4;                              // item tiles per thread whose candidates are held in registers
-constexpr int kRbSpec = kCandFirst;                      // ... candidates per such tile: the compact array (mean 8, 99th
-                                                         // percentile 16 at the usual shapes); the rest are re-read
+// (a few balanced iterations per thread); a row with more (ties by the thousand) walks the memory regions instead.
 constexpr int kRbBins = 2048;
 constexpr int kRbBitBatch = 24;                          // words of the bit mask per thread requested at once
+constexpr int kRbCandBatch = 22;                         // pairs of candidate slots per thread requested at once
 // dynamic LDS of a resolve workgroup: with its 9 KB of static LDS two of them share a CU's 160 KB (a launch
 // of 512 rows is then one round of workgroups on 256 CUs)
-constexpr size_t kResolveLdsBytes = 69 * 1024;
+constexpr size_t kResolveLdsBytes = 69 * 1024, kResolveMaxLdsBytes = 148 * 1024;
 struct ResolveEmitSmem {
     uint32_t hist[kRbBins];
     uint32_t w[kRbWaves];
@@ -1007,45 +1008,47 @@ struct ResolveEmitSmem {
     uint32_t nfew;
     uint32_t tot[kRbWaves];
 };
+__host__ __device__ inline int64_t resolve_off_words(int64_t tiles) { return (tiles + 2) & ~(int64_t)1; }
 
+// first_magic: 2^32 / (first / 2), rounded up (a slot pair's tile by one multiplication: pair number * (first / 2) stays
+// below 2^32)
 __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int rows, int tn, int64_t m, int64_t k,
                                                                   uint32_t* scratch, int32_t* idx_out,
-                                                                  uint32_t cand_cap) {
-    extern __shared__ __attribute__((aligned(16))) uint32_t s_bits[];         // [words], then the candidate list
+                                                                  uint32_t cand_cap, uint32_t first_magic) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_bits[];         // [words], offsets, then the candidate list
     __shared__ ResolveEmitSmem sm;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int64_t r = blockIdx.x;
     const BracketLayout L = bracket_layout(V, rows, tn, m);
-    uint64_t* s_cand = reinterpret_cast<uint64_t*>(s_bits + L.words);         // words is a multiple of 4
+    const int T = (int)L.tiles, F = L.first;
+    uint32_t* s_off = s_bits + L.words;                                       // words is even
+    uint64_t* s_cand = reinterpret_cast<uint64_t*>(s_off + resolve_off_words(T));
     const uint32_t* bits = scratch + L.bits + (size_t)r * L.words;
     const uint32_t* cnt = scratch + L.cnt + (size_t)r * L.tiles;
     const uint64_t* cand = reinterpret_cast<const uint64_t*>(scratch + L.cand) + (size_t)r * L.tiles * tn;
-    const uint64_t* first = reinterpret_cast<const uint64_t*>(scratch + L.first) + (size_t)r * L.tiles * kCandFirst;
+    const uint64_t* first = reinterpret_cast<const uint64_t*>(scratch + L.cand_first) + (size_t)r * L.tiles * F;
     // everything independent is requested up front, in the order of use: the bracket, the candidate counts of
-    // this thread's tiles, the first words of the bit mask, the first candidates of each tile (before their
-    // count is known)
+    // this thread's tiles, the first words of the bit mask, the first slots of the compact candidate array (before it
+    // is known which of them are filled)
     const float hi = reinterpret_cast<const float*>(scratch + L.thr)[2 * r];
     const float lo = reinterpret_cast<const float*>(scratch + L.thr)[2 * r + 1];
-    uint32_t tc[kRbTiles];
-#pragma unroll
-    for (int j = 0; j < kRbTiles; ++j) {
-        const int64_t t = tid + (int64_t)j * kRbThreads;
-        tc[j] = t < L.tiles ? cnt[t] : 0u;
-    }
+    const int per = (T + kRbThreads - 1) / kRbThreads;                        // consecutive tiles of this thread
+    const int t0 = tid * per < T ? tid * per : T, t1 = t0 + per < T ? t0 + per : T;
+    uint32_t band_mine = t0 < t1 ? cnt[t0] : 0u;
     uint32_t wv[kRbBitBatch];
 #pragma unroll
     for (int u = 0; u < kRbBitBatch; ++u) {
         const int64_t w = (int64_t)u * kRbThreads + tid;
         wv[u] = bits[w < L.words ? w : L.words - 1];
     }
-    uint64_t reg[kRbTiles][kRbSpec];
+    const uint32_t pairs_total = (uint32_t)T * (uint32_t)(F / 2);             // slots two at a time (F is even)
+    const u32x4* first2 = reinterpret_cast<const u32x4*>(first);
+    u32x4 reg[kRbCandBatch];
 #pragma unroll
-    for (int j = 0; j < kRbTiles; ++j) {
-        const int64_t t = tid + (int64_t)j * kRbThreads;
-        const uint64_t* p = first + (t < L.tiles ? t : 0) * (int64_t)kCandFirst;
-#pragma unroll
-        for (int i = 0; i < kRbSpec; ++i) reg[j][i] = p[i];
+    for (int u = 0; u < kRbCandBatch; ++u) {
+        const uint32_t j = (uint32_t)u * kRbThreads + tid;
+        reg[u] = first2[j < pairs_total ? j : pairs_total - 1];
     }
     if (tid == 0) sm.nfew = 0u;
     // the row's bits above hi: into LDS, counted on the way
@@ -1063,10 +1066,7 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
         s_bits[w] = x;
         mine += (uint32_t)__popc(x);
     }
-    uint32_t band_mine = 0u;
-#pragma unroll
-    for (int j = 0; j < kRbTiles; ++j) band_mine += tc[j];
-    for (int64_t t = tid + (int64_t)kRbTiles * kRbThreads; t < L.tiles; t += kRbThreads) band_mine += cnt[t];
+    for (int t = t0 + 1; t < t1; ++t) band_mine += cnt[t];
     mine = wave_sum_u32(mine);
     const uint32_t band_incl = wave_prefix_inclusive_u32(band_mine);
     if (lane == 0) sm.w[wave] = mine;
@@ -1084,31 +1084,36 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
     if (miss) return;                                         // uniform: the redo launch handles this row
     uint32_t remain = (uint32_t)k - n_above;                  // candidates to select, 0 <= remain <= n_band
 
-    // candidates of this thread's tiles, from the registers and (crowded or far tiles) from memory
-    auto for_each_own = [&](auto&& f) {
-#pragma unroll
-        for (int j = 0; j < kRbTiles; ++j) {
-#pragma unroll
-            for (int i = 0; i < kRbSpec; ++i)
-                if ((uint32_t)i < tc[j]) f(reg[j][i]);
-            if (tc[j] > (uint32_t)kRbSpec) {                  // a crowded tile (ties): the rest from memory
-                const uint64_t* p = cand + (tid + (int64_t)j * kRbThreads) * tn;
-                for (uint32_t i = kRbSpec; i < tc[j]; ++i) f(p[i]);
-            }
-        }
-        for (int64_t t = tid + (int64_t)kRbTiles * kRbThreads; t < L.tiles; t += kRbThreads) {   // very large V
-            const uint32_t n = cnt[t];
-            const uint64_t* p0 = first + t * kCandFirst;
-            const uint64_t* p = cand + t * tn;
-            for (uint32_t i = 0; i < n; ++i) f(i < (uint32_t)kCandFirst ? p0[i] : p[i]);
-        }
-    };
     const bool dense = remain > 0u && n_band <= cand_cap;     // uniform
     if (dense) {
         uint32_t pos = band_before + band_incl - band_mine;
-        for_each_own([&](uint64_t x) { s_cand[pos++] = x; });
+        for (int t = t0; t < t1; ++t) {
+            s_off[t] = pos;
+            const uint32_t n = cnt[t];
+            for (uint32_t i = (uint32_t)F; i < n; ++i) s_cand[pos + i] = cand[(int64_t)t * tn + (i - F)];   // a crowded tile
+            pos += n;
+        }
+        if (tid == 0) s_off[T] = n_band;
+        __syncthreads();
+        auto pack = [&](uint32_t j, const u32x4 v) {
+            if (j >= pairs_total) return;
+            const uint32_t t = __umulhi(j, first_magic), i = 2u * (j - t * (uint32_t)(F / 2));
+            const uint32_t at = s_off[t], n = s_off[t + 1] - at;
+            if (i < n) s_cand[at + i] = ((uint64_t)v[1] << 32) | v[0];
+            if (i + 1 < n) s_cand[at + i + 1] = ((uint64_t)v[3] << 32) | v[2];
+        };
+#pragma unroll
+        for (int u = 0; u < kRbCandBatch; ++u) pack((uint32_t)u * kRbThreads + tid, reg[u]);
+        for (uint32_t j = (uint32_t)kRbCandBatch * kRbThreads + tid; j < pairs_total; j += kRbThreads) pack(j, first2[j]);
         __syncthreads();
     }
+    // candidates of this thread's tiles from memory (a row with too many for the LDS list)
+    auto for_each_own = [&](auto&& f) {
+        for (int t = t0; t < t1; ++t) {
+            const uint32_t n = cnt[t];
+            for (uint32_t i = 0; i < n; ++i) f(i < (uint32_t)F ? first[(int64_t)t * F + i] : cand[(int64_t)t * tn + (i - F)]);
+        }
+    };
     auto for_each_candidate = [&](auto&& f) {
         if (dense) {
             for (uint32_t i = tid; i < n_band; i += kRbThreads) f(s_cand[i]);
@@ -1211,7 +1216,7 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
     // a time with a running output position (no workgroup barrier inside the walk).  The ids go straight to
     // memory: gathering them in LDS first and writing whole lines afterwards was measured slower -- all rows
     // reach that point together, and the stores of the walk overlap its arithmetic instead
-    const uint64_t* s_pairs = reinterpret_cast<const uint64_t*>(s_bits);      // words is a multiple of 4
+    const uint64_t* s_pairs = reinterpret_cast<const uint64_t*>(s_bits);      // words is even
     const int64_t pairs = L.words / 2;
     const int64_t ppw = (pairs + kRbWaves - 1) / kRbWaves;
     const int64_t pbeg = wave * ppw, pend = pbeg + ppw < pairs ? pbeg + ppw : pairs;
@@ -1293,7 +1298,7 @@ bool scores_supported(int chunks) { return chunks >= 1 && chunks <= 64; }
 // outside any stream capture, by the library's device set-up)
 hipError_t configure_select_lds() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&resolve_emit_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResolveLdsBytes);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResolveMaxLdsBytes);
 }
 
 int64_t select_max_vocab() { return (int64_t)kSelThreads * kMaxBlocksPerRow * kEpt; }
@@ -1308,7 +1313,8 @@ void select_zero_range(int64_t rows, int64_t V, size_t* words) {
 }
 
 // ---- bracketed selection (many hidden rows, bf16): host side
-constexpr int64_t kSample = 8192;                        // sampled tokens per call
+constexpr int kSampleLog2 = 13;
+constexpr int64_t kSample = (int64_t)1 << kSampleLog2;   // sampled tokens per call
 constexpr int64_t kBracketMaxVocab = 393216;             // the row's bit mask (V / 8 bytes) lives in LDS: 48 KiB here
 
 // From 65 hidden rows on (measured: at 60 rows the path that materialises the 30 MB of scores, which then stay
@@ -1319,19 +1325,27 @@ bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k) {
     return dt == DT_BF16 && rows >= kBracketMinRows && V >= 4 * kSample && V <= kBracketMaxVocab;
 }
 
-size_t bracket_scratch_words(int64_t rows, int64_t V) {
-    return bracket_layout(V, (int)rows, bracket_tile_items((int)rows), kSample).total;
+// items per tile of the classify pass: the runs of the kernel that keeps the hidden rows in registers, or the tiles of
+// the tiled kernel (selectors too wide for the former)
+static int bracket_tn(int chunks, int64_t rows, int64_t V) {
+    return panel_supported(DT_BF16, chunks, rows, V) ? (int)panel_runs(chunks, rows, V).items : bracket_tile_items((int)rows);
 }
 
-void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp) {
-    const BracketLayout L = bracket_layout(V, (int)rows, bracket_tile_items((int)rows), kSample);
+size_t bracket_scratch_words(int chunks, int64_t rows, int64_t V) {
+    return bracket_layout(V, (int)rows, bracket_tn(chunks, rows, V), kSample).total;
+}
+
+void bracket_sample(int chunks, int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, int* log2_m,
+                    float** samp) {
+    *log2_m = kSampleLog2;
+    const BracketLayout L = bracket_layout(V, (int)rows, bracket_tn(chunks, rows, V), kSample);
     *ids = reinterpret_cast<int32_t*>(scratch + L.ids);
     *m = L.m;
     *samp = reinterpret_cast<float*>(scratch + L.samp);
 }
 
 hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
-    const int tn = bracket_tile_items(a.rows);
+    const int tn = bracket_tn(a.chunks, a.rows, a.V);
     const BracketLayout L = bracket_layout(a.V, a.rows, tn, kSample);
     // ranks of the bracket in the sample: the number of sampled tokens among the row's k best is
     // hypergeometric with mean m k / V; 6 standard deviations and 8 more on either side
@@ -1342,32 +1356,55 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(bracket_kernel, dim3((unsigned)a.rows), dim3(kRbThreads), 0, stream,
                        reinterpret_cast<const float*>(a.scratch + L.samp), L.m, rank_hi, rank_lo, thr);
     // classify: the full product, nothing stored but bits and candidates
-    GemvArgs g{};
-    g.x = a.hp;
-    g.x_row_bytes = (int64_t)a.chunks * 16;
-    g.M = a.Wv;
-    g.m_row_bytes = (int64_t)a.chunks * 16;
-    g.n_items = a.V;
-    g.chunks = a.chunks;
-    g.rows = a.rows;
     BracketEpi ep{};
     ep.thr = thr;
     ep.bits = a.scratch + L.bits;
     ep.words_per_row = L.words;
-    ep.cand_first = reinterpret_cast<uint64_t*>(a.scratch + L.first);
+    ep.cand_first = reinterpret_cast<uint64_t*>(a.scratch + L.cand_first);
     ep.cand = reinterpret_cast<uint64_t*>(a.scratch + L.cand);
     ep.cnt = a.scratch + L.cnt;
     ep.item_tiles = L.tiles;
-    hipError_t e = launch_tile_mfma_bracket(g, ep, stream);
+    ep.first_cap = L.first;
+    ep.over_cap = tn;
+    hipError_t e;
+    if (panel_supported(DT_BF16, a.chunks, a.rows, a.V)) {
+        PanelArgs p{};
+        p.x = a.hp;
+        p.x_row_bytes = (int64_t)a.chunks * 16;
+        p.M = a.Wv;
+        p.m_row_bytes = (int64_t)a.chunks * 16;
+        p.n_items = a.V;
+        p.chunks = a.chunks;
+        p.rows = a.rows;
+        p.bracket = ep;
+        e = launch_panel_bracket(p, stream);
+    } else {
+        GemvArgs g{};
+        g.x = a.hp;
+        g.x_row_bytes = (int64_t)a.chunks * 16;
+        g.M = a.Wv;
+        g.m_row_bytes = (int64_t)a.chunks * 16;
+        g.n_items = a.V;
+        g.chunks = a.chunks;
+        g.rows = a.rows;
+        e = launch_tile_mfma_bracket(g, ep, stream);
+    }
     if (e != hipSuccess) return e;
-    // LDS of a resolve workgroup: the bit mask, then as many candidate slots as keep two workgroups on a CU
-    const size_t bits_bytes = (size_t)L.words * 4;
-    const size_t room = kResolveLdsBytes > bits_bytes ? kResolveLdsBytes - bits_bytes : 0;
+    // LDS of a resolve workgroup: the bit mask, the tiles' offsets and the row's candidates.  As many slots as keep two
+    // workgroups on a CU where a row's expected candidates fit into that, else as many as one workgroup can have: a row
+    // that packs its candidates is several times faster than one that walks them in memory.
+    const size_t fixed_bytes = ((size_t)L.words + (size_t)resolve_off_words(L.tiles)) * 4;
+    const double expected = (double)((rank_lo < L.m ? rank_lo : L.m) - (rank_hi > 0 ? rank_hi : 0)) / (double)L.m * (double)a.V;
+    const size_t want = fixed_bytes + (size_t)(expected * 1.15) * 8 + 1024;
+    const size_t budget = want <= kResolveLdsBytes ? kResolveLdsBytes : want <= kResolveMaxLdsBytes ? want : kResolveLdsBytes;
+    const size_t room = budget > fixed_bytes ? budget - fixed_bytes : 0;
     uint32_t cand_cap = (uint32_t)(room / 8);
     if (cand_cap < 1024u) cand_cap = 0u;                      // not worth a packing pass
-    const size_t lds = bits_bytes + (size_t)cand_cap * 8;
+    const size_t lds = fixed_bytes + (size_t)cand_cap * 8;
+    const uint32_t half_first = (uint32_t)(L.first / 2);
+    const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + half_first - 1) / half_first);
     hipLaunchKernelGGL(resolve_emit_kernel, dim3((unsigned)a.rows), dim3(kRbThreads), lds, stream, a.V, a.rows, tn, L.m,
-                       a.k, a.scratch, a.idx_out, cand_cap);
+                       a.k, a.scratch, a.idx_out, cand_cap, magic);
     hipLaunchKernelGGL(redo_bracket_kernel<DT_BF16>, dim3((unsigned)(a.rows < kRedoBlocks ? a.rows : kRedoBlocks)),
                        dim3(kSelThreads), 0, stream, a.V, a.rows, tn, L.m, a.k, a.scratch, a.idx_out, a.hp, a.Wv, a.chunks);
     return hipGetLastError();

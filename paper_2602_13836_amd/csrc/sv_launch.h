@@ -20,6 +20,7 @@ hipError_t configure_skinny_mfma_lds();
 hipError_t configure_tile_mfma_lds();
 hipError_t configure_select_lds();
 hipError_t configure_union_lds();
+hipError_t configure_panel_lds();
 
 // out[r, j] = < M[row(r, j), :], x[r, :] >  for j in [0, n_items)
 //   row(r, j) = j                       if idx == nullptr   (dense)
@@ -101,17 +102,17 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream, bool small_ti
 // (thr[r] = {hi, lo}):  f > hi -> bit j of the row's bit mask;  lo <= f <= hi -> (key, id) appended to the
 // candidate region of (r, item tile), whose entry count goes to cnt.  Every word of bits and every cnt entry
 // is written.  Any row count >= 1.
-// Candidates of a (row, item tile): the first kCandFirst in a compact array (a row's are contiguous: the
-// resolve pass streams them), any further ones (tied scores) in the tile-sized region of the pair.
-constexpr int kCandFirst = 16;
+// Candidates of a (row, item tile): the first first_cap in a compact array (a row's are contiguous: the resolve
+// pass streams them), any further ones (tied scores) in a region of the pair's that holds the rest of the tile.
 struct BracketEpi {
     const float* thr;        // [rows][2]
-    uint32_t* bits;          // [rows][words_per_row], words_per_row = item_tiles * tile_items / 32
+    uint32_t* bits;          // [rows][words_per_row], words_per_row = item_tiles * tile items / 32
     int64_t words_per_row;
-    uint64_t* cand_first;    // [rows][item_tiles][kCandFirst]   ((ordered key << 32) | ~id)
-    uint64_t* cand;          // [rows][item_tiles][tile_items]   slots kCandFirst .. of the same list
+    uint64_t* cand_first;    // [rows][item_tiles][first_cap]   ((ordered key << 32) | ~id)
+    uint64_t* cand;          // [rows][item_tiles][over_cap]    slots first_cap .. of the same list
     uint32_t* cnt;           // [rows][item_tiles]
     int64_t item_tiles;
+    int first_cap, over_cap; // first_cap + over_cap = tile items
 };
 int bracket_tile_items(int rows);      // items per tile of the instance launch_tile_mfma_bracket picks
 hipError_t launch_tile_mfma_bracket(const GemvArgs& a, const BracketEpi& ep, hipStream_t stream);
@@ -129,6 +130,36 @@ struct PickEpi {
 };
 int pick_tile_items(int rows);
 hipError_t launch_tile_mfma_pick(const GemvArgs& a, const PickEpi& pk, hipStream_t stream);
+
+// Products with a short reduction (rows of M of up to 64 16-byte units) for more than 64 hidden rows: the hidden rows stay
+// in registers and runs of run_items rows of M stream past them.
+struct PanelArgs {
+    const char* x;           // [rows x d'] bf16, row stride x_row_bytes
+    int64_t x_row_bytes;
+    const char* M;
+    int64_t m_row_bytes;
+    int64_t n_items;
+    int chunks;
+    int rows;
+    float* out;              // [rows x out_row_stride]
+    int64_t out_row_stride;
+    int64_t spread_V;        // launch_panel_sample: item j is row floor(j * spread_V / 2^spread_shift) of M
+    int spread_shift;
+    // filled by the launchers
+    int64_t run_items;
+    const float* row_sub;    // [rows] subtracted from a row's products
+    float* partial;          // [rows][partial_stride][2]
+    int64_t partial_stride;
+    BracketEpi bracket;
+};
+struct PanelRuns { int64_t items, runs; };   // rows of M per run (a multiple of 64) and number of runs
+PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items);
+bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
+hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
+hipError_t launch_panel_bracket(const PanelArgs& a, hipStream_t stream);      // a.bracket: item tiles are the runs
+// out[r, :] = log softmax of the products of row r; ws: panel_log_softmax_ws_floats floats
+size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V);
+hipError_t launch_panel_log_softmax(const PanelArgs& a, float* ws, hipStream_t stream);
 
 // in place: s[r, :] <- log softmax(s[r, :]) for rows of V float32 scores; partial: log_softmax_ws_floats floats
 size_t log_softmax_ws_floats(int64_t rows, int64_t V);
@@ -196,8 +227,8 @@ hipError_t launch_topk_of_scores(const RadixArgs& a, hipStream_t stream);
 // Exact top-k of every row for a batch of hidden rows WITHOUT the score matrix in memory (bf16): the scores of a
 // sample of the vocabulary bracket each row's k-th score, the full product is classified against the bracket
 // in the epilogue of the matrix-core kernel, and the few scores inside the bracket are resolved exactly.
-// Order of use: bracket_sample() says where the sample's ids and scores live in the scratch (the caller has
-// the ids written -- GemvArgs::spread_* -- and the sample scores computed), then launch_bracket_select().
+// Order of use: bracket_sample() says how large the sample is (2^log2_m tokens) and where its scores, and its ids if
+// a kernel needs them as a list, live in the scratch; the caller has them computed, then launch_bracket_select().
 struct BracketArgs {
     const char* hp;        // [rows x d'] bf16
     const char* Wv;        // [V x d'] bf16, dense rows
@@ -209,8 +240,8 @@ struct BracketArgs {
     uint32_t* scratch;     // bracket_scratch_words(rows, V) words; nothing needs clearing
 };
 bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k);
-size_t bracket_scratch_words(int64_t rows, int64_t V);
-void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp);
+size_t bracket_scratch_words(int chunks, int64_t rows, int64_t V);
+void bracket_sample(int chunks, int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, int* log2_m, float** samp);
 hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream);
 
 // measurement aid: a plain coalesced read of `bytes` (a multiple of 16) from buf; sink: stream_read_blocks() words

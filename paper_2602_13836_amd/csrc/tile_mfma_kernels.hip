@@ -29,13 +29,11 @@
 
 #include <type_traits>
 
+#include "tile_epilogue.h"
+
 namespace sv {
 
 namespace {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTK = 64;                  // reduction elements per slice (128 bytes of a row)
 constexpr int kRowB = kTK * 2 + 16;      // padded LDS row (144 B = 36 words)
@@ -54,36 +52,6 @@ __device__ __forceinline__ void sched_pattern() {
         __builtin_amdgcn_sched_group_barrier(0x020, w, 0);                   // global loads
     }
     if constexpr (I + 1 < M) sched_pattern<M, R, W, I + 1>();
-}
-
-// loops whose index must be a compile-time constant inside the body (an instruction's immediate operand)
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-// dst with lanes LO and HI replaced by the two halves of the wavefront-uniform mask m (two v_writelane_b32).
-// The mask comes straight from a vector comparison: on this architecture a vector instruction that reads a
-// scalar register written by the vector instruction just before it needs two wait states in between; the
-// compiler inserts them for its own instructions, not for the operands of an asm block, hence the s_nop.
-template <int LO, int HI>
-__device__ __forceinline__ uint32_t write_lanes(uint32_t dst, uint64_t m) {
-    static_assert(LO >= 0 && LO < 64 && HI >= 0 && HI < 64, "lanes of a 64-wide wavefront");
-    asm("s_nop 1\n\tv_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4"
-        : "+v"(dst)
-        : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)), "n"(LO), "n"(HI));
-    return dst;
-}
-
-// 2 x + (this lane's bit of the wavefront-wide mask m): one add-with-carry whose carry-in is the mask.  The mask
-// must come from a scalar instruction (see write_lanes for why not straight from a vector comparison).
-__device__ __forceinline__ uint32_t shift_in_lane_bit(uint32_t x, uint64_t m) {
-    uint64_t carry_out;
-    asm volatile("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(x), "=s"(carry_out) : "s"(m));
-    return x;
 }
 
 // LDS the bracket epilogue needs (it reuses the operand buffers after the main loop): per tile row the
@@ -499,8 +467,8 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         __syncthreads();                                   // every wavefront is out of the operand buffers
         for (int t = tid; t < TM; t += kThreads) {
             const int row = rt * TM + t;
-            // rows past the end: nothing is above +inf, nothing reaches +inf
-            s_thr[t] = row < a.rows ? reinterpret_cast<const float2*>(ep.thr)[row] : float2{INFINITY, INFINITY};
+            // rows past the end: no score is above +inf, none compares with NaN
+            s_thr[t] = row < a.rows ? reinterpret_cast<const float2*>(ep.thr)[row] : float2{INFINITY, __builtin_nanf("")};
             s_cnt[t] = 0u;
         }
         if (it == IT - 1) {                                // items past the end compare false with everything
@@ -521,10 +489,11 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
             for (int n = 0; n < WN; ++n) words[j][n] = 0u;
         // candidate regions of this tile's rows: region of tile row t at cand_tile + t * row_stride (32-bit
         // arithmetic below: 64-bit multiplications per candidate cost more than everything else there)
-        uint64_t* cand_tile = ep.cand + ((int64_t)rt * TM * ep.item_tiles + it) * TN;
-        const uint32_t row_stride = (uint32_t)(ep.item_tiles * TN);          // < 2^24 (the vocabulary, padded)
-        uint64_t* first_tile = ep.cand_first + ((int64_t)rt * TM * ep.item_tiles + it) * kCandFirst;
-        const uint32_t first_stride = (uint32_t)(ep.item_tiles * kCandFirst);
+        const uint32_t fcap = (uint32_t)ep.first_cap;
+        uint64_t* cand_tile = ep.cand + ((int64_t)rt * TM * ep.item_tiles + it) * ep.over_cap;
+        const uint32_t row_stride = (uint32_t)(ep.item_tiles * ep.over_cap);          // < 2^24 (the vocabulary, padded)
+        uint64_t* first_tile = ep.cand_first + ((int64_t)rt * TM * ep.item_tiles + it) * ep.first_cap;
+        const uint32_t first_stride = (uint32_t)(ep.item_tiles * ep.first_cap);
         static_for<0, WM>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             constexpr int kHalfRows = 4;                   // lanes 32..63 hold the row four below
@@ -581,9 +550,9 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
                 for (int u = 0; u < kPer; ++u) {
                     if (has[u]) {
                         const uint32_t item = (uint32_t)item0 + 32u * (uint32_t)(q[u] % WN);
-                        uint64_t* dst = slot[u] < (uint32_t)kCandFirst
+                        uint64_t* dst = slot[u] < fcap
                                             ? first_tile + (__umul24((uint32_t)row_t[u], first_stride) + slot[u])
-                                            : cand_tile + (__umul24((uint32_t)row_t[u], row_stride) + slot[u]);
+                                            : cand_tile + (__umul24((uint32_t)row_t[u], row_stride) + (slot[u] - fcap));
                         *dst = ((uint64_t)f32_to_ord(f[u]) << 32) | (uint32_t)(~item);
                     }
                 }

@@ -1,0 +1,60 @@
+"""The kernel that keeps the hidden rows in registers (more than 64 rows, selectors of up to 512 elements), at the edges of
+its panels, runs and steps."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+sv = pytest.importorskip("paper_2602_13836_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+def _exact_inputs(rows, V, d_prime, seed, d=64):
+    """Weights and states whose products and sums are exact in every precision used: h' is a whole number of at most 64
+    (exact in bf16), a score a multiple of 2^-6 below 2^10."""
+    rng = np.random.default_rng(seed)
+
+    def bf16(a):
+        return torch.from_numpy(a.astype(np.float32)).cuda().to(torch.bfloat16)
+
+    h = bf16(rng.integers(-1, 2, (rows, d)))
+    Wd = bf16(rng.integers(-1, 2, (d_prime, d)))
+    Wv = bf16(rng.integers(-2, 3, (V, d_prime)) / 64.0)
+    return h, Wd, Wv
+
+
+def _scores(h, Wd, Wv):
+    return (h.double() @ Wd.double().t()) @ Wv.double().t()
+
+
+# rows: one panel and a bit more of each size (128, 256, 512), both sides; d_prime: one unit, odd numbers of units, whole
+# steps, the two widths that registers hold (256, 512) and one past the second; V: whole runs, a run of one item more, one less
+SHAPES = [(65, 32768, 256), (127, 32769, 8), (128, 33000, 24), (129, 40001, 256), (255, 32831, 200), (256, 65536, 248),
+          (257, 32832, 256), (300, 33023, 136), (511, 32895, 256), (512, 65537, 16), (513, 32770, 256), (65, 32768, 264),
+          (200, 33001, 512), (300, 40960, 504), (100, 33333, 520), (1030, 32800, 64)]
+
+
+@pytest.mark.parametrize("rows,V,d_prime", SHAPES)
+def test_log_probabilities_of_a_batch(rows, V, d_prime):
+    h, Wd, Wv = _exact_inputs(rows, V, d_prime, rows + d_prime)
+    ref = torch.log_softmax(_scores(h, Wd, Wv), dim=1)
+    out = torch.full((rows, V), float("nan"), device="cuda")
+    sv.aux_log_softmax(h, Wd, Wv, out=out)
+    # The scores are exact.  A sum of positive exponentials is off by at most 2^-24 per addition of its longest chain --
+    # fewer than 700: a lane's quarter of the values of its run, then the runs' pairs -- and so is its logarithm; the
+    # last subtraction rounds once.
+    tol = 700 * 2.0 ** -24 + 2.0 ** -22 * ref.abs()
+    assert ((out.double() - ref).abs() <= tol).all()
+
+
+@pytest.mark.parametrize("rows,V,d_prime", SHAPES)
+@pytest.mark.parametrize("share", [0.5, 0.05, 0.0005])
+def test_selection_of_a_batch(rows, V, d_prime, share):
+    """Exact scores with many ties: the ids must be those of a full sort, ties to the smaller id."""
+    h, Wd, Wv = _exact_inputs(rows, V, d_prime, 7 * rows + d_prime)
+    k = max(1, int(V * share))
+    idx, _ = sv.select(h, Wd, Wv, k)
+    s = _scores(h, Wd, Wv)
+    # (stable sort by descending score: equal scores stay in ascending id order)
+    want = torch.sort(s, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values
+    assert torch.equal(idx.long(), want)
