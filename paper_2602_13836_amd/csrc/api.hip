@@ -437,6 +437,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         gs.rows = (int)rows;
         gs.out_f32 = samp;
         gs.out_row_stride = m;
+        gs.m_rows = V;
         hipError_t e;
         if (panel) {
             sv::PanelArgs p = panel_args(gs);
@@ -444,7 +445,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
             p.spread_shift = log2_m;
             e = sv::launch_panel_sample(p, s);
         } else {
-            e = sv::launch_tile_mfma(gs, s, true);
+            e = sv::launch_tile_mfma(gs, s);
         }
         if (e != hipSuccess) return SV_ERR_HIP;
         sv::BracketArgs ba{};

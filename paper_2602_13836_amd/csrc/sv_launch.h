@@ -93,9 +93,8 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream);
 // also supports out_bf16 and zero_ptr
 bool ksplit_rows_supported(int dt, const GemvArgs& a);
 hipError_t launch_ksplit_rows(const GemvArgs& a, hipStream_t stream);
-// more than 64 rows of x: LDS-tiled product (launch_skinny_mfma forwards to it); small_tiles: 128 x 128 tiles
-// whatever the row count (few items: more workgroups matter more than operand reuse)
-hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream, bool small_tiles = false);
+// more than 64 rows of x, and some lists from 17 rows on: LDS-tiled product (launch_skinny_mfma forwards to it)
+hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream);
 
 // The tiled product with the epilogue of the bracketed selection instead of a store: nothing of the product
 // is written; per hidden row r and item j the score f = out[r, j] is compared with the row's bracket

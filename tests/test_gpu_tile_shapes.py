@@ -1,0 +1,66 @@
+"""The tiled product for more than 64 hidden rows at the edges of its tiles: every tile shape, ragged rows, item counts and
+reductions, by matrix, by list and by list per row.  Whole-numbered inputs whose sums are exact in float32, so results
+are compared for equality."""
+import pytest
+
+torch = pytest.importorskip("torch")
+sv = pytest.importorskip("paper_2602_13836_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+def _whole(gen, rows, cols, top):
+    return torch.randint(-top, top + 1, (rows, cols), device="cuda", generator=gen).to(torch.bfloat16)
+
+
+def _inputs(rows, d, V, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    # |sum| <= 4096 * 4 * 4 < 2^24: every partial sum is exact
+    h, U = _whole(gen, rows, d, 4), _whole(gen, V, d, 4)
+    return gen, h, U, h.double() @ U.double().t()
+
+
+# items: around one and two tiles of 128 and 256; then enough of them for the wider tiles (128 x 256: several hundred to a
+# round's worth; 256 x 256: full rounds).  d: one 16-byte unit, less than a 64-element slice, one, one and a unit, odd numbers
+# of slices, more slices than stages, rotated walks (16 slices and more), ragged ones among them
+@pytest.mark.parametrize("rows,d,V", [
+    (65, 8, 127), (65, 64, 128), (66, 72, 129), (127, 56, 255), (128, 128, 256), (129, 136, 257), (192, 192, 511),
+    (255, 200, 513), (256, 320, 300), (257, 264, 130), (300, 1024, 777), (384, 1096, 1000), (512, 4096, 515), (513, 520, 259),
+    (130, 72, 33000), (128, 328, 70001), (256, 64, 66000), (400, 200, 66049), (520, 1032, 40003), (700, 136, 50000)])
+def test_dense_product(rows, d, V):
+    _, h, U, ref = _inputs(rows, d, V, rows + d)
+    assert torch.equal(sv.dense_logits(h, U).double(), ref)
+
+
+@pytest.mark.parametrize("rows,d,V,k", [(65, 72, 3000, 129), (200, 520, 5000, 1000), (256, 1032, 40000, 35001), (300, 64, 70000, 66000)])
+def test_shared_list(rows, d, V, k):
+    gen, h, U, ref = _inputs(rows, d, V, k)
+    idx = torch.randint(0, V, (k,), device="cuda", generator=gen).to(torch.int32)
+    assert torch.equal(sv.subset_logits(h, U, idx).double(), ref[:, idx.long()])
+
+
+@pytest.mark.parametrize("rows,d,V,k", [(65, 72, 257, 200), (100, 520, 5000, 1000), (129, 1032, 3001, 500), (300, 64, 1024, 300),
+                                        (512, 136, 2047, 64)])
+@pytest.mark.parametrize("ascending", [True, False])
+def test_list_per_row(rows, d, V, k, ascending):
+    gen, h, U, ref = _inputs(rows, d, V, k + rows)
+    idx = torch.rand((rows, V), device="cuda", generator=gen).topk(k, dim=1).indices.to(torch.int32)
+    if ascending:
+        idx = idx.sort(dim=1).values
+    got = sv.subset_logits(h, U, idx.contiguous(), sorted_lists=ascending)
+    assert torch.equal(got.double(), ref.gather(1, idx.long()))
+
+
+def test_list_into_a_matrix_past_four_gigabytes():
+    """Byte offsets past 32 bits take another loop."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    V, d, rows = 70000, 72, 70
+    U = torch.empty((V, 32768), dtype=torch.bfloat16, device="cuda")[:, :d]          # 64 KB between rows: 4.6 GB
+    U.copy_(_whole(gen, V, d, 4))
+    h = _whole(gen, rows, d, 4)
+    idx = torch.randint(0, V, (700,), device="cuda", generator=gen).to(torch.int32)
+    idx[0], idx[1] = V - 1, 0
+    ref = h.double() @ U[idx.long()].double().t()
+    assert torch.equal(sv.subset_logits(h, U, idx).double(), ref)
