@@ -18,6 +18,8 @@
 #include "sv_device.h"
 #include "sv_launch.h"
 
+#include "memory_to_lds.h"
+
 namespace sv {
 
 namespace {
@@ -178,6 +180,27 @@ __global__ __launch_bounds__(WPB * 64) void skinny_mfma_kernel(SV_HOT_PARAMS, co
     }
 }
 
+// four consecutive items j0 .. j0 + 3 of hidden row row0 + r
+__device__ __forceinline__ void store_ksplit(const GemvArgs& a, const f32x4_t sum, int row0, int r, int rows_here, int64_t j0,
+                                             int64_t n_items) {
+    if (r >= rows_here) return;
+    if (a.out_bf16) {
+        uint16_t* o = a.out_bf16 + (int64_t)(row0 + r) * a.out_row_stride + j0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (j0 + v < n_items) o[v] = f32_to_bf16_rne(sum[v]);
+        return;
+    }
+    float* o = a.out_f32 + (int64_t)(row0 + r) * a.out_row_stride + j0;
+    if (j0 + 3 < n_items && ((reinterpret_cast<uintptr_t>(o) & 15u) == 0)) {
+        *reinterpret_cast<f32x4_t*>(o) = sum;
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (j0 + v < n_items) o[v] = sum[v];
+    }
+}
+
 // Small item counts (a few thousand rows of M): too few 16-row tiles to fill the chip with one
 // wavefront per tile, so the 8 wavefronts of a workgroup share ONE tile and split the reduction:
 // wavefront w takes slices w, w + 8, ... of both operands straight from global memory (x is small and
@@ -279,24 +302,114 @@ __global__ __launch_bounds__(512) void skinny_mfma_ksplit_kernel(SV_HOT_PARAMS, 
     f32x4_t sum = s_part[0][nb][lane];
 #pragma unroll
     for (int w = 1; w < WPB; ++w) sum += s_part[w][nb][lane];
-    const int r = nb * 16 + i;
-    if (r >= rows_here) return;
-    const int64_t j0 = tile0 + 4 * g;
-    if (a.out_bf16) {
-        uint16_t* o = a.out_bf16 + (int64_t)(row0 + r) * a.out_row_stride + j0;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (j0 + v < n_items) o[v] = f32_to_bf16_rne(sum[v]);
+    store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
+}
+
+// The same product, fed from memory to LDS.  What bounded the kernel above is the shape of its loads: 16 rows x 64 bytes per
+// instruction reach a CU at about 30 GB/s from L2 (512 hidden rows x 256 items of 4096: 384 KB per workgroup, 14-15 us),
+// 8 rows x 128 bytes at several times that (the same product 9.7 us; 8 rows x 8192 listed rows of 3840 15.6 -> 12.8; whole
+// steps over 8192 listed rows of 4096: 8 rows 19.8 -> 17.2, 32 rows 30.9 -> 21.7).  Here every wavefront brings its slices in as whole 128-byte lines, 64
+// elements of its 16 rows of M and 16 NB hidden rows at a time, into a ring of DEPTH chunks of its own -- no registers
+// in flight, no barrier, no conditional load -- and reads its fragments from there.  (Rows of 128 bytes, the 16-byte unit u
+// of row r at place u ^ ((r >> 1) & 7): the fragment reads, 16 rows x 4 units, run at 218 B/clk.)  The operands of every
+// MFMA and their order are those of the kernel above, so the result is the same bit for bit.
+// Hidden rows past the last, and units past a row's end, are requested from outside the buffer and arrive as zeros.
+constexpr int kDirectWaves = 8;
+template <int NB, int DEPTH>
+constexpr size_t direct_lds_bytes() { return (size_t)kDirectWaves * DEPTH * (16 + 16 * NB) * 128; }
+template <int NB, int DEPTH>
+__global__ __launch_bounds__(64 * kDirectWaves) void ksplit_direct_kernel(SV_HOT_PARAMS, const GemvArgs rest, const int row_base) {
+    const GemvArgs a = with_hot(rest, m_base, idx_base, x_base, n_items_arg, m_row_bytes_arg, x_row_bytes_arg,
+                                n_items_dev_arg);
+    constexpr int N = 16 * NB;
+    constexpr int kChunkB = (16 + N) * 128;              // 64 elements of the wavefront's rows of M, then of the hidden rows
+    constexpr int kRequests = 2 + 2 * NB;                // 1 KB each, per chunk
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [waves][DEPTH][kChunkB], then the partial sums
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15;
+    const int g = lane >> 4;
+    const int C = a.chunks;
+    const int nslices = (C * 8 + kKC - 1) / kKC;
+    const int row0 = row_base + (int)blockIdx.y * N;
+    const int rows_here = min(a.rows - row0, N);
+    const int64_t n_items = a.n_items_dev ? (int64_t)*a.n_items_dev : a.n_items;
+    const int64_t tile0 = (int64_t)blockIdx.x * 16;
+    if (tile0 >= n_items || rows_here <= 0 || !gate_open(a, n_items)) {
+        prepare_scratch(a);
         return;
     }
-    float* o = a.out_f32 + (int64_t)(row0 + r) * a.out_row_stride + j0;
-    if (j0 + 3 < n_items && ((reinterpret_cast<uintptr_t>(o) & 15u) == 0)) {
-        *reinterpret_cast<f32x4_t*>(o) = sum;
-    } else {
+    const int l8 = lane >> 3;
+    const uint32_t unit0 = (uint32_t)((lane & 7) ^ (l8 >> 1)), unit1 = unit0 ^ 4u;       // of rows l8 and l8 + 8 of a 16-row group
+    uint32_t voff_m[2], voff_x[2 * NB];
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (j0 + v < n_items) o[v] = sum[v];
+    for (int j = 0; j < 2; ++j) {
+        int64_t item = tile0 + 8 * j + l8;
+        if (item > n_items - 1) item = n_items - 1;
+        const uint32_t row = a.idx ? (uint32_t)a.idx[item] : (uint32_t)(item - tile0);
+        voff_m[j] = row * (uint32_t)a.m_row_bytes + (j ? unit1 : unit0) * 16u;
     }
+#pragma unroll
+    for (int j = 0; j < 2 * NB; ++j) {
+        const int r = 8 * j + l8;
+        voff_x[j] = r < rows_here ? (uint32_t)r * (uint32_t)a.x_row_bytes + (j & 1 ? unit1 : unit0) * 16u : kOutside;
+    }
+    const i32x4_t buf_m = buffer_of(a.idx ? a.M : a.M + tile0 * a.m_row_bytes);
+    const i32x4_t buf_x = buffer_of(a.x + (int64_t)row0 * a.x_row_bytes);
+    unsigned char* ring = smem + (size_t)wave * DEPTH * kChunkB;
+    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)(wave * DEPTH * kChunkB);
+    // chunk c of the wavefront: 64 elements of slice wave + 8 (c / 4), part c % 4
+    const int nch = wave < nslices ? 4 * ((nslices - wave + kDirectWaves - 1) / kDirectWaves) : 0;
+    auto request = [&](int c, int stage) {
+        const int first_unit = (wave + kDirectWaves * (c >> 2)) * (kKC / 8) + (c & 3) * 8;
+        const bool out0 = first_unit + (int)unit0 >= C, out1 = first_unit + (int)unit1 >= C;      // (past the last chunk: all of it)
+        const uint32_t soff = (uint32_t)first_unit * 16u, at = lds + (uint32_t)(stage * kChunkB);
+        memory_to_lds<1024>(out0 ? kOutside : voff_m[0], out1 ? kOutside : voff_m[1], buf_m, soff, at);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            memory_to_lds<1024>(out0 ? kOutside : voff_x[2 * nb], out1 ? kOutside : voff_x[2 * nb + 1], buf_x, soff, at + 2048u * (nb + 1));
+    };
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < DEPTH; ++c) request(c, c);
+    const int frag = i * 128 + ((g ^ ((i >> 1) & 7)) * 16);                   // unit 4 kk + g of row i
+    int stage = 0;
+    for (int c = 0; c < nch; ++c) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DEPTH - 1) * kRequests) : "memory");      // chunk c is there
+        const unsigned char* p = ring + stage * kChunkB;
+        u32x4 av[2], bv[2][NB];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            av[kk] = *reinterpret_cast<const u32x4*>(p + (frag ^ (kk * 64)));
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) bv[kk][nb] = *reinterpret_cast<const u32x4*>(p + 2048 * (nb + 1) + (frag ^ (kk * 64)));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                    // read, so its place may be filled again
+        request(c + DEPTH, stage);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[kk]),
+                                                                  __builtin_bit_cast(bf16x8_t, bv[kk][nb]), acc[nb], 0, 0, 0);
+        stage = stage + 1 == DEPTH ? 0 : stage + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                          // (chunks past the end: requested, never read)
+    prepare_scratch(a);
+    __syncthreads();
+    f32x4_t* s_part = reinterpret_cast<f32x4_t*>(smem);                       // [waves][NB][64]
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) s_part[(wave * NB + nb) * 64 + lane] = acc[nb];
+    __syncthreads();
+    if (wave >= NB) return;
+    const int nb = wave;                                   // wavefront nb sums and stores hidden rows 16 nb ..
+    f32x4_t sum = s_part[nb * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < kDirectWaves; ++w) sum += s_part[(w * NB + nb) * 64 + lane];
+    store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
 }
 
 template <int NB>
@@ -316,9 +429,32 @@ hipError_t opt_in_lds_all_nb() {
     return e;
 }
 
+// byte offsets in 32 bits: from a tile's first row for a whole matrix, from the matrix itself for rows by list
+bool direct_fits(const GemvArgs& a) {
+    constexpr int64_t kSpan = (int64_t)kBufferBytes;
+    if (32 * a.x_row_bytes > kSpan || 16 * a.m_row_bytes > kSpan) return false;
+    return a.idx == nullptr || (a.m_rows > 0 && a.m_rows <= kSpan / a.m_row_bytes);
+}
+
+template <int NB, int DEPTH>
+hipError_t launch_direct(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
+    const int64_t bx = (a.n_items + 15) / 16;
+    hipLaunchKernelGGL((ksplit_direct_kernel<NB, DEPTH>), dim3((unsigned)bx, (unsigned)groups), dim3(64 * kDirectWaves),
+                       (direct_lds_bytes<NB, DEPTH>()), stream, SV_HOT_ARGS(a), a, row0);
+    return hipGetLastError();
+}
+
 template <int NB>
 hipError_t launch_ksplit(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
     const int64_t bx = (a.n_items + 15) / 16;
+    if (direct_fits(a)) {
+        DeviceInfo di;
+        const hipError_t e = device_info(&di);
+        if (e != hipSuccess) return e;
+        // one workgroup per CU: a deep ring; more workgroups than that: rings that let two share a CU
+        if (NB == 2) return launch_direct<2, 3>(a, row0, groups, stream);
+        return bx * groups <= di.cus ? launch_direct<1, 4>(a, row0, groups, stream) : launch_direct<1, 2>(a, row0, groups, stream);
+    }
     hipLaunchKernelGGL((skinny_mfma_ksplit_kernel<NB>), dim3((unsigned)bx, (unsigned)groups), dim3(512), 0, stream,
                        SV_HOT_ARGS(a), a, row0);
     return hipGetLastError();
@@ -347,6 +483,12 @@ hipError_t launch_w(const GemvArgs& a, int row0, int nrows, hipStream_t stream) 
 hipError_t configure_skinny_mfma_lds() {
     hipError_t e = opt_in_lds_all_nb<2>();
     if (e == hipSuccess) e = opt_in_lds_all_nb<4>();
+    auto direct = [&](auto kernel, size_t bytes) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    };
+    direct(&ksplit_direct_kernel<1, 2>, direct_lds_bytes<1, 2>());
+    direct(&ksplit_direct_kernel<1, 4>, direct_lds_bytes<1, 4>());
+    direct(&ksplit_direct_kernel<2, 3>, direct_lds_bytes<2, 3>());
     return e;
 }
 
@@ -381,13 +523,11 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream) {
     hipError_t e = device_info(&di);
     if (e != hipSuccess) return e;
     // few items: split the reduction over the wavefronts of a workgroup, 32 hidden rows per workgroup row.
-    // Every workgroup reads its hidden rows from L2 itself and a CU is through with its workgroups one after the
-    // other (time grows in steps of 16 x CUs items), so the more hidden rows, the earlier the other kernel wins:
-    // measured crossovers (d = 3840) between 12288 and 16384 items at 2 and 8 rows, between 8192 and 10240 at
-    // 16 and 32 rows (16384 items: 29 against 33 us at 8 rows, 36 against 53 at 32 rows); from 33 rows on
-    // (d = 4096) between 4096 and 6144 items, where a single tile of the LDS-tiled kernel takes 35 us whatever
-    // the list's length (4096 items: 26 against 35 us; 6144: 39 against 35; 8192: 50 against 35).
-    const int64_t split_items = (int64_t)di.cus * (a.rows <= 4 ? 64 : a.rows <= 8 ? 48 : a.rows <= 32 ? 32 : 20);
+    // Every workgroup reads its hidden rows from L2 itself, so the more of them, the earlier the other kernels win.  Measured
+    // crossovers, whole step: up to 16 rows between 16384 and 24576 items (d = 4096, 16 rows: 16384 items 31 against 33 us,
+    // 20480 43 against 43; d = 2048 the same), at 17 to 32 rows between 12288 and 16384 (32 rows: 33 against 35, 45 against
+    // 39), from 33 rows between 8192 and 12288 (60 rows: 35 against 41, 51 against 42).
+    const int64_t split_items = (int64_t)di.cus * (a.rows <= 16 ? 64 : a.rows <= 32 ? 48 : 32);
     // A count on the device (the union of the rows' sets; a.n_items is its upper bound, often several times the
     // count when the sets overlap) that may fall on either side of such a crossover: launches with complementary
     // gates, of which those that do not serve the list leave at once (about 2 us each).  The crossovers that matter:
@@ -399,9 +539,11 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream) {
     if (a.n_items_dev != nullptr && a.gate_hi == 0 && a.n_items > split_items && a.chunks >= 8 * (kKC / 8)) {
         int64_t cuts[2];
         int ncuts = 0;
-        // (a union of duplicate-free sets of k items has at least k: from three quarters of the crossover on, the
-        // split form has nothing left to win -- 4096 items 26 us against 35 on one tile, 5120 items 33)
-        if (4 * a.n_items_min < 3 * split_items) cuts[ncuts++] = split_items;
+        // (a union of duplicate-free sets of k items has at least k: where that is close to the crossover there is little
+        // for the split form to win, and every list pays for its launch -- 60 sets of 4096 that unite to 50 K rows: 107
+        // against 109.5 us)
+        const int64_t worth = (int64_t)di.cus * (a.rows <= 4 ? 48 : a.rows <= 8 ? 36 : a.rows <= 32 ? 24 : 15);
+        if (a.n_items_min < worth) cuts[ncuts++] = split_items;
         if (a.rows > 32 && a.n_items > (int64_t)di.cus * 128) cuts[ncuts++] = (int64_t)di.cus * 128;
         if (ncuts > 0) {
             GemvArgs part = a;

@@ -16,7 +16,7 @@ def _whole(gen, rows, cols, top):
 def _inputs(rows, d, V, seed):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
-    # |sum| <= 4096 * 4 * 4 < 2^24: every partial sum is exact
+    # |sum| <= 16384 * 4 * 4 < 2^24: every partial sum is exact
     h, U = _whole(gen, rows, d, 4), _whole(gen, V, d, 4)
     return gen, h, U, h.double() @ U.double().t()
 
@@ -40,6 +40,16 @@ def test_shared_list(rows, d, V, k):
     assert torch.equal(sv.subset_logits(h, U, idx).double(), ref[:, idx.long()])
 
 
+# short lists and long rows: the reduction split over the wavefronts of a workgroup (16 items by 16 or 32 hidden rows), with
+# fewer slices of 256 than twice the wavefronts, ragged last slices, and rings deeper than what is left to read
+@pytest.mark.parametrize("rows,d,V,k", [(2, 2048, 400, 1), (3, 2056, 400, 15), (16, 2104, 5000, 4101), (17, 2296, 700, 17),
+                                        (31, 4096, 700, 333), (33, 2304, 700, 300), (64, 6152, 900, 513), (48, 16384, 300, 50)])
+def test_shared_list_of_long_rows(rows, d, V, k):
+    gen, h, U, ref = _inputs(rows, d, V, k + d)
+    idx = torch.randint(0, V, (k,), device="cuda", generator=gen).to(torch.int32)
+    assert torch.equal(sv.subset_logits(h, U, idx).double(), ref[:, idx.long()])
+
+
 @pytest.mark.parametrize("rows,d,V,k", [(65, 72, 257, 200), (100, 520, 5000, 1000), (129, 1032, 3001, 500), (300, 64, 1024, 300),
                                         (512, 136, 2047, 64)])
 @pytest.mark.parametrize("ascending", [True, False])
@@ -52,11 +62,12 @@ def test_list_per_row(rows, d, V, k, ascending):
     assert torch.equal(got.double(), ref.gather(1, idx.long()))
 
 
-def test_list_into_a_matrix_past_four_gigabytes():
-    """Byte offsets past 32 bits take another loop."""
+@pytest.mark.parametrize("rows,d", [(70, 72), (20, 2048)])
+def test_list_into_a_matrix_past_four_gigabytes(rows, d):
+    """Byte offsets past 32 bits take other kernels."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(1)
-    V, d, rows = 70000, 72, 70
+    V = 70000
     U = torch.empty((V, 32768), dtype=torch.bfloat16, device="cuda")[:, :d]          # 64 KB between rows: 4.6 GB
     U.copy_(_whole(gen, V, d, 4))
     h = _whole(gen, rows, d, 4)
