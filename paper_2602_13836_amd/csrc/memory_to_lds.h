@@ -22,6 +22,13 @@ __device__ __forceinline__ void memory_to_lds(uint32_t voff0, uint32_t voff1, i3
         : "v"(voff0), "v"(voff1), "s"(buffer), "s"(soff), "s"(lds), "n"(STEP)
         : "memory", "m0", "scc");
 }
+// one such piece
+__device__ __forceinline__ void memory_to_lds(uint32_t voff, i32x4_t buffer, uint32_t soff, uint32_t lds) {
+    asm volatile("s_nop 4\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 :
+                 : "v"(voff), "s"(buffer), "s"(soff), "s"(lds)
+                 : "memory", "m0");
+}
 __device__ __forceinline__ i32x4_t buffer_of(const char* base) {
     const uint64_t p = reinterpret_cast<uint64_t>(base);
     // (raw buffer: stride 0, byte-addressed, 32-bit data format)

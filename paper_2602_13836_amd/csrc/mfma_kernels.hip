@@ -524,10 +524,10 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream) {
     if (e != hipSuccess) return e;
     // few items: split the reduction over the wavefronts of a workgroup, 32 hidden rows per workgroup row.
     // Every workgroup reads its hidden rows from L2 itself, so the more of them, the earlier the other kernels win.  Measured
-    // crossovers, whole step: up to 16 rows between 16384 and 24576 items (d = 4096, 16 rows: 16384 items 31 against 33 us,
-    // 20480 43 against 43; d = 2048 the same), at 17 to 32 rows between 12288 and 16384 (32 rows: 33 against 35, 45 against
-    // 39), from 33 rows between 8192 and 12288 (60 rows: 35 against 41, 51 against 42).
-    const int64_t split_items = (int64_t)di.cus * (a.rows <= 16 ? 64 : a.rows <= 32 ? 48 : 32);
+    // crossovers: up to 16 rows between 16384 and 24576 items (d = 4096, 16 rows, whole step: 16384 items 31 against 33 us,
+    // 20480 43 against 43; d = 2048 the same), at 17 to 32 rows between 8192 and 12288 (32 rows: 6000 items 15 us against 21,
+    // 12288 25 against 22), from 33 rows between 5120 and 8192 (60 rows: 4096 items 15 against 25, 9000 40 against 25).
+    const int64_t split_items = (int64_t)di.cus * (a.rows <= 16 ? 64 : a.rows <= 32 ? 32 : 20);
     // A count on the device (the union of the rows' sets; a.n_items is its upper bound, often several times the
     // count when the sets overlap) that may fall on either side of such a crossover: launches with complementary
     // gates, of which those that do not serve the list leave at once (about 2 us each).  The crossovers that matter:
@@ -563,14 +563,11 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream) {
         if (a.rows <= 16) return launch_ksplit<1>(a, 0, 1, stream);
         return launch_ksplit<2>(a, 0, (a.rows + 31) / 32, stream);
     }
-    // 33 to 64 hidden rows: the LDS-tiled kernel (whole 128-byte lines per request; it picks its tile by the
-    // list's length).  Measured over list lengths from 6144 to 128256 items at 36, 48 and 60 rows it is as fast
-    // as or faster than eight wavefronts of this kernel with 16 rows of M each (60 rows: 16384 items 37 against
-    // 56 us, 32768 60 against 66, 81920 144 against 155).
+    // 33 to 64 hidden rows: the LDS-tiled kernel (it picks its tile by the list's length).
     if (a.rows > 32) return launch_tile_mfma(a, stream);
-    // 17 to 32 hidden rows: the LDS-tiled kernel on 32 x 64 tiles wins in the middle -- 3 to 15 % between 12288 and
-    // 81920 items (32 rows: 24576 items 48 against 55 us, 40960 71 against 79, 81920 127 against 131), equal at
-    // 8192 -- and loses 3-5 % from 98304 items on (128256: 203 against 193).
+    // 17 to 32 hidden rows: the LDS-tiled kernel up to 81920 items and a bit; from 98304 on it is 3-5 % slower on its plain
+    // loop (128256: 203 against 193), and its ring, which is not, adds a token's products in steps of 16 elements where
+    // this kernel adds them in steps of 32 (twice the rounding error).
     if (a.rows > 16 && a.n_items <= (int64_t)di.cus * 352) return launch_tile_mfma(a, stream);
     // Wide workgroups share one x slice among more rows of M; small problems need more workgroups.
     // But only a workgroup with at least 128 threads per 16 hidden rows stages the x slice behind the

@@ -64,11 +64,13 @@ constexpr size_t bracket_lds_bytes() {
 
 template <int GM, int GN, int WM, int WN, int PIPE>
 constexpr size_t tile_lds_bytes() {
-    return PIPE == 2 ? (size_t)(2 * 32 * GM * WM + 3 * 32 * GN * WN) * kTK * 2 : (size_t)2 * (32 * GM * WM + 32 * GN * WN) * kRowB;
+    return PIPE == 3   ? (size_t)4 * (32 * GM * WM + 32 * GN * WN) * kTK * 2
+           : PIPE == 2 ? (size_t)(2 * 32 * GM * WM + 3 * 32 * GN * WN) * kTK * 2
+                       : (size_t)2 * (32 * GM * WM + 32 * GN * WN) * kRowB;
 }
 
 // GM x GN wavefronts; each owns WM x WN MFMA tiles of 32 x 32: TM = 32 GM WM hidden rows, TN = 32 GN WN items.
-// PIPE: 0 the plain main loop, 1 the interleaved, 2 the alternating one, fed from memory to LDS.  EPI: what happens to the product --
+// PIPE: 0 the plain main loop, 1 the interleaved, 2 the alternating one, 3 the ring (both fed from memory to LDS).  EPI: what happens to the product --
 //   EPI_STORE    it is stored;
 //   EPI_BRACKET  the epilogue of the bracketed selection (Section 3.3 Step 2 for a batch of hidden rows)
 //                classifies it, nothing is stored;
@@ -199,7 +201,73 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
                     acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m], bf[n], acc[m][n], 0, 0, 0);
         }
     };
-    if constexpr (PIPE == 2) {
+    if constexpr (PIPE == 3) {
+        // Up to 64 hidden rows: one pass over M at the rate of the memory system.  A ring of four stages in LDS, three slices
+        // on their way (96 KB of M per CU with 64 x 256 tiles), one barrier per slice: behind it everybody has slice ks and
+        // nobody reads slice ks - 1 any more, whose stage takes slice ks + 3.  Layout and requests as in the loop below.
+        constexpr int kWavesHere = GM * GN, kStageB = (TM + TN) * 128;
+        constexpr int LA = TM / (8 * kWavesHere), LB = TN / (8 * kWavesHere);
+        static_assert(TM % (8 * kWavesHere) == 0 && LB % 2 == 0 && kWavesHere % 2 == 0, "whole requests per wavefront; a constant swizzle");
+        constexpr int kPass = 8 * kWavesHere;                // rows that one request of every wavefront covers
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+        const int swave = __builtin_amdgcn_readfirstlane(wave);
+        const int l8 = lane >> 3;
+        const int unit = (lane & 7) ^ ((4 * (swave & 1) + (l8 >> 1)) & 7);
+        const bool lane_past = (nk - 1) * 8 + unit >= C;     // of the last slice
+        uint32_t voff_a[LA], voff_b[LB];
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const int row = min(rt * TM + kPass * i + 8 * swave + l8, a.rows - 1);
+            voff_a[i] = (uint32_t)(row - rt * TM) * (uint32_t)a.x_row_bytes + (uint32_t)unit * 16u;
+        }
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            int64_t item = tile0 + kPass * i + 8 * swave + l8;
+            if (item > tile_end - 1) item = tile_end - 1;
+            const uint32_t row = a.idx ? (uint32_t)a.idx[item] : (uint32_t)(item - tile0);
+            voff_b[i] = row * (uint32_t)a.m_row_bytes + (uint32_t)unit * 16u;
+        }
+        const i32x4_t buf_a = buffer_of(a.x + (int64_t)rt * TM * a.x_row_bytes);
+        const i32x4_t buf_b = buffer_of(a.idx ? a.M : a.M + tile0 * a.m_row_bytes);
+        auto request = [&](int ks) {
+            const int s = eff(ks);
+            const bool cut = s == nk - 1 && lane_past;
+            const uint32_t at = lds0 + (uint32_t)((ks & 3) * kStageB + swave * 1024);
+#pragma unroll
+            for (int i = 0; i < LB; i += 2)
+                memory_to_lds<kPass * 128>(cut ? kOutside : voff_b[i], cut ? kOutside : voff_b[i + 1], buf_b, (uint32_t)s * 128u,
+                                           at + (uint32_t)(i * kPass * 128));
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+                memory_to_lds(cut ? kOutside : voff_a[i], buf_a, (uint32_t)s * 128u, at + (uint32_t)(TN * 128 + i * kPass * 128));
+        };
+        const int swz = ((lane >> 5) ^ ((lane >> 1) & 7)) * 16;
+        const int fa0 = (TN + wr * 32 * WM + (lane & 31)) * 128 + swz, fb0 = (wc * 32 * WN + (lane & 31)) * 128 + swz;
+        request(0);
+        request(1);
+        request(2);
+        for (int ks = 0; ks < nk; ++ks) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (LA + LB)) : "memory");
+            request(ks + 3);
+            const unsigned char* base = smem + (size_t)(ks & 3) * kStageB;
+#pragma unroll
+            for (int kk = 0; kk < kTK / 16; ++kk) {
+                bf16x8_t af[WM], bf[WN];
+#pragma unroll
+                for (int m = 0; m < WM; ++m)
+                    af[m] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + (fa0 ^ (kk * 32)) + 32 * m * 128));
+#pragma unroll
+                for (int n = 0; n < WN; ++n)
+                    bf[n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + (fb0 ^ (kk * 32)) + 32 * n * 128));
+#pragma unroll
+                for (int m = 0; m < WM; ++m)
+#pragma unroll
+                    for (int n = 0; n < WN; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m], bf[n], acc[m][n], 0, 0, 0);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (slices past the end: requested, never read)
+    } else if constexpr (PIPE == 2) {
         // Two wavefronts share a SIMD and take turns, a barrier ending every turn: while one multiplies a
         // 16-element step (nothing but its MFMAs), the other issues its memory work -- the LDS reads of its NEXT step's
         // fragments and a few requests that bring a later slice from memory straight into LDS -- and waits for none of
@@ -650,6 +718,9 @@ hipError_t configure_tile_mfma_lds() {
         if (e == hipSuccess) e = fn(std::integral_constant<int, EPI_PICK>{});
     };
     if (e == hipSuccess) e = opt_in_lds<1, 8, 2, 1, 0, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<1, 8, 2, 1, 3, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<1, 4, 1, 1, 3, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<2, 4, 1, 1, 3, EPI_STORE>();
     if (e == hipSuccess) e = opt_in_lds<2, 4, 2, 1, 2, EPI_STORE>();
     all_epilogues([](auto ec) { return opt_in_lds<2, 4, 2, 2, 2, decltype(ec)::value>(); });
     all_epilogues([](auto ec) { return opt_in_lds<2, 4, 4, 2, 2, decltype(ec)::value>(); });
@@ -722,29 +793,35 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
     if (a.n_items <= 0 || a.rows <= 0) return hipSuccess;
     // Up to 64 hidden rows (the caller decides when this beats the kernel without LDS tiles) the product is one
     // pass over M at the rate of the memory system, and what matters is how evenly the list's items spread over
-    // the chip.  17 to 32 rows: 32 x 64 tiles (two wavefronts, five workgroups per CU).  33 to 64 rows: 64 x 256
-    // tiles (eight wavefronts, one workgroup per CU) stream best when the list fills its last round of 256 x CUs
-    // items, or more than half of it (a tree step of 60 rows over 50223 rows of U: 110 against 113 us with the
-    // tiles below; all 128256 rows: 197 against 200) -- and for a count on the device, which such a tree step has;
-    // otherwise small tiles with several workgroups per CU: 64 x 64 (four per CU) up to 64 x CUs items, 64 x 128
-    // (four wavefronts, two per CU) beyond.  60 rows, 64 x 64 / 64 x 128 / 64 x 256: 16384 items 37 / 44 / 61 us,
-    // 32768 59 / 60 / 76, 81920 150 / 144 / 161, 98304 186 / 160 / 170.
-    if (a.rows <= 32) return launch_tile<1, 2, 1, 1, 0>(a, stream);
+    // the chip and how much of them is on its way: the ring, which has three slices in flight, on tiles of
+    //   17 to 32 rows: 32 x 128 (four wavefronts, two workgroups per CU) up to one workgroup per CU, and where two per CU
+    //     are nearly full (32 rows x 24576 items 38.7 us against 43.6 on 32 x 64 tiles of the plain loop, 65536 96 against
+    //     98); in between those (49152: 78 against 73), and for short reductions, the 32 x 64 tiles;
+    //   33 to 64 rows: 64 x 256 (eight wavefronts, one workgroup per CU) when the list fills its last round of 256 x CUs
+    //     items, or more than half of it (128256 items 188 us against 192 on the tiles below, 49152 75 against 82) -- and
+    //     for a count on the device, which a tree step has --, of a width that then fills whole rounds; otherwise 64 x 128
+    //     (eight wavefronts of 32 x 32): 60 rows x 9000 / 16384 / 24576 / 32768 / 98304 items 25 / 32 / 42 / 50 / 149 us
+    //     (58 on 64 x 256 tiles for the third; 35 / 36 / 48 / 51 / 153 on the plain loop's 64 x 64 and 64 x 128 tiles).
     if (a.rows <= 64) {
         DeviceInfo di;
         const hipError_t e = device_info(&di);
         if (e != hipSuccess) return e;
+        const bool direct = direct_fits(a);
+        if (a.rows <= 32) {
+            const bool ring = direct && a.chunks > 64 && (a.n_items <= (int64_t)di.cus * 128 || a.n_items >= (int64_t)di.cus * 224);
+            return ring ? launch_tile<1, 4, 1, 1, 3>(a, stream) : launch_tile<1, 2, 1, 1, 0>(a, stream);
+        }
         const int64_t round_items = (int64_t)256 * di.cus, last = a.n_items % round_items;
         // (with a count on the device a.n_items is its upper bound: at most half a round, and the list is short for sure)
         const bool unknown = a.n_items_dev != nullptr && 2 * a.n_items > round_items;
-        if (unknown || last == 0 || 2 * last > round_items) {
-            // ... of a width that fills whole rounds of workgroups (40960 items: 80 against 87 us; unions of 30940 and
-            // 44831 rows: a tree step in 82 and 104 us against 88 and 109)
+        if (!direct || unknown || last == 0 || 2 * last > round_items) {
+            // (40960 items: 80 against 87 us with a width that fills whole rounds; unions of 30940 and 44831 rows: a tree
+            // step in 82 and 104 us against 88 and 109)
             GemvArgs b = a;
             b.balance_cus = di.cus;
-            return launch_tile<1, 8, 2, 1, 0>(b, stream);
+            return direct ? launch_tile<1, 8, 2, 1, 3>(b, stream) : launch_tile<1, 8, 2, 1, 0>(b, stream);
         }
-        return a.n_items <= (int64_t)64 * di.cus ? launch_tile<1, 2, 2, 1, 0>(a, stream) : launch_tile<1, 4, 2, 1, 0>(a, stream);
+        return launch_tile<2, 4, 1, 1, 3>(a, stream);
     }
     if (!direct_fits(a)) return launch_tile<2, 4, 4, 2, 1>(a, stream);
     // A count on the device, up to 128 rows: the shape that is never far from the best, whatever the count turns out to be

@@ -27,6 +27,9 @@ def _inputs(rows, d, V, seed):
 @pytest.mark.parametrize("rows,d,V", [
     (65, 8, 127), (65, 64, 128), (66, 72, 129), (127, 56, 255), (128, 128, 256), (129, 136, 257), (192, 192, 511),
     (255, 200, 513), (256, 320, 300), (257, 264, 130), (300, 1024, 777), (384, 1096, 1000), (512, 4096, 515), (513, 520, 259),
+    # the ring of four stages (17 to 64 rows): fewer slices than stages, ragged ones, 32 x 128, 64 x 128 and 64 x 256 tiles
+    (17, 520, 129), (32, 1032, 300), (24, 584, 57345), (33, 8, 127), (40, 72, 129), (60, 136, 1000), (64, 200, 32769), (48, 1096, 65537),
+    (60, 2056, 70000), (34, 264, 40001),
     (130, 72, 33000), (128, 328, 70001), (256, 64, 66000), (400, 200, 66049), (520, 1032, 40003), (700, 136, 50000)])
 def test_dense_product(rows, d, V):
     _, h, U, ref = _inputs(rows, d, V, rows + d)
