@@ -65,6 +65,22 @@ def test_list_per_row(rows, d, V, k, ascending):
     assert torch.equal(got.double(), ref.gather(1, idx.long()))
 
 
+# several float32 rows over one set of rows of M, large enough that M is read once for all of them: rows of M of one to sixteen
+# KB with ragged ends, more hidden rows than LDS holds at a time, more than a wavefront has lanes, items that do not divide
+@pytest.mark.parametrize("rows,d,V", [(2, 260, 70001), (5, 1028, 20003), (8, 2052, 9000), (70, 64, 5001), (130, 512, 4099),
+                                      (3, 4096, 3001), (37, 3072, 2049)])
+def test_float32_rows_share_one_pass(rows, d, V):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + d)
+    h, U = (torch.randint(-4, 5, (n, d), device="cuda", generator=gen).float() for n in (rows, V))
+    ref = (h.double() @ U.double().t())
+    assert torch.equal(sv.dense_logits(h, U).double(), ref)
+    idx = torch.randint(0, V, (V,), device="cuda", generator=gen).to(torch.int32)
+    idx[::3] = -1
+    want = ref[:, idx.long().clamp(min=0)].masked_fill(idx < 0, float("-inf"))
+    assert torch.equal(sv.subset_logits(h, U, idx, padded=True).double(), want)
+
+
 @pytest.mark.parametrize("rows,d", [(70, 72), (20, 2048)])
 def test_list_into_a_matrix_past_four_gigabytes(rows, d):
     """Byte offsets past 32 bits take other kernels."""
