@@ -425,13 +425,16 @@ __global__ __launch_bounds__(256) void lse_fold_kernel(const float2* partial, in
 // The instance for a shape, as an index: hidden rows per panel and steps held.
 //   0  d' <= 256, panels of 512 (64 rows per wavefront)     1  ... of 256     2  ... of 128 (32 rows per wavefront)
 //   3  d' <= 512, panels of 256 (32 rows per wavefront)
+//   4, 5, 6  d' <= 128: as 0, 1, 2 with half the steps (512 rows x 128256, d' = 128: selection 110 -> 101 us, log-
+//     probabilities 105 -> 95)
 struct Shape { int panel, gi; };
-constexpr Shape kShapes[4] = {{512, 1}, {256, 2}, {128, 2}, {256, 1}};
+constexpr Shape kShapes[7] = {{512, 1}, {256, 2}, {128, 2}, {256, 1}, {512, 1}, {256, 2}, {128, 2}};
 inline int shape_of(int chunks, int rows) {
     if (chunks > 32) return 3;
-    if (rows <= 128) return 2;
+    const int base = chunks <= 16 ? 4 : 0;
+    if (rows <= 128) return base + 2;
     const int pad256 = (rows + 255) / 256, pad512 = (rows + 511) / 512;
-    return 2 * pad512 == pad256 ? 0 : 1;                 // no panel half idle
+    return base + (2 * pad512 == pad256 ? 0 : 1);        // no panel half idle
 }
 template <int EPI, typename F>
 hipError_t with_shape(int shape, F&& f) {
@@ -439,6 +442,9 @@ hipError_t with_shape(int shape, F&& f) {
         case 0: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
         case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
         case 2: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+        case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+        case 5: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+        case 6: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
         default: return f(std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
     }
 }
@@ -457,7 +463,7 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
     PanelArgs a = a0;
     // A sample of a few thousand rows of M is over in one or two steps and costs what fetching the hidden rows costs:
     // small panels (512 rows, 8192 of them: 10.8 us on panels of 128 against 14.0 on panels of 512).
-    const int shape = EPI == EPI_SAMPLE && a.chunks <= 32 ? 2 : shape_of(a.chunks, a.rows);
+    const int shape = EPI == EPI_SAMPLE && a.chunks <= 32 ? (a.chunks <= 16 ? 6 : 2) : shape_of(a.chunks, a.rows);
     const PanelRuns pr = runs_of(shape, a.rows, a.n_items);
     a.run_items = pr.items;
     a.partial_stride = pr.runs * kShapes[shape].gi;
@@ -474,7 +480,7 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
 
 template <int EPI>
 hipError_t opt_in_epi() {
-    for (int shape = 0; shape < 4; ++shape) {
+    for (int shape = 0; shape < 7; ++shape) {
         const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
             constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
             static_assert(panel_lds_bytes<KS, WM, GM, EPI>() <= 160 * 1024, "one workgroup per CU");
