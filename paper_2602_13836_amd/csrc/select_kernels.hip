@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kRowThreads) void emit_rows_kernel(const float* s_a
 //             deviations of the hypergeometric count, -/+ 8);
 //   classify  the full product on the matrix cores, whose epilogue keeps only: one bit per (row, token)
 //             "score > hi" (all of these are selected), and (key, id) of the few per cent of scores inside
-//             [lo, hi] (tile_mfma_kernels.hip);
+//             [lo, hi] (panel_mfma_kernels.hip; tile_mfma_kernels.hip for selectors wider than 512 elements);
 //   resolve   per row, with the row's bits in LDS: popcount of the bits = n_above; the (k - n_above)-th largest
 //             candidate by exact radix selection on (key, ~id) is the threshold; the selected candidates'
 //             bits are set; the ids of the set bits are written in ascending order.  A row whose bracket

@@ -7,21 +7,19 @@
 // With hundreds of hidden rows the product is a real contraction (Section 3.4 counts V d
 // multiply-adds per hidden row): reading M once per 64 hidden rows, as the skinny kernel does, turns
 // into many passes over M.  Here a workgroup owns a TM x TN tile of the output (TM hidden rows, TN
-// rows of M) and walks the reduction in slices of 64 elements: both operand slices go
-// global -> registers -> LDS (double buffered, one barrier per slice) and every wavefront multiplies
-// its part of the tile with v_mfma_f32_32x32x16_bf16 from LDS.  LDS rows are padded to 144 bytes so
-// that the 16-byte operand reads of consecutive lanes fall into distinct banks (measured: full LDS
-// read rate, no bank conflicts).  Workgroups that share rows of M (the different hidden-row tiles of
-// one TN block) are given consecutive slots on the same XCD, so that M comes from HBM once and from
-// that die's L2 afterwards (measured: HBM traffic 1.27 x the size of M at 512 hidden rows).
+// rows of M) and walks the reduction in slices of 64 elements through LDS; every wavefront multiplies
+// its part of the tile with v_mfma_f32_32x32x16_bf16 from there.  Workgroups that share rows of M (the different
+// hidden-row tiles of one TN block) are given consecutive slots on the same XCD, so that M comes from HBM once and from
+// that die's L2 afterwards (measured: HBM traffic 1.3 x the size of M at 512 hidden rows).
 //
-// Three forms of the main loop.  The plain one leaves the order of loads, LDS traffic and MFMAs to the
-// compiler and relies on several workgroups per CU to overlap them: up to 64 hidden rows, where the one pass over M
-// bounds the product.  In the alternating one (more rows) the two wavefronts of a SIMD take turns between multiplying
-// and memory work, a barrier per turn, and slices go from memory to LDS directly.  The interleaved one serves what the
-// alternating one cannot address (rows of 16 MB and more; lists into matrices of more than 4 GB): every wavefront reads
-// its operand fragments one 16-element step ahead and spreads the LDS copy of the next slice over the four steps of the
-// current one, with scheduling-group fences pinning that order against the compiler's own scheduler.
+// Four forms of the main loop.  The plain one (slices through registers into LDS rows padded to 144 bytes) leaves the
+// order of loads, LDS traffic and MFMAs to the compiler and relies on several workgroups per CU to overlap them: 17 to 32
+// hidden rows where the ring does not win.  The ring (17 to 64 rows, bound by the one pass over M) has three slices on
+// their way from memory to LDS.  In the alternating one (more rows) the two wavefronts of a SIMD take turns between
+// multiplying and memory work, a barrier per turn, and slices go from memory to LDS directly.  The interleaved one serves
+// what the alternating one cannot address (rows of 16 MB and more; lists into matrices of more than 4 GB): every wavefront
+// reads its operand fragments one 16-element step ahead and spreads the LDS copy of the next slice over the four steps of
+// the current one, with scheduling-group fences pinning that order against the compiler's own scheduler.
 #include "sv_device.h"
 #include "sv_launch.h"
 
