@@ -245,7 +245,9 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         request(1);
         request(2);
         for (int ks = 0; ks < nk; ++ks) {
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (LA + LB)) : "memory");
+            // (lgkmcnt: this wavefront's own reads of slice ks - 1 are back too -- nothing else keeps the MFMAs that consume
+            // them, and with them their wait, in front of this barrier)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (LA + LB)) : "memory");
             request(ks + 3);
             const unsigned char* base = smem + (size_t)(ks & 3) * kStageB;
 #pragma unroll
