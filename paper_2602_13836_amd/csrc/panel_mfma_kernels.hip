@@ -64,6 +64,12 @@ constexpr size_t panel_lds_bytes() {
     return n > fill ? n : fill;
 }
 
+// orders the LDS accesses of a wavefront's lanes for the compiler; no instruction
+__device__ __forceinline__ void wavefront_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // KS 16-element steps of the reduction are held (rows of M of up to 16 KS elements), WM groups of 32 hidden rows per
 // wavefront, GM wavefronts along the panel; the other 8 / GM share the step's rows of M.
 template <int KS, int WM, int GM, int EPI>
@@ -145,13 +151,16 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                     const int p = q * 64 + lane, u = p % kUnits;
                     *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kRowB + u * 16) = u < C ? v[q] : zero16();
                 }
-                // (a wavefront's own LDS accesses stay in order)
+                // (a wavefront's own LDS accesses stay in order in the hardware; the fences keep the compiler from moving a
+                // lane's reads in front of the other lanes' writes, or the next round's writes in front of these reads)
+                wavefront_fence();
                 if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
 #pragma unroll
                     for (int kk = 0; kk < KS; ++kk)
                         fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
                                                                      s_fill + ((lane & 31) % kRows) * kRowB + (lane >> 5) * 16 + kk * 32));
                 }
+                wavefront_fence();
             }
         __syncthreads();                                 // the fill regions are the stages from here on
     }
