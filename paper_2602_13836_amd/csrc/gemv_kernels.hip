@@ -220,9 +220,12 @@ __global__ __launch_bounds__(256) void gemv_long_rows_kernel(const GemvArgs a) {
 // workgroup row, read M once per hidden row (8 rows x 65536 rows of 4 KB: 300 us, here 55, where one pass over M takes
 // 40).  Bound by the pass over M up to about eight hidden rows, by LDS reads beyond.  A sum's order is that of the
 // kernels above: the same bits.
-template <int NL, int RPI>
+// RAGGED: rows that are not exactly 64 NL units.  Units past a row's end are zeros on both sides -- a lane that has none reads
+// the same zeros, behind the staged rows, for every hidden row --, so that an infinity in a last unit meets no zero (2 to 6 %
+// of such a launch: 16 rows x 5000 rows of 8208 bytes 37.0 us against 35.5; whole rows do not pay for it).
+template <int NL, int RPI, bool RAGGED>
 __global__ __launch_bounds__(256) void gemv_shared_rows_kernel(const GemvArgs a, const int group) {
-    extern __shared__ __attribute__((aligned(16))) u32x4 s_rows[];            // [rows of the group][chunks]
+    extern __shared__ __attribute__((aligned(16))) u32x4 s_rows[];            // [rows of the group][chunks], RAGGED: one unit of zeros
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -233,10 +236,13 @@ __global__ __launch_bounds__(256) void gemv_shared_rows_kernel(const GemvArgs a,
         const u32x4* xp = reinterpret_cast<const u32x4*>(a.x + (int64_t)(row0 + r) * a.x_row_bytes);
         for (int u = tid; u < C; u += 256) s_rows[r * C + u] = xp[u];
     }
+    if (RAGGED && tid == 0) s_rows[nrows * C] = zero16();
     __syncthreads();
     int unit[NL];
 #pragma unroll
     for (int c = 0; c < NL; ++c) unit[c] = min(c * 64 + lane, C - 1);
+    // (a row has more than 32 NL units, the launcher picks NL so: the first half of a lane's units is always there)
+    auto past = [&](int c) { return RAGGED && c >= NL / 2 && c * 64 + lane >= C; };
     const int64_t n = a.n_items, step = (int64_t)gridDim.x * 4 * RPI;
     for (int64_t it = ((int64_t)blockIdx.x * 4 + wave) * RPI; it < n; it += step) {
         u32x4 w[RPI][NL];
@@ -265,7 +271,7 @@ __global__ __launch_bounds__(256) void gemv_shared_rows_kernel(const GemvArgs a,
             for (int r = 0; r < nr; ++r) {
                 u32x4 x[NL];
 #pragma unroll
-                for (int c = 0; c < NL; ++c) x[c] = s_rows[(r0 + r) * C + unit[c]];
+                for (int c = 0; c < NL; ++c) x[c] = s_rows[past(c) ? nrows * C : (r0 + r) * C + unit[c]];
 #pragma unroll
                 for (int q = 0; q < RPI; ++q) {
                     float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -359,10 +365,12 @@ bool shared_rows_wanted(const GemvArgs& a) {
 }
 hipError_t launch_shared(const GemvArgs& a, int cus, hipStream_t stream) {
     const int nl = (a.chunks + 63) / 64;
-    int group = (int)(kSharedLds / ((size_t)a.chunks * 16));                  // hidden rows per workgroup row: at least four
+    const bool ragged = (a.chunks & (a.chunks - 1)) != 0 || a.chunks < 64;    // rows that are not 64, 128, ... 1024 units
+    const size_t zeros = ragged ? 16 : 0;
+    int group = (int)((kSharedLds - zeros) / ((size_t)a.chunks * 16));        // hidden rows per workgroup row: at least four
     if (group > a.rows) group = a.rows;
     const int groups = (a.rows + group - 1) / group;
-    const size_t lds = (size_t)group * a.chunks * 16;
+    const size_t lds = (size_t)group * a.chunks * 16 + zeros;
     auto go = [&](auto kernel, int rpi) {
         int64_t bx = (a.n_items + 4 * rpi - 1) / (4 * rpi);
         const int64_t per_cu = (int64_t)(160 * 1024) / (int64_t)(lds < 20 * 1024 ? 20 * 1024 : lds);   // workgroups a CU holds
@@ -371,11 +379,15 @@ hipError_t launch_shared(const GemvArgs& a, int cus, hipStream_t stream) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)bx, (unsigned)groups), dim3(256), lds, stream, a, group);
         return hipGetLastError();
     };
-    if (nl <= 1) return go(&gemv_shared_rows_kernel<1, 4>, 4);
-    if (nl <= 2) return go(&gemv_shared_rows_kernel<2, 4>, 4);
-    if (nl <= 4) return go(&gemv_shared_rows_kernel<4, 4>, 4);
-    if (nl <= 8) return go(&gemv_shared_rows_kernel<8, 2>, 2);
-    return go(&gemv_shared_rows_kernel<16, 1>, 1);
+#define SV_SHARED(NL, RPI) \
+    if (nl <= NL) return ragged ? go(&gemv_shared_rows_kernel<NL, RPI, true>, RPI) : go(&gemv_shared_rows_kernel<NL, RPI, false>, RPI)
+    SV_SHARED(1, 4);
+    SV_SHARED(2, 4);
+    SV_SHARED(4, 4);
+    SV_SHARED(8, 2);
+    SV_SHARED(16, 1);
+#undef SV_SHARED
+    return hipErrorInvalidValue;
 }
 
 template <int DT, int NL, int WAVES>

@@ -81,6 +81,17 @@ def test_float32_rows_share_one_pass(rows, d, V):
     assert torch.equal(sv.subset_logits(h, U, idx, padded=True).double(), want)
 
 
+# rows whose last 16-byte units do not fill a wavefront: what stands in for the missing ones must not meet an infinity
+@pytest.mark.parametrize("rows,d,V", [(130, 100, 20003), (5, 1028, 20003), (8, 2052, 9000)])
+def test_float32_rows_with_infinities_at_their_end(rows, d, V):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + d)
+    h, U = (torch.randint(1, 5, (n, d), device="cuda", generator=gen).float() for n in (rows, V))
+    h[1, -1], h[2, -3], U[7, -2] = float("inf"), float("-inf"), float("inf")
+    ref = h.double() @ U.double().t()
+    torch.testing.assert_close(sv.dense_logits(h, U).double(), ref, rtol=0, atol=0, equal_nan=True)
+
+
 @pytest.mark.parametrize("rows,d", [(70, 72), (20, 2048)])
 def test_list_into_a_matrix_past_four_gigabytes(rows, d):
     """Byte offsets past 32 bits take other kernels."""
