@@ -369,14 +369,22 @@ hipError_t launch_shared(const GemvArgs& a, int cus, hipStream_t stream) {
     const size_t zeros = ragged ? 16 : 0;
     int group = (int)((kSharedLds - zeros) / ((size_t)a.chunks * 16));        // hidden rows per workgroup row: at least four
     if (group > a.rows) group = a.rows;
-    const int groups = (a.rows + group - 1) / group;
-    const size_t lds = (size_t)group * a.chunks * 16 + zeros;
     auto go = [&](auto kernel, int rpi) {
         int64_t bx = (a.n_items + 4 * rpi - 1) / (4 * rpi);
+        // Few items make few workgroups, each of which walks its hidden rows one after the other: then groups of fewer rows
+        // (at least eight), until there are eight workgroups per CU.  M is small there and comes from L2 the further times.
+        // 64 rows x 4096 rows of 1 KB: 14.1 us with M read once per row, 23.3 with one group, 12.8 with eight; 130 rows x
+        // 9000 of 512 bytes 68.5, 87.9, 54.1 with four.
+        const int64_t least = bx < 8 * cus ? (8 * cus + bx - 1) / bx : 1;
+        int g = (int)((a.rows + least - 1) / least);
+        if (g < 8) g = 8;
+        if (g > group) g = group;
+        const int groups = (a.rows + g - 1) / g;
+        const size_t lds = (size_t)g * a.chunks * 16 + zeros;
         const int64_t per_cu = (int64_t)(160 * 1024) / (int64_t)(lds < 20 * 1024 ? 20 * 1024 : lds);   // workgroups a CU holds
         const int64_t cap = ((int64_t)cus * per_cu + groups - 1) / groups;
         if (bx > cap) bx = cap;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)bx, (unsigned)groups), dim3(256), lds, stream, a, group);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)bx, (unsigned)groups), dim3(256), lds, stream, a, g);
         return hipGetLastError();
     };
 #define SV_SHARED(NL, RPI) \

@@ -66,9 +66,10 @@ def test_list_per_row(rows, d, V, k, ascending):
 
 
 # several float32 rows over one set of rows of M, large enough that M is read once for all of them: rows of M of one to sixteen
-# KB with ragged ends, more hidden rows than LDS holds at a time, more than a wavefront has lanes, items that do not divide
+# KB with ragged ends, more hidden rows than LDS holds at a time, more than a wavefront has lanes, items that do not divide;
+# few items, which make smaller groups of hidden rows (of eight, of a last group of one, of uneven numbers)
 @pytest.mark.parametrize("rows,d,V", [(2, 260, 70001), (5, 1028, 20003), (8, 2052, 9000), (70, 64, 5001), (130, 512, 4099),
-                                      (3, 4096, 3001), (37, 3072, 2049)])
+                                      (3, 4096, 3001), (37, 3072, 2049), (9, 512, 4097), (65, 256, 4096), (41, 260, 6001)])
 def test_float32_rows_share_one_pass(rows, d, V):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(rows + d)
