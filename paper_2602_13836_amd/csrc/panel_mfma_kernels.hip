@@ -38,7 +38,7 @@ namespace {
 
 constexpr int kXcds = 8;
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
-constexpr int kGroups = 256;             // workgroups a launch is cut into (the CUs of the part)
+constexpr int kCusPerXcd = 32;           // (of the part, not asked of the device: a workspace's size follows from the runs)
 constexpr int kRunUnit = 64;             // a run is a multiple of this many rows of M
 
 // EPI_SAMPLE     row(j) = floor(j spread_V / 2^spread_shift), a sample of M's rows; the product is stored
@@ -458,13 +458,31 @@ hipError_t with_shape(int shape, F&& f) {
     }
 }
 
+// How M is cut into runs.  A run and its panels are dealt to one XCD, a CU holds one workgroup, and a workgroup costs its
+// start (the hidden rows' way into registers, about as long as 100 rows of M) and its rows: the number of runs per XCD is
+// the one whose rounds of workgroups are cheapest.  One and two panels: a run per CU and one per two CUs.  Three panels:
+// ten runs per XCD (a run per 256 / 3 CUs would be eleven on most of them, 33 workgroups on 32 CUs: 700 rows x 151936,
+// selection 297 us against 215).  Many panels: at least one run per XCD (20000 rows x 32768, 79 panels: three runs, on
+// three of the eight, took 3406 us, sixteen take 1820).
 PanelRuns runs_of(int shape, int64_t rows, int64_t n_items) {
     const int64_t panels = (rows + kShapes[shape].panel - 1) / kShapes[shape].panel;
-    const int64_t groups = panels < kGroups ? kGroups / panels : 1;
-    PanelRuns r;
-    r.items = ((n_items + groups - 1) / groups + kRunUnit - 1) / kRunUnit * kRunUnit;
-    r.runs = (n_items + r.items - 1) / r.items;
-    return r;
+    PanelRuns best{};
+    double least = 0.0;
+    const bool even = panels <= kCusPerXcd && kCusPerXcd % panels == 0;        // one full round: nothing to weigh
+    for (int64_t per_xcd = even ? kCusPerXcd / panels : kCusPerXcd; per_xcd >= 1; --per_xcd) {
+        PanelRuns r;
+        const int64_t wanted = per_xcd * kXcds;
+        r.items = ((n_items + wanted - 1) / wanted + kRunUnit - 1) / kRunUnit * kRunUnit;
+        r.runs = (n_items + r.items - 1) / r.items;
+        const int64_t rounds = ((r.runs + kXcds - 1) / kXcds * panels + kCusPerXcd - 1) / kCusPerXcd;
+        const double cost = (double)rounds * (double)(r.items + 100);
+        if (best.items == 0 || cost < least) {
+            best = r;
+            least = cost;
+        }
+        if (even) break;
+    }
+    return best;
 }
 
 template <int EPI>

@@ -32,6 +32,9 @@ def _scores(h, Wd, Wv):
 SHAPES = [(65, 32768, 256), (127, 32769, 8), (128, 33000, 24), (129, 40001, 256), (255, 32831, 200), (256, 65536, 248),
           (257, 32832, 256), (300, 33023, 136), (511, 32895, 256), (512, 65537, 16), (513, 32770, 256), (65, 32768, 264),
           (200, 33001, 512), (300, 40960, 504), (100, 33333, 520), (1030, 32800, 64)]
+# numbers of panels that do not divide an XCD's 32 compute units, and more of them than there are: several rounds of workgroups,
+# runs of few and of many steps
+SHAPES += [(700, 40000, 64), (1300, 32790, 256), (2100, 32769, 128), (8500, 32768, 32), (17000, 32800, 16)]
 
 
 @pytest.mark.parametrize("rows,V,d_prime", SHAPES)
