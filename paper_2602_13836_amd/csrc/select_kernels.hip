@@ -1084,17 +1084,39 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
     if (miss) return;                                         // uniform: the redo launch handles this row
     uint32_t remain = (uint32_t)k - n_above;                  // candidates to select, 0 <= remain <= n_band
 
+    // f(tile, place, candidate) for the candidates from place `from` of every tile on, from memory.  A tile is shared by as
+    // many threads as there are for each (thousands of hidden rows leave a row few tiles, of tens of thousands of tokens),
+    // and a thread has several requests on their way (tied scores make long lists).
+    auto walk_tiles = [&](int from, auto&& f) {
+        constexpr int kFlight = 8;
+        const int sharers = T < kRbThreads ? kRbThreads / T : 1;
+        const int sub = tid % sharers;
+        for (int t = tid / sharers; t < T; t += kRbThreads / sharers) {
+            const int n = (int)cnt[t];
+            const uint64_t *p0 = first + (int64_t)t * F, *p = cand + (int64_t)t * tn - F;
+            for (int i = from + sub; i < n; i += kFlight * sharers) {
+                uint64_t x[kFlight];
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) {
+                    const int at = min(i + u * sharers, n - 1);
+                    x[u] = (at < F ? p0 : p)[at];
+                }
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u)
+                    if (i + u * sharers < n) f(t, (uint32_t)(i + u * sharers), x[u]);
+            }
+        }
+    };
     const bool dense = remain > 0u && n_band <= cand_cap;     // uniform
     if (dense) {
         uint32_t pos = band_before + band_incl - band_mine;
         for (int t = t0; t < t1; ++t) {
             s_off[t] = pos;
-            const uint32_t n = cnt[t];
-            for (uint32_t i = (uint32_t)F; i < n; ++i) s_cand[pos + i] = cand[(int64_t)t * tn + (i - F)];   // a crowded tile
-            pos += n;
+            pos += cnt[t];
         }
         if (tid == 0) s_off[T] = n_band;
         __syncthreads();
+        walk_tiles(F, [&](int t, uint32_t i, uint64_t x) { s_cand[s_off[t] + i] = x; });     // a crowded tile's rest
         auto pack = [&](uint32_t j, const u32x4 v) {
             if (j >= pairs_total) return;
             const uint32_t t = __umulhi(j, first_magic), i = 2u * (j - t * (uint32_t)(F / 2));
@@ -1107,18 +1129,11 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
         for (uint32_t j = (uint32_t)kRbCandBatch * kRbThreads + tid; j < pairs_total; j += kRbThreads) pack(j, first2[j]);
         __syncthreads();
     }
-    // candidates of this thread's tiles from memory (a row with too many for the LDS list)
-    auto for_each_own = [&](auto&& f) {
-        for (int t = t0; t < t1; ++t) {
-            const uint32_t n = cnt[t];
-            for (uint32_t i = 0; i < n; ++i) f(i < (uint32_t)F ? first[(int64_t)t * F + i] : cand[(int64_t)t * tn + (i - F)]);
-        }
-    };
     auto for_each_candidate = [&](auto&& f) {
         if (dense) {
             for (uint32_t i = tid; i < n_band; i += kRbThreads) f(s_cand[i]);
-        } else {
-            for_each_own(f);
+        } else {                                              // too many for the LDS list
+            walk_tiles(0, [&](int, uint32_t, uint64_t x) { f(x); });
         }
     };
     if (remain > 0u) {                                        // uniform
