@@ -996,7 +996,10 @@ __device__ __forceinline__ void redo_row(const char* hp_row, const char* Wv, int
 // (a few balanced iterations per thread); a row with more (ties by the thousand) walks the memory regions instead.
 constexpr int kRbBins = 2048;
 constexpr int kRbBitBatch = 24;                          // words of the bit mask per thread requested at once
-constexpr int kRbCandBatch = 22;                         // pairs of candidate slots per thread requested at once
+// Pairs of candidate slots per thread that are requested up front (the row's compact lists are T F / 512 of them per thread:
+// 7 at 32768 tokens, 19 at 128256, 35 at 262144): the launch picks the smallest instance that covers the lists.  What is
+// left of larger ones follows eight pairs at a time.
+constexpr int kRbBatches[3] = {8, 16, 24};
 // dynamic LDS of a resolve workgroup: with its 9 KB of static LDS two of them share a CU's 160 KB (a launch
 // of 512 rows is then one round of workgroups on 256 CUs)
 constexpr size_t kResolveLdsBytes = 69 * 1024, kResolveMaxLdsBytes = 148 * 1024;
@@ -1012,6 +1015,7 @@ __host__ __device__ inline int64_t resolve_off_words(int64_t tiles) { return (ti
 
 // first_magic: 2^32 / (first / 2), rounded up (a slot pair's tile by one multiplication: pair number * (first / 2) stays
 // below 2^32)
+template <int BATCH>
 __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int rows, int tn, int64_t m, int64_t k,
                                                                   uint32_t* scratch, int32_t* idx_out,
                                                                   uint32_t cand_cap, uint32_t first_magic) {
@@ -1044,9 +1048,9 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
     }
     const uint32_t pairs_total = (uint32_t)T * (uint32_t)(F / 2);             // slots two at a time (F is even)
     const u32x4* first2 = reinterpret_cast<const u32x4*>(first);
-    u32x4 reg[kRbCandBatch];
+    u32x4 reg[BATCH];
 #pragma unroll
-    for (int u = 0; u < kRbCandBatch; ++u) {
+    for (int u = 0; u < BATCH; ++u) {
         const uint32_t j = (uint32_t)u * kRbThreads + tid;
         reg[u] = first2[j < pairs_total ? j : pairs_total - 1];
     }
@@ -1125,8 +1129,17 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
             if (i + 1 < n) s_cand[at + i + 1] = ((uint64_t)v[3] << 32) | v[2];
         };
 #pragma unroll
-        for (int u = 0; u < kRbCandBatch; ++u) pack((uint32_t)u * kRbThreads + tid, reg[u]);
-        for (uint32_t j = (uint32_t)kRbCandBatch * kRbThreads + tid; j < pairs_total; j += kRbThreads) pack(j, first2[j]);
+        for (int u = 0; u < BATCH; ++u) pack((uint32_t)u * kRbThreads + tid, reg[u]);
+        for (uint32_t j0 = (uint32_t)BATCH * kRbThreads + tid; j0 < pairs_total; j0 += 8u * kRbThreads) {
+            u32x4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t j = j0 + (uint32_t)u * kRbThreads;
+                v[u] = first2[j < pairs_total ? j : pairs_total - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) pack(j0 + (uint32_t)u * kRbThreads, v[u]);
+        }
         __syncthreads();
     }
     auto for_each_candidate = [&](auto&& f) {
@@ -1312,8 +1325,16 @@ bool scores_supported(int chunks) { return chunks >= 1 && chunks <= 64; }
 // more than 64 KiB of dynamic LDS needs an explicit opt-in per kernel and device (called once per device,
 // outside any stream capture, by the library's device set-up)
 hipError_t configure_select_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&resolve_emit_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResolveMaxLdsBytes);
+    hipError_t e = hipSuccess;
+    auto opt_in = [&](auto kernel) {
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kResolveMaxLdsBytes);
+    };
+    opt_in(&resolve_emit_kernel<kRbBatches[0]>);
+    opt_in(&resolve_emit_kernel<kRbBatches[1]>);
+    opt_in(&resolve_emit_kernel<kRbBatches[2]>);
+    return e;
 }
 
 int64_t select_max_vocab() { return (int64_t)kSelThreads * kMaxBlocksPerRow * kEpt; }
@@ -1418,8 +1439,14 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     const size_t lds = fixed_bytes + (size_t)cand_cap * 8;
     const uint32_t half_first = (uint32_t)(L.first / 2);
     const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + half_first - 1) / half_first);
-    hipLaunchKernelGGL(resolve_emit_kernel, dim3((unsigned)a.rows), dim3(kRbThreads), lds, stream, a.V, a.rows, tn, L.m,
-                       a.k, a.scratch, a.idx_out, cand_cap, magic);
+    auto resolve = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kRbThreads), lds, stream, a.V, a.rows, tn, L.m, a.k, a.scratch,
+                           a.idx_out, cand_cap, magic);
+    };
+    const int64_t pairs_per_thread = (L.tiles * half_first + kRbThreads - 1) / kRbThreads;
+    if (pairs_per_thread <= kRbBatches[0]) resolve(&resolve_emit_kernel<kRbBatches[0]>);
+    else if (pairs_per_thread <= kRbBatches[1]) resolve(&resolve_emit_kernel<kRbBatches[1]>);
+    else resolve(&resolve_emit_kernel<kRbBatches[2]>);
     hipLaunchKernelGGL(redo_bracket_kernel<DT_BF16>, dim3((unsigned)(a.rows < kRedoBlocks ? a.rows : kRedoBlocks)),
                        dim3(kSelThreads), 0, stream, a.V, a.rows, tn, L.m, a.k, a.scratch, a.idx_out, a.hp, a.Wv, a.chunks);
     return hipGetLastError();
