@@ -1090,10 +1090,11 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
 
     // f(tile, place, candidate) for the candidates from place `from` of every tile on, from memory.  A tile is shared by as
     // many threads as there are for each (thousands of hidden rows leave a row few tiles, of tens of thousands of tokens),
-    // and a thread has several requests on their way (tied scores make long lists).
+    // at least four, so that their requests join, and a thread has several requests on their way (512 rows x 262144, k =
+    // 16384, many ties: one thread per tile 296 us, four 246, eight 252).
     auto walk_tiles = [&](int from, auto&& f) {
         constexpr int kFlight = 8;
-        const int sharers = T < kRbThreads ? kRbThreads / T : 1;
+        const int sharers = T * 4 < kRbThreads ? kRbThreads / T : 4;
         const int sub = tid % sharers;
         for (int t = tid / sharers; t < T; t += kRbThreads / sharers) {
             const int n = (int)cnt[t];
@@ -1381,6 +1382,9 @@ void bracket_sample(int chunks, int64_t rows, int64_t V, uint32_t* scratch, int3
 }
 
 hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
+    DeviceInfo di;
+    hipError_t e = device_info(&di);
+    if (e != hipSuccess) return e;
     const int tn = bracket_tn(a.chunks, a.rows, a.V);
     const BracketLayout L = bracket_layout(a.V, a.rows, tn, kSample);
     // ranks of the bracket in the sample: the number of sampled tokens among the row's k best is
@@ -1402,7 +1406,6 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     ep.item_tiles = L.tiles;
     ep.first_cap = L.first;
     ep.over_cap = tn;
-    hipError_t e;
     if (panel_supported(DT_BF16, a.chunks, a.rows, a.V)) {
         PanelArgs p{};
         p.x = a.hp;
@@ -1427,12 +1430,13 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     }
     if (e != hipSuccess) return e;
     // LDS of a resolve workgroup: the bit mask, the tiles' offsets and the row's candidates.  As many slots as keep two
-    // workgroups on a CU where a row's expected candidates fit into that, else as many as one workgroup can have: a row
-    // that packs its candidates is several times faster than one that walks them in memory.
+    // workgroups on a CU; with one row per CU or fewer, where that is of no use, as many as a row's expected candidates need
+    // (256 rows x 262144, k = 16384: 127 us with the candidates packed into LDS, 130 walked in memory, many ties 143 and 151;
+    // 512 rows 241 packed in two rounds of one workgroup per CU, 219 walked in one).
     const size_t fixed_bytes = ((size_t)L.words + (size_t)resolve_off_words(L.tiles)) * 4;
     const double expected = (double)((rank_lo < L.m ? rank_lo : L.m) - (rank_hi > 0 ? rank_hi : 0)) / (double)L.m * (double)a.V;
     const size_t want = fixed_bytes + (size_t)(expected * 1.15) * 8 + 1024;
-    const size_t budget = want <= kResolveLdsBytes ? kResolveLdsBytes : want <= kResolveMaxLdsBytes ? want : kResolveLdsBytes;
+    const size_t budget = a.rows <= di.cus && want > kResolveLdsBytes && want <= kResolveMaxLdsBytes ? want : kResolveLdsBytes;
     const size_t room = budget > fixed_bytes ? budget - fixed_bytes : 0;
     uint32_t cand_cap = (uint32_t)(room / 8);
     if (cand_cap < 1024u) cand_cap = 0u;                      // not worth a packing pass
