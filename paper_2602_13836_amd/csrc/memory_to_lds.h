@@ -36,4 +36,50 @@ __device__ __forceinline__ i32x4_t buffer_of(const char* base) {
                    (int)kBufferBytes, 0x00020000};
 }
 
+// The same for rows that a 32-bit offset does not reach (lists into a matrix of more than 4 GB, rows of 16 MB and more apart):
+// an address per lane.
+__device__ __forceinline__ void memory_to_lds_far(const char* p, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(p), "s"(lds) : "memory", "m0");
+}
+// what a lane past the end of a row reads there
+__device__ __attribute__((aligned(16))) const uint32_t kZeroUnit[4] = {0u, 0u, 0u, 0u};
+
+// Where one lane's 16 bytes of every request come from: NEAR an offset into the request's buffer, FAR an address.
+template <bool FAR>
+struct LaneSource;
+template <>
+struct LaneSource<false> {
+    uint32_t at;
+    __device__ __forceinline__ void set(const char* base, int64_t row, int64_t row_bytes, uint32_t byte) {
+        (void)base;
+        at = (uint32_t)row * (uint32_t)row_bytes + byte;
+    }
+};
+template <>
+struct LaneSource<true> {
+    const char* at;
+    __device__ __forceinline__ void set(const char* base, int64_t row, int64_t row_bytes, uint32_t byte) {
+        at = base + row * row_bytes + byte;
+    }
+};
+// one piece, `soff` bytes on from the lanes' sources (for a lane with `none`: zeros)
+__device__ __forceinline__ void bring(const LaneSource<false>& l, bool none, const i32x4_t buffer, int64_t soff, uint32_t lds) {
+    memory_to_lds(none ? kOutside : l.at, buffer, (uint32_t)soff, lds);
+}
+__device__ __forceinline__ void bring(const LaneSource<true>& l, bool none, const i32x4_t, int64_t soff, uint32_t lds) {
+    memory_to_lds_far(none ? reinterpret_cast<const char*>(kZeroUnit) : l.at + soff, lds);
+}
+// two of them, the second's place STEP bytes behind the first's
+template <int STEP>
+__device__ __forceinline__ void bring(const LaneSource<false>& l0, const LaneSource<false>& l1, bool none0, bool none1,
+                                      const i32x4_t buffer, int64_t soff, uint32_t lds) {
+    memory_to_lds<STEP>(none0 ? kOutside : l0.at, none1 ? kOutside : l1.at, buffer, (uint32_t)soff, lds);
+}
+template <int STEP>
+__device__ __forceinline__ void bring(const LaneSource<true>& l0, const LaneSource<true>& l1, bool none0, bool none1,
+                                      const i32x4_t buffer, int64_t soff, uint32_t lds) {
+    bring(l0, none0, buffer, soff, lds);
+    bring(l1, none1, buffer, soff, lds + STEP);
+}
+
 }  // namespace sv

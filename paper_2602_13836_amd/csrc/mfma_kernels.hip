@@ -201,124 +201,25 @@ __device__ __forceinline__ void store_ksplit(const GemvArgs& a, const f32x4_t su
     }
 }
 
-// Small item counts (a few thousand rows of M): too few 16-row tiles to fill the chip with one
-// wavefront per tile, so the 8 wavefronts of a workgroup share ONE tile and split the reduction:
-// wavefront w takes slices w, w + 8, ... of both operands straight from global memory (x is small and
-// L2-resident), and the partial 16 x 16 N products are summed through LDS at the end.
-// blockIdx.y walks groups of 16 NB hidden rows (a batch of hidden rows against a small M, e.g. the
-// selector's down-projection of Section 3.3 Step 1); output float32 or bf16 (round to nearest even);
-// the launch can also clear scratch words of a later kernel.
-template <int NB>
-__global__ __launch_bounds__(512) void skinny_mfma_ksplit_kernel(SV_HOT_PARAMS, const GemvArgs rest,
-                                                                 const int row_base) {
-    const GemvArgs a = with_hot(rest, m_base, idx_base, x_base, n_items_arg, m_row_bytes_arg, x_row_bytes_arg,
-                                n_items_dev_arg);
-    constexpr int WPB = 8;
-    constexpr int N = 16 * NB;
-    __shared__ f32x4_t s_part[WPB][NB][64];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int i = lane & 15;
-    const int g = lane >> 4;
-    const int C = a.chunks;
-    const int nslices = (C * 8 + kKC - 1) / kKC;
-    prepare_scratch(a);
-    const int row0 = row_base + (int)blockIdx.y * N;
-    const int rows_here = min(a.rows - row0, N);
-    const int64_t n_items = a.n_items_dev ? (int64_t)*a.n_items_dev : a.n_items;
-    const int64_t tile0 = (int64_t)blockIdx.x * 16;
-    if (tile0 >= n_items || rows_here <= 0 || !gate_open(a, n_items)) return;
-
-    int64_t item = tile0 + i;
-    if (item > n_items - 1) item = n_items - 1;
-    const int64_t mrow = a.idx ? (int64_t)a.idx[item] : item;
-    const u32x4* mp = reinterpret_cast<const u32x4*>(a.M + mrow * a.m_row_bytes) + g;
-    const u32x4* xp[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        int r = nb * 16 + i;
-        if (r > rows_here - 1) r = rows_here - 1;         // padding rows repeat the last one, never stored
-        xp[nb] = reinterpret_cast<const u32x4*>(a.x + (int64_t)(row0 + r) * a.x_row_bytes) + g;
-    }
-
-    f32x4_t acc[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    // whole slices are loaded without conditions (no branches between the loads); only a ragged last
-    // slice masks its units
-    const int nwhole = C / (kKC / 8);
-    auto load_slice = [&](int slice, u32x4 (&av)[kSteps], u32x4 (&bv)[NB][kSteps]) {
-        if (slice < nwhole) {
-#pragma unroll
-            for (int s = 0; s < kSteps; ++s) {
-                const int off = slice * (kKC / 8) + s * 4;
-                av[s] = mp[off];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) bv[nb][s] = xp[nb][off];
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < kSteps; ++s) {
-                const int off = slice * (kKC / 8) + s * 4;
-                const bool ok = off + g < C;
-                av[s] = ok ? mp[off] : zero16();
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) bv[nb][s] = ok ? xp[nb][off] : zero16();
-            }
-        }
-    };
-    auto multiply = [&](const u32x4 (&av)[kSteps], const u32x4 (&bv)[NB][kSteps]) {
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[s]),
-                                                                  __builtin_bit_cast(bf16x8_t, bv[nb][s]), acc[nb],
-                                                                  0, 0, 0);
-    };
-    int slice = wave;
-    if constexpr (NB == 1) {
-        // registers allow two slices per wavefront in flight: one memory latency instead of two
-        for (; slice + WPB < nwhole; slice += 2 * WPB) {
-            u32x4 av0[kSteps], bv0[NB][kSteps], av1[kSteps], bv1[NB][kSteps];
-            load_slice(slice, av0, bv0);
-            load_slice(slice + WPB, av1, bv1);
-            multiply(av0, bv0);
-            multiply(av1, bv1);
-        }
-    }
-    for (; slice < nslices; slice += WPB) {
-        u32x4 av[kSteps], bv[NB][kSteps];
-        load_slice(slice, av, bv);
-        multiply(av, bv);
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) s_part[wave][nb][lane] = acc[nb];
-    __syncthreads();
-    if (wave >= NB) return;
-    const int nb = wave;                                   // wavefront nb sums and stores hidden rows 16 nb ..
-    f32x4_t sum = s_part[0][nb][lane];
-#pragma unroll
-    for (int w = 1; w < WPB; ++w) sum += s_part[w][nb][lane];
-    store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
-}
-
-// The same product, fed from memory to LDS.  What bounded the kernel above is the shape of its loads: 16 rows x 64 bytes per
-// instruction reach a CU at about 30 GB/s from L2 (512 hidden rows x 256 items of 4096: 384 KB per workgroup, 14-15 us),
+// Small item counts (a few thousand rows of M): too few 16-row tiles to fill the chip with one wavefront per tile, so the 8
+// wavefronts of a workgroup share ONE tile and split the reduction: wavefront w takes slices w, w + 8, ... of both operands,
+// and the partial 16 x 16 N products are summed through LDS at the end.  blockIdx.y walks groups of 16 NB hidden rows (a batch
+// of hidden rows against a small M, e.g. the selector's down-projection of Section 3.3 Step 1); output float32 or bf16
+// (round to nearest even); the launch can also clear scratch words of a later kernel.
+// What bounds it is the way into the CU, and there the shape of the loads: fragments straight from memory, 16 rows x 64 bytes
+// per instruction, arrive at about 30 GB/s from L2 (512 hidden rows x 256 items of 4096: 384 KB per workgroup, 14-15 us),
 // 8 rows x 128 bytes at several times that (the same product 9.7 us; 8 rows x 8192 listed rows of 3840 15.6 -> 12.8; whole
-// steps over 8192 listed rows of 4096: 8 rows 19.8 -> 17.2, 32 rows 30.9 -> 21.7).  Here every wavefront brings its slices in as whole 128-byte lines, 64
-// elements of its 16 rows of M and 16 NB hidden rows at a time, into a ring of DEPTH chunks of its own -- no registers
-// in flight, no barrier, no conditional load -- and reads its fragments from there.  (Rows of 128 bytes, the 16-byte unit u
-// of row r at place u ^ ((r >> 1) & 7): the fragment reads, 16 rows x 4 units, run at 218 B/clk.)  The operands of every
-// MFMA and their order are those of the kernel above, so the result is the same bit for bit.
-// Hidden rows past the last, and units past a row's end, are requested from outside the buffer and arrive as zeros.
-constexpr int kDirectWaves = 8;
+// steps over 8192 listed rows of 4096: 8 rows 19.8 -> 17.2, 32 rows 30.9 -> 21.7).  So every wavefront brings its slices in
+// as whole 128-byte lines, 64 elements of its 16 rows of M and 16 NB hidden rows at a time, into a ring of DEPTH chunks of its
+// own -- no registers in flight, no barrier, no conditional load -- and reads its fragments from there.  (Rows of 128 bytes, the 16-byte unit u
+// of row r at place u ^ ((r >> 1) & 7): the fragment reads, 16 rows x 4 units, run at 218 B/clk.)
+// Hidden rows past the last arrive as zeros (FAR: repeat it) and are never stored; units past a row's end are zeros.  FAR:
+// lanes' sources are addresses (see memory_to_lds.h), for lists into matrices of more than 4 GB and rows of 128 MB apart.
+constexpr int kSplitWaves = 8;
 template <int NB, int DEPTH>
-constexpr size_t direct_lds_bytes() { return (size_t)kDirectWaves * DEPTH * (16 + 16 * NB) * 128; }
-template <int NB, int DEPTH>
-__global__ __launch_bounds__(64 * kDirectWaves) void ksplit_direct_kernel(SV_HOT_PARAMS, const GemvArgs rest, const int row_base) {
+constexpr size_t ksplit_lds_bytes() { return (size_t)kSplitWaves * DEPTH * (16 + 16 * NB) * 128; }
+template <int NB, int DEPTH, bool FAR>
+__global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS, const GemvArgs rest, const int row_base) {
     const GemvArgs a = with_hot(rest, m_base, idx_base, x_base, n_items_arg, m_row_bytes_arg, x_row_bytes_arg,
                                 n_items_dev_arg);
     constexpr int N = 16 * NB;
@@ -342,33 +243,36 @@ __global__ __launch_bounds__(64 * kDirectWaves) void ksplit_direct_kernel(SV_HOT
     }
     const int l8 = lane >> 3;
     const uint32_t unit0 = (uint32_t)((lane & 7) ^ (l8 >> 1)), unit1 = unit0 ^ 4u;       // of rows l8 and l8 + 8 of a 16-row group
-    uint32_t voff_m[2], voff_x[2 * NB];
+    const char* const base_m = a.idx ? a.M : a.M + tile0 * a.m_row_bytes;
+    const char* const base_x = a.x + (int64_t)row0 * a.x_row_bytes;
+    LaneSource<FAR> src_m[2], src_x[2 * NB];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         int64_t item = tile0 + 8 * j + l8;
         if (item > n_items - 1) item = n_items - 1;
-        const uint32_t row = a.idx ? (uint32_t)a.idx[item] : (uint32_t)(item - tile0);
-        voff_m[j] = row * (uint32_t)a.m_row_bytes + (j ? unit1 : unit0) * 16u;
+        src_m[j].set(base_m, a.idx ? (int64_t)a.idx[item] : item - tile0, a.m_row_bytes, (j ? unit1 : unit0) * 16u);
     }
 #pragma unroll
     for (int j = 0; j < 2 * NB; ++j) {
         const int r = 8 * j + l8;
-        voff_x[j] = r < rows_here ? (uint32_t)r * (uint32_t)a.x_row_bytes + (j & 1 ? unit1 : unit0) * 16u : kOutside;
+        src_x[j].set(base_x, min(r, rows_here - 1), a.x_row_bytes, (j & 1 ? unit1 : unit0) * 16u);
+        if constexpr (!FAR) {
+            if (r >= rows_here) src_x[j].at = kOutside;
+        }
     }
-    const i32x4_t buf_m = buffer_of(a.idx ? a.M : a.M + tile0 * a.m_row_bytes);
-    const i32x4_t buf_x = buffer_of(a.x + (int64_t)row0 * a.x_row_bytes);
+    const i32x4_t buf_m = buffer_of(base_m), buf_x = buffer_of(base_x);
     unsigned char* ring = smem + (size_t)wave * DEPTH * kChunkB;
     const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)(wave * DEPTH * kChunkB);
     // chunk c of the wavefront: 64 elements of slice wave + 8 (c / 4), part c % 4
-    const int nch = wave < nslices ? 4 * ((nslices - wave + kDirectWaves - 1) / kDirectWaves) : 0;
+    const int nch = wave < nslices ? 4 * ((nslices - wave + kSplitWaves - 1) / kSplitWaves) : 0;
     auto request = [&](int c, int stage) {
-        const int first_unit = (wave + kDirectWaves * (c >> 2)) * (kKC / 8) + (c & 3) * 8;
+        const int first_unit = (wave + kSplitWaves * (c >> 2)) * (kKC / 8) + (c & 3) * 8;
         const bool out0 = first_unit + (int)unit0 >= C, out1 = first_unit + (int)unit1 >= C;      // (past the last chunk: all of it)
-        const uint32_t soff = (uint32_t)first_unit * 16u, at = lds + (uint32_t)(stage * kChunkB);
-        memory_to_lds<1024>(out0 ? kOutside : voff_m[0], out1 ? kOutside : voff_m[1], buf_m, soff, at);
+        const int64_t soff = (int64_t)first_unit * 16;
+        const uint32_t at = lds + (uint32_t)(stage * kChunkB);
+        bring<1024>(src_m[0], src_m[1], out0, out1, buf_m, soff, at);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            memory_to_lds<1024>(out0 ? kOutside : voff_x[2 * nb], out1 ? kOutside : voff_x[2 * nb + 1], buf_x, soff, at + 2048u * (nb + 1));
+        for (int nb = 0; nb < NB; ++nb) bring<1024>(src_x[2 * nb], src_x[2 * nb + 1], out0, out1, buf_x, soff, at + 2048u * (nb + 1));
     };
     f32x4_t acc[NB];
 #pragma unroll
@@ -408,7 +312,7 @@ __global__ __launch_bounds__(64 * kDirectWaves) void ksplit_direct_kernel(SV_HOT
     const int nb = wave;                                   // wavefront nb sums and stores hidden rows 16 nb ..
     f32x4_t sum = s_part[nb * 64 + lane];
 #pragma unroll
-    for (int w = 1; w < kDirectWaves; ++w) sum += s_part[(w * NB + nb) * 64 + lane];
+    for (int w = 1; w < kSplitWaves; ++w) sum += s_part[(w * NB + nb) * 64 + lane];
     store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
 }
 
@@ -430,34 +334,31 @@ hipError_t opt_in_lds_all_nb() {
 }
 
 // byte offsets in 32 bits: from a tile's first row for a whole matrix, from the matrix itself for rows by list
-bool direct_fits(const GemvArgs& a) {
+bool near(const GemvArgs& a) {
     constexpr int64_t kSpan = (int64_t)kBufferBytes;
     if (32 * a.x_row_bytes > kSpan || 16 * a.m_row_bytes > kSpan) return false;
     return a.idx == nullptr || (a.m_rows > 0 && a.m_rows <= kSpan / a.m_row_bytes);
 }
 
 template <int NB, int DEPTH>
-hipError_t launch_direct(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
-    const int64_t bx = (a.n_items + 15) / 16;
-    hipLaunchKernelGGL((ksplit_direct_kernel<NB, DEPTH>), dim3((unsigned)bx, (unsigned)groups), dim3(64 * kDirectWaves),
-                       (direct_lds_bytes<NB, DEPTH>()), stream, SV_HOT_ARGS(a), a, row0);
-    return hipGetLastError();
+hipError_t launch_ksplit_depth(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n_items + 15) / 16), (unsigned)groups), dim3(64 * kSplitWaves),
+                           (ksplit_lds_bytes<NB, DEPTH>()), stream, SV_HOT_ARGS(a), a, row0);
+        return hipGetLastError();
+    };
+    return near(a) ? go(&ksplit_kernel<NB, DEPTH, false>) : go(&ksplit_kernel<NB, DEPTH, true>);
 }
 
 template <int NB>
 hipError_t launch_ksplit(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
-    const int64_t bx = (a.n_items + 15) / 16;
-    if (direct_fits(a)) {
-        DeviceInfo di;
-        const hipError_t e = device_info(&di);
-        if (e != hipSuccess) return e;
-        // one workgroup per CU: a deep ring; more workgroups than that: rings that let two share a CU
-        if (NB == 2) return launch_direct<2, 3>(a, row0, groups, stream);
-        return bx * groups <= di.cus ? launch_direct<1, 4>(a, row0, groups, stream) : launch_direct<1, 2>(a, row0, groups, stream);
-    }
-    hipLaunchKernelGGL((skinny_mfma_ksplit_kernel<NB>), dim3((unsigned)bx, (unsigned)groups), dim3(512), 0, stream,
-                       SV_HOT_ARGS(a), a, row0);
-    return hipGetLastError();
+    if (NB == 2) return launch_ksplit_depth<2, 3>(a, row0, groups, stream);
+    DeviceInfo di;
+    const hipError_t e = device_info(&di);
+    if (e != hipSuccess) return e;
+    // one workgroup per CU: a deep ring; more workgroups than that: rings that let two share a CU
+    return (a.n_items + 15) / 16 * groups <= di.cus ? launch_ksplit_depth<1, 4>(a, row0, groups, stream)
+                                                    : launch_ksplit_depth<1, 2>(a, row0, groups, stream);
 }
 
 template <int WPB, int NB>
@@ -483,12 +384,15 @@ hipError_t launch_w(const GemvArgs& a, int row0, int nrows, hipStream_t stream) 
 hipError_t configure_skinny_mfma_lds() {
     hipError_t e = opt_in_lds_all_nb<2>();
     if (e == hipSuccess) e = opt_in_lds_all_nb<4>();
-    auto direct = [&](auto kernel, size_t bytes) {
+    auto opt_in = [&](auto kernel, size_t bytes) {
         if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     };
-    direct(&ksplit_direct_kernel<1, 2>, direct_lds_bytes<1, 2>());
-    direct(&ksplit_direct_kernel<1, 4>, direct_lds_bytes<1, 4>());
-    direct(&ksplit_direct_kernel<2, 3>, direct_lds_bytes<2, 3>());
+    opt_in(&ksplit_kernel<1, 2, false>, ksplit_lds_bytes<1, 2>());
+    opt_in(&ksplit_kernel<1, 2, true>, ksplit_lds_bytes<1, 2>());
+    opt_in(&ksplit_kernel<1, 4, false>, ksplit_lds_bytes<1, 4>());
+    opt_in(&ksplit_kernel<1, 4, true>, ksplit_lds_bytes<1, 4>());
+    opt_in(&ksplit_kernel<2, 3, false>, ksplit_lds_bytes<2, 3>());
+    opt_in(&ksplit_kernel<2, 3, true>, ksplit_lds_bytes<2, 3>());
     return e;
 }
 

@@ -12,14 +12,14 @@
 // hidden-row tiles of one TN block) are given consecutive slots on the same XCD, so that M comes from HBM once and from
 // that die's L2 afterwards (measured: HBM traffic 1.3 x the size of M at 512 hidden rows).
 //
-// Four forms of the main loop.  The plain one (slices through registers into LDS rows padded to 144 bytes) leaves the
+// Three forms of the main loop.  The plain one (slices through registers into LDS rows padded to 144 bytes) leaves the
 // order of loads, LDS traffic and MFMAs to the compiler and relies on several workgroups per CU to overlap them: 17 to 32
 // hidden rows where the ring does not win.  The ring (17 to 64 rows, bound by the one pass over M) has three slices on
 // their way from memory to LDS.  In the alternating one (more rows) the two wavefronts of a SIMD take turns between
-// multiplying and memory work, a barrier per turn, and slices go from memory to LDS directly.  The interleaved one serves
-// what the alternating one cannot address (rows of 16 MB and more; lists into matrices of more than 4 GB): every wavefront
-// reads its operand fragments one 16-element step ahead and spreads the LDS copy of the next slice over the four steps of
-// the current one, with scheduling-group fences pinning that order against the compiler's own scheduler.
+// multiplying and memory work, a barrier per turn, and slices go from memory to LDS directly.  The latter two name a lane's
+// source by a 32-bit offset into a buffer; where that does not reach (rows of 16 MB and more apart -- hidden states that are
+// the last positions of long sequences --, lists into matrices of more than 4 GB) by an address (FAR), which costs a 64-bit
+// addition per request.
 #include "sv_device.h"
 #include "sv_launch.h"
 
@@ -38,21 +38,6 @@ constexpr int kTK = 64;                  // reduction elements per slice (128 by
 constexpr int kRowB = kTK * 2 + 16;      // padded LDS row (144 B = 36 words)
 constexpr int kXcds = 8;
 
-// Wanted instruction order of one 16-element step: M MFMAs with R LDS reads, W LDS writes and W global
-// loads spread evenly between them (the sizes of a scheduling group must be compile-time constants).
-template <int M, int R, int W, int I>
-__device__ __forceinline__ void sched_pattern() {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
-    constexpr int r = (I + 1) * R / M - I * R / M;
-    if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);  // LDS reads
-    constexpr int w = (I + 1) * W / M - I * W / M;
-    if constexpr (w > 0) {
-        __builtin_amdgcn_sched_group_barrier(0x200, w, 0);                   // LDS writes
-        __builtin_amdgcn_sched_group_barrier(0x020, w, 0);                   // global loads
-    }
-    if constexpr (I + 1 < M) sched_pattern<M, R, W, I + 1>();
-}
-
 // LDS the bracket epilogue needs (it reuses the operand buffers after the main loop): per tile row the
 // bracket and a candidate counter (16 bytes reserved), per wavefront the scores of one 32-row band
 template <int GM, int GN, int WM, int WN>
@@ -60,22 +45,23 @@ constexpr size_t bracket_lds_bytes() {
     return (size_t)32 * GM * WM * 16 + (size_t)GM * GN * (16 * WN * 64) * 4;
 }
 
+enum { LOOP_PLAIN = 0, LOOP_TURNS = 1, LOOP_RING = 2 };
 template <int GM, int GN, int WM, int WN, int PIPE>
 constexpr size_t tile_lds_bytes() {
-    return PIPE == 3   ? (size_t)4 * (32 * GM * WM + 32 * GN * WN) * kTK * 2
-           : PIPE == 2 ? (size_t)(2 * 32 * GM * WM + 3 * 32 * GN * WN) * kTK * 2
-                       : (size_t)2 * (32 * GM * WM + 32 * GN * WN) * kRowB;
+    return PIPE == LOOP_RING ? (size_t)4 * (32 * GM * WM + 32 * GN * WN) * kTK * 2
+           : PIPE == LOOP_TURNS ? (size_t)(2 * 32 * GM * WM + 3 * 32 * GN * WN) * kTK * 2
+                                : (size_t)2 * (32 * GM * WM + 32 * GN * WN) * kRowB;
 }
 
 // GM x GN wavefronts; each owns WM x WN MFMA tiles of 32 x 32: TM = 32 GM WM hidden rows, TN = 32 GN WN items.
-// PIPE: 0 the plain main loop, 1 the interleaved, 2 the alternating one, 3 the ring (both fed from memory to LDS).  EPI: what happens to the product --
+// PIPE: the main loop (the last two are fed from memory to LDS, FAR: from addresses).  EPI: what happens to the product --
 //   EPI_STORE    it is stored;
 //   EPI_BRACKET  the epilogue of the bracketed selection (Section 3.3 Step 2 for a batch of hidden rows)
 //                classifies it, nothing is stored;
 //   EPI_PICK     Section 3.3 Step 3 for a batch of hidden rows with one index list each: only the entries
 //                a row asks for are stored, straight to their place in logits_out.
 enum { EPI_STORE = 0, EPI_BRACKET = 1, EPI_PICK = 2 };
-template <int GM, int GN, int WM, int WN, int PIPE, int EPI>
+template <int GM, int GN, int WM, int WN, int PIPE, int EPI, bool FAR>
 __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs a, const BracketEpi ep, const PickEpi pk) {
     constexpr int kThreads = 64 * GM * GN;
     constexpr int kRowsPerPass = kThreads / 8;           // loader: 8 threads per 128-byte row slice
@@ -112,7 +98,7 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
     const int64_t tile0 = it * tn;
     const int64_t tile_end = tile0 + tn < n_items ? tile0 + tn : n_items;
 
-    // loader role: 8 threads cover the 128-byte slice of one row, 32 rows per pass
+    // loader role of the plain loop: 8 threads cover the 128-byte slice of one row, 32 rows per pass
     const int piece = tid & 7, r0 = tid >> 3;
     const u32x4* pa[QA];
     const u32x4* pb[QB];
@@ -199,7 +185,7 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
                     acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m], bf[n], acc[m][n], 0, 0, 0);
         }
     };
-    if constexpr (PIPE == 3) {
+    if constexpr (PIPE == LOOP_RING) {
         // Up to 64 hidden rows: one pass over M at the rate of the memory system.  A ring of four stages in LDS, three slices
         // on their way (96 KB of M per CU with 64 x 256 tiles), one barrier per slice: behind it everybody has slice ks and
         // nobody reads slice ks - 1 any more, whose stage takes slice ks + 3.  Layout and requests as in the loop below.
@@ -212,32 +198,29 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         const int l8 = lane >> 3;
         const int unit = (lane & 7) ^ ((4 * (swave & 1) + (l8 >> 1)) & 7);
         const bool lane_past = (nk - 1) * 8 + unit >= C;     // of the last slice
-        uint32_t voff_a[LA], voff_b[LB];
+        const char* const base_a = a.x + (int64_t)rt * TM * a.x_row_bytes;
+        const char* const base_b = a.idx ? a.M : a.M + tile0 * a.m_row_bytes;
+        LaneSource<FAR> src_a[LA], src_b[LB];
 #pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int row = min(rt * TM + kPass * i + 8 * swave + l8, a.rows - 1);
-            voff_a[i] = (uint32_t)(row - rt * TM) * (uint32_t)a.x_row_bytes + (uint32_t)unit * 16u;
-        }
+        for (int i = 0; i < LA; ++i)
+            src_a[i].set(base_a, min(rt * TM + kPass * i + 8 * swave + l8, a.rows - 1) - rt * TM, a.x_row_bytes, (uint32_t)unit * 16u);
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             int64_t item = tile0 + kPass * i + 8 * swave + l8;
             if (item > tile_end - 1) item = tile_end - 1;
-            const uint32_t row = a.idx ? (uint32_t)a.idx[item] : (uint32_t)(item - tile0);
-            voff_b[i] = row * (uint32_t)a.m_row_bytes + (uint32_t)unit * 16u;
+            src_b[i].set(base_b, a.idx ? (int64_t)a.idx[item] : item - tile0, a.m_row_bytes, (uint32_t)unit * 16u);
         }
-        const i32x4_t buf_a = buffer_of(a.x + (int64_t)rt * TM * a.x_row_bytes);
-        const i32x4_t buf_b = buffer_of(a.idx ? a.M : a.M + tile0 * a.m_row_bytes);
+        const i32x4_t buf_a = buffer_of(base_a), buf_b = buffer_of(base_b);
         auto request = [&](int ks) {
             const int s = eff(ks);
             const bool cut = s == nk - 1 && lane_past;
             const uint32_t at = lds0 + (uint32_t)((ks & 3) * kStageB + swave * 1024);
 #pragma unroll
             for (int i = 0; i < LB; i += 2)
-                memory_to_lds<kPass * 128>(cut ? kOutside : voff_b[i], cut ? kOutside : voff_b[i + 1], buf_b, (uint32_t)s * 128u,
-                                           at + (uint32_t)(i * kPass * 128));
+                bring<kPass * 128>(src_b[i], src_b[i + 1], cut, cut, buf_b, (int64_t)s * 128, at + (uint32_t)(i * kPass * 128));
 #pragma unroll
             for (int i = 0; i < LA; ++i)
-                memory_to_lds(cut ? kOutside : voff_a[i], buf_a, (uint32_t)s * 128u, at + (uint32_t)(TN * 128 + i * kPass * 128));
+                bring(src_a[i], cut, buf_a, (int64_t)s * 128, at + (uint32_t)(TN * 128 + i * kPass * 128));
         };
         const int swz = ((lane >> 5) ^ ((lane >> 1) & 7)) * 16;
         const int fa0 = (TN + wr * 32 * WM + (lane & 31)) * 128 + swz, fb0 = (wc * 32 * WN + (lane & 31)) * 128 + swz;
@@ -267,7 +250,7 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
             }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (slices past the end: requested, never read)
-    } else if constexpr (PIPE == 2) {
+    } else if constexpr (PIPE == LOOP_TURNS) {
         // Two wavefronts share a SIMD and take turns, a barrier ending every turn: while one multiplies a
         // 16-element step (nothing but its MFMAs), the other issues its memory work -- the LDS reads of its NEXT step's
         // fragments and a few requests that bring a later slice from memory straight into LDS -- and waits for none of
@@ -302,28 +285,25 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         const int l8 = lane >> 3;
         const int unit = (lane & 7) ^ ((4 * (swave & 1) + (l8 >> 1)) & 7);
         const bool lane_past = (nk - 1) * 8 + unit >= C;     // of the last slice
-        uint32_t voff_a[LA], voff_b[LB];
+        const char* const base_a = a.x + (int64_t)rt * TM * a.x_row_bytes;
+        const char* const base_b = a.idx ? a.M : a.M + tile0 * a.m_row_bytes;
+        LaneSource<FAR> src_a[LA], src_b[LB];
 #pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int row = min(rt * TM + 64 * i + 8 * swave + l8, a.rows - 1);
-            voff_a[i] = (uint32_t)(row - rt * TM) * (uint32_t)a.x_row_bytes + (uint32_t)unit * 16u;
-        }
+        for (int i = 0; i < LA; ++i)
+            src_a[i].set(base_a, min(rt * TM + 64 * i + 8 * swave + l8, a.rows - 1) - rt * TM, a.x_row_bytes, (uint32_t)unit * 16u);
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             int64_t item = tile0 + 64 * i + 8 * swave + l8;
             if (item > tile_end - 1) item = tile_end - 1;
-            const uint32_t row = a.idx ? (uint32_t)a.idx[item] : (uint32_t)(item - tile0);
-            voff_b[i] = row * (uint32_t)a.m_row_bytes + (uint32_t)unit * 16u;
+            src_b[i].set(base_b, a.idx ? (int64_t)a.idx[item] : item - tile0, a.m_row_bytes, (uint32_t)unit * 16u);
         }
-        const i32x4_t buf_a = buffer_of(a.x + (int64_t)rt * TM * a.x_row_bytes);
-        const i32x4_t buf_b = buffer_of(a.idx ? a.M : a.M + tile0 * a.m_row_bytes);
+        const i32x4_t buf_a = buffer_of(base_a), buf_b = buffer_of(base_b);
         auto request_a = [&](int ks, int stage) {
             const int s = eff(ks);
             const bool cut = s == nk - 1 && lane_past;
 #pragma unroll
             for (int i = 0; i < LA; i += 2)
-                memory_to_lds<8192>(cut ? kOutside : voff_a[i], cut ? kOutside : voff_a[i + 1], buf_a, (uint32_t)s * 128u,
-                                    lds_a + (uint32_t)(stage * kAStage + i * 8192));
+                bring<8192>(src_a[i], src_a[i + 1], cut, cut, buf_a, (int64_t)s * 128, lds_a + (uint32_t)(stage * kAStage + i * 8192));
         };
         auto request_b = [&](int ks, int stage, int lo, int hi) {
             const int s = eff(ks);
@@ -331,8 +311,7 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
 #pragma unroll
             for (int i = 0; i < LB; i += 2)
                 if (i >= lo && i < hi)
-                    memory_to_lds<8192>(cut ? kOutside : voff_b[i], cut ? kOutside : voff_b[i + 1], buf_b, (uint32_t)s * 128u,
-                                        lds_b + (uint32_t)(stage * kBStage + i * 8192));
+                    bring<8192>(src_b[i], src_b[i + 1], cut, cut, buf_b, (int64_t)s * 128, lds_b + (uint32_t)(stage * kBStage + i * 8192));
         };
         // fragments: lane = (row within 32, k-group); unit 2 kk + k-group of a row, swizzled
         const int swz = ((lane >> 5) ^ ((lane >> 1) & 7)) * 16;
@@ -397,87 +376,6 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         if (!second) turn_ends();              // ... and the first ends one turn earlier: the same count for all
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (slices past the end: requested, never read)
         turn_ends();
-    } else if constexpr (PIPE == 1) {
-        // the slice is walked in four 16-element steps with the operand fragments of the next step
-        // already on their way from LDS while the current step multiplies
-        u32x4 ga[QA], gb[QB];
-        bf16x8_t fa[2][WM], fb[2][WN];
-        auto read_frags = [&](int buf, int kk, bf16x8_t (&A)[WM], bf16x8_t (&B)[WN]) {
-            const unsigned char* sa = smem + (size_t)buf * kStage + a_off + kk * 32;
-            const unsigned char* sb = smem + (size_t)buf * kStage + b_off + kk * 32;
-#pragma unroll
-            for (int m = 0; m < WM; ++m)
-                A[m] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(sa + (size_t)(32 * m) * kRowB));
-#pragma unroll
-            for (int n = 0; n < WN; ++n)
-                B[n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(sb + (size_t)(32 * n) * kRowB));
-        };
-        auto mfmas = [&](const bf16x8_t (&A)[WM], const bf16x8_t (&B)[WN]) {
-#pragma unroll
-            for (int m = 0; m < WM; ++m)
-#pragma unroll
-                for (int n = 0; n < WN; ++n)
-                    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[m], B[n], acc[m][n], 0, 0, 0);
-        };
-        // The copy of the next slice into LDS is cut into four parts, one per step; each part's
-        // registers are reloaded with the slice after next at once.  Part 0 goes right after the
-        // barrier (the buffer just read is free then), parts 1..3 in the first three steps.
-        static_assert(QA % 4 == 0 && QB % 4 == 0, "the staged slice is copied in four parts");
-        constexpr int PA = QA / 4, PB = QB / 4;
-        auto load_part = [&](int j, int ks) {
-            const int u = min(eff(ks) * 8 + piece, C - 1);
-#pragma unroll
-            for (int q = 0; q < PB; ++q) gb[j * PB + q] = pb[j * PB + q][u];
-#pragma unroll
-            for (int q = 0; q < PA; ++q) ga[j * PA + q] = pa[j * PA + q][u];
-        };
-        auto store_part = [&](int j, int ks) {
-            unsigned char* base = smem + (size_t)(ks & 1) * kStage + (size_t)r0 * kRowB + piece * 16;
-            const bool past = ks >= nk || eff(ks) * 8 + piece >= C;
-#pragma unroll
-            for (int q = 0; q < PA; ++q)
-                *reinterpret_cast<u32x4*>(base + (size_t)(kRowsPerPass * (j * PA + q)) * kRowB) = past ? zero16() : ga[j * PA + q];
-#pragma unroll
-            for (int q = 0; q < PB; ++q)
-                *reinterpret_cast<u32x4*>(base + (size_t)(TM + kRowsPerPass * (j * PB + q)) * kRowB) = past ? zero16() : gb[j * PB + q];
-        };
-        // one step: fragment reads of the next step, a quarter of the slice copy, and this step's MFMAs,
-        // interleaved so that every memory instruction issues in the shadow of a running MFMA
-        auto interleave = [&]() {
-            sched_pattern<WM * WN, WM + WN, PA + PB, 0>();
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        load(0, ga, gb);
-        store(0, ga, gb);
-        load(1, ga, gb);
-        __syncthreads();
-        store_part(0, 1);
-        load_part(0, 2);
-        read_frags(0, 0, fa[0], fb[0]);
-        for (int ks = 0; ks < nk; ++ks) {
-            const int buf = ks & 1;
-            read_frags(buf, 1, fa[1], fb[1]);
-            store_part(1, ks + 1);
-            load_part(1, ks + 2);
-            mfmas(fa[0], fb[0]);
-            interleave();
-            read_frags(buf, 2, fa[0], fb[0]);
-            store_part(2, ks + 1);
-            load_part(2, ks + 2);
-            mfmas(fa[1], fb[1]);
-            interleave();
-            read_frags(buf, 3, fa[1], fb[1]);
-            store_part(3, ks + 1);
-            load_part(3, ks + 2);
-            mfmas(fa[0], fb[0]);
-            interleave();
-            __syncthreads();     // slice ks + 1 is complete in the other buffer; this one is free again
-            read_frags(buf ^ 1, 0, fa[0], fb[0]);
-            store_part(0, ks + 2);
-            load_part(0, ks + 3);
-            mfmas(fa[1], fb[1]);
-            interleave();
-        }
     } else {
         // Two register sets keep two slices in flight from global memory while a third is multiplied
         // out of LDS: on entry to step(ks, set) the set holds slice ks + 1 (the other set slice ks + 2).
@@ -681,12 +579,30 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         }
 }
 
+// The loops fed from memory to LDS keep byte offsets in 32 bits where these reach: from a tile's first row for a whole matrix,
+// from the matrix itself for rows by list.  The same slices in the same order either way.
+bool near(const GemvArgs& a) {
+    constexpr int64_t kSpan = (int64_t)kBufferBytes;
+    if (256 * a.x_row_bytes > kSpan || 256 * a.m_row_bytes > kSpan) return false;
+    return a.idx == nullptr || (a.m_rows > 0 && a.m_rows <= kSpan / a.m_row_bytes);
+}
+// (the bracketed selection's operands are dense, and a W_vocab with rows of 16 MB would not fit any memory)
+template <int PIPE, int EPI>
+constexpr bool has_far() { return PIPE != LOOP_PLAIN && EPI != EPI_BRACKET; }
+
 // more than 64 KiB of dynamic LDS needs an explicit opt-in per kernel instance and device
 template <int GM, int GN, int WM, int WN, int PIPE, int EPI>
 hipError_t opt_in_lds() {
-    if (tile_lds_bytes<GM, GN, WM, WN, PIPE>() <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_mfma_kernel<GM, GN, WM, WN, PIPE, EPI>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds_bytes<GM, GN, WM, WN, PIPE>());
+    constexpr size_t bytes = tile_lds_bytes<GM, GN, WM, WN, PIPE>();
+    if (bytes <= 64 * 1024) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_mfma_kernel<GM, GN, WM, WN, PIPE, EPI, false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if constexpr (has_far<PIPE, EPI>()) {
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_mfma_kernel<GM, GN, WM, WN, PIPE, EPI, true>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    }
+    return e;
 }
 
 template <int GM, int GN, int WM, int WN, int PIPE, int EPI = EPI_STORE>
@@ -700,10 +616,13 @@ hipError_t launch_tile(const GemvArgs& a, hipStream_t stream, const BracketEpi& 
     const int64_t groups = (IT + kXcds - 1) / kXcds;            // item tiles per XCD, rounded up
     const int64_t bx = groups * RT * kXcds;
     if (bx > 0x7fffffffLL) return hipErrorInvalidValue;         // more tiles than a grid dimension holds
-    const size_t lds = tile_lds_bytes<GM, GN, WM, WN, PIPE>();     // above 64 KiB: opted in by configure_tile_mfma_lds()
-    hipLaunchKernelGGL((tile_mfma_kernel<GM, GN, WM, WN, PIPE, EPI>), dim3((unsigned)bx), dim3(64 * GM * GN), lds, stream,
-                       a, ep, pk);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {                                // LDS above 64 KiB: opted in by configure_tile_mfma_lds()
+        hipLaunchKernelGGL(kernel, dim3((unsigned)bx), dim3(64 * GM * GN), (tile_lds_bytes<GM, GN, WM, WN, PIPE>()), stream, a, ep, pk);
+        return hipGetLastError();
+    };
+    if (PIPE == LOOP_PLAIN || near(a)) return go(&tile_mfma_kernel<GM, GN, WM, WN, PIPE, EPI, false>);
+    if constexpr (has_far<PIPE, EPI>()) return go(&tile_mfma_kernel<GM, GN, WM, WN, PIPE, EPI, true>);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -717,24 +636,13 @@ hipError_t configure_tile_mfma_lds() {
         if (e == hipSuccess) e = fn(std::integral_constant<int, EPI_BRACKET>{});
         if (e == hipSuccess) e = fn(std::integral_constant<int, EPI_PICK>{});
     };
-    if (e == hipSuccess) e = opt_in_lds<1, 8, 2, 1, 0, EPI_STORE>();
-    if (e == hipSuccess) e = opt_in_lds<1, 8, 2, 1, 3, EPI_STORE>();
-    if (e == hipSuccess) e = opt_in_lds<1, 4, 1, 1, 3, EPI_STORE>();
-    if (e == hipSuccess) e = opt_in_lds<2, 4, 1, 1, 3, EPI_STORE>();
-    if (e == hipSuccess) e = opt_in_lds<2, 4, 2, 1, 2, EPI_STORE>();
-    all_epilogues([](auto ec) { return opt_in_lds<2, 4, 2, 2, 2, decltype(ec)::value>(); });
-    all_epilogues([](auto ec) { return opt_in_lds<2, 4, 4, 2, 2, decltype(ec)::value>(); });
-    all_epilogues([](auto ec) { return opt_in_lds<2, 4, 4, 2, 1, decltype(ec)::value>(); });
+    if (e == hipSuccess) e = opt_in_lds<1, 8, 2, 1, LOOP_RING, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<1, 4, 1, 1, LOOP_RING, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<2, 4, 1, 1, LOOP_RING, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<2, 4, 2, 1, LOOP_TURNS, EPI_STORE>();
+    all_epilogues([](auto ec) { return opt_in_lds<2, 4, 2, 2, LOOP_TURNS, decltype(ec)::value>(); });
+    all_epilogues([](auto ec) { return opt_in_lds<2, 4, 4, 2, LOOP_TURNS, decltype(ec)::value>(); });
     return e;
-}
-
-// The loop fed from memory to LDS keeps byte offsets in 32 bits: from a tile's first row for a whole matrix, from the
-// matrix itself for rows by list.  Every loop adds a token's products in the same order, so the choice never changes a
-// result.
-static bool direct_fits(const GemvArgs& a) {
-    constexpr int64_t kSpan = (int64_t)kBufferBytes;
-    if (256 * a.x_row_bytes > kSpan || 256 * a.m_row_bytes > kSpan) return false;
-    return a.idx == nullptr || (a.m_rows > 0 && a.m_rows <= kSpan / a.m_row_bytes);
 }
 
 // Tiles of the alternating loop for more than 64 hidden rows.  A tile walks the whole reduction whatever the list's length,
@@ -772,11 +680,11 @@ int bracket_tile_items(int rows) { (void)rows; return 256; }
 template <int EPI>
 static hipError_t launch_wide(const GemvArgs& a, hipStream_t stream, const BracketEpi& ep, const PickEpi& pk) {
     if (a.n_items <= 0 || a.rows <= 0) return hipSuccess;
-    if (!direct_fits(a)) return launch_tile<2, 4, 4, 2, 1, EPI>(a, stream, ep, pk);
     TileShape s;
     const hipError_t e = shape_for(a, true, &s);
     if (e != hipSuccess) return e;
-    return s == TILE_256x256 ? launch_tile<2, 4, 4, 2, 2, EPI>(a, stream, ep, pk) : launch_tile<2, 4, 2, 2, 2, EPI>(a, stream, ep, pk);
+    return s == TILE_256x256 ? launch_tile<2, 4, 4, 2, LOOP_TURNS, EPI>(a, stream, ep, pk)
+                             : launch_tile<2, 4, 2, 2, LOOP_TURNS, EPI>(a, stream, ep, pk);
 }
 
 hipError_t launch_tile_mfma_bracket(const GemvArgs& a, const BracketEpi& ep, hipStream_t stream) {
@@ -806,34 +714,32 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
         DeviceInfo di;
         const hipError_t e = device_info(&di);
         if (e != hipSuccess) return e;
-        const bool direct = direct_fits(a);
         if (a.rows <= 32) {
-            const bool ring = direct && a.chunks > 64 && (a.n_items <= (int64_t)di.cus * 128 || a.n_items >= (int64_t)di.cus * 224);
-            return ring ? launch_tile<1, 4, 1, 1, 3>(a, stream) : launch_tile<1, 2, 1, 1, 0>(a, stream);
+            const bool ring = a.chunks > 64 && (a.n_items <= (int64_t)di.cus * 128 || a.n_items >= (int64_t)di.cus * 224);
+            return ring ? launch_tile<1, 4, 1, 1, LOOP_RING>(a, stream) : launch_tile<1, 2, 1, 1, LOOP_PLAIN>(a, stream);
         }
         const int64_t round_items = (int64_t)256 * di.cus, last = a.n_items % round_items;
         // (with a count on the device a.n_items is its upper bound: at most half a round, and the list is short for sure)
         const bool unknown = a.n_items_dev != nullptr && 2 * a.n_items > round_items;
-        if (!direct || unknown || last == 0 || 2 * last > round_items) {
+        if (unknown || last == 0 || 2 * last > round_items) {
             // (40960 items: 80 against 87 us with a width that fills whole rounds; unions of 30940 and 44831 rows: a tree
             // step in 82 and 104 us against 88 and 109)
             GemvArgs b = a;
             b.balance_cus = di.cus;
-            return direct ? launch_tile<1, 8, 2, 1, 3>(b, stream) : launch_tile<1, 8, 2, 1, 0>(b, stream);
+            return launch_tile<1, 8, 2, 1, LOOP_RING>(b, stream);
         }
-        return launch_tile<2, 4, 1, 1, 3>(a, stream);
+        return launch_tile<2, 4, 1, 1, LOOP_RING>(a, stream);
     }
-    if (!direct_fits(a)) return launch_tile<2, 4, 4, 2, 1>(a, stream);
     // A count on the device, up to 128 rows: the shape that is never far from the best, whatever the count turns out to be
     // (80 rows x 16384 / 32768 / 128256 items, 128 x 128: 44 / 58 / 203 us, 128 x 256: 55 / 64 / 197).
-    if (a.n_items_dev != nullptr && a.rows <= 128) return launch_tile<2, 4, 2, 1, 2>(a, stream);
+    if (a.n_items_dev != nullptr && a.rows <= 128) return launch_tile<2, 4, 2, 1, LOOP_TURNS>(a, stream);
     TileShape s;
     const hipError_t e = shape_for(a, false, &s);
     if (e != hipSuccess) return e;
     switch (s) {
-        case TILE_128x128: return launch_tile<2, 4, 2, 1, 2>(a, stream);
-        case TILE_128x256: return launch_tile<2, 4, 2, 2, 2>(a, stream);
-        default: return launch_tile<2, 4, 4, 2, 2>(a, stream);
+        case TILE_128x128: return launch_tile<2, 4, 2, 1, LOOP_TURNS>(a, stream);
+        case TILE_128x256: return launch_tile<2, 4, 2, 2, LOOP_TURNS>(a, stream);
+        default: return launch_tile<2, 4, 4, 2, LOOP_TURNS>(a, stream);
     }
 }
 

@@ -93,16 +93,51 @@ def test_float32_rows_with_infinities_at_their_end(rows, d, V):
     torch.testing.assert_close(sv.dense_logits(h, U).double(), ref, rtol=0, atol=0, equal_nan=True)
 
 
-@pytest.mark.parametrize("rows,d", [(70, 72), (20, 2048)])
-def test_list_into_a_matrix_past_four_gigabytes(rows, d):
-    """Byte offsets past 32 bits take other kernels."""
+def _far_rows(gen, n, d, apart):
+    """n rows of d elements, `apart` elements from one to the next."""
+    t = torch.empty((n - 1) * apart + d, dtype=torch.bfloat16, device="cuda").as_strided((n, d), (apart, 1))
+    return t.copy_(_whole(gen, n, d, 4))
+
+
+# Byte offsets past 32 bits: lanes name their sources by address.  The split reduction (16 and 32 hidden rows per workgroup, a
+# ring of each depth), the ring on each of its tiles, and the alternating loop, with whole and ragged reductions
+@pytest.mark.parametrize("rows,d,k", [(2, 2048, 700), (9, 2056, 9000), (16, 4096, 40), (20, 2048, 700), (60, 2328, 1500),
+                                      (20, 584, 9000), (24, 1032, 60000), (40, 72, 700), (48, 1096, 30000), (64, 264, 50000),
+                                      (70, 72, 700), (100, 520, 9000), (128, 1096, 40000), (300, 200, 9000), (513, 1032, 30000)])
+def test_list_into_a_matrix_past_four_gigabytes(rows, d, k):
     gen = torch.Generator(device="cuda")
-    gen.manual_seed(1)
+    gen.manual_seed(rows + d)
     V = 70000
-    U = torch.empty((V, 32768), dtype=torch.bfloat16, device="cuda")[:, :d]          # 64 KB between rows: 4.6 GB
-    U.copy_(_whole(gen, V, d, 4))
+    U = _far_rows(gen, V, d, 32768)                                                  # 64 KB between rows: 4.6 GB
     h = _whole(gen, rows, d, 4)
-    idx = torch.randint(0, V, (700,), device="cuda", generator=gen).to(torch.int32)
+    idx = torch.randint(0, V, (k,), device="cuda", generator=gen).to(torch.int32)
     idx[0], idx[1] = V - 1, 0
     ref = h.double() @ U[idx.long()].double().t()
     assert torch.equal(sv.subset_logits(h, U, idx).double(), ref)
+
+
+def test_lists_of_their_own_into_a_matrix_past_four_gigabytes():
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    rows, d, V, k = 40, 520, 70000, 500
+    U, h = _far_rows(gen, V, d, 32768), _whole(gen, rows, d, 4)
+    idx = torch.rand((rows, V), device="cuda", generator=gen).topk(k, dim=1).indices.to(torch.int32)
+    ref = (h.double() @ U.double().t()).gather(1, idx.long())
+    assert torch.equal(sv.subset_logits(h, U, idx.contiguous()).double(), ref)
+
+
+# hidden states (the last positions of long sequences, say) or rows of the matrix whose distance times a tile's rows is past 32
+# bits: 16 MB for the tiled kernel, 128 MB for the split reduction
+@pytest.mark.parametrize("rows,d,V,h_apart,u_apart", [(20, 1032, 300, 8400000, 1032), (40, 520, 1000, 8400000, 520), (70, 136, 1000, 8400000, 136),
+                                                      (257, 72, 700, 8400000, 80), (40, 200, 100, 200, 8400000), (70, 520, 130, 528, 8400000),
+                                                      (9, 2056, 300, 67200000, 2056), (18, 2104, 40, 2104, 134400000)])
+def test_rows_far_apart(rows, d, V, h_apart, u_apart):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + d)
+    h, U = _far_rows(gen, rows, d, h_apart), _far_rows(gen, V, d, u_apart)
+    ref = h.double() @ U.double().t()
+    assert torch.equal(sv.dense_logits(h, U).double(), ref)
+    idx = torch.rand((rows, V), device="cuda", generator=gen).topk(V // 2 + 1, dim=1).indices.to(torch.int32)
+    for ordered in (False, True):
+        idx = idx.sort(dim=1).values if ordered else idx.contiguous()
+        assert torch.equal(sv.subset_logits(h, U, idx, sorted_lists=ordered).double(), ref.gather(1, idx.long()))
