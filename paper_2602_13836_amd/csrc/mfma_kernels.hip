@@ -264,7 +264,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS,
     unsigned char* ring = smem + (size_t)wave * DEPTH * kChunkB;
     const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)(wave * DEPTH * kChunkB);
     // chunk c of the wavefront: 64 elements of slice wave + 8 (c / 4), part c % 4
-    const int nch = wave < nslices ? 4 * ((nslices - wave + kSplitWaves - 1) / kSplitWaves) : 0;
+    // (of a ragged last slice only what there is: 2056 elements are one chunk more for one wavefront, not four)
+    const int own = wave < nslices ? (nslices - wave + kSplitWaves - 1) / kSplitWaves : 0;
+    const int last_units = C - (wave + kSplitWaves * (own - 1)) * (kKC / 8);
+    const int nch = own > 0 ? 4 * (own - 1) + min(4, (last_units + 7) / 8) : 0;
     auto request = [&](int c, int stage) {
         const int first_unit = (wave + kSplitWaves * (c >> 2)) * (kKC / 8) + (c & 3) * 8;
         const bool out0 = first_unit + (int)unit0 >= C, out1 = first_unit + (int)unit1 >= C;      // (past the last chunk: all of it)
@@ -316,6 +319,108 @@ __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS,
     store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
 }
 
+// The same for rows of M that do not start on (half) cache lines (2056 elements, say).  The pieces of 128 bytes above straddle two
+// lines there and half of what they fetch is thrown away: fragments straight from memory, two slices at a time where registers
+// allow, are faster (us, this form / the one above: 64 hidden rows x 4096 rows of 4112 bytes 10.5 / 12.1, 32 x 8000 10.5 /
+// 12.5, 4 x 16384 11.7 / 13.1; on rows of 4096 bytes 14.0 / 10.0, 13.9 / 9.8, 15.7 / 13.7).  The operands of every MFMA
+// and their order are those above, and so are the results.
+template <int NB>
+__global__ __launch_bounds__(512) void ksplit_fragments_kernel(SV_HOT_PARAMS, const GemvArgs rest,
+                                                                 const int row_base) {
+    const GemvArgs a = with_hot(rest, m_base, idx_base, x_base, n_items_arg, m_row_bytes_arg, x_row_bytes_arg,
+                                n_items_dev_arg);
+    constexpr int WPB = 8;
+    constexpr int N = 16 * NB;
+    __shared__ f32x4_t s_part[WPB][NB][64];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int i = lane & 15;
+    const int g = lane >> 4;
+    const int C = a.chunks;
+    const int nslices = (C * 8 + kKC - 1) / kKC;
+    prepare_scratch(a);
+    const int row0 = row_base + (int)blockIdx.y * N;
+    const int rows_here = min(a.rows - row0, N);
+    const int64_t n_items = a.n_items_dev ? (int64_t)*a.n_items_dev : a.n_items;
+    const int64_t tile0 = (int64_t)blockIdx.x * 16;
+    if (tile0 >= n_items || rows_here <= 0 || !gate_open(a, n_items)) return;
+
+    int64_t item = tile0 + i;
+    if (item > n_items - 1) item = n_items - 1;
+    const int64_t mrow = a.idx ? (int64_t)a.idx[item] : item;
+    const u32x4* mp = reinterpret_cast<const u32x4*>(a.M + mrow * a.m_row_bytes) + g;
+    const u32x4* xp[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        int r = nb * 16 + i;
+        if (r > rows_here - 1) r = rows_here - 1;         // padding rows repeat the last one, never stored
+        xp[nb] = reinterpret_cast<const u32x4*>(a.x + (int64_t)(row0 + r) * a.x_row_bytes) + g;
+    }
+
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // whole slices are loaded without conditions (no branches between the loads); only a ragged last
+    // slice masks its units
+    const int nwhole = C / (kKC / 8);
+    auto load_slice = [&](int slice, u32x4 (&av)[kSteps], u32x4 (&bv)[NB][kSteps]) {
+        if (slice < nwhole) {
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
+                const int off = slice * (kKC / 8) + s * 4;
+                av[s] = mp[off];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) bv[nb][s] = xp[nb][off];
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
+                const int off = slice * (kKC / 8) + s * 4;
+                const bool ok = off + g < C;
+                av[s] = ok ? mp[off] : zero16();
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) bv[nb][s] = ok ? xp[nb][off] : zero16();
+            }
+        }
+    };
+    auto multiply = [&](const u32x4 (&av)[kSteps], const u32x4 (&bv)[NB][kSteps]) {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[s]),
+                                                                  __builtin_bit_cast(bf16x8_t, bv[nb][s]), acc[nb],
+                                                                  0, 0, 0);
+    };
+    int slice = wave;
+    if constexpr (NB == 1) {
+        // registers allow two slices per wavefront in flight: one memory latency instead of two
+        for (; slice + WPB < nwhole; slice += 2 * WPB) {
+            u32x4 av0[kSteps], bv0[NB][kSteps], av1[kSteps], bv1[NB][kSteps];
+            load_slice(slice, av0, bv0);
+            load_slice(slice + WPB, av1, bv1);
+            multiply(av0, bv0);
+            multiply(av1, bv1);
+        }
+    }
+    for (; slice < nslices; slice += WPB) {
+        u32x4 av[kSteps], bv[NB][kSteps];
+        load_slice(slice, av, bv);
+        multiply(av, bv);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) s_part[wave][nb][lane] = acc[nb];
+    __syncthreads();
+    if (wave >= NB) return;
+    const int nb = wave;                                   // wavefront nb sums and stores hidden rows 16 nb ..
+    f32x4_t sum = s_part[0][nb][lane];
+#pragma unroll
+    for (int w = 1; w < WPB; ++w) sum += s_part[w][nb][lane];
+    store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
+}
+
 template <int NB>
 constexpr size_t skinny_lds_bytes() { return (size_t)2 * 16 * NB * kXRowBytes; }
 
@@ -350,8 +455,18 @@ hipError_t launch_ksplit_depth(const GemvArgs& a, int row0, int groups, hipStrea
     return near(a) ? go(&ksplit_kernel<NB, DEPTH, false>) : go(&ksplit_kernel<NB, DEPTH, true>);
 }
 
+// rows of M that suit the form fed from memory to LDS: on cache lines, up to 32 hidden rows also on half lines (us, that form /
+// fragments straight from memory: 16 hidden rows x 10000 rows of 4160 bytes 10.7 / 12.5, 24 x 5000 of 8256 16.2 / 17.0;
+// 33 x 5000 of 4160 14.3 / 12.4)
+bool whole_pieces(const GemvArgs& a) { return rows_start_at(a, a.rows <= 32 ? 64u : 128u); }
+
 template <int NB>
 hipError_t launch_ksplit(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
+    if (!whole_pieces(a)) {
+        hipLaunchKernelGGL((ksplit_fragments_kernel<NB>), dim3((unsigned)((a.n_items + 15) / 16), (unsigned)groups), dim3(512), 0,
+                           stream, SV_HOT_ARGS(a), a, row0);
+        return hipGetLastError();
+    }
     if (NB == 2) return launch_ksplit_depth<2, 3>(a, row0, groups, stream);
     DeviceInfo di;
     const hipError_t e = device_info(&di);
@@ -431,15 +546,18 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream) {
     // crossovers: up to 16 rows between 16384 and 24576 items (d = 4096, 16 rows, whole step: 16384 items 31 against 33 us,
     // 20480 43 against 43; d = 2048 the same), at 17 to 32 rows between 8192 and 12288 (32 rows: 6000 items 15 us against 21,
     // 12288 25 against 22), from 33 rows between 5120 and 8192 (60 rows: 4096 items 15 against 25, 9000 40 against 25).
-    const int64_t split_items = (int64_t)di.cus * (a.rows <= 16 ? 64 : a.rows <= 32 ? 32 : 20);
+    // (Rows of M that take the other form: from 12288 items on at 5 to 16 rows -- 16 rows x 12288 of 7952 bytes 20.0 us, 14000
+    // 23.6, against 20.3 and 20.7 on the kernel that takes over.)
+    const bool whole = whole_pieces(a);
+    const int64_t split_items = (int64_t)di.cus * (a.rows <= 4 ? 64 : a.rows <= 16 ? (whole ? 64 : 48) : a.rows <= 32 ? 32 : 20);
     // A count on the device (the union of the rows' sets; a.n_items is its upper bound, often several times the
     // count when the sets overlap) that may fall on either side of such a crossover: launches with complementary
     // gates, of which those that do not serve the list leave at once (about 2 us each).  The crossovers that matter:
     // the one above, and from 33 rows the one between small tiles with several workgroups per CU and 64 x 256 tiles
     // at half a round of those, 128 x CUs items (the tiled kernel picks its tile by n_items, here the upper end of
-    // the gate: 64 x 128; unions of 16 K to 32 K rows gain ~10 us over 64 x 256 tiles, up to 16 K they pay ~3 us
-    // against 64 x 64 tiles -- a gate of their own would cost every other list 2 us).  60 rows whose 512 / 1024-item sets unite to
-    // 553 / 1401 rows: whole step 31 / 33 us, against 64 / 66 with the kernel picked by the bound.
+    // the gate: 64 x 128; unions of 16 K to 32 K rows gain ~10 us over 64 x 256 tiles, up to 16 K they pay 3 to 8 us
+    // against 64 x 64 tiles -- a gate of their own would cost every other list 2 us).  60 rows whose 512 / 1024-item sets
+    // unite to 553 / 1401 rows: whole step 31 / 33 us, against 64 / 66 with the kernel picked by the bound.
     if (a.n_items_dev != nullptr && a.gate_hi == 0 && a.n_items > split_items && a.chunks >= 8 * (kKC / 8)) {
         int64_t cuts[2];
         int ncuts = 0;

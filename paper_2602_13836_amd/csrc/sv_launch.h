@@ -59,6 +59,10 @@ struct GemvArgs {
                                    // work only if gate_lo < count <= gate_hi and leaves at once otherwise (two launches
                                    // with complementary gates let the device pick the kernel that fits the count)
 };
+// true if every row of M starts at a multiple of `bytes` (a power of two)
+inline bool rows_start_at(const GemvArgs& a, unsigned bytes) {
+    return ((reinterpret_cast<uintptr_t>(a.M) | (uintptr_t)a.m_row_bytes) & (bytes - 1u)) == 0;
+}
 // true if this launch is the one that serves a list of n_items items
 __device__ __forceinline__ bool gate_open(const GemvArgs& a, int64_t n_items) {
     return a.gate_hi == 0 || (n_items > a.gate_lo && n_items <= a.gate_hi);

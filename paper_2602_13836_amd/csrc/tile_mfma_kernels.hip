@@ -637,7 +637,9 @@ hipError_t configure_tile_mfma_lds() {
         if (e == hipSuccess) e = fn(std::integral_constant<int, EPI_PICK>{});
     };
     if (e == hipSuccess) e = opt_in_lds<1, 8, 2, 1, LOOP_RING, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<1, 2, 1, 1, LOOP_RING, EPI_STORE>();
     if (e == hipSuccess) e = opt_in_lds<1, 4, 1, 1, LOOP_RING, EPI_STORE>();
+    if (e == hipSuccess) e = opt_in_lds<2, 2, 1, 1, LOOP_RING, EPI_STORE>();
     if (e == hipSuccess) e = opt_in_lds<2, 4, 1, 1, LOOP_RING, EPI_STORE>();
     if (e == hipSuccess) e = opt_in_lds<2, 4, 2, 1, LOOP_TURNS, EPI_STORE>();
     all_epilogues([](auto ec) { return opt_in_lds<2, 4, 2, 2, LOOP_TURNS, decltype(ec)::value>(); });
@@ -702,19 +704,23 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
     // Up to 64 hidden rows (the caller decides when this beats the kernel without LDS tiles) the product is one
     // pass over M at the rate of the memory system, and what matters is how evenly the list's items spread over
     // the chip and how much of them is on its way: the ring, which has three slices in flight, on tiles of
-    //   17 to 32 rows: 32 x 128 (four wavefronts, two workgroups per CU) up to one workgroup per CU, and where two per CU
-    //     are nearly full (32 rows x 24576 items 38.7 us against 43.6 on 32 x 64 tiles of the plain loop, 65536 96 against
-    //     98); in between those (49152: 78 against 73), and for short reductions, the 32 x 64 tiles;
+    //   17 to 32 rows: 32 x 64 (two wavefronts, three workgroups per CU) up to 64 x CUs items (32 rows of 3840 elements x 10000
+    //     items from HBM 23.5 us against 29.7 on 32 x 128 tiles, 16384 26.1 against 33.9); 32 x 128 (four wavefronts, two
+    //     workgroups per CU) up to one workgroup per CU, and where two per CU are nearly full (32 rows x 24576 items 38.7
+    //     against 43.6 on 32 x 64 tiles of the plain loop, 65536 96 against 98); in between those (49152: 78 against 73), and
+    //     for short reductions, the plain loop's;
     //   33 to 64 rows: 64 x 256 (eight wavefronts, one workgroup per CU) when the list fills its last round of 256 x CUs
     //     items, or more than half of it (128256 items 188 us against 192 on the tiles below, 49152 75 against 82) -- and
-    //     for a count on the device, which a tree step has --, of a width that then fills whole rounds; otherwise 64 x 128
-    //     (eight wavefronts of 32 x 32): 60 rows x 9000 / 16384 / 24576 / 32768 / 98304 items 25 / 32 / 42 / 50 / 149 us
-    //     (58 on 64 x 256 tiles for the third; 35 / 36 / 48 / 51 / 153 on the plain loop's 64 x 64 and 64 x 128 tiles).
+    //     for a count on the device, which a tree step has --, of a width that then fills whole rounds; otherwise 64 x 64
+    //     (four wavefronts, two workgroups per CU) up to 64 x CUs items and 64 x 128 (eight wavefronts of 32 x 32) beyond:
+    //     64 rows of 4096 elements x 9000 / 16384 items from HBM 25.6 / 28.7 us against 33.0 / 36.9 on 64 x 128 tiles, of
+    //     4104 elements 36.4 / 41.0 against 51.3 / 55.3; 60 rows x 24576 / 32768 / 98304 items 42 / 50 / 149 on those.
     if (a.rows <= 64) {
         DeviceInfo di;
         const hipError_t e = device_info(&di);
         if (e != hipSuccess) return e;
         if (a.rows <= 32) {
+            if (a.chunks > 64 && a.n_items <= (int64_t)di.cus * 64) return launch_tile<1, 2, 1, 1, LOOP_RING>(a, stream);
             const bool ring = a.chunks > 64 && (a.n_items <= (int64_t)di.cus * 128 || a.n_items >= (int64_t)di.cus * 224);
             return ring ? launch_tile<1, 4, 1, 1, LOOP_RING>(a, stream) : launch_tile<1, 2, 1, 1, LOOP_PLAIN>(a, stream);
         }
@@ -728,6 +734,7 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
             b.balance_cus = di.cus;
             return launch_tile<1, 8, 2, 1, LOOP_RING>(b, stream);
         }
+        if (a.n_items <= (int64_t)64 * di.cus) return launch_tile<2, 2, 1, 1, LOOP_RING>(a, stream);
         return launch_tile<2, 4, 1, 1, LOOP_RING>(a, stream);
     }
     // A count on the device, up to 128 rows: the shape that is never far from the best, whatever the count turns out to be

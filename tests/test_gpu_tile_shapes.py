@@ -27,9 +27,11 @@ def _inputs(rows, d, V, seed):
 @pytest.mark.parametrize("rows,d,V", [
     (65, 8, 127), (65, 64, 128), (66, 72, 129), (127, 56, 255), (128, 128, 256), (129, 136, 257), (192, 192, 511),
     (255, 200, 513), (256, 320, 300), (257, 264, 130), (300, 1024, 777), (384, 1096, 1000), (512, 4096, 515), (513, 520, 259),
-    # the ring of four stages (17 to 64 rows): fewer slices than stages, ragged ones, 32 x 128, 64 x 128 and 64 x 256 tiles
+    # the ring of four stages (17 to 64 rows): fewer slices than stages, ragged ones, 32 x 64 to 64 x 256 tiles,
+    # rows of M on cache lines (multiples of 64 elements) and off them
     (17, 520, 129), (32, 1032, 300), (24, 584, 57345), (33, 8, 127), (40, 72, 129), (60, 136, 1000), (64, 200, 32769), (48, 1096, 65537),
     (60, 2056, 70000), (34, 264, 40001),
+    (17, 576, 129), (32, 1088, 300), (24, 1048, 65), (20, 576, 20001), (32, 584, 20001), (24, 576, 57345), (33, 64, 16384), (64, 1024, 16383), (40, 1088, 257), (40, 1096, 20001), (64, 136, 30000),
     (130, 72, 33000), (128, 328, 70001), (256, 64, 66000), (400, 200, 66049), (520, 1032, 40003), (700, 136, 50000)])
 def test_dense_product(rows, d, V):
     _, h, U, ref = _inputs(rows, d, V, rows + d)
@@ -44,9 +46,11 @@ def test_shared_list(rows, d, V, k):
 
 
 # short lists and long rows: the reduction split over the wavefronts of a workgroup (16 items by 16 or 32 hidden rows), with
-# fewer slices of 256 than twice the wavefronts, ragged last slices, and rings deeper than what is left to read
+# fewer slices of 256 than twice the wavefronts, ragged last slices, and rings deeper than what is left to read; rows of M on cache
+# lines and off them (two forms)
 @pytest.mark.parametrize("rows,d,V,k", [(2, 2048, 400, 1), (3, 2056, 400, 15), (16, 2104, 5000, 4101), (17, 2296, 700, 17),
-                                        (31, 4096, 700, 333), (33, 2304, 700, 300), (64, 6152, 900, 513), (48, 16384, 300, 50)])
+                                        (31, 4096, 700, 333), (33, 2304, 700, 300), (64, 6152, 900, 513), (48, 16384, 300, 50),
+                                        (9, 2112, 700, 30), (16, 4160, 5000, 4101), (40, 2240, 900, 333), (20, 4288, 700, 100)])
 def test_shared_list_of_long_rows(rows, d, V, k):
     gen, h, U, ref = _inputs(rows, d, V, k + d)
     idx = torch.randint(0, V, (k,), device="cuda", generator=gen).to(torch.int32)
