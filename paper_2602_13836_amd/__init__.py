@@ -156,10 +156,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# (the raw handle comes from a private function; a torch without it goes through the Stream object)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream(stream: Optional[torch.cuda.Stream]) -> int:
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return _current_raw_stream(torch.cuda.current_device())
 
 
 def _idx(idx: torch.Tensor, rows: int) -> Tuple[int, int]:
