@@ -445,16 +445,23 @@ inline int shape_of(int chunks, int rows) {
     const int pad256 = (rows + 255) / 256, pad512 = (rows + 511) / 512;
     return base + (2 * pad512 == pad256 ? 0 : 1);        // no panel half idle
 }
+constexpr int kSampleShape = 2, kSampleShapeShort = 6;     // the ones that launch_panel_sample uses (and 3)
 template <int EPI, typename F>
 hipError_t with_shape(int shape, F&& f) {
+    if constexpr (EPI != EPI_SAMPLE) {
+        switch (shape) {
+            case 0: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+            case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+            case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+            case 5: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+            default: break;
+        }
+    }
     switch (shape) {
-        case 0: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-        case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
         case 2: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
-        case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-        case 5: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
         case 6: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
-        default: return f(std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+        case 3: return f(std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -490,7 +497,7 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
     PanelArgs a = a0;
     // A sample of a few thousand rows of M is over in one or two steps and costs what fetching the hidden rows costs:
     // small panels (512 rows, 8192 of them: 10.8 us on panels of 128 against 14.0 on panels of 512).
-    const int shape = EPI == EPI_SAMPLE && a.chunks <= 32 ? (a.chunks <= 16 ? 6 : 2) : shape_of(a.chunks, a.rows);
+    const int shape = EPI == EPI_SAMPLE && a.chunks <= 32 ? (a.chunks <= 16 ? kSampleShapeShort : kSampleShape) : shape_of(a.chunks, a.rows);
     const PanelRuns pr = runs_of(shape, a.rows, a.n_items);
     a.run_items = pr.items;
     a.partial_stride = pr.runs * kShapes[shape].gi;
@@ -508,6 +515,7 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
 template <int EPI>
 hipError_t opt_in_epi() {
     for (int shape = 0; shape < 7; ++shape) {
+        if (EPI == EPI_SAMPLE && shape != 3 && shape != kSampleShape && shape != kSampleShapeShort) continue;
         const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
             constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
             static_assert(panel_lds_bytes<KS, WM, GM, EPI>() <= 160 * 1024, "one workgroup per CU");
@@ -532,7 +540,6 @@ hipError_t configure_panel_lds() {
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);
 }
-
 
 PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items) { return runs_of(shape_of(chunks, (int)rows), rows, n_items); }
 

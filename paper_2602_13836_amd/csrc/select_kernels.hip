@@ -1365,7 +1365,7 @@ bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k) {
 // items per tile of the classify pass: the runs of the kernel that keeps the hidden rows in registers, or the tiles of
 // the tiled kernel (selectors too wide for the former)
 static int bracket_tn(int chunks, int64_t rows, int64_t V) {
-    return panel_supported(DT_BF16, chunks, rows, V) ? (int)panel_runs(chunks, rows, V).items : bracket_tile_items((int)rows);
+    return panel_supported(DT_BF16, chunks, rows, V) ? (int)panel_runs(chunks, rows, V).items : kKeepTileItems;
 }
 
 size_t bracket_scratch_words(int chunks, int64_t rows, int64_t V) {

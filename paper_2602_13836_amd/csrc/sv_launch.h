@@ -106,7 +106,7 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream);
 // candidate region of (r, item tile), whose entry count goes to cnt.  Every word of bits and every cnt entry
 // is written.  Any row count >= 1.
 // Candidates of a (row, item tile): the first first_cap in a compact array (a row's are contiguous: the resolve
-// pass streams them), any further ones (tied scores) in a region of the pair's that holds the rest of the tile.
+// pass streams them), any further ones (tied scores) in a region of the pair's of over_cap slots.
 struct BracketEpi {
     const float* thr;        // [rows][2]
     uint32_t* bits;          // [rows][words_per_row], words_per_row = item_tiles * tile items / 32
@@ -115,9 +115,10 @@ struct BracketEpi {
     uint64_t* cand;          // [rows][item_tiles][over_cap]    slots first_cap .. of the same list
     uint32_t* cnt;           // [rows][item_tiles]
     int64_t item_tiles;
-    int first_cap, over_cap; // first_cap + over_cap = tile items
+    int first_cap, over_cap; // over_cap = tile items: more than is left of the tile, but a row's regions together are
+                             // where the redo of a row keeps its V slots
 };
-int bracket_tile_items(int rows);      // items per tile of the instance launch_tile_mfma_bracket picks
+constexpr int kKeepTileItems = 256;      // items per tile of the epilogues that keep something per item tile
 hipError_t launch_tile_mfma_bracket(const GemvArgs& a, const BracketEpi& ep, hipStream_t stream);
 
 // The tiled product over ALL rows of M (a.idx == nullptr, a.n_items = V) with the pick epilogue: only
@@ -131,7 +132,6 @@ struct PickEpi {
     int64_t k;
     float* out;              // [rows][k], in the order of idx
 };
-int pick_tile_items(int rows);
 hipError_t launch_tile_mfma_pick(const GemvArgs& a, const PickEpi& pk, hipStream_t stream);
 
 // Products with a short reduction (rows of M of up to 64 16-byte units) for more than 64 hidden rows: the hidden rows stay
@@ -240,7 +240,7 @@ struct BracketArgs {
     int rows;
     int64_t k;
     int32_t* idx_out;      // [rows x k]
-    uint32_t* scratch;     // bracket_scratch_words(rows, V) words; nothing needs clearing
+    uint32_t* scratch;     // bracket_scratch_words(chunks, rows, V) words; nothing needs clearing
 };
 bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k);
 size_t bracket_scratch_words(int chunks, int64_t rows, int64_t V);

@@ -38,6 +38,27 @@ constexpr int kTK = 64;                  // reduction elements per slice (128 by
 constexpr int kRowB = kTK * 2 + 16;      // padded LDS row (144 B = 36 words)
 constexpr int kXcds = 8;
 
+// dst with lanes LO and HI replaced by the two halves of the wavefront-uniform mask m (two v_writelane_b32).
+// The mask comes straight from a vector comparison: on this architecture a vector instruction that reads a
+// scalar register written by the vector instruction just before it needs two wait states in between; the
+// compiler inserts them for its own instructions, not for the operands of an asm block, hence the s_nop.
+template <int LO, int HI>
+__device__ __forceinline__ uint32_t write_lanes(uint32_t dst, uint64_t m) {
+    static_assert(LO >= 0 && LO < 64 && HI >= 0 && HI < 64, "lanes of a 64-wide wavefront");
+    asm("s_nop 1\n\tv_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4"
+        : "+v"(dst)
+        : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)), "n"(LO), "n"(HI));
+    return dst;
+}
+
+// 2 x + (this lane's bit of the wavefront-wide mask m): one add-with-carry whose carry-in is the mask.  The mask
+// must come from a scalar instruction (see write_lanes for why not straight from a vector comparison).
+__device__ __forceinline__ uint32_t shift_in_lane_bit(uint32_t x, uint64_t m) {
+    uint64_t carry_out;
+    asm volatile("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(x), "=s"(carry_out) : "s"(m));
+    return x;
+}
+
 // LDS the bracket epilogue needs (it reuses the operand buffers after the main loop): per tile row the
 // bracket and a candidate counter (16 bytes reserved), per wavefront the scores of one 32-row band
 template <int GM, int GN, int WM, int WN>
@@ -676,9 +697,7 @@ static hipError_t shape_for(const GemvArgs& a, bool wide_only, TileShape* out) {
     return hipSuccess;
 }
 
-// the epilogues that keep something per item tile take tiles of 256 items, whatever the number of hidden rows
-int bracket_tile_items(int rows) { (void)rows; return 256; }
-
+// the epilogues that keep something per item tile: tiles of kKeepTileItems items, whatever the number of hidden rows
 template <int EPI>
 static hipError_t launch_wide(const GemvArgs& a, hipStream_t stream, const BracketEpi& ep, const PickEpi& pk) {
     if (a.n_items <= 0 || a.rows <= 0) return hipSuccess;
@@ -692,8 +711,6 @@ static hipError_t launch_wide(const GemvArgs& a, hipStream_t stream, const Brack
 hipError_t launch_tile_mfma_bracket(const GemvArgs& a, const BracketEpi& ep, hipStream_t stream) {
     return launch_wide<EPI_BRACKET>(a, stream, ep, PickEpi{});
 }
-
-int pick_tile_items(int rows) { return bracket_tile_items(rows); }
 
 hipError_t launch_tile_mfma_pick(const GemvArgs& a, const PickEpi& pk, hipStream_t stream) {
     return launch_wide<EPI_PICK>(a, stream, BracketEpi{}, pk);

@@ -290,13 +290,13 @@ hipError_t configure_union_lds() {
 // no more than reading the union: the product over all of U whose epilogue stores only the asked entries.  Lists
 // declared ascending need only the table of slices; lists in any order are grouped by tile first, which needs
 // the tile counters of a row in LDS.
-static int64_t pick_tiles(int rows, int64_t V) { return (V + pick_tile_items(rows) - 1) / pick_tile_items(rows); }
+static int64_t pick_tiles(int64_t V) { return (V + kKeepTileItems - 1) / kKeepTileItems; }
 bool pick_path_wanted(int dt, const GemvArgs& a, int64_t V, bool sorted) {
     return dt == DT_BF16 && a.rows > 64 && a.idx != nullptr && a.idx_row_stride != 0 && a.out_bf16 == nullptr &&
-           (int64_t)a.rows * a.n_items >= 2 * V && (sorted || pick_tiles(a.rows, V) <= kBucketMaxTiles);
+           (int64_t)a.rows * a.n_items >= 2 * V && (sorted || pick_tiles(V) <= kBucketMaxTiles);
 }
 static size_t pick_table_words(int64_t rows, int64_t V) {
-    return ((size_t)rows * (size_t)(pick_tiles((int)rows, V) + 1) + 3) & ~(size_t)3;
+    return ((size_t)rows * (size_t)(pick_tiles(V) + 1) + 3) & ~(size_t)3;
 }
 size_t pick_ws_bytes(int64_t rows, int64_t V, int64_t k, bool sorted) {
     return (pick_table_words(rows, V) + (sorted ? 0 : 3 * (size_t)rows * (size_t)k)) * sizeof(uint32_t);
@@ -304,15 +304,13 @@ size_t pick_ws_bytes(int64_t rows, int64_t V, int64_t k, bool sorted) {
 
 hipError_t launch_pick_logits(const GemvArgs& a, int64_t V, bool sorted, void* ws, hipStream_t stream) {
     const int64_t k = a.n_items;
-    const int tn = pick_tile_items(a.rows);
-    const int64_t tiles = pick_tiles(a.rows, V);
+    const int64_t tiles = pick_tiles(V);
     uint32_t* table = static_cast<uint32_t*>(ws);
     uint32_t* perm = sorted ? nullptr : table + pick_table_words(a.rows, V);
     int32_t* grouped = sorted ? nullptr : reinterpret_cast<int32_t*>(perm + (size_t)a.rows * (size_t)k);
     float* grouped_out = sorted ? nullptr : reinterpret_cast<float*>(grouped + (size_t)a.rows * (size_t)k);
-    int tile_shift = 0;
-    while ((1 << tile_shift) < tn) ++tile_shift;
-    if ((1 << tile_shift) != tn) return hipErrorInvalidValue;      // tiles are 128 or 256 items
+    constexpr int tile_shift = 8;
+    static_assert((1 << tile_shift) == kKeepTileItems, "a token's tile by a shift");
     if (sorted) {
         const unsigned sb = (unsigned)((k + 1023) / 1024);
         hipLaunchKernelGGL(slice_table_kernel, dim3(sb, (unsigned)a.rows), dim3(256), 0, stream, a.idx, k, tile_shift,
