@@ -1088,16 +1088,16 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
     if (miss) return;                                         // uniform: the redo launch handles this row
     uint32_t remain = (uint32_t)k - n_above;                  // candidates to select, 0 <= remain <= n_band
 
-    // f(tile, place, candidate) for the candidates from place `from` of every tile on, from memory.  A tile is shared by as
+    // f(tile, place, candidate) for the candidates from place `from` of every tile (of count(tile)) on, from memory.  A tile is shared by as
     // many threads as there are for each (thousands of hidden rows leave a row few tiles, of tens of thousands of tokens),
     // at least four, so that their requests join, and a thread has several requests on their way (512 rows x 262144, k =
     // 16384, many ties: one thread per tile 296 us, four 246, eight 252).
-    auto walk_tiles = [&](int from, auto&& f) {
+    auto walk_tiles = [&](int from, auto&& count, auto&& f) {
         constexpr int kFlight = 8;
         const int sharers = T * 4 < kRbThreads ? kRbThreads / T : 4;
         const int sub = tid % sharers;
         for (int t = tid / sharers; t < T; t += kRbThreads / sharers) {
-            const int n = (int)cnt[t];
+            const int n = (int)count(t);
             const uint64_t *p0 = first + (int64_t)t * F, *p = cand + (int64_t)t * tn - F;
             for (int i = from + sub; i < n; i += kFlight * sharers) {
                 uint64_t x[kFlight];
@@ -1121,7 +1121,8 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
         }
         if (tid == 0) s_off[T] = n_band;
         __syncthreads();
-        walk_tiles(F, [&](int t, uint32_t i, uint64_t x) { s_cand[s_off[t] + i] = x; });     // a crowded tile's rest
+        walk_tiles(F, [&](int t) { return s_off[t + 1] - s_off[t]; },          // a crowded tile's rest
+                   [&](int t, uint32_t i, uint64_t x) { s_cand[s_off[t] + i] = x; });
         auto pack = [&](uint32_t j, const u32x4 v) {
             if (j >= pairs_total) return;
             const uint32_t t = __umulhi(j, first_magic), i = 2u * (j - t * (uint32_t)(F / 2));
@@ -1147,7 +1148,7 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
         if (dense) {
             for (uint32_t i = tid; i < n_band; i += kRbThreads) f(s_cand[i]);
         } else {                                              // too many for the LDS list
-            walk_tiles(0, [&](int, uint32_t, uint64_t x) { f(x); });
+            walk_tiles(0, [&](int t) { return cnt[t]; }, [&](int, uint32_t, uint64_t x) { f(x); });
         }
     };
     if (remain > 0u) {                                        // uniform
@@ -1354,8 +1355,10 @@ constexpr int kSampleLog2 = 13;
 constexpr int64_t kSample = (int64_t)1 << kSampleLog2;   // sampled tokens per call
 constexpr int64_t kBracketMaxVocab = 393216;             // the row's bit mask (V / 8 bytes) lives in LDS: 48 KiB here
 
-// From 65 hidden rows on (measured: at 60 rows the path that materialises the 30 MB of scores, which then stay
-// in the last-level cache, takes 71 us against 80 us; at 512 rows 335 us against 160 us)
+// From 65 hidden rows on.  Fewer leave more than half of the smallest panel idle, and their scores stay in the last-level cache
+// when they are written: 60 rows, d' = 256, 32768 / 128256 / 262144 tokens 35 / 63 / 107 us with the scores in memory
+// against 41 / 60 / 93 here, 32 rows 34 / 50 / 81 against 41 / 59 / 91, d' = 512 with 60 rows 37 / 79 / 133 against 51 /
+// 87 / 132; 65 rows x 262144 91 here.
 constexpr int64_t kBracketMinRows = 65;
 bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k) {
     (void)k;
