@@ -49,8 +49,8 @@ struct GemvArgs {
                                    // device; n_items is then an upper bound that sizes the grid
     int plain_order;               // matrix-core kernels: every workgroup walks the reduction from offset 0 (set when
                                    // the place of an item in the list may differ from run to run)
-    int64_t m_rows;                // number of rows of M that idx may name, 0 if the caller does not say (a kernel that
-                                   // keeps row offsets in 32 bits is then not used with an index list)
+    int64_t m_rows;                // number of rows of M that idx may name, 0 if the caller does not say (kernels that can
+                                   // name a row by a 32-bit offset then name it by its address)
     int64_t n_items_min;           // with a count on the device: what the count is expected to reach at least (a hint that
                                    // saves launches, 0 if the caller has none; a smaller count is still served correctly)
     int balance_cus;               // LDS-tiled kernel, product stored: if > 0, the width of an item tile shrinks (in steps
