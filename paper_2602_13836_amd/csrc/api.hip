@@ -51,6 +51,8 @@ hipError_t device_state(const DeviceState** out) {
             if (e != hipSuccess) return e;
             e = configure_select_lds();
             if (e != hipSuccess) return e;
+            e = configure_code_select_lds();
+            if (e != hipSuccess) return e;
             e = configure_union_lds();
             if (e != hipSuccess) return e;
             e = configure_panel_lds();
@@ -120,8 +122,12 @@ SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) 
     w.radix_off = w.s_off + round256((size_t)rows * (size_t)V * sizeof(float));
     w.total = w.radix_off + round256(sv::select_scratch_words(rows, V) * sizeof(uint32_t));
     w.bracket_off = w.s_off;
-    if (sv::bracket_select_supported(dt, rows, V, k)) {
-        const size_t t = w.bracket_off + round256(sv::bracket_scratch_words((int)(d_prime * esize_of(dt) / 16), rows, V) * sizeof(uint32_t));
+    const int chunks = (int)(d_prime * esize_of(dt) / 16);
+    if (sv::code_select_supported(dt, chunks, rows, V)) {
+        const size_t t = w.bracket_off + sv::code_select_scratch_bytes(rows, V);
+        if (t > w.total) w.total = t;
+    } else if (sv::bracket_select_supported(dt, rows, V, k)) {
+        const size_t t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
         if (t > w.total) w.total = t;
     }
     return w;
@@ -411,20 +417,32 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
     float* scores = reinterpret_cast<float*>(base + w.s_off);
     uint32_t* radix = reinterpret_cast<uint32_t*>(base + w.radix_off);
 
-    // A batch of hidden rows whose scores nobody asked for: the selection that never writes the score matrix
+    // A batch of hidden rows whose scores nobody asked for: a byte per score in memory
+    const int vchunks = (int)(d_prime * es / 16);
+    if (!scores_out && tau == -INFINITY && sv::code_select_supported(dt, vchunks, rows, V)) {
+        if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s) != SV_OK) return SV_ERR_HIP;
+        sv::CodeSelectArgs ca{};
+        ca.hp = hp;
+        ca.Wv = static_cast<const char*>(W_vocab);
+        ca.chunks = vchunks;
+        ca.V = V;
+        ca.rows = (int)rows;
+        ca.k = k;
+        ca.idx_out = idx_out;
+        ca.scratch = base + w.bracket_off;
+        return sv::launch_code_select(ca, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
+    }
+    // Wide selectors: the selection that never writes the score matrix
     // (a sample of the vocabulary brackets every row's k-th score; the full product is classified in the
     // epilogue of the matrix-core kernel).  The down-projection launch also writes the sample's ids.
     if (!scores_out && tau == -INFINITY && sv::bracket_select_supported(dt, rows, V, k)) {
         uint32_t* bscratch = reinterpret_cast<uint32_t*>(base + w.bracket_off);
         int32_t* ids = nullptr;
         int64_t m = 0;
-        int log2_m = 0;
         float* samp = nullptr;
-        const int chunks = (int)(d_prime * es / 16);
-        sv::bracket_sample(chunks, rows, V, bscratch, &ids, &m, &log2_m, &samp);
-        // (the kernel that keeps the hidden rows in registers works the sample's ids out itself)
-        const bool panel = sv::panel_supported(dt, chunks, rows, V);
-        if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s, ids, panel ? 0 : m, V) != SV_OK)
+        const int chunks = vchunks;
+        sv::bracket_sample(rows, V, bscratch, &ids, &m, &samp);
+        if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s, ids, m, V) != SV_OK)
             return SV_ERR_HIP;
         sv::GemvArgs gs{};
         gs.x = hp;
@@ -438,16 +456,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         gs.out_f32 = samp;
         gs.out_row_stride = m;
         gs.m_rows = V;
-        hipError_t e;
-        if (panel) {
-            sv::PanelArgs p = panel_args(gs);
-            p.spread_V = V;
-            p.spread_shift = log2_m;
-            e = sv::launch_panel_sample(p, s);
-        } else {
-            e = sv::launch_tile_mfma(gs, s);
-        }
-        if (e != hipSuccess) return SV_ERR_HIP;
+        if (sv::launch_tile_mfma(gs, s) != hipSuccess) return SV_ERR_HIP;
         sv::BracketArgs ba{};
         ba.hp = hp;
         ba.Wv = static_cast<const char*>(W_vocab);
@@ -469,7 +478,6 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
 
     // Step 1b: s = W_vocab h'.  One hidden row: a bandwidth-bound stream over W_vocab fused with the
     // first histogram pass of the selection.  Several rows: a real matrix product -> matrix cores.
-    const int vchunks = (int)(d_prime * es / 16);
     sv::GemvArgs g2{};
     g2.x = hp;
     g2.x_row_bytes = d_prime * es;

@@ -4,7 +4,7 @@
 //
 // What bounds it.  With d' = 256 a 256 x 256 output tile is four 64-element slices of main loop: the tiled kernel spends
 // more time filling its pipeline, and in its epilogue, than multiplying (512 rows x 151936: 45 us of product of which
-// the matrix cores need 20, 85-97 us with the epilogue of the bracketed selection).  Here the hidden rows are STATIONARY:
+// the matrix cores need 20).  Here the hidden rows are STATIONARY:
 // a wavefront keeps the fragments of its 32 WM hidden rows for the whole reduction in registers (128 of them at
 // 64 rows x 256 elements), and a workgroup that owns a panel of TM = 32 WM GM hidden rows streams a long run of rows
 // of M past them, 64 (32) rows at a time, double buffered in LDS and requested two steps ahead.  A step is then
@@ -12,15 +12,15 @@
 // first tile's, and one barrier per step.  The matrix is read once per panel (once in all up to 512 hidden rows).
 //
 // Where the epilogue reduces or selects along the rows of M (the two that store nothing), M is the MFMA's first operand:
-// a lane then holds 16 scores of ONE hidden row, whose bracket, running maximum and counters stay in its registers.
+// a lane then holds 16 scores of ONE hidden row, whose map to codes or running maximum stays in its registers.
 // (Tried and not used: the two wavefronts of a SIMD half a step apart, so that one multiplies while the other is in its
 // epilogue, and a sub-tile's epilogue cut into pieces between the MFMAs of the next one: 103 and 92-95 us against 97 for
 // the sums of 1024 rows x 151936 -- the matrix cores alone take 65, at the clock their load leaves.)
 //
-// Measured (512 rows x 151936, d' = 256): the classifying product of the selection 97 us on the tiled kernel, 79 here --
-// of which 39 are the panel's start and MFMAs, 15 the comparisons, 5 the bit masks, 26 the candidates --, the whole
-// selection 166 -> 138; log-probabilities of 1024 rows x 151936 579 -> 237 us (sums 97, stored product 145 under a
-// profiler: 622 MB at 4.3 TB/s).
+// Measured: the selection's product with its codes, 512 rows x 151936, d' = 256: 48 us (without the codes' stores 41, of
+// which the matrix cores are busy 20; codes kept for a step and stored behind the next requests 58; to lines of 1 KB, rows of
+// one unit side by side, 47); log-probabilities of 1024 rows x 151936 579 us on the tiled kernel, 230 here (sums 97, stored
+// product 145 under a profiler: 622 MB at 4.3 TB/s).
 //
 // The sums are the ones the tiled kernel makes (v_mfma_f32_32x32x16_bf16 over ascending k from zero), bit for bit.
 #include "sv_device.h"
@@ -44,8 +44,8 @@ constexpr int kRunUnit = 64;             // a run is a multiple of this many row
 // EPI_SAMPLE     row(j) = floor(j spread_V / 2^spread_shift), a sample of M's rows; the product is stored
 // EPI_LOGP       the product minus a value per hidden row (the normaliser of Section 3.4) is stored
 // EPI_LSE        only (maximum, sum of exponentials relative to it) per hidden row and run of rows of M
-// EPI_BRACKET    the bracketed selection's classification (see tile_mfma_kernels.hip)
-enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_BRACKET = 3 };
+// EPI_CODES      a byte per score is stored, a monotone function of the score per hidden row (the selection of a batch)
+enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_CODES = 3 };
 
 template <int KS>
 constexpr int lds_row_bytes() { return KS * 32 + 16; }        // padded like the tiled kernel's rows: full read rate
@@ -58,7 +58,6 @@ constexpr int fill_rows() { return KS > 16 ? 16 : 32; }       // hidden rows a w
 template <int KS, int WM, int GM, int EPI>
 constexpr size_t panel_lds_bytes() {
     size_t n = 2 * stage_bytes<KS>();
-    if (EPI == EPI_BRACKET) n += (size_t)kWaves * WM * 4096 + (size_t)32 * WM * GM * 4;      // a sub-tile's scores, counters
     if (EPI == EPI_LOGP) n += (size_t)32 * WM * GM * 4;
     const size_t fill = (size_t)kWaves * fill_rows<KS>() * lds_row_bytes<KS>();
     return n > fill ? n : fill;
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     constexpr int kTI = step_items<KS>();
     constexpr int SUB = kTI / (32 * GI);                 // 32-row sub-tiles per wavefront and step
     constexpr int TM = 32 * WM * GM;
-    constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_BRACKET;               // M is the MFMA's first operand
+    constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_CODES;               // M is the MFMA's first operand
     constexpr int kRowB = lds_row_bytes<KS>();
     constexpr int kUnits = 2 * KS;                       // 16-byte units of a staged row
     constexpr int Q = kTI * kUnits / kThreads;           // ... per thread and step
@@ -167,21 +166,19 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
 
     // ---- per-workgroup state of the epilogues, behind the two stages
     unsigned char* s_epi = smem + 2 * stage_bytes<KS>();
-    [[maybe_unused]] f32x4_t* s_dump = reinterpret_cast<f32x4_t*>(s_epi) + (size_t)wave * (WM * 4 * 64);   // EPI_BRACKET: scores
     [[maybe_unused]] float* s_sub = reinterpret_cast<float*>(s_epi);          // EPI_LOGP: [TM]
     const int half = lane >> 5;
-    // EPI_BRACKET, of hidden row row_w + 32 m + lane % 32: the bracket, and how many candidates the run has so far
-    [[maybe_unused]] float thr_hi[WM], thr_lo[WM];
-    [[maybe_unused]] uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_epi + (size_t)kWaves * WM * 4096);
-    if constexpr (EPI == EPI_BRACKET) {
-        for (int t = tid; t < TM; t += kThreads) s_cnt[t] = 0u;
+    // EPI_CODES, of hidden row row_w + 32 m + lane % 32: what makes a score a code, and where the lane's codes go
+    [[maybe_unused]] float map_scale[WM], map_bias[WM];
+    [[maybe_unused]] char* code_row[WM];
+    if constexpr (EPI == EPI_CODES) {
 #pragma unroll
         for (int m = 0; m < WM; ++m) {
-            const int row = row_w + 32 * m + (lane & 31);
-            const float2 t = reinterpret_cast<const float2*>(a.bracket.thr)[min(row, a.rows - 1)];
-            // rows past the end: no score is above +inf, none compares with NaN
-            thr_hi[m] = row < a.rows ? t.x : INFINITY;
-            thr_lo[m] = row < a.rows ? t.y : __builtin_nanf("");
+            const int row = min(row_w + 32 * m + (lane & 31), a.rows - 1);
+            const float2 t = reinterpret_cast<const float2*>(a.code_map)[row];
+            map_scale[m] = t.x;
+            map_bias[m] = t.y;
+            code_row[m] = reinterpret_cast<char*>(a.codes) + (int64_t)row * a.code_stride + 16 * half;
         }
     }
     if constexpr (EPI == EPI_LOGP) {
@@ -230,12 +227,6 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     // first row of M of the wavefront's sub-tile s of step t
     auto item_of = [&](int t, int s) { return i0 + t * kTI + (gi * SUB + s) * 32; };
 
-    // EPI_BRACKET: the candidate lists of the lane's hidden rows, one per (row, run)
-    [[maybe_unused]] const uint32_t fcap = (uint32_t)a.bracket.first_cap;
-    [[maybe_unused]] const uint32_t lists = (uint32_t)a.bracket.item_tiles;
-    [[maybe_unused]] const uint32_t list0 = (uint32_t)(row_w + (lane & 31)) * lists + (uint32_t)run;
-    [[maybe_unused]] const uint32_t list_step = 32u * lists;
-    [[maybe_unused]] uint32_t word_even = 0u;            // the bits of the step's first sub-tile
     auto epilogue = [&](int t, int s) {
         const int j0 = item_of(t, s);
         if constexpr (EPI == EPI_SAMPLE || EPI == EPI_LOGP) {
@@ -291,84 +282,29 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                 run_max[m] = mx;
             }
         }
-        if constexpr (EPI == EPI_BRACKET) {
-            // element e of acc[m]: hidden row 32 m + lane % 32, item 8 (e / 4) + 4 (lane / 32) + e % 4.  Per score two
-            // comparisons, each shifted into a word per lane by an add whose carry-in is the comparison's mask.
-            static_assert(WM <= 2, "the band bits of a lane are one word");
-            if (j0 + 32 > i1) {                          // items past the run compare false with everything
+        if constexpr (EPI == EPI_CODES) {
+            // element e of acc[m]: hidden row 32 m + lane % 32, item 8 (e / 4) + 4 (lane / 32) + e % 4.  Byte b of word w of a
+            // 32-item unit is the code of item 8 b + w: the lane's four words lie next to each other.
+            if (j0 + 32 > i1) {                          // items past the run: below everything
                 int left = i1 - j0 - 4 * half;
                 asm volatile("" : "+v"(left));
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
 #pragma unroll
-                    for (int m = 0; m < WM; ++m) acc[m][e] = 8 * (e >> 2) + (e & 3) >= left ? __builtin_nanf("") : acc[m][e];
+                    for (int m = 0; m < WM; ++m) acc[m][e] = 8 * (e >> 2) + (e & 3) >= left ? -INFINITY : acc[m][e];
             }
-            uint32_t above[WM], inside = 0u;             // bit 15 - e: above hi; bit 31 - 16 m - e: inside the bracket
 #pragma unroll
             for (int m = 0; m < WM; ++m) {
-                uint32_t up = 0u, in = 0u;
+                u32x4 w;
 #pragma unroll
-                for (int e = 15; e >= 0; --e) {          // (e = 15 first: it ends in the highest bit)
-                    up = 2u * up + (acc[m][e] > thr_hi[m] ? 1u : 0u);
-                    in = 2u * in + (acc[m][e] >= thr_lo[m] ? 1u : 0u);
+                for (int c = 0; c < 4; ++c) {
+                    uint32_t x = 0u;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        x = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(acc[m][4 * b + c], map_scale[m], map_bias[m]), b, x);
+                    w[c] = x;
                 }
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    s_dump[(m * 4 + q4) * 64 + lane] = f32x4_t{acc[m][4 * q4], acc[m][4 * q4 + 1], acc[m][4 * q4 + 2], acc[m][4 * q4 + 3]};
-                above[m] = up;                           // bit e
-                inside |= (in & ~up) << (16 * m);        // bit 16 m + e
-            }
-            // the lane's scores inside a bracket (about one) are taken out, up to four per round
-            while (__builtin_amdgcn_ballot_w64(inside != 0u)) {
-                constexpr int kPer = 4;
-                int q[kPer];
-                bool has[kPer];
-                float f[kPer];
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    has[u] = inside != 0u;
-                    q[u] = has[u] ? __ffs((int)inside) - 1 : 0;                  // 16 m + e
-                    inside &= inside - 1u;                                       // (0 stays 0)
-                    f[u] = reinterpret_cast<const float*>(s_dump)[((q[u] >> 2) * 64 + lane) * 4 + (q[u] & 3)];
-                }
-                uint32_t at[kPer];
-#pragma unroll
-                for (int u = 0; u < kPer; ++u)
-                    at[u] = has[u] ? atomicAdd(&s_cnt[gm * 32 * WM + 32 * (q[u] >> 4) + (lane & 31)], 1u) : 0u;   // < run_items
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    if (has[u]) {
-                        const int m = WM == 1 ? 0 : q[u] >> 4, e = q[u] & 15;
-                        const uint32_t list = list0 + (m == 0 ? 0u : list_step);
-                        const uint32_t item = (uint32_t)(j0 + 8 * (e >> 2) + 4 * half + (e & 3));
-                        uint64_t* dst = at[u] < fcap ? a.bracket.cand_first + ((uint64_t)list * fcap + at[u])
-                                                     : a.bracket.cand + ((uint64_t)list * (uint32_t)a.bracket.over_cap + (at[u] - fcap));
-                        *dst = ((uint64_t)f32_to_ord(f[u]) << 32) | (uint32_t)(~item);
-                    }
-                }
-            }
-            // The words of the bit masks: a lane has the bits of items 4 half + {0..3}, 8 + .., 16 + .., 24 + ..; spread to
-            // those places and joined with the other half's.  Lanes 0..31 then store the word of their first hidden row,
-            // lanes 32..63 that of the second, two sub-tiles at a time where a step has two.
-            uint32_t word = 0u;
-#pragma unroll
-            for (int m = 0; m < WM; ++m) {
-                uint32_t x = above[m];
-                x = (x | (x << 8)) & 0x00FF00FFu;
-                x = ((x | (x << 4)) & 0x0F0F0F0Fu) << (4 * half);
-                x |= (uint32_t)__shfl_xor((int)x, 32);
-                if (WM == 1 || m == half) word = x;
-            }
-            const int brow = row_w + (WM == 1 ? lane & 31 : lane);
-            const bool bok = brow < a.rows && (WM == 2 || half == 0);
-            if constexpr (SUB == 2) {
-                if (s == 0) word_even = word;
-                if (s == 1 && bok) {
-                    uint32_t* o = a.bracket.bits + (int64_t)brow * a.bracket.words_per_row + (j0 - 32) / 32;
-                    *reinterpret_cast<uint2*>(o) = uint2{word_even, word};
-                }
-            } else {
-                if (bok) a.bracket.bits[(int64_t)brow * a.bracket.words_per_row + j0 / 32] = word;
+                if (row_w + 32 * m + (lane & 31) < a.rows) *reinterpret_cast<u32x4*>(code_row[m] + j0) = w;
             }
         }
     };
@@ -402,17 +338,6 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             if (lane < 32 && row < a.rows)
                 reinterpret_cast<float2*>(a.partial)[(int64_t)row * a.partial_stride + run * GI + gi] = float2{mx, sum};
         }
-    }
-    if constexpr (EPI == EPI_BRACKET) {
-        // words past the last step (of the last run) name no item
-        const int tail0 = nt * (kTI / 32), tail = run_items / 32 - tail0;
-        for (int w = tid; w < tail * TM; w += kThreads) {
-            const int row = panel * TM + w / tail;
-            if (row < a.rows) a.bracket.bits[(int64_t)row * a.bracket.words_per_row + i0 / 32 + tail0 + w % tail] = 0u;
-        }
-        __syncthreads();                                 // all candidates of the run are counted
-        for (int t = tid; t < TM; t += kThreads)
-            if (panel * TM + t < a.rows) a.bracket.cnt[(int64_t)(panel * TM + t) * lists + run] = s_cnt[t];
     }
 }
 
@@ -533,7 +458,7 @@ hipError_t configure_panel_lds() {
     hipError_t e = opt_in_epi<EPI_SAMPLE>();
     if (e == hipSuccess) e = opt_in_epi<EPI_LOGP>();
     if (e == hipSuccess) e = opt_in_epi<EPI_LSE>();
-    if (e == hipSuccess) e = opt_in_epi<EPI_BRACKET>();
+    if (e == hipSuccess) e = opt_in_epi<EPI_CODES>();
     return e;
 }
 
@@ -544,7 +469,7 @@ bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
 PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items) { return runs_of(shape_of(chunks, (int)rows), rows, n_items); }
 
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_SAMPLE>(a, stream); }
-hipError_t launch_panel_bracket(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_BRACKET>(a, stream); }
+hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_CODES>(a, stream); }
 
 size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V) {
     const int64_t pairs = panel_runs(chunks, rows, V).runs * kShapes[shape_of(chunks, (int)rows)].gi;

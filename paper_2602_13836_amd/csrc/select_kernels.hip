@@ -748,6 +748,7 @@ __global__ __launch_bounds__(kRowThreads) void emit_rows_kernel(const float* s_a
 // ------------------------------------------------------------------------------------------
 // Bracketed selection: a batch of hidden rows without the score matrix
 // ------------------------------------------------------------------------------------------
+// (selectors wider than 512 elements; narrower ones: code_select_kernels.hip)
 // With hundreds of hidden rows the scores s [rows x V] are hundreds of megabytes: writing them and reading
 // them back for the histogram, the collect and the emit passes costs several times the product that makes
 // them.  Here they never reach memory:
@@ -757,7 +758,7 @@ __global__ __launch_bounds__(kRowThreads) void emit_rows_kernel(const float* s_a
 //             deviations of the hypergeometric count, -/+ 8);
 //   classify  the full product on the matrix cores, whose epilogue keeps only: one bit per (row, token)
 //             "score > hi" (all of these are selected), and (key, id) of the few per cent of scores inside
-//             [lo, hi] (panel_mfma_kernels.hip; tile_mfma_kernels.hip for selectors wider than 512 elements);
+//             [lo, hi] (tile_mfma_kernels.hip);
 //   resolve   per row, with the row's bits in LDS: popcount of the bits = n_above; the (k - n_above)-th largest
 //             candidate by exact radix selection on (key, ~id) is the threshold; the selected candidates'
 //             bits are set; the ids of the set bits are written in ascending order.  A row whose bracket
@@ -1351,34 +1352,24 @@ void select_zero_range(int64_t rows, int64_t V, size_t* words) {
 }
 
 // ---- bracketed selection (many hidden rows, bf16): host side
-constexpr int kSampleLog2 = 13;
-constexpr int64_t kSample = (int64_t)1 << kSampleLog2;   // sampled tokens per call
+constexpr int64_t kSample = 8192;                        // sampled tokens per call
 constexpr int64_t kBracketMaxVocab = 393216;             // the row's bit mask (V / 8 bytes) lives in LDS: 48 KiB here
 
-// From 65 hidden rows on.  Fewer leave more than half of the smallest panel idle, and their scores stay in the last-level cache
-// when they are written: 60 rows, d' = 256, 32768 / 128256 / 262144 tokens 35 / 63 / 107 us with the scores in memory
-// against 41 / 60 / 93 here, 32 rows 34 / 50 / 81 against 41 / 59 / 91, d' = 512 with 60 rows 37 / 79 / 133 against 51 /
-// 87 / 132; 65 rows x 262144 91 here.
+// From 65 hidden rows on: the tiled kernel has tiles of 128 of them there, and fewer rows' scores stay in the last-level cache
+// when they are written (60 rows, d' = 512, 32768 / 128256 / 262144 tokens 37 / 79 / 133 us with the scores in memory
+// against 51 / 87 / 132).
 constexpr int64_t kBracketMinRows = 65;
 bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k) {
     (void)k;
     return dt == DT_BF16 && rows >= kBracketMinRows && V >= 4 * kSample && V <= kBracketMaxVocab;
 }
 
-// items per tile of the classify pass: the runs of the kernel that keeps the hidden rows in registers, or the tiles of
-// the tiled kernel (selectors too wide for the former)
-static int bracket_tn(int chunks, int64_t rows, int64_t V) {
-    return panel_supported(DT_BF16, chunks, rows, V) ? (int)panel_runs(chunks, rows, V).items : kKeepTileItems;
+size_t bracket_scratch_words(int64_t rows, int64_t V) {
+    return bracket_layout(V, (int)rows, kKeepTileItems, kSample).total;
 }
 
-size_t bracket_scratch_words(int chunks, int64_t rows, int64_t V) {
-    return bracket_layout(V, (int)rows, bracket_tn(chunks, rows, V), kSample).total;
-}
-
-void bracket_sample(int chunks, int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, int* log2_m,
-                    float** samp) {
-    *log2_m = kSampleLog2;
-    const BracketLayout L = bracket_layout(V, (int)rows, bracket_tn(chunks, rows, V), kSample);
+void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp) {
+    const BracketLayout L = bracket_layout(V, (int)rows, kKeepTileItems, kSample);
     *ids = reinterpret_cast<int32_t*>(scratch + L.ids);
     *m = L.m;
     *samp = reinterpret_cast<float*>(scratch + L.samp);
@@ -1388,7 +1379,7 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     DeviceInfo di;
     hipError_t e = device_info(&di);
     if (e != hipSuccess) return e;
-    const int tn = bracket_tn(a.chunks, a.rows, a.V);
+    constexpr int tn = kKeepTileItems;
     const BracketLayout L = bracket_layout(a.V, a.rows, tn, kSample);
     // ranks of the bracket in the sample: the number of sampled tokens among the row's k best is
     // hypergeometric with mean m k / V; 6 standard deviations and 8 more on either side
@@ -1409,28 +1400,15 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     ep.item_tiles = L.tiles;
     ep.first_cap = L.first;
     ep.over_cap = tn;
-    if (panel_supported(DT_BF16, a.chunks, a.rows, a.V)) {
-        PanelArgs p{};
-        p.x = a.hp;
-        p.x_row_bytes = (int64_t)a.chunks * 16;
-        p.M = a.Wv;
-        p.m_row_bytes = (int64_t)a.chunks * 16;
-        p.n_items = a.V;
-        p.chunks = a.chunks;
-        p.rows = a.rows;
-        p.bracket = ep;
-        e = launch_panel_bracket(p, stream);
-    } else {
-        GemvArgs g{};
-        g.x = a.hp;
-        g.x_row_bytes = (int64_t)a.chunks * 16;
-        g.M = a.Wv;
-        g.m_row_bytes = (int64_t)a.chunks * 16;
-        g.n_items = a.V;
-        g.chunks = a.chunks;
-        g.rows = a.rows;
-        e = launch_tile_mfma_bracket(g, ep, stream);
-    }
+    GemvArgs g{};
+    g.x = a.hp;
+    g.x_row_bytes = (int64_t)a.chunks * 16;
+    g.M = a.Wv;
+    g.m_row_bytes = (int64_t)a.chunks * 16;
+    g.n_items = a.V;
+    g.chunks = a.chunks;
+    g.rows = a.rows;
+    e = launch_tile_mfma_bracket(g, ep, stream);
     if (e != hipSuccess) return e;
     // LDS of a resolve workgroup: the bit mask, the tiles' offsets and the row's candidates.  As many slots as keep two
     // workgroups on a CU; with one row per CU or fewer, where that is of no use, as many as a row's expected candidates need

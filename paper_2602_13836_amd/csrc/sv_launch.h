@@ -19,6 +19,7 @@ hipError_t device_info(DeviceInfo* out);
 hipError_t configure_skinny_mfma_lds();
 hipError_t configure_tile_mfma_lds();
 hipError_t configure_select_lds();
+hipError_t configure_code_select_lds();
 hipError_t configure_union_lds();
 hipError_t configure_panel_lds();
 
@@ -153,13 +154,18 @@ struct PanelArgs {
     const float* row_sub;    // [rows] subtracted from a row's products
     float* partial;          // [rows][partial_stride][2]
     int64_t partial_stride;
-    BracketEpi bracket;
+    // launch_panel_codes: code(r, j) = the product times code_map[2 r] plus code_map[2 r + 1], to the nearest of 0 .. 255, at
+    // byte (j % 8) * 4 + j / 8 % 4 of the 32-byte unit j / 32 of row r (code_stride bytes apart); units past the last item's
+    // are not written, items past the last get code 0
+    const float* code_map;
+    uint8_t* codes;
+    int64_t code_stride;
 };
 struct PanelRuns { int64_t items, runs; };   // rows of M per run (a multiple of 64) and number of runs
 PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items);
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
-hipError_t launch_panel_bracket(const PanelArgs& a, hipStream_t stream);      // a.bracket: item tiles are the runs
+hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream);
 // out[r, :] = log softmax of the products of row r; ws: panel_log_softmax_ws_floats floats
 size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V);
 hipError_t launch_panel_log_softmax(const PanelArgs& a, float* ws, hipStream_t stream);
@@ -230,8 +236,8 @@ hipError_t launch_topk_of_scores(const RadixArgs& a, hipStream_t stream);
 // Exact top-k of every row for a batch of hidden rows WITHOUT the score matrix in memory (bf16): the scores of a
 // sample of the vocabulary bracket each row's k-th score, the full product is classified against the bracket
 // in the epilogue of the matrix-core kernel, and the few scores inside the bracket are resolved exactly.
-// Order of use: bracket_sample() says how large the sample is (2^log2_m tokens) and where its scores, and its ids if
-// a kernel needs them as a list, live in the scratch; the caller has them computed, then launch_bracket_select().
+// Order of use: bracket_sample() says how large the sample is and where its scores and its ids live in the
+// scratch; the caller has them computed, then launch_bracket_select().
 struct BracketArgs {
     const char* hp;        // [rows x d'] bf16
     const char* Wv;        // [V x d'] bf16, dense rows
@@ -240,12 +246,27 @@ struct BracketArgs {
     int rows;
     int64_t k;
     int32_t* idx_out;      // [rows x k]
-    uint32_t* scratch;     // bracket_scratch_words(chunks, rows, V) words; nothing needs clearing
+    uint32_t* scratch;     // bracket_scratch_words(rows, V) words; nothing needs clearing
 };
 bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k);
-size_t bracket_scratch_words(int chunks, int64_t rows, int64_t V);
-void bracket_sample(int chunks, int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, int* log2_m, float** samp);
+size_t bracket_scratch_words(int64_t rows, int64_t V);
+void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp);
 hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream);
+
+// The same for selectors of up to 512 elements, a byte per score in memory (code_select_kernels.hip)
+struct CodeSelectArgs {
+    const char* hp;        // [rows x d'] bf16
+    const char* Wv;        // [V x d'] bf16, dense rows
+    int chunks;            // d' * 2 / 16
+    int64_t V;
+    int rows;
+    int64_t k;
+    int32_t* idx_out;      // [rows x k]
+    char* scratch;         // code_select_scratch_bytes(rows, V) bytes, 256-byte aligned; nothing needs clearing
+};
+bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V);
+size_t code_select_scratch_bytes(int64_t rows, int64_t V);
+hipError_t launch_code_select(const CodeSelectArgs& a, hipStream_t stream);
 
 // measurement aid: a plain coalesced read of `bytes` (a multiple of 16) from buf; sink: stream_read_blocks() words
 inline int stream_read_blocks(int cus) { return cus * 64; }

@@ -1,0 +1,73 @@
+"""The selection of a batch by one-byte codes, where its map is of no use or its lists leave LDS.  Scores are exact (whole
+numbers in steps of 2^-6), so the ids must be those of a full sort, ties to the smaller id."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+sv = pytest.importorskip("paper_2602_13836_amd")
+
+pytestmark = pytest.mark.gpu
+
+SAMPLE = 4096            # sampled tokens: floor(j V / 4096)
+
+
+def _bf16(a):
+    return torch.from_numpy(a.astype(np.float32)).cuda().to(torch.bfloat16)
+
+
+def _inputs(rows, V, d_prime, seed, d=64):
+    rng = np.random.default_rng(seed)
+    return (rng.integers(-1, 2, (rows, d)), rng.integers(-1, 2, (d_prime, d)), rng.integers(-2, 3, (V, d_prime)) / 64.0)
+
+
+def _check(h, Wd, Wv, k):
+    h, Wd, Wv = _bf16(h), _bf16(Wd), _bf16(Wv)
+    idx, _ = sv.select(h, Wd, Wv, k)
+    s = (h.double() @ Wd.double().t()) @ Wv.double().t()
+    want = torch.sort(s, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values
+    assert torch.equal(idx.long(), want)
+
+
+# units of 32 codes and rounds of 1024 of them at their edges, d' of one unit to the widest
+@pytest.mark.parametrize("rows,V,d_prime,k", [(65, 32768, 256, 1), (66, 32769, 8, 32769), (70, 65536, 512, 64), (65, 65537, 40, 3000),
+                                              (65, 98303, 256, 9000), (260, 40000, 128, 500), (65, 393216, 16, 20000),
+                                              (65, 262145, 24, 131072)])
+def test_edges(rows, V, d_prime, k):
+    _check(*_inputs(rows, V, d_prime, rows + k), k)
+
+
+# a list of entries that is longer than its LDS (wide intervals: half of the tokens are wanted), more rows than CUs among them
+@pytest.mark.parametrize("rows,V", [(300, 200000), (65, 393216)])
+def test_lists_longer_than_lds(rows, V):
+    _check(*_inputs(rows, V, 256, rows), V // 2)
+
+
+def test_rows_of_zeros_and_plateaus():
+    """Rows without any difference between tokens; rows with two, three or a few different scores, so that tens of thousands
+    share the code that decides."""
+    rows, V, d_prime = 70, 50000, 64
+    h, Wd, Wv = _inputs(rows, V, d_prime, 3)
+    h[10] = 0
+    h[69] = 0
+    h[20:30] = 0
+    h[20:30, 0] = np.arange(10) % 3 - 1
+    Wd[:, 0] = 0
+    Wd[0, 0] = 1                                   # rows 20 to 29 see only the first column of W_vocab
+    Wv[:, 0] = np.sign(Wv[:, 0]) / 64.0
+    for k in (1, 100, 16000, 33000, 50000):
+        _check(h, Wd, Wv, k)
+
+
+@pytest.mark.parametrize("k", [200, 5000, 20000])
+@pytest.mark.parametrize("best", [True, False])
+def test_samples_that_mislead(k, best):
+    """The sampled tokens are the best of all, or the worst: the k-th score lies outside of what the sample says."""
+    rows, V, d_prime = 66, 40000, 32
+    h, Wd, Wv = _inputs(rows, V, d_prime, k)
+    h[:, 1] = 1
+    Wd[:, 1] = 0
+    Wd[0, :] = 0
+    Wd[0, 1] = 1                                   # h'[0] = 1 in every row
+    Wv[:, 0] = 0
+    Wv[np.arange(SAMPLE) * V // SAMPLE, 0] = 64.0 if best else -64.0
+    _check(h, Wd, Wv, k)
