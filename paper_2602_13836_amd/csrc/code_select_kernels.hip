@@ -36,7 +36,8 @@ constexpr int kSampleLog2 = 12;
 constexpr int64_t kSample = (int64_t)1 << kSampleLog2;   // sampled tokens per call
 constexpr int kHeld = (int)(kSample / kMapThreads);
 constexpr int64_t kMaxVocab = 262144 + 131072;           // a bit per token in LDS (48 KB)
-constexpr int64_t kMinVocab = 32768;
+constexpr int64_t kMinVocab = 16384;
+
 
 struct CodeLayout {
     int64_t stride;          // bytes between rows of codes: an odd multiple of 256, off the memory channels' period
@@ -161,11 +162,12 @@ constexpr uint32_t kTop = 0x80808080u, kLow = 0x7F7F7F7Fu, kOne = 0x01010101u;
 // lane with the most).  512 rows x 151936, k = 8192, two workgroups per CU: 36 us, of which a workgroup's first pass over the
 // codes is 11, the choice within code C 5, the ids 4 (a second pass over the codes instead of the list: 48; the codes held in
 // registers: 64, they spill; a lane's place in the list by an atomic of its own: 54).
-// The list holds list_cap entries in LDS, what follows is in memory.
-__global__ __launch_bounds__(kThreads, 8) void code_resolve_kernel(int64_t V, int64_t k, const uint8_t* codes, int64_t stride,
+// The list holds list_cap entries in LDS, what follows is in memory.  GROUP: 3 leaves room for two workgroups per CU.
+template <int GROUP>
+__global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kernel(int64_t V, int64_t k, const uint8_t* codes, int64_t stride,
                                                                    const char* hp, const char* Wv, int chunks, uint64_t* spill,
                                                                    int32_t* idx_out, uint32_t list_cap) {
-    constexpr int kGroup = 3;                                 // rounds whose codes are requested together
+    constexpr int kGroup = GROUP;                             // rounds whose codes are requested together
     extern __shared__ __attribute__((aligned(16))) uint32_t s_sel[];
     unsigned char* const s_stage = reinterpret_cast<unsigned char*>(s_sel) + resolve_sel_bytes(V);
     uint32_t* const s_list = reinterpret_cast<uint32_t*>(s_stage + kStageBytes);
@@ -478,13 +480,25 @@ __global__ __launch_bounds__(kThreads, 8) void code_resolve_kernel(int64_t V, in
 
 }  // namespace
 
-bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V) {
-    return panel_supported(dt, chunks, rows, V) && V >= kMinVocab && V <= kMaxVocab;
+// From how many rows on.  The chain of five launches and a workgroup's walk over its row cost 30 us and more whatever the rows are,
+// which the scores in memory (their histogram, two more passes over them) reach with rows and vocabulary: d' = 256, 32768 /
+// 128256 / 262144 tokens, 16 rows 34 / 42 / 57 us with the scores in memory against 33 / 47 / 67 here, 32 rows 35 / 49 / 73
+// against 34 / 50 / 71, 40 rows 36 / 54 / 90 against 36 / 50 / 72, 60 rows 36 / 61 / 101 against 34 / 49 / 70.  A row of many ids
+// takes its workgroup longer (k = 30000 of 128256: 32 rows 51 against 60, 60 rows 63 against 62).  Short rows of W_vocab gain
+// earlier (d' = 64, 16 rows, 32768 / 128256: 35 / 44 against 29 / 39; 8 rows, whose chain over the scores is a shorter one,
+// 24 / 30 against 26 / 35), long ones later (d' = 512, 64 rows: 38 / 71 against 46 / 69).
+inline int64_t min_rows(int chunks, int64_t V, int64_t k) { return chunks > 32 ? 65 : 8 * k > V ? 60 : chunks > 16 ? 40 : 16; }
+bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
+    return panel_codes_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab;
 }
 
 // (more than 64 KB of LDS: an opt-in)
 hipError_t configure_code_select_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&code_resolve_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOneLds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&code_resolve_kernel<3>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOneLds);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&code_resolve_kernel<6>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOneLds);
 }
 
 size_t code_select_scratch_bytes(int64_t rows, int64_t V) { return code_layout(V, rows).total; }
@@ -531,9 +545,13 @@ hipError_t launch_code_select(const CodeSelectArgs& a, hipStream_t stream) {
     const size_t want = ((size_t)(entries * 1.17) + 256) * 4, most = (a.rows > di.cus ? kTwoLds : kOneLds);
     size_t list_bytes = fixed + want <= most ? want : (fixed + 4096 <= most ? most - fixed : 4096);
     list_bytes &= ~(size_t)15;
-    hipLaunchKernelGGL(code_resolve_kernel, dim3((unsigned)a.rows), dim3(kThreads), resolve_sel_bytes(a.V) + kStageBytes + list_bytes,
-                       stream, a.V, a.k, p.codes, L.stride, a.hp, a.Wv, a.chunks,
-                       reinterpret_cast<uint64_t*>(a.scratch + L.spill), a.idx_out, (uint32_t)(list_bytes / 4));
+    auto resolve = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kThreads), resolve_sel_bytes(a.V) + kStageBytes + list_bytes, stream,
+                           a.V, a.k, p.codes, L.stride, a.hp, a.Wv, a.chunks, reinterpret_cast<uint64_t*>(a.scratch + L.spill),
+                           a.idx_out, (uint32_t)(list_bytes / 4));
+    };
+    if (a.rows <= di.cus) resolve(&code_resolve_kernel<6>);
+    else resolve(&code_resolve_kernel<3>);
     return hipGetLastError();
 }
 

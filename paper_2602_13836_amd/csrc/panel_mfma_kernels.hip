@@ -49,15 +49,15 @@ enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_CODES = 3 };
 
 template <int KS>
 constexpr int lds_row_bytes() { return KS * 32 + 16; }        // padded like the tiled kernel's rows: full read rate
-template <int KS>
-constexpr int step_items() { return KS > 16 ? 32 : 64; }      // rows of M per step
-template <int KS>
-constexpr size_t stage_bytes() { return (size_t)step_items<KS>() * lds_row_bytes<KS>(); }
+template <int KS, int GM>
+constexpr int step_items() { return KS > 16 ? 32 : GM > 2 ? 64 : 128; }      // rows of M per step
+template <int KS, int GM>
+constexpr size_t stage_bytes() { return (size_t)step_items<KS, GM>() * lds_row_bytes<KS>(); }
 template <int KS>
 constexpr int fill_rows() { return KS > 16 ? 16 : 32; }       // hidden rows a wavefront fetches through LDS at a time
 template <int KS, int WM, int GM, int EPI>
 constexpr size_t panel_lds_bytes() {
-    size_t n = 2 * stage_bytes<KS>();
+    size_t n = 2 * stage_bytes<KS, GM>();
     if (EPI == EPI_LOGP) n += (size_t)32 * WM * GM * 4;
     const size_t fill = (size_t)kWaves * fill_rows<KS>() * lds_row_bytes<KS>();
     return n > fill ? n : fill;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void wavefront_fence() {
 template <int KS, int WM, int GM, int EPI>
 __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a) {
     constexpr int GI = kWaves / GM;                      // wavefronts along the rows of M
-    constexpr int kTI = step_items<KS>();
+    constexpr int kTI = step_items<KS, GM>();
     constexpr int SUB = kTI / (32 * GI);                 // 32-row sub-tiles per wavefront and step
     constexpr int TM = 32 * WM * GM;
     constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_CODES;               // M is the MFMA's first operand
@@ -105,26 +105,28 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     u32x4 stage[Q];
     const char* m_base = EPI == EPI_SAMPLE ? a.M : a.M + (int64_t)i0 * a.m_row_bytes;
     const uint32_t m_row_bytes = (uint32_t)a.m_row_bytes;                    // n_items * m_row_bytes < 2^32: panel_supported
+    // A run is a whole number of 32 KB of M, the memory channels' period: runs that walked in step would all be at the same
+    // channels, so every run starts its steps at another row (60 rows x 128256, codes: 17.6 -> 15.6 us; three steps on
+    // their way instead of one had made it 24).
+    const int turn = run * 11 % kTI;
+    auto row_of = [&](int q) { return ((q * kThreads + tid) / kUnits + turn) % kTI; };
     auto request = [&](int t) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const int p = q * kThreads + tid;
-            const int u = p % kUnits;
-            uint32_t row = (uint32_t)min(t * kTI + p / kUnits, i1 - i0 - 1);
+            const int u = (q * kThreads + tid) % kUnits;
+            uint32_t row = (uint32_t)min(t * kTI + row_of(q), i1 - i0 - 1);
             if constexpr (EPI == EPI_SAMPLE) row = (uint32_t)(((uint64_t)(row + (uint32_t)i0) * (uint64_t)a.spread_V) >> a.spread_shift);
             stage[q] = *reinterpret_cast<const u32x4*>(m_base + (row * m_row_bytes + (uint32_t)(u < C ? u : C - 1) * 16u));
         }
     };
     auto put = [&](int t) {
-        unsigned char* base = smem + (size_t)(t & 1) * stage_bytes<KS>();
+        unsigned char* base = smem + (size_t)(t & 1) * stage_bytes<KS, GM>();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const int p = q * kThreads + tid;
-            *reinterpret_cast<u32x4*>(base + (p / kUnits) * kRowB + (p % kUnits) * 16) = p % kUnits < C ? stage[q] : zero16();
+            const int u = (q * kThreads + tid) % kUnits;
+            *reinterpret_cast<u32x4*>(base + row_of(q) * kRowB + u * 16) = u < C ? stage[q] : zero16();
         }
     };
-    request(0);
-
     // This wavefront's hidden rows: lane = (row within a group of 32, k-group), like every operand of the MFMA.  They come
     // through LDS (a part of all of it per wavefront, before the first stage is filled): whole rows per load instruction,
     // where the operand's own shape, 32 bytes of 32 rows, took 15 us for the 256 KB of a panel.
@@ -132,40 +134,44 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     bf16x8_t fx[WM][KS];
     {
         constexpr int kRows = fill_rows<KS>();           // rows per round
-        constexpr int kLoads = kRows * kUnits / 64;
+        constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows;
         unsigned char* s_fill = smem + (size_t)wave * kRows * kRowB;
+        auto fetch = [&](int round, u32x4 (&v)[kLoads]) {
 #pragma unroll
-        for (int m = 0; m < WM; ++m)
-#pragma unroll
-            for (int part = 0; part < 32 / kRows; ++part) {
-                u32x4 v[kLoads];
-#pragma unroll
-                for (int q = 0; q < kLoads; ++q) {
-                    const int p = q * 64 + lane, u = p % kUnits;
-                    const int row = min(row_w + 32 * m + kRows * part + p / kUnits, a.rows - 1);   // padding rows: never stored
-                    v[q] = reinterpret_cast<const u32x4*>(a.x + (int64_t)row * a.x_row_bytes)[u < C ? u : C - 1];
-                }
-#pragma unroll
-                for (int q = 0; q < kLoads; ++q) {
-                    const int p = q * 64 + lane, u = p % kUnits;
-                    *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kRowB + u * 16) = u < C ? v[q] : zero16();
-                }
-                // (a wavefront's own LDS accesses stay in order in the hardware; the fences keep the compiler from moving a
-                // lane's reads in front of the other lanes' writes, or the next round's writes in front of these reads)
-                wavefront_fence();
-                if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
-#pragma unroll
-                    for (int kk = 0; kk < KS; ++kk)
-                        fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                                                     s_fill + ((lane & 31) % kRows) * kRowB + (lane >> 5) * 16 + kk * 32));
-                }
-                wavefront_fence();
+            for (int q = 0; q < kLoads; ++q) {
+                const int p = q * 64 + lane, u = p % kUnits;
+                const int row = min(row_w + kRows * round + p / kUnits, a.rows - 1);   // padding rows: never stored
+                v[q] = reinterpret_cast<const u32x4*>(a.x + (int64_t)row * a.x_row_bytes)[u < C ? u : C - 1];
             }
+        };
+        u32x4 v[kLoads];
+        fetch(0, v);                                     // (in front of M's requests: loads come back in order)
+        request(0);
+#pragma unroll
+        for (int round = 0; round < kRounds; ++round) {
+            const int m = round * kRows / 32, part = round % (32 / kRows);
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                const int p = q * 64 + lane, u = p % kUnits;
+                *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kRowB + u * 16) = u < C ? v[q] : zero16();
+            }
+            if (round + 1 < kRounds) fetch(round + 1, v);
+            // (a wavefront's own LDS accesses stay in order in the hardware; the fences keep the compiler from moving a
+            // lane's reads in front of the other lanes' writes, or the next round's writes in front of these reads)
+            wavefront_fence();
+            if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
+#pragma unroll
+                for (int kk = 0; kk < KS; ++kk)
+                    fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
+                                                                 s_fill + ((lane & 31) % kRows) * kRowB + (lane >> 5) * 16 + kk * 32));
+            }
+            wavefront_fence();
+        }
         __syncthreads();                                 // the fill regions are the stages from here on
     }
 
     // ---- per-workgroup state of the epilogues, behind the two stages
-    unsigned char* s_epi = smem + 2 * stage_bytes<KS>();
+    unsigned char* s_epi = smem + 2 * stage_bytes<KS, GM>();
     [[maybe_unused]] float* s_sub = reinterpret_cast<float*>(s_epi);          // EPI_LOGP: [TM]
     const int half = lane >> 5;
     // EPI_CODES, of hidden row row_w + 32 m + lane % 32: what makes a score a code, and where the lane's codes go
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     f32x16_t acc[WM];
     const int b_lane = (lane & 31) * kRowB + (lane >> 5) * 16;
     auto multiply = [&](int t, int s) {
-        const unsigned char* sb = smem + (size_t)(t & 1) * stage_bytes<KS>() + (size_t)((gi * SUB + s) * 32) * kRowB + b_lane;
+        const unsigned char* sb = smem + (size_t)(t & 1) * stage_bytes<KS, GM>() + (size_t)((gi * SUB + s) * 32) * kRowB + b_lane;
 #pragma unroll
         for (int m = 0; m < WM; ++m)
 #pragma unroll
@@ -304,7 +310,8 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                         x = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(acc[m][4 * b + c], map_scale[m], map_bias[m]), b, x);
                     w[c] = x;
                 }
-                if (row_w + 32 * m + (lane & 31) < a.rows) *reinterpret_cast<u32x4*>(code_row[m] + j0) = w;
+                // (j0 >= i1: a step longer than what is left of the run, whose next units are another workgroup's)
+                if (row_w + 32 * m + (lane & 31) < a.rows && j0 < i1) *reinterpret_cast<u32x4*>(code_row[m] + j0) = w;
             }
         }
     };
@@ -361,9 +368,12 @@ __global__ __launch_bounds__(256) void lse_fold_kernel(const float2* partial, in
 //   3  d' <= 512, panels of 256 (32 rows per wavefront)
 //   4, 5, 6  d' <= 128: as 0, 1, 2 with half the steps (512 rows x 128256, d' = 128: selection 110 -> 101 us, log-
 //     probabilities 105 -> 95)
+//   7, 8  panels of 64, codes only: d' <= 256, <= 128; steps of twice as many rows of M
 struct Shape { int panel, gi; };
-constexpr Shape kShapes[7] = {{512, 1}, {256, 2}, {128, 2}, {256, 1}, {512, 1}, {256, 2}, {128, 2}};
+constexpr int kNShapes = 9;
+constexpr Shape kShapes[kNShapes] = {{512, 1}, {256, 2}, {128, 2}, {256, 1}, {512, 1}, {256, 2}, {128, 2}, {64, 4}, {64, 4}};
 inline int shape_of(int chunks, int rows) {
+    if (rows <= 64) return chunks > 16 ? 7 : 8;
     if (chunks > 32) return 3;
     const int base = chunks <= 16 ? 4 : 0;
     if (rows <= 128) return base + 2;
@@ -379,6 +389,13 @@ hipError_t with_shape(int shape, F&& f) {
             case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
             case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
             case 5: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+            default: break;
+        }
+    }
+    if constexpr (EPI == EPI_CODES) {
+        switch (shape) {
+            case 7: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+            case 8: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
             default: break;
         }
     }
@@ -422,7 +439,8 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
     PanelArgs a = a0;
     // A sample of a few thousand rows of M is over in one or two steps and costs what fetching the hidden rows costs:
     // small panels (512 rows, 8192 of them: 10.8 us on panels of 128 against 14.0 on panels of 512).
-    const int shape = EPI == EPI_SAMPLE && a.chunks <= 32 ? (a.chunks <= 16 ? kSampleShapeShort : kSampleShape) : shape_of(a.chunks, a.rows);
+    const int shape = EPI != EPI_SAMPLE ? shape_of(a.chunks, a.rows)
+                      : a.chunks <= 16 ? kSampleShapeShort : a.chunks <= 32 ? kSampleShape : 3;
     const PanelRuns pr = runs_of(shape, a.rows, a.n_items);
     a.run_items = pr.items;
     a.partial_stride = pr.runs * kShapes[shape].gi;
@@ -439,7 +457,8 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
 
 template <int EPI>
 hipError_t opt_in_epi() {
-    for (int shape = 0; shape < 7; ++shape) {
+    for (int shape = 0; shape < kNShapes; ++shape) {
+        if (EPI != EPI_CODES && shape >= 7) continue;
         if (EPI == EPI_SAMPLE && shape != 3 && shape != kSampleShape && shape != kSampleShapeShort) continue;
         const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
             constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
@@ -462,6 +481,9 @@ hipError_t configure_panel_lds() {
     return e;
 }
 
+bool panel_codes_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
+    return dt == DT_BF16 && rows >= 1 && chunks >= 1 && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
+}
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);
 }

@@ -164,6 +164,7 @@ struct PanelArgs {
 struct PanelRuns { int64_t items, runs; };   // rows of M per run (a multiple of 64) and number of runs
 PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items);
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
+bool panel_codes_supported(int dt, int chunks, int64_t rows, int64_t n_items);     // launch_panel_sample, launch_panel_codes
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
 hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream);
 // out[r, :] = log softmax of the products of row r; ws: panel_log_softmax_ws_floats floats
@@ -264,7 +265,7 @@ struct CodeSelectArgs {
     int32_t* idx_out;      // [rows x k]
     char* scratch;         // code_select_scratch_bytes(rows, V) bytes, 256-byte aligned; nothing needs clearing
 };
-bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V);
+bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k);
 size_t code_select_scratch_bytes(int64_t rows, int64_t V);
 hipError_t launch_code_select(const CodeSelectArgs& a, hipStream_t stream);
 

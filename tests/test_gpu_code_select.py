@@ -31,9 +31,21 @@ def _check(h, Wd, Wv, k):
 # units of 32 codes and rounds of 1024 of them at their edges, d' of one unit to the widest
 @pytest.mark.parametrize("rows,V,d_prime,k", [(65, 32768, 256, 1), (66, 32769, 8, 32769), (70, 65536, 512, 64), (65, 65537, 40, 3000),
                                               (65, 98303, 256, 9000), (260, 40000, 128, 500), (65, 393216, 16, 20000),
-                                              (65, 262145, 24, 131072)])
+                                              (65, 262145, 24, 131072),
+                                              # panels of 64 rows: steps of 128 rows of W_vocab, runs shorter than that and of one and a half
+                                              (40, 16384, 256, 300), (64, 16385, 200, 5000), (16, 49000, 128, 1500), (41, 40960, 256, 2000),
+                                              (60, 262144, 248, 8192), (17, 24001, 8, 700)])
 def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
+
+
+def test_less_scratch_than_codes_need():
+    """20 rows of 33500 tokens fit the library's static scratch with their scores in memory, but not as codes."""
+    h, Wd, Wv = (_bf16(a) for a in _inputs(20, 33500, 64, 5))
+    idx, _ = sv.select(h, Wd, Wv, 1000)
+    idx_static = torch.full_like(idx, -1)
+    sv.select_static(h, Wd, Wv, 1000, idx_static)
+    assert torch.equal(idx, idx_static)
 
 
 # a list of entries that is longer than its LDS (wide intervals: half of the tokens are wanted), more rows than CUs among them
