@@ -7,7 +7,7 @@
 // the matrix cores need 20).  Here the hidden rows are STATIONARY:
 // a wavefront keeps the fragments of its 32 WM hidden rows for the whole reduction in registers (128 of them at
 // 64 rows x 256 elements), and a workgroup that owns a panel of TM = 32 WM GM hidden rows streams a long run of rows
-// of M past them, 64 (32) rows at a time, double buffered in LDS and requested two steps ahead.  A step is then
+// of M past them, 64 (32) rows at a time, from memory to a ring of three stages in LDS.  A step is then
 // nothing but LDS reads of M's fragments (one per WM MFMAs), MFMAs and the epilogue; there is no prologue but the
 // first tile's, and one barrier per step.  The matrix is read once per panel (once in all up to 512 hidden rows).
 //
@@ -30,6 +30,7 @@
 
 #include <type_traits>
 
+#include "memory_to_lds.h"
 #include "tile_epilogue.h"
 
 namespace sv {
@@ -47,19 +48,21 @@ constexpr int kRunUnit = 64;             // a run is a multiple of this many row
 // EPI_CODES      a byte per score is stored, a monotone function of the score per hidden row (the selection of a batch)
 enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_CODES = 3 };
 
-template <int KS>
-constexpr int lds_row_bytes() { return KS * 32 + 16; }        // padded like the tiled kernel's rows: full read rate
 template <int KS, int GM>
 constexpr int step_items() { return KS > 16 ? 32 : GM > 2 ? 64 : 128; }      // rows of M per step
 template <int KS, int GM>
-constexpr size_t stage_bytes() { return (size_t)step_items<KS, GM>() * lds_row_bytes<KS>(); }
+constexpr size_t stage_bytes() { return (size_t)step_items<KS, GM>() * KS * 32; }
+template <int KS, int GM>
+constexpr int stages() { return stage_bytes<KS, GM>() > 32 * 1024 ? 2 : 3; }
 template <int KS>
-constexpr int fill_rows() { return KS > 16 ? 16 : 32; }       // hidden rows a wavefront fetches through LDS at a time
+constexpr int fill_row_bytes() { return KS * 32 + 16; }       // hidden rows on their way to registers: padded for the read rate
+template <int KS>
+constexpr int fill_rows() { return KS > 16 ? 8 : 16; }        // ... that a wavefront brings at a time
 template <int KS, int WM, int GM, int EPI>
 constexpr size_t panel_lds_bytes() {
-    size_t n = 2 * stage_bytes<KS, GM>();
+    size_t n = stages<KS, GM>() * stage_bytes<KS, GM>();
     if (EPI == EPI_LOGP) n += (size_t)32 * WM * GM * 4;
-    const size_t fill = (size_t)kWaves * fill_rows<KS>() * lds_row_bytes<KS>();
+    const size_t fill = (stages<KS, GM>() - 1) * stage_bytes<KS, GM>() + (size_t)kWaves * fill_rows<KS>() * fill_row_bytes<KS>();
     return n > fill ? n : fill;
 }
 
@@ -78,11 +81,15 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     constexpr int SUB = kTI / (32 * GI);                 // 32-row sub-tiles per wavefront and step
     constexpr int TM = 32 * WM * GM;
     constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_CODES;               // M is the MFMA's first operand
-    constexpr int kRowB = lds_row_bytes<KS>();
-    constexpr int kUnits = 2 * KS;                       // 16-byte units of a staged row
-    constexpr int Q = kTI * kUnits / kThreads;           // ... per thread and step
-    static_assert(kTI * kUnits % kThreads == 0 && kTI % (32 * GI) == 0, "whole loader passes, whole sub-tiles");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [2][kTI][kRowB], then the epilogue's
+    constexpr int kRowB = KS * 32;                       // a staged row
+    constexpr int kUnits = 2 * KS;                       // ... in units of 16 bytes
+    constexpr int kPieces = kTI * kRowB / 1024;          // 1 KB pieces of a step
+    constexpr int LR = kPieces / kWaves;                 // ... that a wavefront brings
+    constexpr int NS = stages<KS, GM>();
+    // stores of a wavefront per step whose rows are all there
+    constexpr int kStores = EPI == EPI_LSE ? 0 : EPI == EPI_CODES ? SUB * WM : SUB * WM * 16;
+    static_assert(kPieces % kWaves == 0 && kTI % (32 * GI) == 0 && kUnits <= 64 && kUnits >= 16, "whole pieces, whole sub-tiles");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [NS][kTI][kRowB], then the epilogue's
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -99,34 +106,31 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     const int i1 = i0 + run_items < n_items ? i0 + run_items : n_items;
     const int nt = (i1 - i0 + kTI - 1) / kTI;
 
-    // loader: consecutive threads on consecutive 16-byte units of a row (units past its end: the last one again,
-    // zeroed on the way into LDS; rows past the run: the run's last row again, never used)
-    // (branch-free, from one uniform address: a load inside a condition makes the compiler wait for everything in flight)
-    u32x4 stage[Q];
-    const char* m_base = EPI == EPI_SAMPLE ? a.M : a.M + (int64_t)i0 * a.m_row_bytes;
-    const uint32_t m_row_bytes = (uint32_t)a.m_row_bytes;                    // n_items * m_row_bytes < 2^32: panel_supported
+    // M goes from memory to LDS: a step in pieces of 1 KB (64 lanes x 16 bytes), NS - 1 steps on their way.  Unit u of row r
+    // lies at place u ^ (r % 16) of its row, so that the 16 rows a fragment read meets at a time are in different banks; the
+    // lanes' addresses make that order.  Units past a row's end arrive as zeros; rows past the run: the run's last row again,
+    // never used.  (Through registers, the compiler waited for the last step's stores in front of every write to LDS: it
+    // cannot know how many there were.)
     // A run is a whole number of 32 KB of M, the memory channels' period: runs that walked in step would all be at the same
-    // channels, so every run starts its steps at another row (60 rows x 128256, codes: 17.6 -> 15.6 us; three steps on
-    // their way instead of one had made it 24).
-    const int turn = run * 11 % kTI;
-    auto row_of = [&](int q) { return ((q * kThreads + tid) / kUnits + turn) % kTI; };
-    auto request = [&](int t) {
+    // channels, so every run starts its steps at another piece (60 rows x 128256, codes: 17.6 -> 15.6 us).
+    const char* m_base = EPI == EPI_SAMPLE ? a.M : a.M + (int64_t)i0 * a.m_row_bytes;
+    const i32x4_t m_buf = buffer_of(m_base);
+    const uint32_t m_row_bytes = (uint32_t)a.m_row_bytes;                    // n_items * m_row_bytes < 2^32: panel_supported
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    const int turn = run * 11 % kPieces;
+    auto request = [&](int t, int stage) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = (q * kThreads + tid) % kUnits;
-            uint32_t row = (uint32_t)min(t * kTI + row_of(q), i1 - i0 - 1);
+        for (int i = 0; i < LR; ++i) {
+            const int piece = (i * kWaves + wave + turn) % kPieces;
+            const int r = piece * (64 / kUnits) + lane / kUnits;
+            const uint32_t u = (uint32_t)((lane % kUnits) ^ (r & 15));
+            uint32_t row = (uint32_t)min(t * kTI + r, i1 - i0 - 1);
             if constexpr (EPI == EPI_SAMPLE) row = (uint32_t)(((uint64_t)(row + (uint32_t)i0) * (uint64_t)a.spread_V) >> a.spread_shift);
-            stage[q] = *reinterpret_cast<const u32x4*>(m_base + (row * m_row_bytes + (uint32_t)(u < C ? u : C - 1) * 16u));
+            memory_to_lds((int)u < C ? row * m_row_bytes + u * 16u : kOutside, m_buf, 0u,
+                          lds0 + (uint32_t)(stage * (int)stage_bytes<KS, GM>() + piece * 1024));
         }
     };
-    auto put = [&](int t) {
-        unsigned char* base = smem + (size_t)(t & 1) * stage_bytes<KS, GM>();
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int u = (q * kThreads + tid) % kUnits;
-            *reinterpret_cast<u32x4*>(base + row_of(q) * kRowB + u * 16) = u < C ? stage[q] : zero16();
-        }
-    };
+
     // This wavefront's hidden rows: lane = (row within a group of 32, k-group), like every operand of the MFMA.  They come
     // through LDS (a part of all of it per wavefront, before the first stage is filled): whole rows per load instruction,
     // where the operand's own shape, 32 bytes of 32 rows, took 15 us for the 256 KB of a panel.
@@ -134,8 +138,8 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     bf16x8_t fx[WM][KS];
     {
         constexpr int kRows = fill_rows<KS>();           // rows per round
-        constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows;
-        unsigned char* s_fill = smem + (size_t)wave * kRows * kRowB;
+        constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows, kFillB = fill_row_bytes<KS>();
+        unsigned char* s_fill = smem + (NS - 1) * stage_bytes<KS, GM>() + (size_t)wave * kRows * kFillB;
         auto fetch = [&](int round, u32x4 (&v)[kLoads]) {
 #pragma unroll
             for (int q = 0; q < kLoads; ++q) {
@@ -144,34 +148,38 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                 v[q] = reinterpret_cast<const u32x4*>(a.x + (int64_t)row * a.x_row_bytes)[u < C ? u : C - 1];
             }
         };
-        u32x4 v[kLoads];
-        fetch(0, v);                                     // (in front of M's requests: loads come back in order)
-        request(0);
+        u32x4 v[2][kLoads];
+        fetch(0, v[0]);                                  // (in front of M's requests: loads come back in order)
+        fetch(1, v[1]);
+#pragma unroll
+        for (int t = 0; t < NS - 1; ++t)
+            if (t < nt) request(t, t);
 #pragma unroll
         for (int round = 0; round < kRounds; ++round) {
             const int m = round * kRows / 32, part = round % (32 / kRows);
 #pragma unroll
             for (int q = 0; q < kLoads; ++q) {
                 const int p = q * 64 + lane, u = p % kUnits;
-                *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kRowB + u * 16) = u < C ? v[q] : zero16();
+                *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kFillB + u * 16) = u < C ? v[round & 1][q] : zero16();
             }
-            if (round + 1 < kRounds) fetch(round + 1, v);
+            if (round + 2 < kRounds) fetch(round + 2, v[round & 1]);
             // (a wavefront's own LDS accesses stay in order in the hardware; the fences keep the compiler from moving a
             // lane's reads in front of the other lanes' writes, or the next round's writes in front of these reads)
             wavefront_fence();
-            if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
+            if ((lane & 31) / kRows == part) {
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk)
                     fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                                                 s_fill + ((lane & 31) % kRows) * kRowB + (lane >> 5) * 16 + kk * 32));
+                                                                 s_fill + ((lane & 31) % kRows) * kFillB + (lane >> 5) * 16 + kk * 32));
             }
             wavefront_fence();
         }
-        __syncthreads();                                 // the fill regions are the stages from here on
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the first steps
+        __syncthreads();                                 // ... are there; the fill regions are a stage from here on
     }
 
-    // ---- per-workgroup state of the epilogues, behind the two stages
-    unsigned char* s_epi = smem + 2 * stage_bytes<KS, GM>();
+    // ---- per-workgroup state of the epilogues, behind the stages
+    unsigned char* s_epi = smem + NS * stage_bytes<KS, GM>();
     [[maybe_unused]] float* s_sub = reinterpret_cast<float*>(s_epi);          // EPI_LOGP: [TM]
     const int half = lane >> 5;
     // EPI_CODES, of hidden row row_w + 32 m + lane % 32: what makes a score a code, and where the lane's codes go
@@ -189,6 +197,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     }
     if constexpr (EPI == EPI_LOGP) {
         for (int t = tid; t < TM; t += kThreads) s_sub[t] = panel * TM + t < a.rows ? a.row_sub[panel * TM + t] : 0.0f;
+        __syncthreads();
     }
     float run_max[WM], run_sum[WM];                      // EPI_LSE: of hidden row row_w + 32 m + lane % 32
 #pragma unroll
@@ -198,9 +207,12 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     }
 
     f32x16_t acc[WM];
-    const int b_lane = (lane & 31) * kRowB + (lane >> 5) * 16;
-    auto multiply = [&](int t, int s) {
-        const unsigned char* sb = smem + (size_t)(t & 1) * stage_bytes<KS, GM>() + (size_t)((gi * SUB + s) * 32) * kRowB + b_lane;
+    // places of the lane's units 2 kk + lane / 32, kk < 8, of row lane % 32 (kk + 8: 256 bytes on)
+    uint32_t b_lane[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b_lane[j] = (uint32_t)((lane & 31) * kRowB + (((lane >> 5) ^ (lane & 15)) * 16 ^ (j * 32)));
+    auto multiply = [&](int stage, int s) {
+        const unsigned char* sb = smem + stage * (int)stage_bytes<KS, GM>() + (gi * SUB + s) * 32 * kRowB;
 #pragma unroll
         for (int m = 0; m < WM; ++m)
 #pragma unroll
@@ -213,7 +225,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
         auto read = [&](int g, bf16x8_t (&b)[kAhead]) {
 #pragma unroll
             for (int i = 0; i < kAhead; ++i)
-                b[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(sb + (g * kAhead + i) * 32));
+                b[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(sb + b_lane[(g * kAhead + i) & 7] + (g * kAhead + i) / 8 * 256));
         };
         read(0, fb[0]);
 #pragma unroll
@@ -316,22 +328,32 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
         }
     };
 
-    // LDS is complete, and the other stage free, at this barrier; loads and stores to memory stay in flight
-    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    put(0);
-    request(1);
-    barrier();
+    // A step ends when the next one's pieces are there: all but the requests and stores that came after them (the counter
+    // holds 63).  Then the barrier: everybody has read this step's stage.
+    const bool all_rows = row_w + 32 * WM <= a.rows;
+    auto step_ends = [&](bool requested) {
+        constexpr int kSt = kStores < 63 - LR ? kStores : 63 - LR;
+        if (NS > 2 && requested) {
+            if (all_rows) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LR + kSt) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LR) : "memory");
+        } else {
+            if (all_rows) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kSt) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    int stage = 0;
     for (int t = 0; t < nt; ++t) {
-        // stage t + 1 (read last in step t - 1, before the barrier) is filled, then its registers are requested again:
-        // in flight for a whole step
-        put(t + 1);
-        request(t + 2);
+        // the stage of step t - 1 takes step t + NS - 1
+        const bool more = t + NS - 1 < nt;
+        if (more) request(t + NS - 1, stage == 0 ? NS - 1 : stage - 1);
 #pragma unroll 1
         for (int s = 0; s < SUB; ++s) {
-            multiply(t, s);
+            multiply(stage, s);
             epilogue(t, s);
         }
-        barrier();
+        if (t + 1 < nt) step_ends(more);
+        stage = stage == NS - 1 ? 0 : stage + 1;
     }
 
     if constexpr (EPI == EPI_LSE) {
