@@ -295,6 +295,8 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         //     and 1 of slice s (its stage was slice s - 1's).  Slice s + 1 has to be there at turn b + 6: every wavefront
         //     waits at the end of turn b + 5 until only its requests for M of slice s + 2 are outstanding.
         // A ragged last slice: units past a row's end are requested from outside the buffer and arrive as zeros.
+        // A ragged last tile of hidden rows: groups of 32 that are past the end are not multiplied, and what a multiply turn does
+        // not do shortens it (140 rows x 4096 x 128256 254 -> 224 us, 200 264 -> 252, 300 417 -> 401).
         static_assert(GM * GN == 8, "eight wavefronts: two per SIMD");
         constexpr int kAStage = TM * 128, kBStage = TN * 128;
         constexpr int LA = TM / 64, LB = TN / 64;            // requests per wavefront and slice (8 rows each)
@@ -310,8 +312,13 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         const char* const base_b = a.idx ? a.M : a.M + tile0 * a.m_row_bytes;
         LaneSource<FAR> src_a[LA], src_b[LB];
 #pragma unroll
-        for (int i = 0; i < LA; ++i)
-            src_a[i].set(base_a, min(rt * TM + 64 * i + 8 * swave + l8, a.rows - 1) - rt * TM, a.x_row_bytes, (uint32_t)unit * 16u);
+        for (int i = 0; i < LA; ++i) {
+            const int row = rt * TM + 64 * i + 8 * swave + l8;
+            src_a[i].set(base_a, min(row, a.rows - 1) - rt * TM, a.x_row_bytes, (uint32_t)unit * 16u);
+            if constexpr (!FAR) {
+                if (row >= a.rows) src_a[i].at = kOutside;   // zeros, from nowhere
+            }
+        }
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             int64_t item = tile0 + 64 * i + 8 * swave + l8;
@@ -358,42 +365,50 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         read_frags(0, 0, 0, fa[0], fb[0]);
         __builtin_amdgcn_s_waitcnt(0xC07F);
         if (second) turn_ends();               // the second group starts one turn later ...
-        int st0 = 0, st1 = 1, st2 = 2;         // stages of M: slice ks, ks + 1, ks + 2
-        for (int ks = 0; ks < nk; ++ks) {
-            const int sta = ks & 1;
-            static_for<0, 4>([&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                // memory turn
-                if constexpr (m < 3) read_frags(sta, st0, m + 1, fa[(m + 1) & 1], fb[(m + 1) & 1]);
-                else read_frags(sta ^ 1, st1, 0, fa[0], fb[0]);
-                if constexpr (m == 0) request_b(ks + 2, st2, 0, LB0);
-                if constexpr (m == 1) request_b(ks + 2, st2, LB0, LB);
-                if constexpr (m == 3) request_a(ks + 2, sta);
-                if constexpr (m == 2) {
-                    __builtin_amdgcn_s_waitcnt(0xC07F);      // the slice's last reads: done before this turn ends
-                    if (second) slice_landed();
-                }
-                turn_ends();
-                // multiply turn
-                __builtin_amdgcn_s_setprio(1);
+        // (SOME: only the wavefront's first `live` groups of 32 hidden rows are any)
+        const int live = __builtin_amdgcn_readfirstlane((a.rows - (rt * TM + (swave / GN) * 32 * WM) + 31) / 32);
+        auto walk = [&](auto some) {
+            int st0 = 0, st1 = 1, st2 = 2;         // stages of M: slice ks, ks + 1, ks + 2
+            for (int ks = 0; ks < nk; ++ks) {
+                const int sta = ks & 1;
+                static_for<0, 4>([&](auto mc) {
+                    constexpr int m = decltype(mc)::value;
+                    // memory turn
+                    if constexpr (m < 3) read_frags(sta, st0, m + 1, fa[(m + 1) & 1], fb[(m + 1) & 1]);
+                    else read_frags(sta ^ 1, st1, 0, fa[0], fb[0]);
+                    if constexpr (m == 0) request_b(ks + 2, st2, 0, LB0);
+                    if constexpr (m == 1) request_b(ks + 2, st2, LB0, LB);
+                    if constexpr (m == 3) request_a(ks + 2, sta);
+                    if constexpr (m == 2) {
+                        __builtin_amdgcn_s_waitcnt(0xC07F);      // the slice's last reads: done before this turn ends
+                        if (second) slice_landed();
+                    }
+                    turn_ends();
+                    // multiply turn
+                    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                for (int i = 0; i < WM; ++i)
+                    for (int i = 0; i < WM; ++i) {
+                        if (decltype(some)::value && i >= live) break;           // uniform
 #pragma unroll
-                    for (int n = 0; n < WN; ++n)
-                        acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[m & 1][i], fb[m & 1][n], acc[i][n], 0, 0, 0);
-                __builtin_amdgcn_s_setprio(0);
-                __builtin_amdgcn_sched_barrier(0);
-                __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): what the last memory turn read is there
-                if constexpr (m == 2) {
-                    if (!second) slice_landed();
-                }
-                turn_ends();
-            });
-            const int st = st0;
-            st0 = st1;
-            st1 = st2;
-            st2 = st;
-        }
+                        for (int n = 0; n < WN; ++n)
+                            acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[m & 1][i], fb[m & 1][n], acc[i][n], 0, 0, 0);
+                    }
+                    __builtin_amdgcn_s_setprio(0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): what the last memory turn read is there
+                    if constexpr (m == 2) {
+                        if (!second) slice_landed();
+                    }
+                    turn_ends();
+                });
+                const int st = st0;
+                st0 = st1;
+                st1 = st2;
+                st2 = st;
+            }
+        };
+        if (live >= WM) walk(std::false_type{});
+        else walk(std::true_type{});       // (the same turns, and as many)
         if (!second) turn_ends();              // ... and the first ends one turn earlier: the same count for all
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (slices past the end: requested, never read)
         turn_ends();
