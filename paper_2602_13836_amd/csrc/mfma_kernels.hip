@@ -216,15 +216,17 @@ __device__ __forceinline__ void store_ksplit(const GemvArgs& a, const f32x4_t su
 // Hidden rows past the last arrive as zeros (FAR: repeat it) and are never stored; units past a row's end are zeros.  FAR:
 // lanes' sources are addresses (see memory_to_lds.h), for lists into matrices of more than 4 GB and rows of 128 MB apart.
 constexpr int kSplitWaves = 8;
-template <int NB, int DEPTH>
-constexpr size_t ksplit_lds_bytes() { return (size_t)kSplitWaves * DEPTH * (16 + 16 * NB) * 128; }
-template <int NB, int DEPTH, bool FAR>
+template <int MB, int NB, int DEPTH>
+constexpr size_t ksplit_lds_bytes() { return (size_t)kSplitWaves * DEPTH * 16 * (MB + NB) * 128; }
+// MB groups of 16 rows of M, NB of 16 hidden rows
+template <int MB, int NB, int DEPTH, bool FAR>
 __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS, const GemvArgs rest, const int row_base) {
     const GemvArgs a = with_hot(rest, m_base, idx_base, x_base, n_items_arg, m_row_bytes_arg, x_row_bytes_arg,
                                 n_items_dev_arg);
     constexpr int N = 16 * NB;
-    constexpr int kChunkB = (16 + N) * 128;              // 64 elements of the wavefront's rows of M, then of the hidden rows
-    constexpr int kRequests = 2 + 2 * NB;                // 1 KB each, per chunk
+    constexpr int kChunkB = 16 * (MB + NB) * 128;        // 64 elements of the wavefront's rows of M, then of the hidden rows
+    constexpr int kRequests = 2 * (MB + NB);             // 1 KB each, per chunk
+    static_assert(MB * NB <= kSplitWaves, "a wavefront sums each block");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [waves][DEPTH][kChunkB], then the partial sums
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS,
     const int row0 = row_base + (int)blockIdx.y * N;
     const int rows_here = min(a.rows - row0, N);
     const int64_t n_items = a.n_items_dev ? (int64_t)*a.n_items_dev : a.n_items;
-    const int64_t tile0 = (int64_t)blockIdx.x * 16;
+    const int64_t tile0 = (int64_t)blockIdx.x * (16 * MB);
     if (tile0 >= n_items || rows_here <= 0 || !gate_open(a, n_items)) {
         prepare_scratch(a);
         return;
@@ -245,12 +247,12 @@ __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS,
     const uint32_t unit0 = (uint32_t)((lane & 7) ^ (l8 >> 1)), unit1 = unit0 ^ 4u;       // of rows l8 and l8 + 8 of a 16-row group
     const char* const base_m = a.idx ? a.M : a.M + tile0 * a.m_row_bytes;
     const char* const base_x = a.x + (int64_t)row0 * a.x_row_bytes;
-    LaneSource<FAR> src_m[2], src_x[2 * NB];
+    LaneSource<FAR> src_m[2 * MB], src_x[2 * NB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < 2 * MB; ++j) {
         int64_t item = tile0 + 8 * j + l8;
         if (item > n_items - 1) item = n_items - 1;
-        src_m[j].set(base_m, a.idx ? (int64_t)a.idx[item] : item - tile0, a.m_row_bytes, (j ? unit1 : unit0) * 16u);
+        src_m[j].set(base_m, a.idx ? (int64_t)a.idx[item] : item - tile0, a.m_row_bytes, (j & 1 ? unit1 : unit0) * 16u);
     }
 #pragma unroll
     for (int j = 0; j < 2 * NB; ++j) {
@@ -273,13 +275,16 @@ __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS,
         const bool out0 = first_unit + (int)unit0 >= C, out1 = first_unit + (int)unit1 >= C;      // (past the last chunk: all of it)
         const int64_t soff = (int64_t)first_unit * 16;
         const uint32_t at = lds + (uint32_t)(stage * kChunkB);
-        bring<1024>(src_m[0], src_m[1], out0, out1, buf_m, soff, at);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) bring<1024>(src_x[2 * nb], src_x[2 * nb + 1], out0, out1, buf_x, soff, at + 2048u * (nb + 1));
+        for (int mb = 0; mb < MB; ++mb) bring<1024>(src_m[2 * mb], src_m[2 * mb + 1], out0, out1, buf_m, soff, at + 2048u * mb);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) bring<1024>(src_x[2 * nb], src_x[2 * nb + 1], out0, out1, buf_x, soff, at + 2048u * (MB + nb));
     };
-    f32x4_t acc[NB];
+    f32x4_t acc[MB][NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < DEPTH; ++c) request(c, c);
     const int frag = i * 128 + ((g ^ ((i >> 1) & 7)) * 16);                   // unit 4 kk + g of row i
@@ -287,36 +292,41 @@ __global__ __launch_bounds__(64 * kSplitWaves) void ksplit_kernel(SV_HOT_PARAMS,
     for (int c = 0; c < nch; ++c) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DEPTH - 1) * kRequests) : "memory");      // chunk c is there
         const unsigned char* p = ring + stage * kChunkB;
-        u32x4 av[2], bv[2][NB];
+        u32x4 av[2][MB], bv[2][NB];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            av[kk] = *reinterpret_cast<const u32x4*>(p + (frag ^ (kk * 64)));
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) bv[kk][nb] = *reinterpret_cast<const u32x4*>(p + 2048 * (nb + 1) + (frag ^ (kk * 64)));
+            for (int mb = 0; mb < MB; ++mb) av[kk][mb] = *reinterpret_cast<const u32x4*>(p + 2048 * mb + (frag ^ (kk * 64)));
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) bv[kk][nb] = *reinterpret_cast<const u32x4*>(p + 2048 * (MB + nb) + (frag ^ (kk * 64)));
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                    // read, so its place may be filled again
         request(c + DEPTH, stage);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[kk]),
-                                                                  __builtin_bit_cast(bf16x8_t, bv[kk][nb]), acc[nb], 0, 0, 0);
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[kk][mb]),
+                                                                          __builtin_bit_cast(bf16x8_t, bv[kk][nb]), acc[mb][nb], 0, 0, 0);
         stage = stage + 1 == DEPTH ? 0 : stage + 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                          // (chunks past the end: requested, never read)
     prepare_scratch(a);
     __syncthreads();
-    f32x4_t* s_part = reinterpret_cast<f32x4_t*>(smem);                       // [waves][NB][64]
+    f32x4_t* s_part = reinterpret_cast<f32x4_t*>(smem);                       // [waves][MB NB][64]
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) s_part[(wave * NB + nb) * 64 + lane] = acc[nb];
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) s_part[(wave * MB * NB + mb * NB + nb) * 64 + lane] = acc[mb][nb];
     __syncthreads();
-    if (wave >= NB) return;
-    const int nb = wave;                                   // wavefront nb sums and stores hidden rows 16 nb ..
-    f32x4_t sum = s_part[nb * 64 + lane];
+    if (wave >= MB * NB) return;
+    const int mb = wave / NB, nb = wave % NB;              // a wavefront sums and stores 16 x 16 results
+    f32x4_t sum = s_part[wave * 64 + lane];
 #pragma unroll
-    for (int w = 1; w < kSplitWaves; ++w) sum += s_part[(w * NB + nb) * 64 + lane];
-    store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 4 * g, n_items);
+    for (int w = 1; w < kSplitWaves; ++w) sum += s_part[(w * MB * NB + wave) * 64 + lane];
+    store_ksplit(a, sum, row0, nb * 16 + i, rows_here, tile0 + 16 * mb + 4 * g, n_items);
 }
 
 // The same for rows of M that do not start on (half) cache lines (2056 elements, say).  The pieces of 128 bytes above straddle two
@@ -445,14 +455,14 @@ bool near(const GemvArgs& a) {
     return a.idx == nullptr || (a.m_rows > 0 && a.m_rows <= kSpan / a.m_row_bytes);
 }
 
-template <int NB, int DEPTH>
+template <int MB, int NB, int DEPTH>
 hipError_t launch_ksplit_depth(const GemvArgs& a, int row0, int groups, hipStream_t stream) {
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n_items + 15) / 16), (unsigned)groups), dim3(64 * kSplitWaves),
-                           (ksplit_lds_bytes<NB, DEPTH>()), stream, SV_HOT_ARGS(a), a, row0);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n_items + 16 * MB - 1) / (16 * MB)), (unsigned)groups), dim3(64 * kSplitWaves),
+                           (ksplit_lds_bytes<MB, NB, DEPTH>()), stream, SV_HOT_ARGS(a), a, row0);
         return hipGetLastError();
     };
-    return near(a) ? go(&ksplit_kernel<NB, DEPTH, false>) : go(&ksplit_kernel<NB, DEPTH, true>);
+    return near(a) ? go(&ksplit_kernel<MB, NB, DEPTH, false>) : go(&ksplit_kernel<MB, NB, DEPTH, true>);
 }
 
 // rows of M that suit the form fed from memory to LDS: on cache lines, up to 32 hidden rows also on half lines (us, that form /
@@ -467,13 +477,13 @@ hipError_t launch_ksplit(const GemvArgs& a, int row0, int groups, hipStream_t st
                            stream, SV_HOT_ARGS(a), a, row0);
         return hipGetLastError();
     }
-    if (NB == 2) return launch_ksplit_depth<2, 3>(a, row0, groups, stream);
+    if (NB == 2) return launch_ksplit_depth<1, 2, 3>(a, row0, groups, stream);
     DeviceInfo di;
     const hipError_t e = device_info(&di);
     if (e != hipSuccess) return e;
     // one workgroup per CU: a deep ring; more workgroups than that: rings that let two share a CU
-    return (a.n_items + 15) / 16 * groups <= di.cus ? launch_ksplit_depth<1, 4>(a, row0, groups, stream)
-                                                    : launch_ksplit_depth<1, 2>(a, row0, groups, stream);
+    return (a.n_items + 15) / 16 * groups <= di.cus ? launch_ksplit_depth<1, 1, 4>(a, row0, groups, stream)
+                                                    : launch_ksplit_depth<1, 1, 2>(a, row0, groups, stream);
 }
 
 template <int WPB, int NB>
@@ -502,12 +512,14 @@ hipError_t configure_skinny_mfma_lds() {
     auto opt_in = [&](auto kernel, size_t bytes) {
         if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     };
-    opt_in(&ksplit_kernel<1, 2, false>, ksplit_lds_bytes<1, 2>());
-    opt_in(&ksplit_kernel<1, 2, true>, ksplit_lds_bytes<1, 2>());
-    opt_in(&ksplit_kernel<1, 4, false>, ksplit_lds_bytes<1, 4>());
-    opt_in(&ksplit_kernel<1, 4, true>, ksplit_lds_bytes<1, 4>());
-    opt_in(&ksplit_kernel<2, 3, false>, ksplit_lds_bytes<2, 3>());
-    opt_in(&ksplit_kernel<2, 3, true>, ksplit_lds_bytes<2, 3>());
+    opt_in(&ksplit_kernel<1, 1, 2, false>, ksplit_lds_bytes<1, 1, 2>());
+    opt_in(&ksplit_kernel<1, 1, 2, true>, ksplit_lds_bytes<1, 1, 2>());
+    opt_in(&ksplit_kernel<1, 1, 4, false>, ksplit_lds_bytes<1, 1, 4>());
+    opt_in(&ksplit_kernel<1, 1, 4, true>, ksplit_lds_bytes<1, 1, 4>());
+    opt_in(&ksplit_kernel<1, 2, 3, false>, ksplit_lds_bytes<1, 2, 3>());
+    opt_in(&ksplit_kernel<1, 2, 3, true>, ksplit_lds_bytes<1, 2, 3>());
+    opt_in(&ksplit_kernel<2, 2, 2, false>, ksplit_lds_bytes<2, 2, 2>());
+    opt_in(&ksplit_kernel<2, 2, 2, true>, ksplit_lds_bytes<2, 2, 2>());
     return e;
 }
 
@@ -533,6 +545,11 @@ hipError_t launch_ksplit_rows(const GemvArgs& a, hipStream_t stream) {
     // few workgroups: 16 hidden rows each (twice as many workgroups, each pulling a third less through its CU)
     const int64_t tiles = (a.n_items + 15) / 16;
     if (tiles * ((a.rows + 31) / 32) * 4 <= di.cus) return launch_ksplit<1>(a, 0, (a.rows + 15) / 16, stream);
+    // many: 32 rows of M by 32 hidden rows, which pull 512 KB through a CU for twice the results of 384 KB (1024 hidden rows x 4096
+    // into 256, whose smaller blocks make two rounds of workgroups: 22.6 -> 16 us; log-probabilities of 600, 700 rows x 16384 46.5
+    // -> 42.8, 48.6 -> 45.3; 512 rows, one round, 34.7 -> 35.7)
+    if ((a.n_items + 31) / 32 * ((a.rows + 31) / 32) * 16 >= (int64_t)di.cus * 9 && whole_pieces(a))
+        return launch_ksplit_depth<2, 2, 2>(a, 0, (a.rows + 31) / 32, stream);
     return launch_ksplit<2>(a, 0, (a.rows + 31) / 32, stream);
 }
 
