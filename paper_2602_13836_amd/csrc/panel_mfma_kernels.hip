@@ -54,15 +54,17 @@ template <int KS, int GM>
 constexpr size_t stage_bytes() { return (size_t)step_items<KS, GM>() * KS * 32; }
 template <int KS, int GM>
 constexpr int stages() { return stage_bytes<KS, GM>() > 32 * 1024 ? 2 : 3; }
-template <int KS>
-constexpr int fill_row_bytes() { return KS * 32 + 16; }       // hidden rows on their way to registers: padded for the read rate
-template <int KS>
-constexpr int fill_rows() { return KS > 16 ? 8 : 16; }        // ... that a wavefront brings at a time
+// While the hidden rows come in, LDS holds so many steps of M ...
+template <int KS, int GM>
+constexpr int early_steps() { return KS > 8 ? 1 : stages<KS, GM>() - 1; }
+// ... and so many hidden rows per wavefront at a time
+template <int KS, int GM>
+constexpr int fill_rows() { return KS > 16 || stages<KS, GM>() == 2 ? 16 : 32; }
 template <int KS, int WM, int GM, int EPI>
 constexpr size_t panel_lds_bytes() {
     size_t n = stages<KS, GM>() * stage_bytes<KS, GM>();
     if (EPI == EPI_LOGP) n += (size_t)32 * WM * GM * 4;
-    const size_t fill = (stages<KS, GM>() - 1) * stage_bytes<KS, GM>() + (size_t)kWaves * fill_rows<KS>() * fill_row_bytes<KS>();
+    const size_t fill = early_steps<KS, GM>() * stage_bytes<KS, GM>() + (size_t)kWaves * fill_rows<KS, GM>() * KS * 32;
     return n > fill ? n : fill;
 }
 
@@ -137,9 +139,9 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     const int row_w = panel * TM + gm * 32 * WM;         // first hidden row of the wavefront
     bf16x8_t fx[WM][KS];
     {
-        constexpr int kRows = fill_rows<KS>();           // rows per round
-        constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows, kFillB = fill_row_bytes<KS>();
-        unsigned char* s_fill = smem + (NS - 1) * stage_bytes<KS, GM>() + (size_t)wave * kRows * kFillB;
+        constexpr int kRows = fill_rows<KS, GM>();       // rows per round
+        constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows;
+        unsigned char* s_fill = smem + early_steps<KS, GM>() * stage_bytes<KS, GM>() + (size_t)wave * kRows * kRowB;
         auto fetch = [&](int round, u32x4 (&v)[kLoads]) {
 #pragma unroll
             for (int q = 0; q < kLoads; ++q) {
@@ -148,29 +150,29 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                 v[q] = reinterpret_cast<const u32x4*>(a.x + (int64_t)row * a.x_row_bytes)[u < C ? u : C - 1];
             }
         };
-        u32x4 v[2][kLoads];
-        fetch(0, v[0]);                                  // (in front of M's requests: loads come back in order)
-        fetch(1, v[1]);
+        u32x4 v[kLoads];
+        fetch(0, v);                                     // (in front of M's requests: loads come back in order)
 #pragma unroll
-        for (int t = 0; t < NS - 1; ++t)
+        for (int t = 0; t < early_steps<KS, GM>(); ++t)
             if (t < nt) request(t, t);
 #pragma unroll
         for (int round = 0; round < kRounds; ++round) {
             const int m = round * kRows / 32, part = round % (32 / kRows);
 #pragma unroll
-            for (int q = 0; q < kLoads; ++q) {
-                const int p = q * 64 + lane, u = p % kUnits;
-                *reinterpret_cast<u32x4*>(s_fill + (p / kUnits) * kFillB + u * 16) = u < C ? v[round & 1][q] : zero16();
+            for (int q = 0; q < kLoads; ++q) {           // (units at the places that M's have)
+                const int p = q * 64 + lane, u = p % kUnits, r = p / kUnits;
+                *reinterpret_cast<u32x4*>(s_fill + r * kRowB + (u ^ (r & 15)) * 16) = u < C ? v[q] : zero16();
             }
-            if (round + 2 < kRounds) fetch(round + 2, v[round & 1]);
+            if (round + 1 < kRounds) fetch(round + 1, v);
             // (a wavefront's own LDS accesses stay in order in the hardware; the fences keep the compiler from moving a
             // lane's reads in front of the other lanes' writes, or the next round's writes in front of these reads)
             wavefront_fence();
-            if ((lane & 31) / kRows == part) {
+            if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
+                const unsigned char* mine = s_fill + ((lane & 31) % kRows) * kRowB;
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk)
                     fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                                                 s_fill + ((lane & 31) % kRows) * kFillB + (lane >> 5) * 16 + kk * 32));
+                                                                 mine + (((2 * kk + (lane >> 5)) ^ (lane & 15)) * 16)));
             }
             wavefront_fence();
         }
@@ -342,6 +344,9 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
+#pragma unroll
+    for (int t = early_steps<KS, GM>(); t < NS - 1; ++t)
+        if (t < nt) request(t, t);
     int stage = 0;
     for (int t = 0; t < nt; ++t) {
         // the stage of step t - 1 takes step t + NS - 1
