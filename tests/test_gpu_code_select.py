@@ -83,3 +83,20 @@ def test_samples_that_mislead(k, best):
     Wv[:, 0] = 0
     Wv[np.arange(SAMPLE) * V // SAMPLE, 0] = 64.0 if best else -64.0
     _check(h, Wd, Wv, k)
+
+
+@pytest.mark.parametrize("far", [2.0 ** 6, 2.0 ** 20])
+@pytest.mark.parametrize("k", [300, 4000])
+def test_scores_far_from_all_others(k, far):
+    """A few tokens of every row score far above and far below the rest, sampled ones among them: one step of the map's first
+    histogram holds nearly the whole sample.  (Their own scores round; all of those above are selected, none of those below.)"""
+    rows, V, d_prime = 65, 33000, 64
+    h, Wd, Wv = _inputs(rows, V, d_prime, k)
+    h[:, 1] = 1
+    Wd[:, 1] = 0
+    Wd[0, :] = 0
+    Wd[0, 1] = 1                                   # h'[0] = 1 in every row
+    Wv[:, 0] = 0
+    Wv[::1009, 0] = far
+    Wv[5::2003, 0] = -far
+    _check(h, Wd, Wv, k)
