@@ -498,14 +498,18 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
 
 }  // namespace
 
-// From how many rows on.  The chain of five launches and a workgroup's walk over its row cost 30 us and more whatever the rows are,
-// which the scores in memory (their histogram, two more passes over them) reach with rows and vocabulary: d' = 256, 32768 /
-// 128256 / 262144 tokens, 16 rows 34 / 42 / 57 us with the scores in memory against 33 / 47 / 67 here, 32 rows 35 / 49 / 73
-// against 34 / 50 / 71, 40 rows 36 / 54 / 90 against 36 / 50 / 72, 60 rows 36 / 61 / 101 against 34 / 49 / 70.  A row of many ids
-// takes its workgroup longer (k = 30000 of 128256: 32 rows 51 against 60, 60 rows 63 against 62).  Short rows of W_vocab gain
-// earlier (d' = 64, 16 rows, 32768 / 128256: 35 / 44 against 29 / 39; 8 rows, whose chain over the scores is a shorter one,
-// 24 / 30 against 26 / 35), long ones later (d' = 512, 64 rows: 38 / 71 against 46 / 69).
-inline int64_t min_rows(int chunks, int64_t V, int64_t k) { return chunks > 32 ? 65 : 8 * k > V ? 60 : chunks > 16 ? 40 : 16; }
+// From how many rows on.  The chain of five launches and a workgroup's walk over its row cost about as much whatever the rows
+// are, which the scores in memory (their histogram, two more passes over them) reach with rows and vocabulary.  us, scores in memory
+// / codes, 32768, 128256, 262144 tokens, k = V / 32: d' = 256, 9 rows 31 / 28, 38 / 41, 51 / 61, 16 rows 33 / 30, 42 / 43, 57 / 64,
+// 24 rows 34 / 30, 45 / 44, 66 / 64, 36 rows 36 / 30, 53 / 44, 86 / 65; d' = 128, 9 rows 29 / 23, 36 / 35; 8 rows, whose chain over the
+// scores is a shorter one, 24 / 26 and more.  A row of many ids takes its workgroup longer (k = 30000 of 128256: d' = 256, 40 rows
+// 55 / 57, 60 rows 63 / 58; d' = 128, 16 rows 42 / 48; k = 16000 of 64000, 40 rows 40 / 37).  d' > 256: there are no panels of 64
+// rows, and 64 on one of 256 take 46 and 69 against 38 and 71.
+inline int64_t min_rows(int chunks, int64_t V, int64_t k) {
+    if (chunks > 32) return 65;
+    if (8 * k > V) return chunks > 16 ? 60 : 40;
+    return chunks > 16 ? (V <= 65536 ? 9 : 24) : (V <= 131072 ? 9 : 16);
+}
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
     return panel_codes_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab;
 }

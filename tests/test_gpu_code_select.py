@@ -34,7 +34,7 @@ def _check(h, Wd, Wv, k):
                                               (65, 262145, 24, 131072),
                                               # panels of 64 rows: steps of 128 rows of W_vocab, runs shorter than that and of one and a half
                                               (40, 16384, 256, 300), (64, 16385, 200, 5000), (16, 49000, 128, 1500), (41, 40960, 256, 2000),
-                                              (60, 262144, 248, 8192), (17, 24001, 8, 700)])
+                                              (60, 262144, 248, 8192), (17, 24001, 8, 700), (9, 16384, 256, 100), (24, 70000, 256, 900)])
 def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
 
