@@ -25,7 +25,7 @@ SV_OP_AUX_LOG_SOFTMAX = 6
 SV_IDX_PADDED = 4        # OR into idx_mode: the list may hold padding slots (-1)
 SV_IDX_SORTED = 8        # OR into idx_mode: every list is sorted by ascending id (what select emits)
 MAX_KD = 64
-SELECT_SAMPLE = 8192     # sampled tokens of the batch selection: ids floor(j * V / SELECT_SAMPLE)
+SELECT_SAMPLE = 8192     # sampled tokens of a batch's selection: ids floor(j * V / SELECT_SAMPLE), up to d' = 512 every second one
 
 EXPORTS = (
     "specvocab_version",

@@ -1,6 +1,6 @@
 // Products with a SHORT reduction for many hidden rows (the selector's W_vocab h', Section 3.3 Step 1, for a batch,
 // and Section 3.4's distribution over the whole vocabulary):
-//     s[r, j] = < M[row(j), :], x[r, :] >      r < rows (more than 64), rows of M of at most 512 elements, bf16
+//     s[r, j] = < M[row(j), :], x[r, :] >      r < rows (more than 64; codes also for fewer), rows of M of at most 512 elements, bf16
 //
 // What bounds it.  With d' = 256 a 256 x 256 output tile is four 64-element slices of main loop: the tiled kernel spends
 // more time filling its pipeline, and in its epilogue, than multiplying (512 rows x 151936: 45 us of product of which

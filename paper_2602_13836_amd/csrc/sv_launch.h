@@ -135,7 +135,7 @@ struct PickEpi {
 };
 hipError_t launch_tile_mfma_pick(const GemvArgs& a, const PickEpi& pk, hipStream_t stream);
 
-// Products with a short reduction (rows of M of up to 64 16-byte units) for more than 64 hidden rows: the hidden rows stay
+// Products with a short reduction (rows of M of up to 64 16-byte units) for many hidden rows: the hidden rows stay
 // in registers and runs of run_items rows of M stream past them.
 struct PanelArgs {
     const char* x;           // [rows x d'] bf16, row stride x_row_bytes

@@ -100,3 +100,27 @@ def test_scores_far_from_all_others(k, far):
     Wv[::1009, 0] = far
     Wv[5::2003, 0] = -far
     _check(h, Wd, Wv, k)
+
+
+@pytest.mark.parametrize("rows", [40, 300])
+def test_replays_of_a_captured_call(rows):
+    V, d_prime, k = 40000, 128, 1500
+    h, Wd, Wv = (_bf16(a) for a in _inputs(rows, V, d_prime, rows))
+    idx = torch.zeros((rows, k), dtype=torch.int32, device="cuda")
+    ws = torch.empty(sv.workspace_bytes(sv.SV_OP_SELECT, rows, 64, V, k, d_prime, 0, sv.SV_BF16, 0), dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        sv.select(h, Wd, Wv, k, idx_out=idx, ws=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sv.select(h, Wd, Wv, k, idx_out=idx, ws=ws)
+    for seed in range(3):
+        h.copy_(_bf16(_inputs(rows, V, d_prime, 100 + seed)[0]))
+        ws.fill_(seed * 85)
+        graph.replay()
+        got = idx.clone()
+        want, _ = sv.select(h, Wd, Wv, k)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
