@@ -60,52 +60,66 @@ __host__ __device__ inline CodeLayout code_layout(int64_t V, int64_t rows) {
 // ---- map: one workgroup per row, its part of the sample in registers
 // map[r] = {scale, bias} from where the rank_hi-th and the rank_lo-th largest of the row's sample scores lie (1 <= rank_hi <=
 // rank_lo <= kSample): in a histogram of equal steps from the smallest to the largest, so the interval is up to two steps
-// wider than those two scores -- and drawn again over itself where that is much wider, as a few scores far from all others
-// make it (what bounds this kernel is its chain of barriers: 60 rows 3.5 us, 512 rows 5.6, where two
+// wider than those two scores -- and drawn again over itself, as long as that helps, where that is much wider, as a few scores far
+// from all others make it (what bounds this kernel is its chain of barriers: 60 rows 3.5 us, 512 rows 5.6, where two
 // levels of the scores' bits took 6.1 and 7.5).
+// Scores beyond kFar, infinite ones among them, only count as above or below all others, and those that are no number as below:
+// so the map is finite, its scale is above zero, and infinite scores get the codes at its ends.  (One infinite score in the sample used
+// to send all of the row's scores through memory: 40 rows x 128256, d' = 256: 2270 us against 43.  A score that is no number gets
+// code 0; the matrix instructions make all of those negative, and their bits rank below minus infinity.)
 // past_hi / past_lo: the wanted rank lies beyond the sample's largest / smallest score, by which the interval is stretched.
+constexpr float kFar = 1e37f;
+constexpr int kMaxPasses = 16;                            // a thousandth of the width each, usually
 __global__ __launch_bounds__(kMapThreads) void code_map_kernel(const float* samp, int rank_hi, int rank_lo, int past_hi,
                                                                int past_lo, float2* map) {
     constexpr int kSteps = 2 * kMapThreads;
     __shared__ uint32_t s_hist[kSteps];
     __shared__ uint32_t s_w[kMapWaves];
     __shared__ float s_min[kMapWaves], s_max[kMapWaves];
+    __shared__ uint32_t s_over[kMapWaves];
     __shared__ uint32_t s_out[4];
     const int tid = threadIdx.x;
     const float* s = samp + (int64_t)blockIdx.x * kSample;
     float v[kHeld];
 #pragma unroll
     for (int u = 0; u < kHeld; ++u) v[u] = s[u * kMapThreads + tid];
-    float hi = v[0], lo = v[0];
+    float hi = -kFar, lo = kFar;
+    uint32_t far = 0u;
 #pragma unroll
-    for (int u = 1; u < kHeld; ++u) {
-        hi = fmaxf(hi, v[u]);
-        lo = fminf(lo, v[u]);
+    for (int u = 0; u < kHeld; ++u) {
+        const bool near = fabsf(v[u]) <= kFar;
+        hi = fmaxf(hi, near ? v[u] : hi);
+        lo = fminf(lo, near ? v[u] : lo);
+        far += v[u] > kFar ? 1u : 0u;
     }
     hi = wave_max_f32(hi);
     lo = -wave_max_f32(-lo);
+    far = wave_sum_u32(far);
     if ((tid & 63) == 0) {
         s_max[tid >> 6] = hi;
         s_min[tid >> 6] = lo;
+        s_over[tid >> 6] = far;
     }
     s_hist[2 * tid] = s_hist[2 * tid + 1] = 0u;
     __syncthreads();
+    uint32_t over = 0u;                                       // sample scores above hi
 #pragma unroll
     for (int w = 0; w < kMapWaves; ++w) {
         hi = fmaxf(hi, s_max[w]);
         lo = fminf(lo, s_min[w]);
+        over += s_over[w];
     }
-    uint32_t over = 0u;                                       // sample scores above hi
-    for (int pass = 0;; ++pass) {
+    for (int pass = 1;; ++pass) {
         const float step = (hi - lo) * (1.0f / kSteps), inv = (float)kSteps / (hi - lo);
 #pragma unroll
         for (int u = 0; u < kHeld; ++u)
-            if (v[u] >= lo && v[u] <= hi)                     // (a step out of range, or of no number at all: the first or last)
+            if (v[u] >= lo && v[u] <= hi)                     // (a step out of range, or of no number (equal scores): the first or last)
                 atomicAdd(&s_hist[(uint32_t)fminf(fmaxf((v[u] - lo) * inv, 0.0f), (float)(kSteps - 1))], 1u);
         __syncthreads();
         const uint32_t c0 = s_hist[2 * tid], c1 = s_hist[2 * tid + 1];
         if (tid == 0) {
-            s_out[0] = s_out[1] = kSteps - 1;                 // (where no step holds a rank -- scores that are no numbers)
+            s_out[0] = (uint32_t)rank_hi <= over ? kSteps - 1 : 0;            // (where no step holds the rank)
+            s_out[1] = (uint32_t)rank_lo <= over ? kSteps - 1 : 0;
             s_out[2] = 0u;
             s_out[3] = (uint32_t)kSample;
         }
@@ -122,11 +136,11 @@ __global__ __launch_bounds__(kMapThreads) void code_map_kernel(const float* samp
         look((uint32_t)rank_hi, s_out, false);
         look((uint32_t)rank_lo, s_out + 1, true);
         __syncthreads();
-        const float first = lo;
-        hi = first + (float)(s_out[0] + 1u) * step;
+        const float first = lo, width = hi - lo;
+        if (s_out[0] < kSteps - 1) hi = first + (float)(s_out[0] + 1u) * step;            // (as exactly as it can be)
         lo = first + (float)s_out[1] * step;
         const uint32_t held = s_out[3] - s_out[2];
-        if (pass == 2 || held <= 2u * (uint32_t)(rank_lo - rank_hi) + 64u) break;          // uniform
+        if (held <= 2u * (uint32_t)(rank_lo - rank_hi) + 64u || !(hi - lo < width) || pass == kMaxPasses) break;    // uniform
         uint32_t mine = 0u;
 #pragma unroll
         for (int u = 0; u < kHeld; ++u) mine += v[u] > hi ? 1u : 0u;

@@ -85,7 +85,7 @@ def test_samples_that_mislead(k, best):
     _check(h, Wd, Wv, k)
 
 
-@pytest.mark.parametrize("far", [2.0 ** 6, 2.0 ** 20])
+@pytest.mark.parametrize("far", [2.0 ** 6, 2.0 ** 20, 2.0 ** 50])
 @pytest.mark.parametrize("k", [300, 4000])
 def test_scores_far_from_all_others(k, far):
     """A few tokens of every row score far above and far below the rest, sampled ones among them: one step of the map's first
@@ -100,6 +100,29 @@ def test_scores_far_from_all_others(k, far):
     Wv[::1009, 0] = far
     Wv[5::2003, 0] = -far
     _check(h, Wd, Wv, k)
+
+
+@pytest.mark.parametrize("rows", [12, 40, 70])
+@pytest.mark.parametrize("up,down,none", [(1009, 2003, 3001), (2, 2003, 3001), (1009, 2, 3001), (1009, 2003, 4), (1, 2003, 3001)])
+@pytest.mark.parametrize("k", [20, 300, 20000])
+def test_scores_that_are_infinite(rows, up, down, none, k):
+    """Every `up`-th token scores infinity, every `down`-th minus infinity, every `none`-th no number, which is never selected (as where
+    the scores go through memory) as long as there are k others."""
+    V, d_prime = 33000, 64
+    h, Wd, Wv = _inputs(rows, V, d_prime, k)
+    h[:, 1] = 1
+    Wd[:, 1] = 0
+    Wd[0, :] = 0
+    Wd[0, 1] = 1                                   # h'[0] = 1 in every row
+    Wv[:, 0] = 0
+    Wv[::up, 0] = np.inf
+    Wv[5::down, 0] = -np.inf
+    Wv[7::none, 0] = np.nan
+    h, Wd, Wv = _bf16(h), _bf16(Wd), _bf16(Wv)
+    s = ((h.double() @ Wd.double().t()) @ Wv.double().t()).nan_to_num(nan=-1e39, posinf=1e38, neginf=-1e38)
+    want = torch.sort(s, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values
+    idx, _ = sv.select(h, Wd, Wv, k)
+    assert torch.equal(idx.long(), want)
 
 
 @pytest.mark.parametrize("rows", [40, 300])
