@@ -144,8 +144,8 @@ int specvocab_workspace_bytes(int op, int64_t rows, int64_t d, int64_t V, int64_
  * depend on the token id modulo the sampling stride; certain for inputs built so that the sampled tokens score unlike
  * all others) a row takes tens of microseconds more, up to a few milliseconds.  From 65 hidden rows on wider selectors keep
  * only the few per cent of scores inside a bracket from 8192 sampled tokens; a row whose bracket misses is recomputed by a slow exact
- * path, about a millisecond per such row.  Every other shape, every call with scores_out, and a workspace that is large enough
- * for s but not for the bytes and their lists (specvocab_workspace_bytes gives the larger), materialises s in the workspace. */
+ * path, about a millisecond per such row.  Every other shape and every call with scores_out materialises s in the workspace.
+ * The workspace is the same either way: 12 bytes per score and some kilobytes per row. */
 int specvocab_select(const void* h, int64_t rows, int64_t d, int64_t ldh,
                      const void* W_down, int64_t d_prime,
                      const void* W_vocab, int64_t V,

@@ -114,7 +114,7 @@ inline int ensure_device() {
 struct SelectWs {
     size_t hp_off, s_off, radix_off, total;
     size_t bracket_off;      // scratch of the bracketed selection and of the one by codes (instead of the score matrix)
-    size_t codes_total;      // what the selection by codes needs (0: not for this shape); with less, the scores go to memory
+    bool codes;              // the selection by codes serves this shape where nobody asks for scores
 };
 SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) {
     SelectWs w;
@@ -123,14 +123,11 @@ SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) 
     w.radix_off = w.s_off + round256((size_t)rows * (size_t)V * sizeof(float));
     w.total = w.radix_off + round256(sv::select_scratch_words(rows, V) * sizeof(uint32_t));
     w.bracket_off = w.s_off;
-    w.codes_total = 0;
-    const int chunks = (int)(d_prime * esize_of(dt) / 16);
-    if (sv::code_select_supported(dt, chunks, rows, V, k)) {
-        w.codes_total = w.bracket_off + sv::code_select_scratch_bytes(rows, V);
-    } else if (sv::bracket_select_supported(dt, rows, V, k)) {
-        const size_t t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
-        if (t > w.total) w.total = t;
-    }
+    w.codes = sv::code_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
+    size_t t = 0;
+    if (w.codes) t = w.bracket_off + sv::code_select_scratch_bytes(rows, V);         // (less than the scores and their lists take)
+    else if (sv::bracket_select_supported(dt, rows, V, k)) t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
+    if (t > w.total) w.total = t;
     return w;
 }
 
@@ -367,8 +364,7 @@ int specvocab_workspace_bytes(int op, int64_t rows, int64_t d, int64_t V, int64_
         case SV_OP_SELECT: {
             const int st = check_select_shape(rows, d, V, k, d_prime, dt);
             if (st != SV_OK) return st;
-            const SelectWs w = select_ws(rows, V, d_prime, k, dt);
-            *bytes_out = w.total > w.codes_total ? w.total : w.codes_total;
+            *bytes_out = select_ws(rows, V, d_prime, k, dt).total;
             return SV_OK;
         }
         case SV_OP_SUBSET_LOGITS:
@@ -421,7 +417,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
 
     // A batch of hidden rows whose scores nobody asked for: a byte per score in memory
     const int vchunks = (int)(d_prime * es / 16);
-    if (!scores_out && tau == -INFINITY && w.codes_total && ws_bytes >= w.codes_total) {
+    if (!scores_out && tau == -INFINITY && w.codes) {
         if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s) != SV_OK) return SV_ERR_HIP;
         sv::CodeSelectArgs ca{};
         ca.hp = hp;
@@ -437,7 +433,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
     // Wide selectors: the selection that never writes the score matrix
     // (a sample of the vocabulary brackets every row's k-th score; the full product is classified in the
     // epilogue of the matrix-core kernel).  The down-projection launch also writes the sample's ids.
-    if (!scores_out && tau == -INFINITY && w.codes_total == 0 && sv::bracket_select_supported(dt, rows, V, k)) {
+    if (!scores_out && tau == -INFINITY && sv::bracket_select_supported(dt, rows, V, k)) {
         uint32_t* bscratch = reinterpret_cast<uint32_t*>(base + w.bracket_off);
         int32_t* ids = nullptr;
         int64_t m = 0;

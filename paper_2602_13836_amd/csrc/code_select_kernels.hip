@@ -12,7 +12,8 @@
 //             once more, by the same matrix instructions in the same order, and ranked by (score, smaller id first).
 // The result is exact with respect to those scores whatever the map is, because the map is monotone: a poor one only
 // leaves more tokens in code C (a map that misses the k-th score altogether, as many as there are below lo or above hi).
-// As many keys as fit stay in LDS; more go to memory.
+// As many keys as fit stay in LDS; more go to memory.  All of it lies where the scores would (12 bytes per score with the lists that
+// their selection keeps), in 11 of them.
 //
 // Measured (512 rows x 151936, d' = 256, k = 8192; kernels under a profiler): sample 8 us, map 7, codes 48, resolve 36; the
 // whole selection 133 -> 106 us.  The form it replaces kept a bit per score (above hi) and a list of (key, id) of the scores
@@ -41,21 +42,24 @@ constexpr int64_t kMinVocab = 16384;
 
 struct CodeLayout {
     int64_t stride;          // bytes between rows of codes: an odd multiple of 256, off the memory channels' period
-    // offsets in bytes from the scratch base (multiples of 256)
-    size_t samp, map, codes, spill, total;
+    int64_t entries;         // of a row's list that memory has room for (a list has 3 to 16 % of V as a rule)
+    // offsets in bytes from the scratch base (multiples of 8); the sample and the map lie where keys do, which come after them
+    size_t codes, keys, list, samp, map, total;
 };
-__host__ __device__ inline size_t up256(size_t n) { return (n + 255) & ~(size_t)255; }
-__host__ __device__ inline CodeLayout code_layout(int64_t V, int64_t rows) {
+inline CodeLayout code_layout(int64_t V, int64_t rows) {
     CodeLayout L;
-    L.stride = (int64_t)(up256((size_t)V) | 256);
+    L.stride = (V + 255) / 256 * 256 | 256;
+    L.entries = V / 2;
     size_t o = 0;
-    L.samp = o;   o += up256((size_t)rows * kSample * 4);
-    L.map = o;    o += up256((size_t)rows * 8);
-    L.codes = o;  o += up256((size_t)rows * (size_t)L.stride);
-    L.spill = o;  o += up256((size_t)rows * (size_t)V * 12);
+    L.codes = o;  o += (size_t)rows * (size_t)L.stride;
+    L.keys = o;   o += (size_t)rows * (size_t)V * 8;
+    L.list = o;   o += (size_t)rows * (size_t)L.entries * 4;
     L.total = o;
+    L.samp = L.keys;
+    L.map = L.samp + (size_t)rows * kSample * 4;             // (a key per token is twice as much and more: kMinVocab)
     return L;
 }
+static_assert(kMinVocab * 8 >= kSample * 4 + 8, "the sample and the map fit where the keys go");
 
 // ---- map: one workgroup per row, its part of the sample in registers
 // map[r] = {scale, bias} from where the rank_hi-th and the rank_lo-th largest of the row's sample scores lie (1 <= rank_hi <=
@@ -76,38 +80,58 @@ __global__ __launch_bounds__(kMapThreads) void code_map_kernel(const float* samp
     __shared__ uint32_t s_hist[kSteps];
     __shared__ uint32_t s_w[kMapWaves];
     __shared__ float s_min[kMapWaves], s_max[kMapWaves];
-    __shared__ uint32_t s_over[kMapWaves];
     __shared__ uint32_t s_out[4];
     const int tid = threadIdx.x;
     const float* s = samp + (int64_t)blockIdx.x * kSample;
     float v[kHeld];
 #pragma unroll
     for (int u = 0; u < kHeld; ++u) v[u] = s[u * kMapThreads + tid];
-    float hi = -kFar, lo = kFar;
-    uint32_t far = 0u;
+    float hi = v[0], lo = v[0];
 #pragma unroll
-    for (int u = 0; u < kHeld; ++u) {
-        const bool near = fabsf(v[u]) <= kFar;
-        hi = fmaxf(hi, near ? v[u] : hi);
-        lo = fminf(lo, near ? v[u] : lo);
-        far += v[u] > kFar ? 1u : 0u;
+    for (int u = 1; u < kHeld; ++u) {
+        hi = fmaxf(hi, v[u]);
+        lo = fminf(lo, v[u]);
     }
-    hi = wave_max_f32(hi);
-    lo = -wave_max_f32(-lo);
-    far = wave_sum_u32(far);
-    if ((tid & 63) == 0) {
-        s_max[tid >> 6] = hi;
-        s_min[tid >> 6] = lo;
-        s_over[tid >> 6] = far;
-    }
-    s_hist[2 * tid] = s_hist[2 * tid + 1] = 0u;
-    __syncthreads();
+    auto widest = [&]() {                                     // of all threads'
+        hi = wave_max_f32(hi);
+        lo = -wave_max_f32(-lo);
+        if ((tid & 63) == 0) {
+            s_max[tid >> 6] = hi;
+            s_min[tid >> 6] = lo;
+        }
+        s_hist[2 * tid] = s_hist[2 * tid + 1] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kMapWaves; ++w) {
+            hi = fmaxf(hi, s_max[w]);
+            lo = fminf(lo, s_min[w]);
+        }
+    };
+    auto above_hi = [&]() {                                   // sample scores; s_w is free before and after
+        uint32_t mine = 0u, all = 0u;
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) mine += v[u] > hi ? 1u : 0u;
+        mine = wave_sum_u32(mine);
+        if ((tid & 63) == 0) s_w[tid >> 6] = mine;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kMapWaves; ++w) all += s_w[w];
+        __syncthreads();
+        return all;
+    };
+    widest();
     uint32_t over = 0u;                                       // sample scores above hi
+    if (__builtin_expect(!(hi <= kFar && lo >= -kFar), 0)) {  // uniform
+        hi = -kFar;
+        lo = kFar;
 #pragma unroll
-    for (int w = 0; w < kMapWaves; ++w) {
-        hi = fmaxf(hi, s_max[w]);
-        lo = fminf(lo, s_min[w]);
-        over += s_over[w];
+        for (int u = 0; u < kHeld; ++u) {
+            hi = fmaxf(hi, fabsf(v[u]) <= kFar ? v[u] : hi);
+            lo = fminf(lo, fabsf(v[u]) <= kFar ? v[u] : lo);
+        }
+        __syncthreads();                                      // everybody has read the first ones
+        widest();
+        over = above_hi();
     }
     for (int pass = 1;; ++pass) {
         const float step = (hi - lo) * (1.0f / kSteps), inv = (float)kSteps / (hi - lo);
@@ -141,18 +165,9 @@ __global__ __launch_bounds__(kMapThreads) void code_map_kernel(const float* samp
         lo = first + (float)s_out[1] * step;
         const uint32_t held = s_out[3] - s_out[2];
         if (held <= 2u * (uint32_t)(rank_lo - rank_hi) + 64u || !(hi - lo < width) || pass == kMaxPasses) break;    // uniform
-        uint32_t mine = 0u;
-#pragma unroll
-        for (int u = 0; u < kHeld; ++u) mine += v[u] > hi ? 1u : 0u;
-        mine = wave_sum_u32(mine);
         __syncthreads();                                      // s_w and the histogram have been read
-        if ((tid & 63) == 0) s_w[tid >> 6] = mine;
         s_hist[2 * tid] = s_hist[2 * tid + 1] = 0u;
-        __syncthreads();
-        over = 0u;
-#pragma unroll
-        for (int w = 0; w < kMapWaves; ++w) over += s_w[w];
-        __syncthreads();                                      // ... before the next scan writes s_w
+        over = above_hi();
     }
     if (tid == 0) {
         // (by three times the interval: the sample's largest score alone may lie well below the k-th of them all)
@@ -194,12 +209,15 @@ constexpr uint32_t kTop = 0x80808080u, kLow = 0x7F7F7F7Fu, kOne = 0x01010101u;
 // lane with the most).  512 rows x 151936, k = 8192, two workgroups per CU: 36 us, of which a workgroup's first pass over the
 // codes is 11, the choice within code C 5, the ids 4 (a second pass over the codes instead of the list: 48; the codes held in
 // registers: 64, they spill; a lane's place in the list by an atomic of its own: 54).
-// The list holds list_cap entries in LDS, what follows is in memory.  GROUP: 3 leaves room for two workgroups per CU.
+// The list holds list_cap entries in LDS and mem_cap in memory.  Where it holds too few -- or a code below 128 decides -- the codes are walked
+// once more for their histogram and once for the choice (40 rows x 128256
+// whose sampled tokens are their best: 2140 us, of which the scores of the 124000 tokens that share code 0 are all but 100; with a
+// list that grew to all tokens, in 13 bytes of workspace per score, 2260).
+// GROUP: 3 leaves room for two workgroups per CU.
 template <int GROUP>
 __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kernel(int64_t V, int64_t k, const uint8_t* codes, int64_t stride,
-                                                                   const char* hp, const char* Wv, int chunks, uint64_t* spill,
-                                                                   int32_t* idx_out, uint32_t list_cap) {
-    constexpr int kGroup = GROUP;                             // rounds whose codes are requested together
+                                                                   const char* hp, const char* Wv, int chunks, uint64_t* keys,
+                                                                   uint32_t* list, int32_t* idx_out, uint32_t list_cap, uint32_t mem_cap) {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_sel[];
     unsigned char* const s_stage = reinterpret_cast<unsigned char*>(s_sel) + resolve_sel_bytes(V);
     uint32_t* const s_list = reinterpret_cast<uint32_t*>(s_stage + kStageBytes);
@@ -213,10 +231,12 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
     const int rounds = (units + kThreads - 1) / kThreads;
     const u32x4* const row = reinterpret_cast<const u32x4*>(codes + r * stride);
     const int u0 = wave * rounds * 64 + lane;
-    uint64_t* const keys_mem = spill + r * V;                 // [rows][V] keys, then [rows][V] entries of the list
-    uint32_t* const list_mem = reinterpret_cast<uint32_t*>(spill + gridDim.x * V) + r * V;
-    // f(unit, codes) for the lane's units, with all lanes (units past the last: codes of 0)
-    auto for_each_unit = [&](auto&& f) {
+    uint64_t* const keys_mem = keys + r * V;
+    uint32_t* const list_mem = list + r * (int64_t)mem_cap;
+    // f(unit, codes) for the lane's units, with all lanes (units past the last: codes of 0); the codes of `group` rounds are
+    // requested together
+    auto for_each_unit = [&](auto group, auto&& f) {
+        constexpr int kGroup = decltype(group)::value;
         for (int j0 = 0; j0 < rounds; j0 += kGroup) {
             u32x4 q[kGroup][2];
 #pragma unroll
@@ -249,21 +269,18 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
         return;
     }
     if (tid < kBins) sm.hist[tid] = 0u;
-    if (tid == 0) {
-        sm.n_list = sm.n_keys = 0u;
-        sm.out[2] = 0u;
-    }
+    if (tid == 0) sm.n_list = sm.n_keys = 0u;
     __syncthreads();
 
     // entry: id and code
     auto put_entry = [&](uint32_t at, uint32_t entry) {
         if (at < list_cap) s_list[at] = entry;
-        if (at >= list_cap) list_mem[at] = entry;
+        else if (at - list_cap < mem_cap) list_mem[at - list_cap] = entry;
     };
     // (the lane's codes go to LDS as well, where a byte can be fetched by its number)
     unsigned char* const s_mine = s_stage + tid * 32;
     uint32_t full = 0u;
-    for_each_unit([&](int u, const u32x4 (&q)[2]) {
+    for_each_unit(std::integral_constant<int, GROUP>{}, [&](int u, const u32x4 (&q)[2]) {
         reinterpret_cast<u32x4*>(s_mine)[0] = q[0];
         reinterpret_cast<u32x4*>(s_mine)[1] = q[1];
         uint32_t in = 0u, above = 0u;                         // bit 8 b + w: byte b of word w is 128 .. 254, is 255
@@ -305,70 +322,95 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
     full = 0u;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) full += sm.w2[w];
-    uint32_t n_list = sm.n_list;
-    auto for_each_entry = [&](uint32_t from, auto&& f) {
-        for (uint32_t i = from + tid; i < min(n_list, list_cap); i += kThreads) f(s_list[i]);
-        for (uint32_t i = max(from, list_cap) + tid; i < n_list; i += kThreads) f(list_mem[i]);
+    auto same = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };     // (in a scalar register)
+    full = same(full);
+    const uint32_t n_list = same(sm.n_list), wanted = (uint32_t)k;
+    auto for_each_entry = [&](auto&& f) {
+        for (uint32_t i = tid; i < min(n_list, list_cap); i += kThreads) f(s_list[i]);
+        for (uint32_t i = list_cap + tid; i < n_list; i += kThreads) f(list_mem[i - list_cap]);
     };
     // the code of the k-th score: its number, the scores above it, its scores
-    auto locate = [&]() {
+    const bool top = wanted <= full;                          // above hi
+    const bool walk = !top && (wanted > full + n_list || n_list > list_cap + mem_cap);
+    uint32_t C = 255u, above = 0u, n = full;
+    if (__builtin_expect(!top, 1)) {                          // uniform
+        if (__builtin_expect(!walk, 1)) {
+            for_each_entry([&](uint32_t e) { atomicAdd(&sm.hist[e & 255u], 1u); });
+        } else {
+            for_each_unit(std::integral_constant<int, 1>{}, [&](int u, const u32x4 (&q)[2]) {   // (equal codes in a row together)
+                reinterpret_cast<u32x4*>(s_mine)[0] = q[0];
+                reinterpret_cast<u32x4*>(s_mine)[1] = q[1];
+                const uint32_t valid = u < units ? (uint32_t)min((int64_t)32, V - 32 * (int64_t)u) : 0u;
+                uint32_t code = 255u, run = 0u;
+                for (uint32_t p = 0; p < valid; ++p) {
+                    const uint32_t x = s_mine[(p & 7u) * 4u + (p >> 3)];
+                    if (x != code) {
+                        if (code != 255u) atomicAdd(&sm.hist[code], run);
+                        code = x;
+                        run = 0u;
+                    }
+                    ++run;
+                }
+                if (code != 255u) atomicAdd(&sm.hist[code], run);
+            });
+        }
+        __syncthreads();
         const uint32_t c = tid < kBins ? (tid == 255 ? full : sm.hist[tid]) : 0u;
-        const uint32_t above = block_suffix_exclusive<kWaves>(c, sm.w);
-        if (above < (uint32_t)k && (uint32_t)k <= above + c) {
+        const uint32_t higher = block_suffix_exclusive<kWaves>(c, sm.w);
+        if (higher < wanted && wanted <= higher + c) {
             sm.out[0] = (uint32_t)tid;
-            sm.out[1] = above;
+            sm.out[1] = higher;
             sm.out[2] = c;
         }
         __syncthreads();
-    };
-    for_each_entry(0u, [&](uint32_t e) { atomicAdd(&sm.hist[e & 255u], 1u); });
-    __syncthreads();
-    locate();
-    if (sm.out[2] == 0u) {                                    // uniform: below lo.  The codes 0 .. 127 join the list
-        __syncthreads();
-        const uint32_t had = n_list;
-        for_each_unit([&](int u, const u32x4 (&q)[2]) {
-            reinterpret_cast<u32x4*>(s_mine)[0] = q[0];
-            reinterpret_cast<u32x4*>(s_mine)[1] = q[1];
-            for (uint32_t p = 0; p < 32u && 32 * (int64_t)u + p < V; ++p) {
-                const uint32_t x = s_mine[(p & 7u) * 4u + (p >> 3)];
-                if (x < 128u) put_entry(atomicAdd(&sm.n_list, 1u), ((32u * (uint32_t)u + p) << 8) | x);
-            }
-        });
-        __threadfence_block();
-        __syncthreads();
-        n_list = sm.n_list;
-        for_each_entry(had, [&](uint32_t e) { atomicAdd(&sm.hist[e & 255u], 1u); });
-        __syncthreads();
-        locate();
-    } else if (sm.out[0] == 255u) {                           // uniform: above hi.  The ids that became bits are not selected yet
-        for (int j = 0; j < rounds; ++j) {
-            const int u = u0 + 64 * j;
-            if (u >= units) break;
-            for (uint32_t bits = s_sel[u]; bits; bits &= bits - 1u)
-                put_entry(atomicAdd(&sm.n_list, 1u), ((32u * (uint32_t)u + (uint32_t)__builtin_ctz(bits)) << 8) | 255u);
-            s_sel[u] = 0u;
-        }
-        __threadfence_block();
-        __syncthreads();
-        n_list = sm.n_list;
+        C = same(sm.out[0]);
+        above = same(sm.out[1]);
+        n = same(sm.out[2]);
     }
-    const uint32_t C = sm.out[0], n = sm.out[2];
-    const uint32_t need = (uint32_t)k - sm.out[1];            // of the n scores of code C: 1 <= need <= n
+    const uint32_t need = wanted - above;                     // of the n scores of code C: 1 <= need <= n
     const bool whole = need == n, in_lds = n <= kKeysInLds;
 
-    // the list's ids above code C become bits; those of code C too, if all are selected, or they go to the list of keys
+    // ids above code C become bits; those of code C too, if all are selected, or they go to the list of keys
     // (an inverted id each, with the score on top as soon as it is known)
     auto select_id = [&](uint32_t id) { atomicOr(&s_sel[id >> 5], 1u << (id & 31u)); };
-    for_each_entry(0u, [&](uint32_t e) {
-        const uint32_t c = e & 255u, id = e >> 8;
-        if (c > C || (whole && c == C)) select_id(id);
-        else if (c == C) {
-            const uint32_t at = atomicAdd(&sm.n_keys, 1u);
-            if (in_lds) s_keys[kKeysInLds - 1u - at] = (uint64_t)(~id);
-            if (!in_lds) keys_mem[at] = (uint64_t)(~id);
+    auto put_key = [&](uint32_t at, uint32_t id) {
+        if (in_lds) s_keys[kKeysInLds - 1u - at] = (uint64_t)(~id);
+        if (!in_lds) keys_mem[at] = (uint64_t)(~id);
+    };
+    auto put_keys = [&](int u, uint32_t bits) {               // of a lane's unit
+        if (bits == 0u) return;
+        for (uint32_t at = atomicAdd(&sm.n_keys, (uint32_t)__popc(bits)); bits; bits &= bits - 1u)
+            put_key(at++, 32u * (uint32_t)u + (uint32_t)__builtin_ctz(bits));
+    };
+    if (__builtin_expect(top, 0)) {                           // uniform: the codes of 255 are bits already
+        for (int j = 0; j < rounds && !whole; ++j) {
+            const int u = u0 + 64 * j;
+            if (u >= units) break;
+            put_keys(u, s_sel[u]);
+            s_sel[u] = 0u;
         }
-    });
+    } else if (__builtin_expect(walk, 0)) {
+        for_each_unit(std::integral_constant<int, 1>{}, [&](int u, const u32x4 (&q)[2]) {
+            uint32_t more = 0u, equal = 0u;
+#pragma unroll
+            for (int p = 0; p < 32; ++p) {                    // byte p / 8 of word p % 8
+                const uint32_t x = (q[(p & 7) >> 2][p & 3] >> (8 * (p >> 3))) & 255u;
+                more |= x > C ? 1u << p : 0u;
+                equal |= x == C ? 1u << p : 0u;
+            }
+            if (u >= units) return;
+            const int64_t left = V - 32 * (int64_t)u;
+            if (left < 32) equal &= (1u << left) - 1u;        // (codes of 0 follow)
+            s_sel[u] = more | (whole ? equal : 0u);
+            if (!whole) put_keys(u, equal);
+        });
+    } else {
+        for_each_entry([&](uint32_t e) {
+            const uint32_t c = e & 255u, id = e >> 8;
+            if (c > C || (whole && c == C)) select_id(id);
+            else if (c == C) put_key(atomicAdd(&sm.n_keys, 1u), id);
+        });
+    }
     if (!whole) {                                             // uniform: the `need` largest scores of code C are wanted
         auto choose = [&](auto lds) {
             constexpr bool LDS = decltype(lds)::value;        // the keys are there, and not in memory
@@ -583,8 +625,8 @@ hipError_t launch_code_select(const CodeSelectArgs& a, hipStream_t stream) {
     list_bytes &= ~(size_t)15;
     auto resolve = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kThreads), resolve_sel_bytes(a.V) + kStageBytes + list_bytes, stream,
-                           a.V, a.k, p.codes, L.stride, a.hp, a.Wv, a.chunks, reinterpret_cast<uint64_t*>(a.scratch + L.spill),
-                           a.idx_out, (uint32_t)(list_bytes / 4));
+                           a.V, a.k, p.codes, L.stride, a.hp, a.Wv, a.chunks, reinterpret_cast<uint64_t*>(a.scratch + L.keys),
+                           reinterpret_cast<uint32_t*>(a.scratch + L.list), a.idx_out, (uint32_t)(list_bytes / 4), (uint32_t)L.entries);
     };
     if (a.rows <= di.cus) resolve(&code_resolve_kernel<6>);
     else resolve(&code_resolve_kernel<3>);

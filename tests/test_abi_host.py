@@ -55,6 +55,11 @@ def test_workspace_bytes(lib):
         sv.workspace_bytes(99)
     assert e.value.status == 3
     assert lib.specvocab_workspace_bytes(0, 1, 8, 8, 1, 8, 0, 1, 0, None) == 1
+    # the selection of a batch by one-byte codes (bf16) takes no more than the one over scores in memory (which float32 always is)
+    for rows, V, k, d_prime in ((9, 16384, 100, 8), (24, 128256, 4008, 256), (60, 128256, 4096, 256), (64, 393216, 1, 128),
+                                (65, 16385, 16385, 512), (512, 151936, 8192, 256), (4099, 32771, 9, 64)):
+        by = {dt: sv.workspace_bytes(sv.SV_OP_SELECT, rows, 4096, V, k, d_prime, 0, dt) for dt in (sv.SV_BF16, sv.SV_F32)}
+        assert by[sv.SV_BF16] <= by[sv.SV_F32], (rows, V)
 
 
 # fake, never dereferenced device addresses: every call below must fail validation on the host

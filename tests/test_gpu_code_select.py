@@ -39,9 +39,13 @@ def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
 
 
-def test_less_scratch_than_codes_need():
-    """20 rows of 33500 tokens fit the library's static scratch with their scores in memory, but not as codes."""
-    h, Wd, Wv = (_bf16(a) for a in _inputs(20, 33500, 64, 5))
+def test_static_scratch_nearly_full():
+    """20 rows of 33500 tokens: what the library's static scratch just holds.  The sums of real numbers round, so equal ids also say
+    that both calls ran the same kernels."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    h, Wd, Wv = (torch.randn(n, generator=gen, device="cuda").to(torch.bfloat16) for n in ((20, 512), (64, 512), (33500, 64)))
+    assert 8 << 20 > sv.workspace_bytes(sv.SV_OP_SELECT, 20, 512, 33500, 1000, 64, 0, sv.SV_BF16, 0) > 7.5 * 2 ** 20
     idx, _ = sv.select(h, Wd, Wv, 1000)
     idx_static = torch.full_like(idx, -1)
     sv.select_static(h, Wd, Wv, 1000, idx_static)
@@ -68,6 +72,26 @@ def test_rows_of_zeros_and_plateaus():
     Wv[:, 0] = np.sign(Wv[:, 0]) / 64.0
     for k in (1, 100, 16000, 33000, 50000):
         _check(h, Wd, Wv, k)
+
+
+@pytest.mark.parametrize("share", [1.0, 0.9, 0.55])
+@pytest.mark.parametrize("k", [1, 9000, 20000, 39999])
+def test_lists_longer_than_their_memory(share, k):
+    """More than half of the tokens share a score that the map has an interval for, and most of their codes do not fit the list; some
+    rows select among them, some have them above or below the k-th score.  Nothing past the workspace is written."""
+    rows, V, d_prime = 68, 40000, 32
+    h, Wd, Wv = _inputs(rows, V, d_prime, k)
+    h[:, 1:] = 0
+    h[:, 0] = np.arange(rows) % 5 - 2              # h' = (h[0], 0, ...)
+    Wd[:, 0] = 0
+    Wd[0, 0] = 1
+    Wv[np.random.default_rng(k).random(V) < share, 0] = 1 / 64.0
+    _check(h, Wd, Wv, k)
+    h, Wd, Wv = _bf16(h), _bf16(Wd), _bf16(Wv)
+    need = sv.workspace_bytes(sv.SV_OP_SELECT, rows, 64, V, k, d_prime, 0, sv.SV_BF16, 0)
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    idx, _ = sv.select(h, Wd, Wv, k, ws=ws[:need])
+    assert torch.equal(idx, sv.select(h, Wd, Wv, k)[0]) and bool((ws[need:] == 0x5A).all())
 
 
 @pytest.mark.parametrize("k", [200, 5000, 20000])
