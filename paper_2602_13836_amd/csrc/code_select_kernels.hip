@@ -200,7 +200,8 @@ struct ResolveSmem {
 // dynamic LDS: a bit per token (ids that are selected) | the stage, whose end takes the keys | the list
 __host__ __device__ inline size_t resolve_sel_bytes(int64_t V) { return (size_t)((V + 127) / 128) * 16; }
 
-constexpr uint32_t kTop = 0x80808080u, kLow = 0x7F7F7F7Fu, kOne = 0x01010101u;
+constexpr uint32_t kDense = 576;                         // selected ids of 2048
+constexpr uint32_t kLow = 0x7F7F7F7Fu, kOne = 0x01010101u;
 
 // One workgroup per row.  Wavefront w has `rounds` rounds of 64 units of 32 codes, lane l the units (w rounds + j) 64 + l: a
 // round is 2 KB of consecutive codes, and ids ascend with (wavefront, round, lane, bit).  Codes of 255 become bits at once;
@@ -520,7 +521,10 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
     }
     __syncthreads();
 
-    // the ids of the set bits, ascending
+    // The ids of the set bits, ascending.  A lane stores those of its own unit one after the other, each store to as many lines as
+    // there are lanes; where they are many (from about a quarter of the tokens on) all lanes share two units at a time instead, and the stores
+    // are whole lines: half of 128256 tokens wanted, mean of 9 to 512 rows, 108 -> 72 us; half of 262144 194 -> 121; an eighth of
+    // them that way 87 -> 110.
     uint32_t total = 0u;
     for (int j = 0; j < rounds; ++j) {
         const int u = u0 + 64 * j;
@@ -540,9 +544,20 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
         const int u = u0 + 64 * j;
         uint32_t bits = u < units ? s_sel[u] : 0u;
         const uint32_t c = (uint32_t)__popc(bits);
-        const uint32_t incl = wave_prefix_inclusive_u32(c);
+        const uint32_t incl = wave_prefix_inclusive_u32(c), here = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (here >= kDense) {                                 // uniform: a lane per token, two units at a time
+            const uint32_t first = 32u * (uint32_t)(u - lane) + (uint32_t)lane;
+            for (int i = 0; i < 64; i += 2) {
+                const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bits, i), b1 = (uint32_t)__builtin_amdgcn_readlane((int)bits, i + 1);
+                const uint32_t at = __builtin_amdgcn_mbcnt_hi(b1, __builtin_amdgcn_mbcnt_lo(b0, base));
+                if (((lane < 32 ? b0 : b1) >> (lane & 31)) & 1u)
+                    *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(out) + at * 4u) = first + 32u * (uint32_t)i;
+                base += (uint32_t)(__popc(b0) + __popc(b1));
+            }
+            continue;
+        }
         uint32_t at = (base + incl - c) * 4u;
-        base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        base += here;
         const uint32_t id0 = 32u * (uint32_t)u;
         while (bits) {
             *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(out) + at) = id0 + (uint32_t)__builtin_ctz(bits);
@@ -555,16 +570,37 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
 }  // namespace
 
 // From how many rows on.  The chain of five launches and a workgroup's walk over its row cost about as much whatever the rows
-// are, which the scores in memory (their histogram, two more passes over them) reach with rows and vocabulary.  us, scores in memory
-// / codes, 32768, 128256, 262144 tokens, k = V / 32: d' = 256, 9 rows 31 / 28, 38 / 41, 51 / 61, 16 rows 33 / 30, 42 / 43, 57 / 64,
-// 24 rows 34 / 30, 45 / 44, 66 / 64, 36 rows 36 / 30, 53 / 44, 86 / 65; d' = 128, 9 rows 29 / 23, 36 / 35; 8 rows, whose chain over the
-// scores is a shorter one, 24 / 26 and more.  A row of many ids takes its workgroup longer (k = 30000 of 128256: d' = 256, 40 rows
-// 55 / 57, 60 rows 63 / 58; d' = 128, 16 rows 42 / 48; k = 16000 of 64000, 40 rows 40 / 37).  d' > 256: there are no panels of 64
-// rows, and 64 on one of 256 take 46 and 69 against 38 and 71.
+// are, which the scores in memory (their histogram, two more passes over them) reach with rows and vocabulary; and a row with many ids
+// takes its workgroup longer.  So the line goes by the share of the tokens that is wanted, in sixteenths, the vocabulary and the width
+// (up to 128, up to 256 elements).  us, scores in memory / codes, on either side of the line:
+//   V / 32     d' = 256, 128256 tokens: 16 rows 42.6 / 45.1, 24 rows 46.5 / 44.3; 32768: 9 rows 31.6 / 29.5; d' = 128, 128256: 9 rows 36.5 / 33.6;
+//              8 rows, whose chain over the scores is a shorter one, 24 / 26 and more
+//   V / 8      d' = 256, 128256: 24 rows 44.0 / 47.9, 32 rows 47.4 / 47.8; 65536: 16 rows 32.6 / 33.5, 20 rows 34.5 / 33.9; d' = 128, 128256:
+//              16 rows 38.5 / 39.4, 20 rows 41.9 / 39.8
+//   V / 4      d' = 256, 128256: 48 rows 54.8 / 56.6, 60 rows 61.1 / 57.9; 262144: 48 rows 94.1 / 87.2; d' = 128, 128256: 48 rows 48.4 / 49.0
+//   V / 2      d' = 256, 128256: 64 rows 63.0 / 62.5; 32768: 48 rows 33.4 / 34.4, 60 rows 36.3 / 34.3; d' = 128, 65536: 40 rows 37.3 / 38.1, 48
+//              rows 39.5 / 38.5
+// d' > 256: there are no panels of 64 rows; from 65 rows on (64 on a panel of 256 take 46 and 69 us against 38 and 71), where the alternative
+// is the scores in memory (vocabularies below the bracketed selection's) from as many as fill the chip: d' = 512, 32767: 65 rows 41.8 / 42.6, 100
+// rows 53.2 / 49.5; 20000: 128 rows 45.1 / 45.0, 160 rows 56.7 / 51.2; half of 25000 wanted: 128 rows 47.0 / 48.8, 160 rows 56.8 / 53.9.
 inline int64_t min_rows(int chunks, int64_t V, int64_t k) {
-    if (chunks > 32) return 65;
-    if (8 * k > V) return chunks > 16 ? 60 : 40;
-    return chunks > 16 ? (V <= 65536 ? 9 : 24) : (V <= 131072 ? 9 : 16);
+    constexpr int64_t never = 65;                             // (from 65 rows on codes are always the shorter way)
+    if (chunks > 32) return V >= 32768 ? 65 : 8 * k > V ? 129 : 2600000 / V + 1 > 65 ? 2600000 / V + 1 : 65;
+    const int64_t share = (16 * k + V - 1) / V;
+    if (share > 4) {
+        if (V <= 32768) return chunks <= 16 ? 9 : 60;
+        if (V <= 65536 && chunks <= 16) return 48;
+        return V > 131072 && share >= 8 && share < 16 ? 60 : never;
+    }
+    if (chunks <= 16) {
+        if (share <= 1) return V <= 131072 ? 9 : 16;
+        if (share <= 2) return V <= (chunks <= 8 ? 131072 : 100000) ? 9 : chunks <= 8 ? 16 : 20;      // (up to 64 elements: 16 rows x 151936 44.7 / 40.7)
+        return V <= 65536 ? (share <= 3 ? 9 : 16) : share <= 3 ? 32 : 48;
+    }
+    if (share <= 1) return V <= 65536 ? 9 : 24;
+    if (share <= 2) return V <= 32768 ? 9 : V <= 65536 ? 20 : 32;
+    if (share <= 3) return V <= 32768 ? 9 : 40;
+    return V <= 32768 ? 24 : V <= 131072 ? 60 : 48;
 }
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
     return panel_codes_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab;

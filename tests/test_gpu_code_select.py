@@ -34,7 +34,10 @@ def _check(h, Wd, Wv, k):
                                               (65, 262145, 24, 131072),
                                               # panels of 64 rows: steps of 128 rows of W_vocab, runs shorter than that and of one and a half
                                               (40, 16384, 256, 300), (64, 16385, 200, 5000), (16, 49000, 128, 1500), (41, 40960, 256, 2000),
-                                              (60, 262144, 248, 8192), (17, 24001, 8, 700), (9, 16384, 256, 100), (24, 70000, 256, 900)])
+                                              (60, 262144, 248, 8192), (17, 24001, 8, 700), (9, 16384, 256, 100), (24, 70000, 256, 900),
+                                              # ids a lane per token: from less to more than that many in 64 units, few units, the last one cut
+                                              (12, 16385, 128, 16000), (9, 32768, 40, 9300), (30, 20001, 64, 5200), (64, 200000, 256, 100000),
+                                              (300, 50017, 256, 14000)])
 def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
 
