@@ -37,6 +37,7 @@ namespace {
 constexpr int kTK = 64;                  // reduction elements per slice (128 bytes of a row)
 constexpr int kRowB = kTK * 2 + 16;      // padded LDS row (144 B = 36 words)
 constexpr int kXcds = 8;
+constexpr unsigned kRound = 256;         // workgroups that the part runs at a time where a CU holds one
 
 // dst with lanes LO and HI replaced by the two halves of the wavefront-uniform mask m (two v_writelane_b32).
 // The mask comes straight from a vector comparison: on this architecture a vector instruction that reads a
@@ -366,7 +367,12 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
         __builtin_amdgcn_s_waitcnt(0xC07F);
         if (second) turn_ends();               // the second group starts one turn later ...
         // (SOME: only the wavefront's first `live` groups of 32 hidden rows are any)
-        const int live = __builtin_amdgcn_readfirstlane((a.rows - (rt * TM + (swave / GN) * 32 * WM) + 31) / 32);
+        int live = __builtin_amdgcn_readfirstlane((a.rows - (rt * TM + (swave / GN) * 32 * WM) + 31) / 32);
+        // (A 128 x 256 tile that has one group of four would be done with its slices so much sooner than the whole tiles of the same rows
+        // of M that these find them gone from L2: 140 rows x 4096 x 28000, 3.25 million L2 misses against 2.49, 66 us against 55 -- and 61 when
+        // nothing was left out.  So it multiplies the first wavefronts' other group too, unless there is more than one round of
+        // workgroups, where whoever is ahead goes on to the next: 285 rows x 60000 191 against 187.)
+        if (TM == 128 && TN == 256 && swave < GN && live == 1 && gridDim.x <= kRound) live = WM;
         auto walk = [&](auto some) {
             int st0 = 0, st1 = 1, st2 = 2;         // stages of M: slice ks, ks + 1, ks + 2
             for (int ks = 0; ks < nk; ++ks) {

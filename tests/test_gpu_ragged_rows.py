@@ -25,3 +25,14 @@ def test_last_tile(rows, V, d, far):
         h = apart[:, :d]
     out = torch.full((rows, V), float("nan"), device="cuda")
     assert torch.equal(sv.dense_logits(h, U, out=out).double(), ref)
+
+
+@pytest.mark.parametrize("rows,V,d", [(129, 28000, 200), (160, 31000, 4096), (130, 32768, 136)])
+def test_one_group_of_a_last_tile(rows, V, d):
+    """128 x 256 tiles in one round of workgroups whose last tile of hidden rows has 32 of them at most.  The group beside them is multiplied too, and stores nothing."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + V)
+    h, U = (torch.randint(-4, 5, (n, d), device="cuda", generator=gen).to(torch.bfloat16) for n in (rows, V))
+    out = torch.full((rows + 1, V), float("nan"), device="cuda")
+    sv.dense_logits(h, U, out=out[:rows])
+    assert torch.equal(out[:rows].double(), h.double() @ U.double().t()) and bool(out[rows].isnan().all())
