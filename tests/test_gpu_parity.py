@@ -804,18 +804,18 @@ def test_exact_selector_reduces_to_dense_topk():
 
 # ---------------------------------------------------------------- selection for a batch without the score matrix
 BATCH_SELECT_SHAPES = [
-    # rows, d,  d',  V,     k        (bf16, 65 rows or more, V >= 32768, no scores output: the bracketed selection)
-    (65, 256, 32, 32768, 100),       # 128-row tiles, one of them half empty; the smallest vocabulary of the path
+    # rows, d,  d',  V,     k        (bf16, 65 rows or more, d' <= 512, V >= 16384, no scores output: the selection by one-byte codes)
+    (65, 256, 32, 32768, 100),       # a panel of 128 rows, half empty
     (70, 256, 32, 33000, 500),
-    (100, 1024, 256, 50001, 4096),   # ragged last item tile
+    (100, 1024, 256, 50001, 4096),   # ragged last run
     (128, 256, 40, 40007, 1),        # k = 1
-    (130, 256, 64, 36000, 18000),    # two 128-row tiles with the hand-ordered loop, half the vocabulary selected
-    (300, 256, 64, 50001, 5000),     # three 128-row tiles
-    (512, 512, 256, 40000, 2048),    # 256 x 256 tiles
+    (130, 256, 64, 36000, 18000),    # a panel of 256 rows, half the vocabulary selected
+    (300, 256, 64, 50001, 5000),     # one of 512
+    (512, 512, 256, 40000, 2048),    # ... full
     (257, 256, 128, 70001, 70001),   # k = V: everything is selected
     (90, 256, 24, 45000, 44999),     # k = V - 1
-    (66, 256, 32, 140000, 8192),     # more item tiles than the resolve step holds in registers
-    (12, 512, 64, 40000, 3000),      # below 65 rows: the path that materialises the scores (a control)
+    (66, 256, 32, 140000, 8192),     # several rounds of codes per thread
+    (8, 512, 64, 40000, 3000),       # few rows: the path that materialises the scores (a control)
 ]
 
 
@@ -823,7 +823,7 @@ BATCH_SELECT_SHAPES = [
 def test_select_batch_without_score_matrix(rows, d, dp, V, k):
     """65 or more bf16 rows and no scores output: the selection that never writes s.  Checked against the
     oracle (band rule) and bit for bit against the path that materialises s (asking for the scores selects it;
-    both compute s with the same matrix-core kernel)."""
+    both add a score's products in the same order there)."""
     say(f"batch select rows={rows} d={d} d'={dp} V={V} k={k}")
     rng = np.random.default_rng(rows * 7 + V + k)
     h = rand(rng, (rows, d), 1.0, "bf16")
@@ -842,8 +842,8 @@ def test_select_batch_without_score_matrix(rows, d, dp, V, k):
 
 
 def _adversarial_selector(rng, V, dp, sign):
-    """W_vocab whose sampled rows (ids floor(j V / SELECT_SAMPLE)) are all zero while every other row scores
-    sign * (positive integer) against an all-ones h': the sample says nothing about the rest."""
+    """W_vocab whose sampled rows (ids floor(j V / SELECT_SAMPLE); the codes' sample is every second one of them) are all zero
+    while every other row scores sign * (positive integer) against an all-ones h': the sample says nothing about the rest."""
     Wv = (sign * rng.integers(1, 4, (V, dp))).astype(np.float32)
     sampled = (np.arange(sv.SELECT_SAMPLE, dtype=np.int64) * V) // sv.SELECT_SAMPLE
     Wv[sampled] = 0.0
@@ -851,9 +851,9 @@ def _adversarial_selector(rng, V, dp, sign):
 
 
 @pytest.mark.parametrize("rows,V,k", [(65, 40000, 2000), (70, 65536, 8192), (130, 33001, 33001)])
-def test_select_batch_redoes_rows_whose_bracket_missed(rows, V, k):
+def test_select_batch_with_a_useless_sample(rows, V, k):
     """Inputs built to defeat the sample: every sampled token scores 0, every other token scores high, so far
-    more than k scores lie above the bracket and every row is redone by the exact one-workgroup path.
+    more than k scores lie above every row's interval, share its top code and are computed again.
     Integer-valued, hence exact: ids must equal the oracle's."""
     say(f"batch select with a useless sample rows={rows} V={V} k={k}")
     rng = np.random.default_rng(V + rows)
@@ -872,7 +872,7 @@ def test_select_batch_redoes_rows_whose_bracket_missed(rows, V, k):
 
 def test_select_batch_when_the_sample_holds_all_the_best():
     """The mirror case: every token outside the sample scores below it, so the k best are sampled tokens with
-    exactly tied scores (all 0): the bracket holds, the tie rule decides among thousands of candidates."""
+    exactly tied scores (all 0): the tie rule decides among the thousands that share a code."""
     say("batch select, the best tokens are exactly the sampled ones")
     rng = np.random.default_rng(4242)
     rows, V, k, dp, d = 67, 50000, 3000, 16, 16
