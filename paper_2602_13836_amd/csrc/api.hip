@@ -126,7 +126,7 @@ SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) 
     w.codes = sv::code_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
     size_t t = 0;
     if (w.codes) t = w.bracket_off + sv::code_select_scratch_bytes(rows, V);         // (less than the scores and their lists take)
-    else if (sv::bracket_select_supported(dt, rows, V, k)) t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
+    else if (sv::bracket_select_supported(dt, rows, V)) t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
     if (t > w.total) w.total = t;
     return w;
 }
@@ -433,7 +433,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
     // Wide selectors: the selection that never writes the score matrix
     // (a sample of the vocabulary brackets every row's k-th score; the full product is classified in the
     // epilogue of the matrix-core kernel).  The down-projection launch also writes the sample's ids.
-    if (!scores_out && tau == -INFINITY && sv::bracket_select_supported(dt, rows, V, k)) {
+    if (!scores_out && tau == -INFINITY && sv::bracket_select_supported(dt, rows, V)) {
         uint32_t* bscratch = reinterpret_cast<uint32_t*>(base + w.bracket_off);
         int32_t* ids = nullptr;
         int64_t m = 0;

@@ -434,6 +434,8 @@ hipError_t with_shape(int shape, F&& f) {
     }
 }
 
+struct PanelRuns { int64_t items, runs; };   // rows of M per run (a multiple of kRunUnit) and number of runs
+
 // How M is cut into runs.  A run and its panels are dealt to one XCD, a CU holds one workgroup, and a workgroup costs its
 // start (the hidden rows' way into registers, about as long as 100 rows of M) and its rows: the number of runs per XCD is
 // the one whose rounds of workgroups are cheapest.  One and two panels: a run per CU and one per two CUs.  Three panels:
@@ -515,19 +517,23 @@ bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);
 }
 
-PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items) { return runs_of(shape_of(chunks, (int)rows), rows, n_items); }
-
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_SAMPLE>(a, stream); }
 hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_CODES>(a, stream); }
 
+// (maximum, sum) pairs of a hidden row
+static int64_t pairs_of(int chunks, int64_t rows, int64_t V) {
+    const int shape = shape_of(chunks, (int)rows);
+    return runs_of(shape, rows, V).runs * kShapes[shape].gi;
+}
+
 size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V) {
-    const int64_t pairs = panel_runs(chunks, rows, V).runs * kShapes[shape_of(chunks, (int)rows)].gi;
+    const int64_t pairs = pairs_of(chunks, rows, V);
     return (size_t)rows * (size_t)(2 * pairs + 1);
 }
 
 hipError_t launch_panel_log_softmax(const PanelArgs& a0, float* ws, hipStream_t stream) {
     PanelArgs a = a0;
-    const int64_t pairs = panel_runs(a.chunks, a.rows, a.n_items).runs * kShapes[shape_of(a.chunks, a.rows)].gi;
+    const int64_t pairs = pairs_of(a.chunks, a.rows, a.n_items);
     float* lse = ws + (size_t)a.rows * (size_t)pairs * 2;
     a.partial = ws;
     hipError_t e = launch_epi<EPI_LSE>(a, stream);

@@ -771,31 +771,25 @@ __global__ __launch_bounds__(kRowThreads) void emit_rows_kernel(const float* s_a
 struct BracketLayout {
     int64_t V;
     int rows;
-    int tn;              // items per tile (run) of the classify pass
-    int first;           // candidates of a (row, tile) that live in the compact array
     int64_t tiles;       // item tiles per row
     int64_t words;       // bit-mask words per row
-    int64_t m;           // sample size
     int64_t nb;          // 4096-id vocabulary blocks (the redo path)
     // offsets in uint32 words from the scratch base (all multiples of 4: 16-byte aligned)
     size_t ids, samp, thr, flag, bits, cnt, sure, boff, state, cand_first, cand, total;
 };
 __host__ __device__ inline size_t quad4(size_t n) { return (n + 3) & ~(size_t)3; }
-// (a bracket holds 3.2 % of a row's scores at k / V = 1/18 and at most 7 %: a compact list of a sixteenth of its items
-// and six more overflows for one list in thousands in the former case; the latter pays a second round trip)
-__host__ __device__ inline BracketLayout bracket_layout(int64_t V, int rows, int tn, int64_t m) {
+constexpr int kTile = kKeepTileItems;                    // items per tile of the classify pass
+constexpr int64_t kSample = 8192;                        // sampled tokens per call
+__host__ __device__ inline BracketLayout bracket_layout(int64_t V, int rows) {
     BracketLayout L;
     L.V = V;
     L.rows = rows;
-    L.tn = tn;
-    L.first = (tn / 16 + 7) & ~1;
-    L.tiles = (V + tn - 1) / tn;
-    L.words = L.tiles * (tn / 32);
-    L.m = m;
+    L.tiles = (V + kTile - 1) / kTile;
+    L.words = L.tiles * (kTile / 32);
     L.nb = (V + (int64_t)kEpt * kSelThreads - 1) / ((int64_t)kEpt * kSelThreads);
     size_t o = 0;
-    L.ids = o;    o += quad4((size_t)m);
-    L.samp = o;   o += quad4((size_t)rows * m);
+    L.ids = o;    o += (size_t)kSample;
+    L.samp = o;   o += (size_t)rows * kSample;
     L.thr = o;    o += quad4((size_t)rows * 2);
     L.flag = o;   o += quad4((size_t)rows);
     L.bits = o;   o += quad4((size_t)rows * L.words);
@@ -803,8 +797,8 @@ __host__ __device__ inline BracketLayout bracket_layout(int64_t V, int rows, int
     L.sure = o;   o += quad4((size_t)rows * L.nb);
     L.boff = o;   o += quad4((size_t)rows * L.nb);
     L.state = o;  o += (size_t)rows * 8;
-    L.cand_first = o;  o += quad4((size_t)rows * L.tiles * L.first * 2);
-    L.cand = o;   o += (size_t)rows * L.tiles * tn * 2;      // (the redo of a row needs V slots)
+    L.cand_first = o;  o += quad4((size_t)rows * L.tiles * kBracketFirst * 2);
+    L.cand = o;   o += (size_t)rows * L.tiles * kTile * 2;      // (the redo of a row needs V slots)
     L.total = o;
     return L;
 }
@@ -812,31 +806,24 @@ __host__ __device__ inline BracketLayout bracket_layout(int64_t V, int rows, int
 // thr[r] = {hi, lo} from the row's m sample scores: hi = the largest value of the 2^-23-wide key interval
 // that holds the sample's rank_hi-th largest score (+inf if rank_hi < 1), lo = the smallest value of the
 // interval that holds the rank_lo-th largest (-inf if rank_lo > m)
-__global__ __launch_bounds__(kRbThreads) void bracket_kernel(const float* samp, int64_t m, int64_t rank_hi,
-                                                             int64_t rank_lo, float* thr) {
+__global__ __launch_bounds__(kRbThreads) void bracket_kernel(const float* samp, int64_t rank_hi, int64_t rank_lo, float* thr) {
     __shared__ uint32_t s_h1[kHistBins];
     __shared__ uint32_t s_h2[2][2048];
     __shared__ uint32_t s_w[kRbWaves];
     __shared__ uint32_t s_out[4];
     const int tid = threadIdx.x;
-    const float* s = samp + (int64_t)blockIdx.x * m;
-    // the first 32 sample scores of every thread stay in registers for both passes (all of them at the usual
-    // sample size); all loads leave at once, entries past the end repeat the last one and are not counted
-    constexpr int kHeld = 32;
+    const float* s = samp + (int64_t)blockIdx.x * kSample;
+    // the sample's scores stay in registers for both passes
+    constexpr int kHeld = (int)(kSample / kRbThreads);
     float held[kHeld];
 #pragma unroll
-    for (int u = 0; u < kHeld; ++u) {
-        const int64_t j = (int64_t)u * kRbThreads + tid;
-        held[u] = s[j < m ? j : m - 1];
-    }
+    for (int u = 0; u < kHeld; ++u) held[u] = s[u * kRbThreads + tid];
     for (int b = tid; b < kHistBins; b += kRbThreads) s_h1[b] = 0u;
     for (int b = tid; b < 2 * 2048; b += kRbThreads) (&s_h2[0][0])[b] = 0u;
     __syncthreads();
     auto for_each_key = [&](auto&& f) {
 #pragma unroll
-        for (int u = 0; u < kHeld; ++u)
-            if ((int64_t)u * kRbThreads + tid < m) f(f32_to_ord(held[u]));
-        for (int64_t j = (int64_t)kHeld * kRbThreads + tid; j < m; j += kRbThreads) f(f32_to_ord(s[j]));
+        for (int u = 0; u < kHeld; ++u) f(f32_to_ord(held[u]));
     };
     for_each_key([&](uint32_t key) { atomicAdd(&s_h1[key >> kKeyLowBits], 1u); });
     __syncthreads();
@@ -844,7 +831,7 @@ __global__ __launch_bounds__(kRbThreads) void bracket_kernel(const float* samp, 
     uint32_t c[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) c[i] = s_h1[tid * PER + i];
-    const bool has_hi = rank_hi >= 1, has_lo = rank_lo <= m;
+    const bool has_hi = rank_hi >= 1, has_lo = rank_lo <= kSample;
     uint32_t bin_hi = 0u, rem_hi = 0u, bin_lo = 0u, rem_lo = 0u;
     if (has_hi) {                                             // uniform
         locate_bin_w<PER, kRbWaves>(c, (uint32_t)rank_hi, s_w, s_out);
@@ -997,10 +984,9 @@ __device__ __forceinline__ void redo_row(const char* hp_row, const char* Wv, int
 // (a few balanced iterations per thread); a row with more (ties by the thousand) walks the memory regions instead.
 constexpr int kRbBins = 2048;
 constexpr int kRbBitBatch = 24;                          // words of the bit mask per thread requested at once
-// Pairs of candidate slots per thread that are requested up front (the row's compact lists are T F / 512 of them per thread:
-// 7 at 32768 tokens, 19 at 128256, 35 at 262144): the launch picks the smallest instance that covers the lists.  What is
-// left of larger ones follows eight pairs at a time.
-constexpr int kRbBatches[3] = {8, 16, 24};
+// Pairs of candidate slots per thread that are requested at a time, the first ones with everything else up front (a row's compact
+// lists have 5.5 of them per thread at 32768 tokens, 21.5 at 128256, 44 at 262144; with 16 or 24 up front 1 to 2 % slower).
+constexpr int kRbPairs = 8;
 // dynamic LDS of a resolve workgroup: with its 9 KB of static LDS two of them share a CU's 160 KB (a launch
 // of 512 rows is then one round of workgroups on 256 CUs)
 constexpr size_t kResolveLdsBytes = 69 * 1024, kResolveMaxLdsBytes = 148 * 1024;
@@ -1014,24 +1000,22 @@ struct ResolveEmitSmem {
 };
 __host__ __device__ inline int64_t resolve_off_words(int64_t tiles) { return (tiles + 2) & ~(int64_t)1; }
 
-// first_magic: 2^32 / (first / 2), rounded up (a slot pair's tile by one multiplication: pair number * (first / 2) stays
-// below 2^32)
-template <int BATCH>
-__global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int rows, int tn, int64_t m, int64_t k,
-                                                                  uint32_t* scratch, int32_t* idx_out,
-                                                                  uint32_t cand_cap, uint32_t first_magic) {
+__global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int rows, int64_t k, uint32_t* scratch, int32_t* idx_out,
+                                                                  uint32_t cand_cap) {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_bits[];         // [words], offsets, then the candidate list
     __shared__ ResolveEmitSmem sm;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int64_t r = blockIdx.x;
-    const BracketLayout L = bracket_layout(V, rows, tn, m);
-    const int T = (int)L.tiles, F = L.first;
+    const BracketLayout L = bracket_layout(V, rows);
+    const int T = (int)L.tiles;
+    constexpr int F = kBracketFirst;
+    static_assert(F % 2 == 0, "slots go in pairs");
     uint32_t* s_off = s_bits + L.words;                                       // words is even
     uint64_t* s_cand = reinterpret_cast<uint64_t*>(s_off + resolve_off_words(T));
     const uint32_t* bits = scratch + L.bits + (size_t)r * L.words;
     const uint32_t* cnt = scratch + L.cnt + (size_t)r * L.tiles;
-    const uint64_t* cand = reinterpret_cast<const uint64_t*>(scratch + L.cand) + (size_t)r * L.tiles * tn;
+    const uint64_t* cand = reinterpret_cast<const uint64_t*>(scratch + L.cand) + (size_t)r * L.tiles * kTile;
     const uint64_t* first = reinterpret_cast<const uint64_t*>(scratch + L.cand_first) + (size_t)r * L.tiles * F;
     // everything independent is requested up front, in the order of use: the bracket, the candidate counts of
     // this thread's tiles, the first words of the bit mask, the first slots of the compact candidate array (before it
@@ -1047,11 +1031,11 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
         const int64_t w = (int64_t)u * kRbThreads + tid;
         wv[u] = bits[w < L.words ? w : L.words - 1];
     }
-    const uint32_t pairs_total = (uint32_t)T * (uint32_t)(F / 2);             // slots two at a time (F is even)
+    const uint32_t pairs_total = (uint32_t)T * (uint32_t)(F / 2);             // slots two at a time
     const u32x4* first2 = reinterpret_cast<const u32x4*>(first);
-    u32x4 reg[BATCH];
+    u32x4 reg[kRbPairs];
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
+    for (int u = 0; u < kRbPairs; ++u) {
         const uint32_t j = (uint32_t)u * kRbThreads + tid;
         reg[u] = first2[j < pairs_total ? j : pairs_total - 1];
     }
@@ -1089,17 +1073,16 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
     if (miss) return;                                         // uniform: the redo launch handles this row
     uint32_t remain = (uint32_t)k - n_above;                  // candidates to select, 0 <= remain <= n_band
 
-    // f(tile, place, candidate) for the candidates from place `from` of every tile (of count(tile)) on, from memory.  A tile is shared by as
-    // many threads as there are for each (thousands of hidden rows leave a row few tiles, of tens of thousands of tokens),
-    // at least four, so that their requests join, and a thread has several requests on their way (512 rows x 262144, k =
-    // 16384, many ties: one thread per tile 296 us, four 246, eight 252).
+    // f(tile, place, candidate) for the candidates from place `from` of every tile (of count(tile)) on, from memory.  Two threads share
+    // a tile, so that their requests join, and a thread has several requests on their way (512 rows x 262144, d' = 520, k = 16384, many
+    // ties: one thread per tile 390 us, two 365, four 386, eight 478; 1000 rows without ties 633, 618, 637, 709).
     auto walk_tiles = [&](int from, auto&& count, auto&& f) {
         constexpr int kFlight = 8;
-        const int sharers = T * 4 < kRbThreads ? kRbThreads / T : 4;
+        constexpr int sharers = 2;
         const int sub = tid % sharers;
         for (int t = tid / sharers; t < T; t += kRbThreads / sharers) {
             const int n = (int)count(t);
-            const uint64_t *p0 = first + (int64_t)t * F, *p = cand + (int64_t)t * tn - F;
+            const uint64_t *p0 = first + (int64_t)t * F, *p = cand + (int64_t)t * kTile - F;
             for (int i = from + sub; i < n; i += kFlight * sharers) {
                 uint64_t x[kFlight];
 #pragma unroll
@@ -1126,22 +1109,21 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
                    [&](int t, uint32_t i, uint64_t x) { s_cand[s_off[t] + i] = x; });
         auto pack = [&](uint32_t j, const u32x4 v) {
             if (j >= pairs_total) return;
-            const uint32_t t = __umulhi(j, first_magic), i = 2u * (j - t * (uint32_t)(F / 2));
+            const uint32_t t = j / (uint32_t)(F / 2), i = 2u * (j - t * (uint32_t)(F / 2));
             const uint32_t at = s_off[t], n = s_off[t + 1] - at;
             if (i < n) s_cand[at + i] = ((uint64_t)v[1] << 32) | v[0];
             if (i + 1 < n) s_cand[at + i + 1] = ((uint64_t)v[3] << 32) | v[2];
         };
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) pack((uint32_t)u * kRbThreads + tid, reg[u]);
-        for (uint32_t j0 = (uint32_t)BATCH * kRbThreads + tid; j0 < pairs_total; j0 += 8u * kRbThreads) {
-            u32x4 v[8];
+        for (int u = 0; u < kRbPairs; ++u) pack((uint32_t)u * kRbThreads + tid, reg[u]);
+        for (uint32_t j0 = (uint32_t)kRbPairs * kRbThreads + tid; j0 < pairs_total; j0 += (uint32_t)kRbPairs * kRbThreads) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < kRbPairs; ++u) {
                 const uint32_t j = j0 + (uint32_t)u * kRbThreads;
-                v[u] = first2[j < pairs_total ? j : pairs_total - 1];
+                reg[u] = first2[j < pairs_total ? j : pairs_total - 1];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) pack(j0 + (uint32_t)u * kRbThreads, v[u]);
+            for (int u = 0; u < kRbPairs; ++u) pack(j0 + (uint32_t)u * kRbThreads, reg[u]);
         }
         __syncthreads();
     }
@@ -1281,13 +1263,13 @@ __global__ __launch_bounds__(kRbThreads) void resolve_emit_kernel(int64_t V, int
 // which is the normal case)
 constexpr int kRedoBlocks = 32;
 template <int DT>
-__global__ __launch_bounds__(kSelThreads) void redo_bracket_kernel(int64_t V, int rows, int tn, int64_t m, int64_t k,
-                                                                   uint32_t* scratch, int32_t* idx_out, const char* hp,
+__global__ __launch_bounds__(kSelThreads) void redo_bracket_kernel(int64_t V, int rows, int64_t k, uint32_t* scratch,
+                                                                   int32_t* idx_out, const char* hp,
                                                                    const char* Wv, int chunks) {
     __shared__ RedoSmem rs;
     __shared__ int s_todo[kSelThreads];
     __shared__ uint32_t s_ntodo;
-    const BracketLayout L = bracket_layout(V, rows, tn, m);
+    const BracketLayout L = bracket_layout(V, rows);
     const int tid = threadIdx.x;
     // all flags are read at once (one round trip); this workgroup's share of the flagged rows goes to a list
     for (int64_t base = 0; base < rows; base += kSelThreads) {
@@ -1311,7 +1293,7 @@ __global__ __launch_bounds__(kSelThreads) void redo_bracket_kernel(int64_t V, in
             p.state = scratch + L.state + (size_t)r * 8;
             p.hist = nullptr;
             p.binfo = p.state + 4;
-            p.cand = reinterpret_cast<uint64_t*>(scratch + L.cand) + (size_t)r * L.tiles * tn;   // >= V entries
+            p.cand = reinterpret_cast<uint64_t*>(scratch + L.cand) + (size_t)r * L.tiles * kTile;   // >= V entries
             p.sure = scratch + L.sure + (size_t)r * L.nb;
             p.offset = scratch + L.boff + (size_t)r * L.nb;
             __syncthreads();                                      // the LDS of the previous row's redo is free again
@@ -1328,16 +1310,8 @@ bool scores_supported(int chunks) { return chunks >= 1 && chunks <= 64; }
 // more than 64 KiB of dynamic LDS needs an explicit opt-in per kernel and device (called once per device,
 // outside any stream capture, by the library's device set-up)
 hipError_t configure_select_lds() {
-    hipError_t e = hipSuccess;
-    auto opt_in = [&](auto kernel) {
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)kResolveMaxLdsBytes);
-    };
-    opt_in(&resolve_emit_kernel<kRbBatches[0]>);
-    opt_in(&resolve_emit_kernel<kRbBatches[1]>);
-    opt_in(&resolve_emit_kernel<kRbBatches[2]>);
-    return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&resolve_emit_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kResolveMaxLdsBytes);
 }
 
 int64_t select_max_vocab() { return (int64_t)kSelThreads * kMaxBlocksPerRow * kEpt; }
@@ -1352,26 +1326,27 @@ void select_zero_range(int64_t rows, int64_t V, size_t* words) {
 }
 
 // ---- bracketed selection (many hidden rows, bf16): host side
-constexpr int64_t kSample = 8192;                        // sampled tokens per call
 constexpr int64_t kBracketMaxVocab = 393216;             // the row's bit mask (V / 8 bytes) lives in LDS: 48 KiB here
 
-// From 65 hidden rows on: the tiled kernel has tiles of 128 of them there, and fewer rows' scores stay in the last-level cache
-// when they are written (60 rows, d' = 512, 32768 / 128256 / 262144 tokens 37 / 79 / 133 us with the scores in memory
-// against 51 / 87 / 132).
+// From 65 hidden rows on, where the tiled kernel's tiles begin.  The scores' way through memory grows with rows and vocabulary and hardly
+// with k, this one's last step with k, so the bracket is the shorter way for k up to V / 8 from about 8.5 million scores on, and the
+// longer one below, by up to a quarter (us, d' = 520, k = V / 32, scores in memory / bracketed: 128256 tokens, 65 rows 78 / 78, 100 rows 91 / 82, 262144, 65
+// rows 145 / 136; 65536, 100 rows 55 / 58, 128 rows 62 / 59; 32768, 65 rows 41 / 49, 128 rows 46 / 51, 200 rows 6 % less; k = V / 4: 128256, 100 rows
+// 93 / 108, equal at 160 to 200).  The line does not follow that: over short vocabularies the two add a score's products in different
+// orders, and which of two tokens that tie within rounding is selected would change with it.
 constexpr int64_t kBracketMinRows = 65;
-bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k) {
-    (void)k;
+bool bracket_select_supported(int dt, int64_t rows, int64_t V) {
     return dt == DT_BF16 && rows >= kBracketMinRows && V >= 4 * kSample && V <= kBracketMaxVocab;
 }
 
 size_t bracket_scratch_words(int64_t rows, int64_t V) {
-    return bracket_layout(V, (int)rows, kKeepTileItems, kSample).total;
+    return bracket_layout(V, (int)rows).total;
 }
 
 void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp) {
-    const BracketLayout L = bracket_layout(V, (int)rows, kKeepTileItems, kSample);
+    const BracketLayout L = bracket_layout(V, (int)rows);
     *ids = reinterpret_cast<int32_t*>(scratch + L.ids);
-    *m = L.m;
+    *m = kSample;
     *samp = reinterpret_cast<float*>(scratch + L.samp);
 }
 
@@ -1379,16 +1354,15 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     DeviceInfo di;
     hipError_t e = device_info(&di);
     if (e != hipSuccess) return e;
-    constexpr int tn = kKeepTileItems;
-    const BracketLayout L = bracket_layout(a.V, a.rows, tn, kSample);
+    const BracketLayout L = bracket_layout(a.V, a.rows);
     // ranks of the bracket in the sample: the number of sampled tokens among the row's k best is
     // hypergeometric with mean m k / V; 6 standard deviations and 8 more on either side
-    const double q = (double)a.k / (double)a.V, mean = (double)L.m * q;
-    const double sd = sqrt((double)L.m * q * (1.0 - q));
+    const double q = (double)a.k / (double)a.V, mean = (double)kSample * q;
+    const double sd = sqrt((double)kSample * q * (1.0 - q));
     const int64_t rank_hi = (int64_t)floor(mean - 6.0 * sd - 8.0), rank_lo = (int64_t)ceil(mean + 6.0 * sd + 8.0);
     float* thr = reinterpret_cast<float*>(a.scratch + L.thr);
     hipLaunchKernelGGL(bracket_kernel, dim3((unsigned)a.rows), dim3(kRbThreads), 0, stream,
-                       reinterpret_cast<const float*>(a.scratch + L.samp), L.m, rank_hi, rank_lo, thr);
+                       reinterpret_cast<const float*>(a.scratch + L.samp), rank_hi, rank_lo, thr);
     // classify: the full product, nothing stored but bits and candidates
     BracketEpi ep{};
     ep.thr = thr;
@@ -1398,8 +1372,6 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     ep.cand = reinterpret_cast<uint64_t*>(a.scratch + L.cand);
     ep.cnt = a.scratch + L.cnt;
     ep.item_tiles = L.tiles;
-    ep.first_cap = L.first;
-    ep.over_cap = tn;
     GemvArgs g{};
     g.x = a.hp;
     g.x_row_bytes = (int64_t)a.chunks * 16;
@@ -1412,28 +1384,20 @@ hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream) {
     if (e != hipSuccess) return e;
     // LDS of a resolve workgroup: the bit mask, the tiles' offsets and the row's candidates.  As many slots as keep two
     // workgroups on a CU; with one row per CU or fewer, where that is of no use, as many as a row's expected candidates need
-    // (256 rows x 262144, k = 16384: 127 us with the candidates packed into LDS, 130 walked in memory, many ties 143 and 151;
-    // 512 rows 241 packed in two rounds of one workgroup per CU, 219 walked in one).
+    // (d' = 520, k = V / 16, 262144 tokens: 256 rows 201 us with the candidates packed into LDS, 221 walked in memory, many ties 239 and
+    // 269; 1000 rows 663 packed in rounds of one workgroup per CU, 645 walked in rounds of two).
     const size_t fixed_bytes = ((size_t)L.words + (size_t)resolve_off_words(L.tiles)) * 4;
-    const double expected = (double)((rank_lo < L.m ? rank_lo : L.m) - (rank_hi > 0 ? rank_hi : 0)) / (double)L.m * (double)a.V;
+    const double expected = (double)((rank_lo < kSample ? rank_lo : kSample) - (rank_hi > 0 ? rank_hi : 0)) / (double)kSample * (double)a.V;
     const size_t want = fixed_bytes + (size_t)(expected * 1.15) * 8 + 1024;
     const size_t budget = a.rows <= di.cus && want > kResolveLdsBytes && want <= kResolveMaxLdsBytes ? want : kResolveLdsBytes;
     const size_t room = budget > fixed_bytes ? budget - fixed_bytes : 0;
     uint32_t cand_cap = (uint32_t)(room / 8);
     if (cand_cap < 1024u) cand_cap = 0u;                      // not worth a packing pass
     const size_t lds = fixed_bytes + (size_t)cand_cap * 8;
-    const uint32_t half_first = (uint32_t)(L.first / 2);
-    const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + half_first - 1) / half_first);
-    auto resolve = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kRbThreads), lds, stream, a.V, a.rows, tn, L.m, a.k, a.scratch,
-                           a.idx_out, cand_cap, magic);
-    };
-    const int64_t pairs_per_thread = (L.tiles * half_first + kRbThreads - 1) / kRbThreads;
-    if (pairs_per_thread <= kRbBatches[0]) resolve(&resolve_emit_kernel<kRbBatches[0]>);
-    else if (pairs_per_thread <= kRbBatches[1]) resolve(&resolve_emit_kernel<kRbBatches[1]>);
-    else resolve(&resolve_emit_kernel<kRbBatches[2]>);
+    hipLaunchKernelGGL(resolve_emit_kernel, dim3((unsigned)a.rows), dim3(kRbThreads), lds, stream, a.V, a.rows, a.k, a.scratch, a.idx_out,
+                       cand_cap);
     hipLaunchKernelGGL(redo_bracket_kernel<DT_BF16>, dim3((unsigned)(a.rows < kRedoBlocks ? a.rows : kRedoBlocks)),
-                       dim3(kSelThreads), 0, stream, a.V, a.rows, tn, L.m, a.k, a.scratch, a.idx_out, a.hp, a.Wv, a.chunks);
+                       dim3(kSelThreads), 0, stream, a.V, a.rows, a.k, a.scratch, a.idx_out, a.hp, a.Wv, a.chunks);
     return hipGetLastError();
 }
 

@@ -106,20 +106,22 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream);
 // (thr[r] = {hi, lo}):  f > hi -> bit j of the row's bit mask;  lo <= f <= hi -> (key, id) appended to the
 // candidate region of (r, item tile), whose entry count goes to cnt.  Every word of bits and every cnt entry
 // is written.  Any row count >= 1.
-// Candidates of a (row, item tile): the first first_cap in a compact array (a row's are contiguous: the resolve
-// pass streams them), any further ones (tied scores) in a region of the pair's of over_cap slots.
+// Candidates of a (row, item tile): the first kBracketFirst in a compact array (a row's are contiguous: the resolve
+// pass streams them), any further ones (tied scores) in a region of the pair's of kKeepTileItems slots -- more than is left of
+// the tile, but a row's regions together are where the redo of a row keeps its V slots.
+// (A bracket holds 3.2 % of a row's scores at k / V = 1/18 and at most 7 %: a compact list of a sixteenth of its items
+// and six more overflows for one list in thousands in the former case; the latter pays a second round trip.)
+constexpr int kKeepTileItems = 256;      // items per tile of the epilogues that keep something per item tile
+constexpr int kBracketFirst = kKeepTileItems / 16 + 6;
 struct BracketEpi {
     const float* thr;        // [rows][2]
     uint32_t* bits;          // [rows][words_per_row], words_per_row = item_tiles * tile items / 32
     int64_t words_per_row;
-    uint64_t* cand_first;    // [rows][item_tiles][first_cap]   ((ordered key << 32) | ~id)
-    uint64_t* cand;          // [rows][item_tiles][over_cap]    slots first_cap .. of the same list
+    uint64_t* cand_first;    // [rows][item_tiles][kBracketFirst]    ((ordered key << 32) | ~id)
+    uint64_t* cand;          // [rows][item_tiles][kKeepTileItems]   slots kBracketFirst .. of the same list
     uint32_t* cnt;           // [rows][item_tiles]
     int64_t item_tiles;
-    int first_cap, over_cap; // over_cap = tile items: more than is left of the tile, but a row's regions together are
-                             // where the redo of a row keeps its V slots
 };
-constexpr int kKeepTileItems = 256;      // items per tile of the epilogues that keep something per item tile
 hipError_t launch_tile_mfma_bracket(const GemvArgs& a, const BracketEpi& ep, hipStream_t stream);
 
 // The tiled product over ALL rows of M (a.idx == nullptr, a.n_items = V) with the pick epilogue: only
@@ -161,8 +163,6 @@ struct PanelArgs {
     uint8_t* codes;
     int64_t code_stride;
 };
-struct PanelRuns { int64_t items, runs; };   // rows of M per run (a multiple of 64) and number of runs
-PanelRuns panel_runs(int chunks, int64_t rows, int64_t n_items);
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
 bool panel_codes_supported(int dt, int chunks, int64_t rows, int64_t n_items);     // launch_panel_sample, launch_panel_codes
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
@@ -249,7 +249,7 @@ struct BracketArgs {
     int32_t* idx_out;      // [rows x k]
     uint32_t* scratch;     // bracket_scratch_words(rows, V) words; nothing needs clearing
 };
-bool bracket_select_supported(int dt, int64_t rows, int64_t V, int64_t k);
+bool bracket_select_supported(int dt, int64_t rows, int64_t V);
 size_t bracket_scratch_words(int64_t rows, int64_t V);
 void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp);
 hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream);
@@ -263,7 +263,7 @@ struct CodeSelectArgs {
     int rows;
     int64_t k;
     int32_t* idx_out;      // [rows x k]
-    char* scratch;         // code_select_scratch_bytes(rows, V) bytes, 256-byte aligned; nothing needs clearing
+    char* scratch;         // code_select_scratch_bytes(rows, V) bytes, 16-byte aligned; nothing needs clearing
 };
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k);
 size_t code_select_scratch_bytes(int64_t rows, int64_t V);

@@ -521,11 +521,12 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
             for (int n = 0; n < WN; ++n) words[j][n] = 0u;
         // candidate regions of this tile's rows: region of tile row t at cand_tile + t * row_stride (32-bit
         // arithmetic below: 64-bit multiplications per candidate cost more than everything else there)
-        const uint32_t fcap = (uint32_t)ep.first_cap;
-        uint64_t* cand_tile = ep.cand + ((int64_t)rt * TM * ep.item_tiles + it) * ep.over_cap;
-        const uint32_t row_stride = (uint32_t)(ep.item_tiles * ep.over_cap);          // < 2^24 (the vocabulary, padded)
-        uint64_t* first_tile = ep.cand_first + ((int64_t)rt * TM * ep.item_tiles + it) * ep.first_cap;
-        const uint32_t first_stride = (uint32_t)(ep.item_tiles * ep.first_cap);
+        static_assert(TN == kKeepTileItems, "lists are kept per tile of that many items");
+        constexpr uint32_t fcap = (uint32_t)kBracketFirst;
+        uint64_t* cand_tile = ep.cand + ((int64_t)rt * TM * ep.item_tiles + it) * TN;
+        const uint32_t row_stride = (uint32_t)(ep.item_tiles * TN);                   // < 2^24 (the vocabulary, padded)
+        uint64_t* first_tile = ep.cand_first + ((int64_t)rt * TM * ep.item_tiles + it) * kBracketFirst;
+        const uint32_t first_stride = (uint32_t)(ep.item_tiles * kBracketFirst);
         static_for<0, WM>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             constexpr int kHalfRows = 4;                   // lanes 32..63 hold the row four below
