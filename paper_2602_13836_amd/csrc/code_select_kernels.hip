@@ -10,6 +10,9 @@
 //   resolve   one workgroup per row, the row's codes in registers: their histogram names the code C that holds the k-th
 //             score.  Everything above C is selected; the scores of code C itself -- a few dozen tokens -- are computed
 //             once more, by the same matrix instructions in the same order, and ranked by (score, smaller id first).
+// A score is the same float32 as where it goes through memory, bit for bit: up to 256 elements all matrix-core kernels add its products in
+// ascending order from zero (v_mfma_f32_16x16x32_bf16 adds its 32 as two 16s), and wider selectors come here from 65 rows on, where the
+// tiled kernel does too.
 // The result is exact with respect to those scores whatever the map is, because the map is monotone: a poor one only
 // leaves more tokens in code C (a map that misses the k-th score altogether, as many as there are below lo or above hi).
 // As many keys as fit stay in LDS; more go to memory.  All of it lies where the scores would (12 bytes per score with the lists that

@@ -174,3 +174,20 @@ def test_replays_of_a_captured_call(rows):
         want, _ = sv.select(h, Wd, Wv, k)
         torch.cuda.synchronize()
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("rows,V,d_prime", [(9, 32768, 256), (16, 40000, 128), (17, 16384, 256), (24, 60000, 200), (32, 90112, 128), (20, 90113, 64),
+                                            (32, 128256, 256), (33, 100000, 256), (60, 33000, 248), (65, 20000, 512), (130, 40000, 512)])
+def test_one_sum_per_score(rows, V, d_prime):
+    """A call adds a score's products the same way whether or not it is asked for the scores.  All rows of W_vocab hold the same numbers in
+    different orders and h' is one number d' times, so all scores are equal but for their rounding, which decides what is selected."""
+    rng = np.random.default_rng(rows + V)
+    base = rng.normal(size=d_prime) + 1.0
+    Wv = _bf16(rng.permuted(np.tile(base, (V, 1)), axis=1))
+    h = _bf16(rng.normal(size=(rows, 64)) + 2.0)
+    Wd = _bf16(np.full((d_prime, 64), 1 / 64))
+    k = V // 20
+    idx, _ = sv.select(h, Wd, Wv, k)
+    with_scores, sc = sv.select(h, Wd, Wv, k, want_scores=True)
+    assert len(sc.unique()) > rows                 # (they do round differently)
+    assert torch.equal(idx, with_scores)
