@@ -1332,8 +1332,8 @@ constexpr int64_t kBracketMaxVocab = 393216;             // the row's bit mask (
 // with k, this one's last step with k, so the bracket is the shorter way for k up to V / 8 from about 8.5 million scores on, and the
 // longer one below, by up to a quarter (us, d' = 520, k = V / 32, scores in memory / bracketed: 128256 tokens, 65 rows 78 / 78, 100 rows 91 / 82, 262144, 65
 // rows 145 / 136; 65536, 100 rows 55 / 58, 128 rows 62 / 59; 32768, 65 rows 41 / 49, 128 rows 46 / 51, 200 rows 6 % less; k = V / 4: 128256, 100 rows
-// 93 / 108, equal at 160 to 200).  The line does not follow that: over short vocabularies the two add a score's products in different
-// orders, and which of two tokens that tie within rounding is selected would change with it.
+// 93 / 108, equal at 160 to 200).  The line does not follow that: from 1024 elements on the two may walk a row from
+// different starts, and which of two tokens that tie within rounding is selected would change with it.
 constexpr int64_t kBracketMinRows = 65;
 bool bracket_select_supported(int dt, int64_t rows, int64_t V) {
     return dt == DT_BF16 && rows >= kBracketMinRows && V >= 4 * kSample && V <= kBracketMaxVocab;
