@@ -42,27 +42,25 @@ constexpr int kHeld = (int)(kSample / kMapThreads);
 constexpr int64_t kMaxVocab = 262144 + 131072;           // a bit per token in LDS (48 KB)
 constexpr int64_t kMinVocab = 16384;
 
-
 struct CodeLayout {
     int64_t stride;          // bytes between rows of codes: an odd multiple of 256, off the memory channels' period
     int64_t entries;         // of a row's list that memory has room for (a list has 3 to 16 % of V as a rule)
-    // offsets in bytes from the scratch base (multiples of 8); the sample and the map lie where keys do, which come after them
-    size_t codes, keys, list, samp, map, total;
+    // offsets in bytes from the scratch base (multiples of 8; the codes' of 256)
+    size_t samp, map, codes, keys, list, total;
 };
 inline CodeLayout code_layout(int64_t V, int64_t rows) {
     CodeLayout L;
     L.stride = (V + 255) / 256 * 256 | 256;
     L.entries = V / 2;
     size_t o = 0;
+    L.samp = o;   o += (size_t)rows * kSample * 4;
+    L.map = o;    o += ((size_t)rows * 8 + 255) & ~(size_t)255;             // (rows of codes start on lines)
     L.codes = o;  o += (size_t)rows * (size_t)L.stride;
     L.keys = o;   o += (size_t)rows * (size_t)V * 8;
     L.list = o;   o += (size_t)rows * (size_t)L.entries * 4;
     L.total = o;
-    L.samp = L.keys;
-    L.map = L.samp + (size_t)rows * kSample * 4;             // (a key per token is twice as much and more: kMinVocab)
     return L;
 }
-static_assert(kMinVocab * 8 >= kSample * 4 + 8, "the sample and the map fit where the keys go");
 
 // ---- map: one workgroup per row, its part of the sample in registers
 // map[r] = {scale, bias} from where the rank_hi-th and the rank_lo-th largest of the row's sample scores lie (1 <= rank_hi <=
