@@ -138,14 +138,14 @@ int specvocab_workspace_bytes(int op, int64_t rows, int64_t d, int64_t V, int64_
  * scores_out: device [rows x k] float32 receiving s[r, idx_out[r, j]], or NULL.
  * Requires 1 <= k <= V, 1 <= d_prime, rows >= 1; V above 4194304 is SV_ERR_UNSUPPORTED.
  * Cost.  With bf16, scores_out == NULL, d_prime <= 512, 16384 <= V <= 393216 and more than a handful of hidden rows (9
- * to 65, by d_prime, V and k) memory holds a byte per score instead of s: the scores of 4096 evenly spaced tokens (ids
+ * to 160, by d_prime, V and k) memory holds a byte per score instead of s: the scores of 4096 evenly spaced tokens (ids
  * floor(j V / 4096)) decide how a row's scores map to bytes, and the scores that share the k-th one's byte are computed again
  * and resolved exactly.  The result is the same exact top-k; where the sample misleads (about 1e-5 of rows on scores that do not
  * depend on the token id modulo the sampling stride; certain for inputs built so that the sampled tokens score unlike
- * all others) a row takes tens of microseconds more, up to a few milliseconds.  From 65 hidden rows on wider selectors keep
+ * all others) a row takes tens of microseconds more, up to a few milliseconds.  From 65 hidden rows and 32768 tokens on wider selectors keep
  * only the few per cent of scores inside a bracket from 8192 sampled tokens; a row whose bracket misses is recomputed by a slow exact
- * path, about a millisecond per such row.  Every other shape and every call with scores_out materialises s in the workspace.
- * The workspace is the same either way: 12 bytes per score and some kilobytes per row. */
+ * path, about a millisecond per such row.  Every other shape, every call with scores_out and every
+ * threshold materialises s in the workspace, which is the same size either way: 12 bytes per score and some kilobytes per row. */
 int specvocab_select(const void* h, int64_t rows, int64_t d, int64_t ldh,
                      const void* W_down, int64_t d_prime,
                      const void* W_vocab, int64_t V,

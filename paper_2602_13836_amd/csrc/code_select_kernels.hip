@@ -18,8 +18,8 @@
 // As many keys as fit stay in LDS; more go to memory.  All of it lies where the scores would (12 bytes per score with the lists that
 // their selection keeps), in 11 of them.
 //
-// Measured (512 rows x 151936, d' = 256, k = 8192; kernels under a profiler): sample 8 us, map 7, codes 48, resolve 36; the
-// whole selection 133 -> 106 us.  The form it replaces kept a bit per score (above hi) and a list of (key, id) of the scores
+// Measured (512 rows x 151936, d' = 256, k = 8192; kernels under a profiler): h' 11 us, sample 8, map 5, codes 50, resolve 37; the
+// whole selection 133 -> 103 us.  The form it replaces kept a bit per score (above hi) and a list of (key, id) of the scores
 // between lo and hi per row and run -- 40 us of comparisons, LDS and scattered stores on top of the product --, needed a
 // sample twice as large for its lists to be short, and an idle launch for rows whose bracket had missed.
 #include "sv_device.h"
@@ -208,7 +208,7 @@ constexpr uint32_t kLow = 0x7F7F7F7Fu, kOne = 0x01010101u;
 // round is 2 KB of consecutive codes, and ids ascend with (wavefront, round, lane, bit).  Codes of 255 become bits at once;
 // ids with codes from 128 to 254 (three or four per cent) go to a list, on which everything else works.
 // What bounds it: vector arithmetic, of which the loops over a lane's set bits are the larger part (they run as long as the
-// lane with the most).  512 rows x 151936, k = 8192, two workgroups per CU: 36 us, of which a workgroup's first pass over the
+// lane with the most).  512 rows x 151936, k = 8192, two workgroups per CU: 37 us, of which a workgroup's first pass over the
 // codes is 11, the choice within code C 5, the ids 4 (a second pass over the codes instead of the list: 48; the codes held in
 // registers: 64, they spill; a lane's place in the list by an atomic of its own: 54).
 // The list holds list_cap entries in LDS and mem_cap in memory.  Where it holds too few -- or a code below 128 decides -- the codes are walked

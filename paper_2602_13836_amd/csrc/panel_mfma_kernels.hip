@@ -17,7 +17,7 @@
 // epilogue, and a sub-tile's epilogue cut into pieces between the MFMAs of the next one: 103 and 92-95 us against 97 for
 // the sums of 1024 rows x 151936 -- the matrix cores alone take 65, at the clock their load leaves.)
 //
-// Measured: the selection's product with its codes, 512 rows x 151936, d' = 256: 48 us (without the codes' stores 41, of
+// Measured: the selection's product with its codes, 512 rows x 151936, d' = 256: 48 to 50 us (without the codes' stores 41, of
 // which the matrix cores are busy 20; codes kept for a step and stored behind the next requests 58; to lines of 1 KB, rows of
 // one unit side by side, 47); log-probabilities of 1024 rows x 151936 579 us on the tiled kernel, 230 here (sums 97, stored
 // product 145 under a profiler: 622 MB at 4.3 TB/s).

@@ -8,7 +8,7 @@ sv = pytest.importorskip("paper_2602_13836_amd")
 
 pytestmark = pytest.mark.gpu
 
-SAMPLE = 4096            # sampled tokens: floor(j V / 4096)
+SAMPLE = sv.SELECT_CODE_SAMPLE
 
 
 def _bf16(a):
