@@ -53,6 +53,8 @@ hipError_t device_state(const DeviceState** out) {
             if (e != hipSuccess) return e;
             e = configure_code_select_lds();
             if (e != hipSuccess) return e;
+            e = configure_key_select_lds();
+            if (e != hipSuccess) return e;
             e = configure_union_lds();
             if (e != hipSuccess) return e;
             e = configure_panel_lds();
@@ -114,7 +116,7 @@ inline int ensure_device() {
 struct SelectWs {
     size_t hp_off, s_off, radix_off, total;
     size_t bracket_off;      // scratch of the bracketed selection and of the one by codes (instead of the score matrix)
-    bool codes;              // the selection by codes serves this shape where nobody asks for scores
+    bool keys, codes;        // the selection by two bytes per score, by one, serves this shape where nobody asks for scores
 };
 SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) {
     SelectWs w;
@@ -123,9 +125,11 @@ SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) 
     w.radix_off = w.s_off + round256((size_t)rows * (size_t)V * sizeof(float));
     w.total = w.radix_off + round256(sv::select_scratch_words(rows, V) * sizeof(uint32_t));
     w.bracket_off = w.s_off;
-    w.codes = sv::code_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
+    w.keys = sv::key_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
+    w.codes = !w.keys && sv::code_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
     size_t t = 0;
-    if (w.codes) t = w.bracket_off + sv::code_select_scratch_bytes(rows, V);         // (less than the scores and their lists take)
+    if (w.keys) t = w.bracket_off + sv::key_select_scratch_bytes(rows, V);
+    else if (w.codes) t = w.bracket_off + sv::code_select_scratch_bytes(rows, V);         // (less than the scores and their lists take)
     else if (sv::bracket_select_supported(dt, rows, V)) t = w.bracket_off + round256(sv::bracket_scratch_words(rows, V) * sizeof(uint32_t));
     if (t > w.total) w.total = t;
     return w;
@@ -415,9 +419,9 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
     float* scores = reinterpret_cast<float*>(base + w.s_off);
     uint32_t* radix = reinterpret_cast<uint32_t*>(base + w.radix_off);
 
-    // A batch of hidden rows whose scores nobody asked for: a byte per score in memory
+    // Hidden rows whose scores nobody asked for: two bytes per score in memory, or one
     const int vchunks = (int)(d_prime * es / 16);
-    if (!scores_out && tau == -INFINITY && w.codes) {
+    if (!scores_out && tau == -INFINITY && (w.keys || w.codes)) {
         if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, nullptr, 0, s) != SV_OK) return SV_ERR_HIP;
         sv::CodeSelectArgs ca{};
         ca.hp = hp;
@@ -428,6 +432,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         ca.k = k;
         ca.idx_out = idx_out;
         ca.scratch = base + w.bracket_off;
+        if (w.keys) return sv::launch_key_select(ca, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
         return sv::launch_code_select(ca, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
     }
     // Wide selectors: the selection that never writes the score matrix

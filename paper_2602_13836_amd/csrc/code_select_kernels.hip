@@ -570,41 +570,16 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
 
 }  // namespace
 
-// From how many rows on.  The chain of five launches and a workgroup's walk over its row cost about as much whatever the rows
-// are, which the scores in memory (their histogram, two more passes over them) reach with rows and vocabulary; and a row with many ids
-// takes its workgroup longer.  So the line goes by the share of the tokens that is wanted, in sixteenths, the vocabulary and the width
-// (up to 128, up to 256 elements).  us, scores in memory / codes, on either side of the line:
-//   V / 32     d' = 256, 128256 tokens: 16 rows 42.6 / 45.1, 24 rows 46.5 / 44.3; 32768: 9 rows 31.6 / 29.5; d' = 128, 128256: 9 rows 36.5 / 33.6;
-//              8 rows, whose chain over the scores is a shorter one, 24 / 26 and more
-//   V / 8      d' = 256, 128256: 24 rows 44.0 / 47.9, 32 rows 47.4 / 47.8; 65536: 16 rows 32.6 / 33.5, 20 rows 34.5 / 33.9; d' = 128, 128256:
-//              16 rows 38.5 / 39.4, 20 rows 41.9 / 39.8
-//   V / 4      d' = 256, 128256: 48 rows 54.8 / 56.6, 60 rows 61.1 / 57.9; 262144: 48 rows 94.1 / 87.2; d' = 128, 128256: 48 rows 48.4 / 49.0
-//   V / 2      d' = 256, 128256: 64 rows 63.0 / 62.5; 32768: 48 rows 33.4 / 34.4, 60 rows 36.3 / 34.3; d' = 128, 65536: 40 rows 37.3 / 38.1, 48
-//              rows 39.5 / 38.5
-// d' > 256: there are no panels of 64 rows; from 65 rows on (64 on a panel of 256 take 46 and 69 us against 38 and 71), where the alternative
-// is the scores in memory (vocabularies below the bracketed selection's) from as many as fill the chip: d' = 512, 32767: 65 rows 41.8 / 42.6, 100
-// rows 53.2 / 49.5; 20000: 128 rows 45.1 / 45.0, 160 rows 56.7 / 51.2; half of 25000 wanted: 128 rows 47.0 / 48.8, 160 rows 56.8 / 53.9.
+// From 65 rows on, where two bytes per score are not the shorter way (key_select_kernels.hip).  d' > 256: vocabularies below the
+// bracketed selection's, whose alternative is the scores in memory, from as many rows as fill the chip (us, scores / codes): d' = 512, 32767: 65
+// rows 41.8 / 42.6, 100 rows 53.2 / 49.5; 20000: 128 rows 45.1 / 45.0, 160 rows 56.7 / 51.2; half of 25000 wanted: 128 rows 47.0 / 48.8, 160 rows
+// 56.8 / 53.9.
 inline int64_t min_rows(int chunks, int64_t V, int64_t k) {
-    constexpr int64_t never = 65;                             // (from 65 rows on codes are always the shorter way)
     if (chunks > 32) return V >= 32768 ? 65 : 8 * k > V ? 129 : 2600000 / V + 1 > 65 ? 2600000 / V + 1 : 65;
-    const int64_t share = (16 * k + V - 1) / V;
-    if (share > 4) {
-        if (V <= 32768) return chunks <= 16 ? 9 : 60;
-        if (V <= 65536 && chunks <= 16) return 48;
-        return V > 131072 && share >= 8 && share < 16 ? 60 : never;
-    }
-    if (chunks <= 16) {
-        if (share <= 1) return V <= 131072 ? 9 : 16;
-        if (share <= 2) return V <= (chunks <= 8 ? 131072 : 100000) ? 9 : chunks <= 8 ? 16 : 20;      // (up to 64 elements: 16 rows x 151936 44.7 / 40.7)
-        return V <= 65536 ? (share <= 3 ? 9 : 16) : share <= 3 ? 32 : 48;
-    }
-    if (share <= 1) return V <= 65536 ? 9 : 24;
-    if (share <= 2) return V <= 32768 ? 9 : V <= 65536 ? 20 : 32;
-    if (share <= 3) return V <= 32768 ? 9 : 40;
-    return V <= 32768 ? 24 : V <= 131072 ? 60 : 48;
+    return 65;
 }
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
-    return panel_codes_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab;
+    return panel_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab;
 }
 
 // (more than 64 KB of LDS: an opt-in)

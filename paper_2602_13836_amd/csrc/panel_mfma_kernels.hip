@@ -38,6 +38,8 @@ namespace sv {
 namespace {
 
 constexpr int kXcds = 8;
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+typedef short i16x2_t __attribute__((ext_vector_type(2)));
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int kCusPerXcd = 32;           // (of the part, not asked of the device: a workspace's size follows from the runs)
 constexpr int kRunUnit = 64;             // a run is a multiple of this many rows of M
@@ -46,7 +48,8 @@ constexpr int kRunUnit = 64;             // a run is a multiple of this many row
 // EPI_LOGP       the product minus a value per hidden row (the normaliser of Section 3.4) is stored
 // EPI_LSE        only (maximum, sum of exponentials relative to it) per hidden row and run of rows of M
 // EPI_CODES      a byte per score is stored, a monotone function of the score per hidden row (the selection of a batch)
-enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_CODES = 3 };
+// EPI_KEYS       two bytes per score: half precision, as a number that orders like it
+enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_CODES = 3, EPI_KEYS = 4 };
 
 template <int KS, int GM>
 constexpr int step_items() { return KS > 16 ? 32 : GM > 2 ? 64 : 128; }      // rows of M per step
@@ -82,14 +85,14 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     constexpr int kTI = step_items<KS, GM>();
     constexpr int SUB = kTI / (32 * GI);                 // 32-row sub-tiles per wavefront and step
     constexpr int TM = 32 * WM * GM;
-    constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_CODES;               // M is the MFMA's first operand
+    constexpr bool kSwap = EPI == EPI_LSE || EPI == EPI_CODES || EPI == EPI_KEYS;             // M is the MFMA's first operand
     constexpr int kRowB = KS * 32;                       // a staged row
     constexpr int kUnits = 2 * KS;                       // ... in units of 16 bytes
     constexpr int kPieces = kTI * kRowB / 1024;          // 1 KB pieces of a step
     constexpr int LR = kPieces / kWaves;                 // ... that a wavefront brings
     constexpr int NS = stages<KS, GM>();
     // stores of a wavefront per step whose rows are all there
-    constexpr int kStores = EPI == EPI_LSE ? 0 : EPI == EPI_CODES ? SUB * WM : SUB * WM * 16;
+    constexpr int kStores = EPI == EPI_LSE ? 0 : EPI == EPI_CODES ? SUB * WM : EPI == EPI_KEYS ? SUB * WM * 2 : SUB * WM * 16;
     static_assert(kPieces % kWaves == 0 && kTI % (32 * GI) == 0 && kUnits <= 64 && kUnits >= 16, "whole pieces, whole sub-tiles");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [NS][kTI][kRowB], then the epilogue's
     const int tid = threadIdx.x;
@@ -195,6 +198,27 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             map_scale[m] = t.x;
             map_bias[m] = t.y;
             code_row[m] = reinterpret_cast<char*>(a.codes) + (int64_t)row * a.code_stride + 16 * half;
+        }
+    }
+    if constexpr (EPI == EPI_KEYS) {
+#pragma unroll
+        for (int m = 0; m < WM; ++m) {
+            const int row = min(row_w + 32 * m + (lane & 31), a.rows - 1);
+            code_row[m] = reinterpret_cast<char*>(a.codes) + (int64_t)row * a.code_stride + 32 * half;
+            u16x2_t top = {0, 0};                        // the largest of the row's elements, without their signs
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) {
+                const u32x4 x = __builtin_bit_cast(u32x4, fx[m][kk]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t w = x[i] & 0x7FFF7FFFu;
+                    top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2_t, w));
+                }
+            }
+            uint32_t e = umax32(top[0], top[1]) >> 7;
+            e = umax32(e, (uint32_t)__shfl_xor((int)e, 32));
+            e = e < 1u ? 1u : e > 253u ? 253u : e;
+            map_scale[m] = __uint_as_float((254u - e) << 23);
         }
     }
     if constexpr (EPI == EPI_LOGP) {
@@ -328,6 +352,39 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                 if (row_w + 32 * m + (lane & 31) < a.rows && j0 < i1) *reinterpret_cast<u32x4*>(code_row[m] + j0) = w;
             }
         }
+        if constexpr (EPI == EPI_KEYS) {
+            // Elements as above.  Word 8 h + 4 g + c of a 32-item unit (64 bytes) holds the keys of items 8 g + 4 h + c, in its
+            // lower half, and 16 more: the lane's eight words lie next to each other.
+#pragma unroll
+            for (int m = 0; m < WM; ++m) {
+                u32x4 w[2];
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        // (plus zero: -0 and 0 are the same score)
+                        const auto p = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf(acc[m][4 * g + c], map_scale[m], 0.0f),
+                                                                  __builtin_fmaf(acc[m][4 * g + 8 + c], map_scale[m], 0.0f));
+                        const i16x2_t x = __builtin_bit_cast(i16x2_t, p);
+                        const i16x2_t sign = x >> (short)15;
+                        w[g][c] = __builtin_bit_cast(uint32_t, x) ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u);
+                    }
+                if (j0 + 32 > i1) {                      // items past the run: below everything
+                    int left = i1 - j0 - 4 * half;
+                    asm volatile("" : "+v"(left));
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            w[g][c] &= (8 * g + c < left ? 0xFFFFu : 0u) | (8 * g + 16 + c < left ? 0xFFFF0000u : 0u);
+                }
+                if (row_w + 32 * m + (lane & 31) < a.rows && j0 < i1) {
+                    u32x4* o = reinterpret_cast<u32x4*>(code_row[m] + 2 * (int64_t)j0);
+                    o[0] = w[0];
+                    o[1] = w[1];
+                }
+            }
+        }
     };
 
     // A step ends when the next one's pieces are there: all but the requests and stores that came after them (the counter
@@ -395,7 +452,7 @@ __global__ __launch_bounds__(256) void lse_fold_kernel(const float2* partial, in
 //   3  d' <= 512, panels of 256 (32 rows per wavefront)
 //   4, 5, 6  d' <= 128: as 0, 1, 2 with half the steps (512 rows x 128256, d' = 128: selection 110 -> 101 us, log-
 //     probabilities 105 -> 95)
-//   7, 8  panels of 64, codes only: d' <= 256, <= 128; steps of twice as many rows of M
+//   7, 8  panels of 64, keys only: d' <= 256, <= 128; steps of twice as many rows of M
 struct Shape { int panel, gi; };
 constexpr int kNShapes = 9;
 constexpr Shape kShapes[kNShapes] = {{512, 1}, {256, 2}, {128, 2}, {256, 1}, {512, 1}, {256, 2}, {128, 2}, {64, 4}, {64, 4}};
@@ -419,7 +476,7 @@ hipError_t with_shape(int shape, F&& f) {
             default: break;
         }
     }
-    if constexpr (EPI == EPI_CODES) {
+    if constexpr (EPI == EPI_KEYS) {
         switch (shape) {
             case 7: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
             case 8: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
@@ -487,7 +544,7 @@ hipError_t launch_epi(const PanelArgs& a0, hipStream_t stream) {
 template <int EPI>
 hipError_t opt_in_epi() {
     for (int shape = 0; shape < kNShapes; ++shape) {
-        if (EPI != EPI_CODES && shape >= 7) continue;
+        if (EPI != EPI_KEYS && shape >= 7) continue;
         if (EPI == EPI_SAMPLE && shape != 3 && shape != kSampleShape && shape != kSampleShapeShort) continue;
         const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
             constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
@@ -507,10 +564,11 @@ hipError_t configure_panel_lds() {
     if (e == hipSuccess) e = opt_in_epi<EPI_LOGP>();
     if (e == hipSuccess) e = opt_in_epi<EPI_LSE>();
     if (e == hipSuccess) e = opt_in_epi<EPI_CODES>();
+    if (e == hipSuccess) e = opt_in_epi<EPI_KEYS>();
     return e;
 }
 
-bool panel_codes_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
+bool panel_keys_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows >= 1 && chunks >= 1 && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
 }
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
@@ -518,6 +576,7 @@ bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
 }
 
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_SAMPLE>(a, stream); }
+hipError_t launch_panel_keys(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_KEYS>(a, stream); }
 hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_CODES>(a, stream); }
 
 // (maximum, sum) pairs of a hidden row

@@ -20,6 +20,7 @@ hipError_t configure_skinny_mfma_lds();
 hipError_t configure_tile_mfma_lds();
 hipError_t configure_select_lds();
 hipError_t configure_code_select_lds();
+hipError_t configure_key_select_lds();
 hipError_t configure_union_lds();
 hipError_t configure_panel_lds();
 
@@ -159,14 +160,18 @@ struct PanelArgs {
     // launch_panel_codes: code(r, j) = the product times code_map[2 r] plus code_map[2 r + 1], to the nearest of 0 .. 255, at
     // byte (j % 8) * 4 + j / 8 % 4 of the 32-byte unit j / 32 of row r (code_stride bytes apart); units past the last item's
     // are not written, items past the last get code 0
+    // launch_panel_keys: a number of 16 bits that orders like the product among those of its row; those of items j % 32 = 8 g + 4 h + c and
+    // 16 more (g < 2, h < 2, c < 4) in the halves of word 8 h + 4 g + c of the 64-byte unit j / 32; items past the last get 0, others more
+    // (unless they are no number)
     const float* code_map;
     uint8_t* codes;
     int64_t code_stride;
 };
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
-bool panel_codes_supported(int dt, int chunks, int64_t rows, int64_t n_items);     // launch_panel_sample, launch_panel_codes
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
 hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream);
+bool panel_keys_supported(int dt, int chunks, int64_t rows, int64_t n_items);      // launch_panel_keys (the others: panel_supported)
+hipError_t launch_panel_keys(const PanelArgs& a, hipStream_t stream);
 // out[r, :] = log softmax of the products of row r; ws: panel_log_softmax_ws_floats floats
 size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V);
 hipError_t launch_panel_log_softmax(const PanelArgs& a, float* ws, hipStream_t stream);
@@ -254,7 +259,7 @@ size_t bracket_scratch_words(int64_t rows, int64_t V);
 void bracket_sample(int64_t rows, int64_t V, uint32_t* scratch, int32_t** ids, int64_t* m, float** samp);
 hipError_t launch_bracket_select(const BracketArgs& a, hipStream_t stream);
 
-// The same for selectors of up to 512 elements, a byte per score in memory (code_select_kernels.hip)
+// The same for selectors of up to 512 elements, a byte (code_select_kernels.hip) or two (key_select_kernels.hip) per score in memory
 struct CodeSelectArgs {
     const char* hp;        // [rows x d'] bf16
     const char* Wv;        // [V x d'] bf16, dense rows
@@ -263,11 +268,14 @@ struct CodeSelectArgs {
     int rows;
     int64_t k;
     int32_t* idx_out;      // [rows x k]
-    char* scratch;         // code_select_scratch_bytes(rows, V) bytes, 16-byte aligned; nothing needs clearing
+    char* scratch;         // code_select_scratch_bytes or key_select_scratch_bytes (rows, V) bytes, 16-byte aligned; nothing needs clearing
 };
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k);
 size_t code_select_scratch_bytes(int64_t rows, int64_t V);
 hipError_t launch_code_select(const CodeSelectArgs& a, hipStream_t stream);
+bool key_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k);
+size_t key_select_scratch_bytes(int64_t rows, int64_t V);
+hipError_t launch_key_select(const CodeSelectArgs& a, hipStream_t stream);
 
 // measurement aid: a plain coalesced read of `bytes` (a multiple of 16) from buf; sink: stream_read_blocks() words
 inline int stream_read_blocks(int cus) { return cus * 64; }

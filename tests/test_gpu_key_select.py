@@ -1,0 +1,87 @@
+"""The selection by two-byte keys at the edges of its parts (32768 tokens), where its sample misleads, where its lists or ties leave
+their room and where half precision says nothing.  Scores are exact (whole numbers times a power of two), so the ids must be those of a
+full sort, ties to the smaller id."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+sv = pytest.importorskip("paper_2602_13836_amd")
+
+pytestmark = pytest.mark.gpu
+
+PART = 32768
+
+
+def _bf16(a):
+    return torch.from_numpy(a.astype(np.float32)).cuda().to(torch.bfloat16)
+
+
+def _inputs(rows, V, d_prime, seed, d=64):
+    rng = np.random.default_rng(seed)
+    return (rng.integers(-1, 2, (rows, d)), rng.integers(-1, 2, (d_prime, d)), rng.integers(-2, 3, (V, d_prime)) / 64.0)
+
+
+def _check(h, Wd, Wv, k, scale=1.0):
+    h, Wd, Wv = _bf16(h), _bf16(Wd), _bf16(Wv * scale)
+    need = sv.workspace_bytes(sv.SV_OP_SELECT, h.shape[0], h.shape[1], Wv.shape[0], k, Wd.shape[0], 0, sv.SV_BF16, 0)
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    idx, _ = sv.select(h, Wd, Wv, k, ws=ws[:need])
+    s = (h.double() @ Wd.double().t()) @ Wv.double().t()
+    want = torch.sort(s, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values
+    assert torch.equal(idx.long(), want)
+    assert bool((ws[need:] == 0x5A).all())             # nothing past the workspace is written
+
+
+# a part, one token more or less, several parts a workgroup, the largest vocabulary; panels of 64, 128 and 256 hidden rows
+@pytest.mark.parametrize("rows,V,d_prime,k", [(9, 16384, 256, 4), (16, PART, 128, 900), (33, PART + 1, 40, PART + 1), (64, 2 * PART - 1, 8, 20000),
+                                              (24, 2 * PART + 33, 256, 30000), (64, 8 * PART, 128, 6000), (50, 12 * PART, 64, 90000),
+                                              (64, 11 * PART + 7, 256, 1), (2, 16385, 128, 2000), (8, 131072, 16, 16384),
+                                              (65, PART, 256, 5000), (128, 65536, 200, 8000), (200, 20000, 64, 3000), (70, 100001, 512, 2500),
+                                              (130, 70000, 264, 69999)])
+def test_edges(rows, V, d_prime, k):
+    _check(*_inputs(rows, V, d_prime, rows + k), k)
+
+
+@pytest.mark.parametrize("V,k", [(40000, 200), (40000, 9000), (150001, 4000)])
+@pytest.mark.parametrize("best", [True, False])
+def test_samples_that_mislead(V, k, best):
+    """The tokens of the sampled units are the best of all, or the worst: the k-th score lies outside of the bracket."""
+    rows, d_prime = 20, 32
+    h, Wd, Wv = _inputs(rows, V, d_prime, k)
+    h[:, 1] = 1
+    Wd[:, 1] = 0
+    Wd[0, :] = 0
+    Wd[0, 1] = 1                                       # h'[0] = 1 in every row
+    Wv[:, 0] = 0
+    units = (V + 31) // 32
+    sampled = (np.arange(256) * units // 256)[:, None] * 32 + np.arange(32)
+    Wv[sampled[sampled < V], 0] = 64.0 if best else -64.0
+    _check(h, Wd, Wv, k)
+
+
+@pytest.mark.parametrize("k", [1000, 12000, 40000])
+def test_parts_of_one_score(k):
+    """Nearly all tokens of the second part share a score that decides in some of the rows: more than a part's list holds, and than LDS
+    holds ties."""
+    rows, V, d_prime = 15, 3 * PART, 32
+    h, Wd, Wv = _inputs(rows, V, d_prime, k)
+    h[:, 1:] = 0
+    h[:, 0] = np.arange(rows) % 5 - 2                  # h' = (h[0], 0, ...), zeros among them
+    Wd[:, 0] = 0
+    Wd[0, 0] = 1
+    Wv[PART: 2 * PART - 100, 0] = 1 / 64.0
+    _check(h, Wd, Wv, k)
+
+
+# scores that half precision rounds to zero or to its largest number: ties by the tens of thousands
+@pytest.mark.parametrize("scale", [2.0 ** -100, 2.0 ** -20, 2.0 ** 18, 2.0 ** 100])
+@pytest.mark.parametrize("k", [77, 30000])
+def test_scores_out_of_the_range_of_halves(scale, k):
+    _check(*_inputs(12, 70000, 64, k), k, scale)
+
+
+def test_hidden_rows_of_any_size():
+    """Every row's keys are relative to the row's largest element."""
+    rows, V, d_prime, k = 40, 50000, 128, 1500
+    h, Wd, Wv = _inputs(rows, V, d_prime, 7)
+    _check(h * 2.0 ** np.linspace(-60, 60, rows).astype(int)[:, None], Wd, Wv, k)
