@@ -472,15 +472,10 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         return sv::launch_bracket_select(ba, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
     }
 
-    // Step 1a: h' = W_down h, stored in the storage dtype (bf16: rounded to nearest even); the same launch
-    // clears the selection's counters and histogram
+    // Short rows of scores are selected from by one launch; longer ones go through a histogram, whose counters are cleared on the way
+    const bool one_launch = sv::row_select_supported(V);
     size_t zero_words = 0;
-    sv::select_zero_range(rows, V, &zero_words);
-    if (launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, radix, zero_words, s) != SV_OK)
-        return SV_ERR_HIP;
-
-    // Step 1b: s = W_vocab h'.  One hidden row: a bandwidth-bound stream over W_vocab fused with the
-    // first histogram pass of the selection.  Several rows: a real matrix product -> matrix cores.
+    if (!one_launch) sv::select_zero_range(rows, V, &zero_words);
     sv::GemvArgs g2{};
     g2.x = hp;
     g2.x_row_bytes = d_prime * es;
@@ -491,10 +486,16 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
     g2.rows = (int)rows;
     g2.out_f32 = scores;
     g2.out_row_stride = V;
-    if (sv::skinny_mfma_supported(dt, g2)) {
-        if (sv::launch_skinny_mfma(g2, s) != hipSuccess) return SV_ERR_HIP;
-        if (sv::launch_hist(scores, V, k, (int)rows, radix, s) != hipSuccess) return SV_ERR_HIP;
-    } else if (sv::scores_supported(vchunks)) {
+    const bool matrix = sv::skinny_mfma_supported(dt, g2), stream_scores = !matrix && sv::scores_supported(vchunks);
+    const bool down = stream_scores && one_launch && sv::scores_down_supported((int)(d * es / 16), d_prime);
+
+    // Step 1a: h' = W_down h, stored in the storage dtype (bf16: rounded to nearest even), unless the next launch makes it
+    if (!down && launch_down_projection(h, rows, d, ldh, W_down, d_prime, dt, hp, zero_words ? radix : nullptr, zero_words, s) != SV_OK)
+        return SV_ERR_HIP;
+
+    // Step 1b: s = W_vocab h'.  One hidden row: a bandwidth-bound stream over W_vocab fused with the
+    // first histogram pass of the selection.  Several rows: a real matrix product -> matrix cores.
+    if (stream_scores) {
         sv::ScoresArgs sa{};
         sa.hp = hp;
         sa.Wv = static_cast<const char*>(W_vocab);
@@ -503,10 +504,16 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
         sa.chunks = vchunks;
         sa.rows = (int)rows;
         sa.s = scores;
-        if (sv::launch_scores_hist(dt, sa, radix, s) != hipSuccess) return SV_ERR_HIP;
+        if (down) {
+            sa.h = static_cast<const char*>(h);
+            sa.h_row_bytes = ldh * es;
+            sa.h_chunks = (int)(d * es / 16);
+            sa.Wd = static_cast<const char*>(W_down);
+        }
+        if (sv::launch_scores_hist(dt, sa, one_launch ? nullptr : radix, s) != hipSuccess) return SV_ERR_HIP;
     } else {
-        if (sv::launch_gemv(dt, g2, s) != hipSuccess) return SV_ERR_HIP;
-        if (sv::launch_hist(scores, V, k, (int)rows, radix, s) != hipSuccess) return SV_ERR_HIP;
+        if ((matrix ? sv::launch_skinny_mfma(g2, s) : sv::launch_gemv(dt, g2, s)) != hipSuccess) return SV_ERR_HIP;
+        if (!one_launch && sv::launch_hist(scores, V, k, (int)rows, radix, s) != hipSuccess) return SV_ERR_HIP;
     }
 
     // Step 2: exact top-k, ascending ids
@@ -519,8 +526,7 @@ static int select_impl(const void* h, int64_t rows, int64_t d, int64_t ldh, cons
     ra.scores_out = scores_out;
     ra.tau = tau;
     ra.scratch = radix;
-    if (sv::launch_topk_of_scores(ra, s) != hipSuccess) return SV_ERR_HIP;
-    return SV_OK;
+    return (one_launch ? sv::launch_row_select(ra, s) : sv::launch_topk_of_scores(ra, s)) == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
 int specvocab_select(const void* h, int64_t rows, int64_t d, int64_t ldh, const void* W_down,

@@ -40,7 +40,7 @@ constexpr int kSampleLog2 = 12;
 constexpr int64_t kSample = (int64_t)1 << kSampleLog2;   // sampled tokens per call
 constexpr int kHeld = (int)(kSample / kMapThreads);
 constexpr int64_t kMaxVocab = 262144 + 131072;           // a bit per token in LDS (48 KB)
-constexpr int64_t kMinVocab = 16384;
+constexpr int64_t kMinVocab = 16384;          // (shorter rows: row_select_kernel)
 
 struct CodeLayout {
     int64_t stride;          // bytes between rows of codes: an odd multiple of 256, off the memory channels' period
@@ -579,7 +579,7 @@ inline int64_t min_rows(int chunks, int64_t V, int64_t k) {
     return 65;
 }
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
-    return panel_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab;
+    return panel_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab && !row_select_preferred(chunks, rows, V);
 }
 
 // (more than 64 KB of LDS: an opt-in)

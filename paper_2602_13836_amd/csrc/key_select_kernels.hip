@@ -40,7 +40,7 @@ constexpr int kBinBits = 11, kBins = 1 << kBinBits;      // two per thread
 constexpr int kBinShift = 16 - kBinBits;                 // keys per bin of the sample's histogram, as a power of two
 constexpr int64_t kSample = 8 * kThreads;
 constexpr int64_t kMaxVocab = 262144 + 131072;           // a bit per token in LDS (48 KB)
-constexpr int64_t kMinVocab = 16384;
+constexpr int64_t kMinVocab = 16384;          // (shorter rows: row_select_kernel)
 static_assert(kBins == 2 * kThreads && kMaxVocab < ((int64_t)1 << (32 - kBinBits)), "an entry is an id and a bin");
 
 constexpr int kPart = 32 * kThreads;                     // tokens of a part: a unit per thread
@@ -531,7 +531,8 @@ __global__ __launch_bounds__(kThreads) void key_emit_kernel(const unsigned char*
 //               37.9 / 36.2, 160 x 50000 41.0 / 42.9.  d' = 128: 128 x 17000 29.3 / 27.8, 100 x 50000 31.3 / 31.3, 128 x 50000 31.9 / 32.5.
 //               d' = 512: 128 x 128256 74.8 / 70.0, 256 x 50000 54.4 / 53.5, 160 x 128256 77.0 / 78.5, 65 x 262144 111.5 / 114.7.
 bool key_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
-    if (!panel_keys_supported(dt, chunks, rows, V) || V < kMinVocab || V > kMaxVocab) return false;
+    if (!panel_keys_supported(dt, chunks, rows, V) || V < kMinVocab || V > kMaxVocab || row_select_preferred(chunks, rows, V)) return false;
+    if (rows > 256) return false;                             // (more than one round of workgroups: 300 rows x 16384, d' = 512 49.5 / 49.5, 1024 82 / 89)
     if (rows > 64) return rows * V <= (chunks > 32 ? 16800000 : chunks > 16 && rows <= 128 ? 8400000 : 4400000);
     if (rows > 8) return chunks <= 16 || rows >= 24 || 4 * k <= V;
     return rows > 1 && chunks <= 16 && 8 * k <= V;

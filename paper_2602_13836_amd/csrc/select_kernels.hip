@@ -8,6 +8,7 @@
 // address serialise at ~50 ns each), so there is no "last block" hand-over and no contended counter.
 // Up to eight hidden rows the kernels are shaped for latency (few launches, redundant work per block);
 // beyond that for throughput (small workgroups, 16-byte loads, the row-wide results computed once).
+// Rows of up to 16384 scores are selected from in one launch (row_select_kernel below) without a histogram pass; what follows is for longer ones.
 //   scores_hist   streams W_vocab once.  A selector row is short (d' = d/16 .. d/8: a few hundred
 //                 bytes), so a wavefront is split into groups of G lanes, one row per group, and
 //                 every load instruction still covers 1 KiB of consecutive memory.  Each score is
@@ -166,14 +167,18 @@ __device__ __forceinline__ void locate_bin_w(const uint32_t (&c)[PER], uint32_t 
 // would run past the last row is moved back to end at it (rows it re-computes are not stored or counted
 // again); vocabularies shorter than one window clamp row by row instead.
 // (leading plain arguments are preloaded into scalar registers with the wavefront; the struct is not)
-template <int DT, int G, int UNR, bool FULL>
+// HIST: the scores are counted as well (scratch zeroed by an earlier launch).  DOWN: every workgroup makes h' itself, from a
+// W_down of up to kDownUnits 16-byte units (a launch of 4 us for 1 us of work where d' is a handful of rows of a small model).
+constexpr int kDownUnits = 4096, kDownRowUnits = 128;
+template <int DT, int G, int UNR, bool FULL, bool HIST, bool DOWN>
 __global__ __launch_bounds__(kScoreThreads) void scores_hist_kernel(const char* __restrict__ hp_base,
                                                                     const char* __restrict__ wv_base, const int64_t V,
                                                                     float* __restrict__ s_base, const int chunks,
                                                                     const ScoresArgs a, uint32_t* scratch) {
     constexpr int RPW = 64 / G;                       // vocabulary rows per wave-wide load
     constexpr int64_t kWindow = (int64_t)RPW * UNR;   // rows per wavefront and iteration
-    __shared__ uint32_t lh[kHistBins];
+    __shared__ uint32_t lh[HIST ? kHistBins : 1];
+    __shared__ __attribute__((aligned(16))) uint32_t s_hp[DOWN ? 4 * G : 1];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -183,9 +188,42 @@ __global__ __launch_bounds__(kScoreThreads) void scores_hist_kernel(const char* 
     const int C = FULL ? G : chunks;
     const int64_t row_bytes = (int64_t)C * 16;
 
-    for (int b = tid; b < kHistBins; b += kScoreThreads) lh[b] = 0u;
+    if constexpr (HIST)
+        for (int b = tid; b < kHistBins; b += kScoreThreads) lh[b] = 0u;
     const int gc = (FULL || g < C) ? g : C - 1;
-    const u32x4 xraw = reinterpret_cast<const u32x4*>(hp_base + r * row_bytes)[gc];
+    if constexpr (DOWN) {
+        // a wavefront per element of h', two at a time; a lane has one or two units of the hidden row
+        const u32x4* const h = reinterpret_cast<const u32x4*>(a.h + r * a.h_row_bytes);
+        const int units = a.h_chunks, dp = C * (DT == DT_BF16 ? 8 : 4);
+        u32x4 x[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) x[u] = lane + 64 * u < units ? h[lane + 64 * u] : zero16();
+        for (int i0 = wave; i0 < dp; i0 += 2 * kScoreWaves) {
+            u32x4 w[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int row = min(i0 + i * kScoreWaves, dp - 1), c = min(lane + 64 * u, units - 1);
+                    w[i][u] = reinterpret_cast<const u32x4*>(a.Wd)[row * units + c];
+                }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int row = i0 + i * kScoreWaves;
+                float acc = 0.0f;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (lane + 64 * u < units) acc = dot16<DT>(w[i][u], x[u], acc);
+                acc = wave_sum(acc);
+                if (lane == 0 && row < dp) {
+                    if constexpr (DT == DT_BF16) reinterpret_cast<uint16_t*>(s_hp)[row] = f32_to_bf16_rne(acc);
+                    else s_hp[row] = __float_as_uint(acc);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const u32x4 xraw = DOWN ? reinterpret_cast<const u32x4*>(s_hp)[gc] : reinterpret_cast<const u32x4*>(hp_base + r * row_bytes)[gc];
     const u32x4 xreg = (FULL || g < C) ? xraw : zero16();   // units past the end of a row meet zeros
     float* s = s_base + r * V;
     __syncthreads();
@@ -224,13 +262,14 @@ __global__ __launch_bounds__(kScoreThreads) void scores_hist_kernel(const char* 
                 const int64_t v = b0 + (int64_t)u * RPW + sub;
                 if (g == 0 && v >= base && v < V) {
                     s[v] = acc;
-                    atomicAdd(&lh[f32_to_ord(acc) >> kKeyLowBits], 1u);
+                    if constexpr (HIST) atomicAdd(&lh[f32_to_ord(acc) >> kKeyLowBits], 1u);
                 }
             }
         }
     };
     if (V < kWindow) run(std::true_type{});
     else run(std::false_type{});
+    if constexpr (!HIST) return;
     __syncthreads();
 
     const SelLayout L = sel_layout(V, a.rows);
@@ -286,29 +325,202 @@ __global__ __launch_bounds__(kScoreThreads) void hist_kernel(const float* s_all,
     }
 }
 
-template <int DT, int G>
+template <int DT, int G, int UNR, bool HIST, bool DOWN>
 hipError_t launch_scores_g(const ScoresArgs& a, uint32_t* scratch, int cus, hipStream_t stream) {
-    constexpr int UNR = 8;
     const int64_t per_block = (int64_t)(64 / G) * UNR * kScoreWaves;
     int64_t bx = (a.V + per_block - 1) / per_block;
     int64_t cap = ((int64_t)cus + a.rows - 1) / a.rows;         // one long-lived block per CU
     if (cap < 1) cap = 1;
     if (bx > cap) bx = cap;
     if (a.chunks == G)
-        hipLaunchKernelGGL((scores_hist_kernel<DT, G, UNR, true>), dim3((unsigned)bx, (unsigned)a.rows),
+        hipLaunchKernelGGL((scores_hist_kernel<DT, G, UNR, true, HIST, DOWN>), dim3((unsigned)bx, (unsigned)a.rows),
                            dim3(kScoreThreads), 0, stream, a.hp, a.Wv, a.V, a.s, a.chunks, a, scratch);
     else
-        hipLaunchKernelGGL((scores_hist_kernel<DT, G, UNR, false>), dim3((unsigned)bx, (unsigned)a.rows),
+        hipLaunchKernelGGL((scores_hist_kernel<DT, G, UNR, false, HIST, DOWN>), dim3((unsigned)bx, (unsigned)a.rows),
                            dim3(kScoreThreads), 0, stream, a.hp, a.Wv, a.V, a.s, a.chunks, a, scratch);
     return hipGetLastError();
 }
 
+// Without a histogram a workgroup costs next to nothing but its rows: few rows of W_vocab go to four times as many
+// workgroups (8192 rows of 128 bytes: 8 CUs would pull 128 KB each).
+template <int DT, int G>
+hipError_t launch_scores_n(const ScoresArgs& a, uint32_t* scratch, int cus, hipStream_t stream) {
+    if (scratch) return launch_scores_g<DT, G, 8, true, false>(a, scratch, cus, stream);
+    const bool few = a.V * a.rows <= (int64_t)(64 / G) * 8 * kScoreWaves * cus / 4;
+    if (a.Wd) return few ? launch_scores_g<DT, G, 2, false, true>(a, scratch, cus, stream) : launch_scores_g<DT, G, 8, false, true>(a, scratch, cus, stream);
+    return few ? launch_scores_g<DT, G, 2, false, false>(a, scratch, cus, stream) : launch_scores_g<DT, G, 8, false, false>(a, scratch, cus, stream);
+}
+
 template <int DT>
 hipError_t launch_scores_dt(const ScoresArgs& a, uint32_t* scratch, int cus, hipStream_t stream) {
-    if (a.chunks <= 8) return launch_scores_g<DT, 8>(a, scratch, cus, stream);
-    if (a.chunks <= 16) return launch_scores_g<DT, 16>(a, scratch, cus, stream);
-    if (a.chunks <= 32) return launch_scores_g<DT, 32>(a, scratch, cus, stream);
-    return launch_scores_g<DT, 64>(a, scratch, cus, stream);
+    if (a.chunks <= 8) return launch_scores_n<DT, 8>(a, scratch, cus, stream);
+    if (a.chunks <= 16) return launch_scores_n<DT, 16>(a, scratch, cus, stream);
+    if (a.chunks <= 32) return launch_scores_n<DT, 32>(a, scratch, cus, stream);
+    return launch_scores_n<DT, 64>(a, scratch, cus, stream);
+}
+
+// ------------------------------------------------------------------------------------------
+// short rows: everything after the scores in one launch
+// ------------------------------------------------------------------------------------------
+// One workgroup per row, whose scores it keeps in registers (4096 J of them, thread t the four from 4 (1024 j + t) on):
+// a histogram of the keys' top 13 bits names the bin of the k-th largest, and the few scores of that bin are ranked by counting
+// against each other (two more digits where they are many).  Then every score knows whether it is selected -- above the k-th, or
+// equal to it and among the first of those -- and where it goes.
+// What bounds it is the chain of barriers and the LDS atomics of the histogram, not the row: 8192 scores 6.8 us where collect and
+// emit take 5.7 and 5.3 (and up to three launches more from two rows on); the selection of one float32 row of d = 256 over 8192 tokens 19.8
+// -> 11.9 us with h' made by the scores' launch, 40 bf16 rows, d' = 256, over 10000 tokens 30.8 -> 21.3, 256 rows over 16384 35 -> 33.
+// Not used: eight groups of 4096 (30000 scores: 21.6 us, the registers spill).
+constexpr int kRowFew = 256;
+template <int J>
+constexpr int row_top_bits() { return J > 2 ? 14 : 13; }
+template <int J>
+__global__ __launch_bounds__(kSelThreads) void row_select_kernel(const float* s_all, int64_t V, int64_t k, int32_t* idx_out,
+                                                                 float* scores_out, float tau) {
+    constexpr int kTop = row_top_bits<J>(), kBins = 1 << kTop, kPer = kBins / kSelThreads, kLow = 32 - kTop;
+    static_assert(J * kSelWaves <= 256 && 4096 * J <= 65535, "four counts per lane; two counts in a word");
+    typedef float row_f32x4 __attribute__((ext_vector_type(4), aligned(4)));      // (rows need not start on 16 bytes)
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_hist[];         // [kBins]
+    __shared__ __attribute__((aligned(16))) uint32_t s_few[kRowFew];
+    __shared__ uint32_t s_w[kSelWaves], s_out[4], s_ans[2], s_n;
+    __shared__ uint32_t s_cnt[256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = (int)V;
+    const float* s = s_all + (int64_t)blockIdx.x * V;
+    float val[J][4];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int v0 = 4 * (j * kSelThreads + tid);
+        if (v0 + 3 < n) {
+            const row_f32x4 q = *reinterpret_cast<const row_f32x4*>(s + v0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[j][e] = q[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[j][e] = v0 + e < n ? s[v0 + e] : 0.0f;
+        }
+    }
+    auto there = [&](int j, int e) { return 4 * (j * kSelThreads + tid) + e < n; };
+#pragma unroll
+    for (int i = 0; i < kPer / 4; ++i) reinterpret_cast<u32x4*>(s_hist)[i * kSelThreads + tid] = zero16();
+    if (tid < kRowFew) s_few[tid] = 0u;                   // (0: below every number)
+    if (tid == 0) s_n = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (there(j, e)) atomicAdd(&s_hist[f32_to_ord(val[j][e]) >> kLow], 1u);
+    __syncthreads();
+    uint32_t c[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) c[i] = s_hist[tid * kPer + i];
+    locate_bin<kPer>(c, (uint32_t)k, s_w, s_out);
+    const uint32_t B = s_out[0], left = s_out[2];
+    uint32_t remain = (uint32_t)k - s_out[1];             // of the bin's scores: 1 <= remain <= left
+    const bool whole = remain == left;                    // all of them
+    uint32_t T = B << kLow;                               // whole: the smallest key selected; else the k-th score's, ...
+    uint32_t take = 0u;                                   // ... and how many of those equal to it
+    if (!whole) {                                         // uniform
+        if (left <= (uint32_t)kRowFew) {
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t key = f32_to_ord(val[j][e]);
+                    if (there(j, e) && (key >> kLow) == B) s_few[atomicAdd(&s_n, 1u)] = key;
+                }
+            __syncthreads();
+            // four lanes per score
+            const uint32_t mine = (uint32_t)(tid >> 2) < left ? s_few[tid >> 2] : 0u;
+            uint32_t above = 0u;                          // larger ones, and equal ones above them
+            if ((uint32_t)(tid >> 2) < left)
+                for (uint32_t i = tid & 3u; 4u * i < left; i += 4u) {
+                    const u32x4 o = reinterpret_cast<const u32x4*>(s_few)[i];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) above += (o[e] > mine ? 1u : 0u) + (o[e] == mine ? 0x10000u : 0u);
+                }
+            above += dpp_u32<DPP_QUAD_1032>(above);
+            above += dpp_u32<DPP_QUAD_2301>(above);
+            const uint32_t larger = above & 0xffffu, equal = above >> 16;
+            if ((uint32_t)(tid >> 2) < left && larger < remain && remain <= larger + equal) {     // (all equal ones write the same)
+                s_ans[0] = mine;
+                s_ans[1] = remain - larger;
+            }
+            __syncthreads();
+            T = s_ans[0];
+            take = s_ans[1];
+        } else {
+            uint32_t prefix = B;
+            int decided = kTop;
+#pragma unroll 1
+            for (int pass = 0; pass < 2; ++pass) {
+                const int w = pass == 0 ? 10 : kLow - 10, shift = 32 - decided - w;
+                __syncthreads();                          // s_out and the histogram have been read
+                s_hist[tid] = 0u;
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t key = f32_to_ord(val[j][e]);
+                        if (there(j, e) && (key >> (32 - decided)) == prefix) atomicAdd(&s_hist[(key >> shift) & ((1u << w) - 1u)], 1u);
+                    }
+                __syncthreads();
+                const uint32_t one[1] = {s_hist[tid]};
+                locate_bin<1>(one, remain, s_w, s_out);
+                prefix = (prefix << w) | s_out[0];
+                remain -= s_out[1];
+                decided += w;
+            }
+            T = prefix;
+            take = remain;
+        }
+    }
+    // counts of (j, wavefront): scores above the k-th, and equal ones in the upper half
+    uint32_t pack[J], incl[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        pack[j] = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t key = f32_to_ord(val[j][e]);
+            if (there(j, e)) pack[j] += key > T || (whole && key == T) ? 1u : key == T ? 0x10000u : 0u;
+        }
+        incl[j] = wave_prefix_inclusive_u32(pack[j]);
+        if (lane == 63) s_cnt[j * kSelWaves + wave] = incl[j];
+    }
+    __syncthreads();
+    int32_t* out = idx_out + (int64_t)blockIdx.x * k;
+    float* sc = scores_out ? scores_out + (int64_t)blockIdx.x * k : nullptr;
+    uint32_t base = 0u;                                   // of the 64 counts before
+#pragma unroll
+    for (int j0 = 0; j0 < J; j0 += 4) {
+        const uint32_t mine = lane < (J - j0) * kSelWaves ? s_cnt[j0 * kSelWaves + lane] : 0u;
+        const uint32_t upto = wave_prefix_inclusive_u32(mine);
+#pragma unroll
+        for (int jj = 0; jj < 4 && j0 + jj < J; ++jj) {
+            const int j = j0 + jj;
+            const uint32_t from = base + (uint32_t)__shfl((int)(upto - mine), jj * kSelWaves + wave) + incl[j] - pack[j];
+            uint32_t larger = from & 0xffffu, equal = from >> 16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (!there(j, e)) continue;
+                const uint32_t key = f32_to_ord(val[j][e]);
+                const bool is_larger = key > T || (whole && key == T), is_equal = !is_larger && key == T;
+                if (is_larger || (is_equal && equal < take)) {
+                    const uint32_t at = larger + (equal < take ? equal : take);
+                    if (at < (uint32_t)k) {               // always
+                        const bool keep = val[j][e] >= tau;                    // below the threshold: a padding slot
+                        out[at] = keep ? 4 * (j * kSelThreads + tid) + e : -1;
+                        if (sc) sc[at] = keep ? val[j][e] : -INFINITY;
+                    }
+                }
+                larger += is_larger ? 1u : 0u;
+                equal += is_equal ? 1u : 0u;
+            }
+        }
+        base += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1306,10 +1518,14 @@ __global__ __launch_bounds__(kSelThreads) void redo_bracket_kernel(int64_t V, in
 }  // namespace
 
 bool scores_supported(int chunks) { return chunks >= 1 && chunks <= 64; }
+bool scores_down_supported(int h_chunks, int64_t d_prime) { return h_chunks <= kDownRowUnits && (int64_t)h_chunks * d_prime <= kDownUnits; }
 
 // more than 64 KiB of dynamic LDS needs an explicit opt-in per kernel and device (called once per device,
 // outside any stream capture, by the library's device set-up)
 hipError_t configure_select_lds() {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&row_select_kernel<4>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)(sizeof(uint32_t) << row_top_bits<4>()));
+    if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&resolve_emit_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)kResolveMaxLdsBytes);
 }
@@ -1421,6 +1637,24 @@ hipError_t launch_hist(const float* s, int64_t V, int64_t k, int rows, uint32_t*
     hipLaunchKernelGGL(hist_kernel, dim3((unsigned)bx, (unsigned)rows), dim3(kScoreThreads), 0, stream, s, V,
                        scratch, rows);
     return hipGetLastError();
+}
+
+constexpr int64_t kRowSelectVocab = 4 * 4096;
+bool row_select_supported(int64_t V) { return V <= kRowSelectVocab; }
+// (at exactly 16384 tokens two-byte and one-byte scores are there too, and shorter for many rows: 128 rows, d' = 128, k = 2000 26.2 us against 29.1,
+// 512 rows, d' = 256 41.8 against 49.9; selectors of more than 256 elements 39 against 32 up to 256 rows)
+bool row_select_preferred(int chunks, int64_t rows, int64_t V) { return V <= kRowSelectVocab && (rows <= 64 || (chunks > 32 && rows <= 256)); }
+
+hipError_t launch_row_select(const RadixArgs& a, hipStream_t stream) {
+    auto run = [&](auto kernel, auto groups) {
+        constexpr size_t lds = sizeof(uint32_t) << row_top_bits<decltype(groups)::value>();
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kSelThreads), lds, stream, a.s, a.V, a.k, a.idx_out, a.scores_out, a.tau);
+        return hipGetLastError();
+    };
+    if (a.V <= 4096) return run(&row_select_kernel<1>, std::integral_constant<int, 1>{});
+    if (a.V <= 2 * 4096) return run(&row_select_kernel<2>, std::integral_constant<int, 2>{});
+    if (a.V <= kRowSelectVocab) return run(&row_select_kernel<4>, std::integral_constant<int, 4>{});
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_topk_of_scores(const RadixArgs& a, hipStream_t stream) {

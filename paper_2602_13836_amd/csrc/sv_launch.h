@@ -216,8 +216,15 @@ struct ScoresArgs {
     int chunks;            // d_prime * esize / 16
     int rows;
     float* s;              // [rows x V]
+    // Wd != nullptr: h' is not there yet but made on the way (hp is not looked at), where scores_down_supported
+    const char* h;         // rows of h_chunks 16-byte units, h_row_bytes apart
+    int64_t h_row_bytes;
+    int h_chunks;
+    const char* Wd;        // [d_prime x h_chunks units]
 };
 bool scores_supported(int chunks);
+bool scores_down_supported(int h_chunks, int64_t d_prime);
+// scratch == nullptr: no histogram
 hipError_t launch_scores_hist(int dt, const ScoresArgs& a, uint32_t* scratch, hipStream_t stream);
 // the histogram pass alone, for scores produced by another kernel
 hipError_t launch_hist(const float* s, int64_t V, int64_t k, int rows, uint32_t* scratch, hipStream_t stream);
@@ -238,6 +245,10 @@ int64_t select_max_vocab();
 size_t select_scratch_words(int64_t rows, int64_t V);
 void select_zero_range(int64_t rows, int64_t V, size_t* words);
 hipError_t launch_topk_of_scores(const RadixArgs& a, hipStream_t stream);
+// the same for short rows in one launch, without a histogram pass and without scratch
+bool row_select_supported(int64_t V);
+bool row_select_preferred(int chunks, int64_t rows, int64_t V);         // ... to the selections by one or two bytes per score
+hipError_t launch_row_select(const RadixArgs& a, hipStream_t stream);
 
 // Exact top-k of every row for a batch of hidden rows WITHOUT the score matrix in memory (bf16): the scores of a
 // sample of the vocabulary bracket each row's k-th score, the full product is classified against the bracket
