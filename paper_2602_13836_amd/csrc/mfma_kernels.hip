@@ -568,32 +568,23 @@ hipError_t launch_skinny_mfma(const GemvArgs& a, hipStream_t stream) {
     const bool whole = whole_pieces(a);
     const int64_t split_items = (int64_t)di.cus * (a.rows <= 4 ? 64 : a.rows <= 16 ? (whole ? 64 : 48) : a.rows <= 32 ? 32 : 20);
     // A count on the device (the union of the rows' sets; a.n_items is its upper bound, often several times the
-    // count when the sets overlap) that may fall on either side of such a crossover: launches with complementary
-    // gates, of which those that do not serve the list leave at once (about 2 us each).  The crossovers that matter:
-    // the one above, and from 33 rows the one between small tiles with several workgroups per CU and 64 x 256 tiles
-    // at half a round of those, 128 x CUs items (the tiled kernel picks its tile by n_items, here the upper end of
-    // the gate: 64 x 128; unions of 16 K to 32 K rows gain ~10 us over 64 x 256 tiles, up to 16 K they pay 3 to 8 us
-    // against 64 x 64 tiles -- a gate of their own would cost every other list 2 us).  60 rows whose 512 / 1024-item sets
+    // count when the sets overlap) that may fall on either side of that crossover: two launches with complementary
+    // gates, of which the one that does not serve the list leaves at once (about 2 us).  60 rows whose 512 / 1024-item sets
     // unite to 553 / 1401 rows: whole step 31 / 33 us, against 64 / 66 with the kernel picked by the bound.
+    // (From 33 rows on the tiled kernel's width follows the count, and there is no second crossover.)
     if (a.n_items_dev != nullptr && a.gate_hi == 0 && a.n_items > split_items && a.chunks >= 8 * (kKC / 8)) {
-        int64_t cuts[2];
-        int ncuts = 0;
         // (a union of duplicate-free sets of k items has at least k: where that is close to the crossover there is little
         // for the split form to win, and every list pays for its launch -- 60 sets of 4096 that unite to 50 K rows: 107
         // against 109.5 us)
         const int64_t worth = (int64_t)di.cus * (a.rows <= 4 ? 48 : a.rows <= 8 ? 36 : a.rows <= 32 ? 24 : 15);
-        if (a.n_items_min < worth) cuts[ncuts++] = split_items;
-        if (a.rows > 32 && a.n_items > (int64_t)di.cus * 128) cuts[ncuts++] = (int64_t)di.cus * 128;
-        if (ncuts > 0) {
+        if (a.n_items_min < worth) {
             GemvArgs part = a;
-            for (int c = 0; c < ncuts; ++c) {
-                part.n_items = cuts[c];               // sizes the grid: enough for every list this launch serves
-                part.gate_hi = cuts[c];
-                e = launch_skinny_mfma(part, stream);
-                if (e != hipSuccess) return e;
-                part.gate_lo = cuts[c];
-            }
+            part.n_items = split_items;               // sizes the grid: enough for every list this launch serves
+            part.gate_hi = split_items;
+            e = launch_skinny_mfma(part, stream);
+            if (e != hipSuccess) return e;
             part.n_items = a.n_items;
+            part.gate_lo = split_items;
             part.gate_hi = INT64_MAX;
             return launch_skinny_mfma(part, stream);
         }

@@ -102,8 +102,7 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
     const int RT = (a.rows + TM - 1) / TM;
     // Width of an item tile: TN, or (a.balance_cus workgroups at a time, product stored) the smallest multiple of
     // 32 with which the list still takes as many rounds of workgroups as with TN -- 50223 items on 256 CUs: 225
-    // tiles of 224 items instead of 197 of 256.  The wavefronts past that width multiply copies of the tile's last
-    // row and store nothing.
+    // tiles of 224 items instead of 197 of 256.  The wavefronts past that width have nothing to do.
     int64_t tn = TN;
     if (EPI == EPI_STORE && a.balance_cus > 0 && n_items > 0) {
         const int64_t per_round = (int64_t)TN * a.balance_cus;
@@ -233,43 +232,67 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
             src_b[i].set(base_b, a.idx ? (int64_t)a.idx[item] : item - tile0, a.m_row_bytes, (uint32_t)unit * 16u);
         }
         const i32x4_t buf_a = buffer_of(base_a), buf_b = buffer_of(base_b);
-        auto request = [&](int ks) {
-            const int s = eff(ks);
-            const bool cut = s == nk - 1 && lane_past;
-            const uint32_t at = lds0 + (uint32_t)((ks & 3) * kStageB + swave * 1024);
-#pragma unroll
-            for (int i = 0; i < LB; i += 2)
-                bring<kPass * 128>(src_b[i], src_b[i + 1], cut, cut, buf_b, (int64_t)s * 128, at + (uint32_t)(i * kPass * 128));
-#pragma unroll
-            for (int i = 0; i < LA; ++i)
-                bring(src_a[i], cut, buf_a, (int64_t)s * 128, at + (uint32_t)(TN * 128 + i * kPass * 128));
-        };
         const int swz = ((lane >> 5) ^ ((lane >> 1) & 7)) * 16;
         const int fa0 = (TN + wr * 32 * WM + (lane & 31)) * 128 + swz, fb0 = (wc * 32 * WN + (lane & 31)) * 128 + swz;
-        request(0);
-        request(1);
-        request(2);
-        for (int ks = 0; ks < nk; ++ks) {
-            // (lgkmcnt: this wavefront's own reads of slice ks - 1 are back too -- nothing else keeps the MFMAs that consume
-            // them, and with them their wait, in front of this barrier)
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (LA + LB)) : "memory");
-            request(ks + 3);
-            const unsigned char* base = smem + (size_t)(ks & 3) * kStageB;
+        // What lies past the tile's width is neither requested nor multiplied (a wavefront requests the first MINE of its LB
+        // pieces of M; `none`: its own items are all past the width), so a round takes what its width needs and lists of any
+        // length can have this shape: unions of 12497 / 22481 / 32210 / 50313 rows, 33 to 64 hidden rows, a whole step
+        // 37.3 / 53.5 / 65.8 / 105.3 -> 32.8 / 50.8 / 64.4 / 102.3 us, 3 to 5 of them a launch of the smaller tiles that short
+        // unions were given before and that all others had to skip.
+        constexpr bool kNarrow = GM == 1 && GN == 8 && WN == 1;      // (the shape whose width follows the list)
+        const bool none = kNarrow && wc * 32 >= (int)tn;
+        auto walk = [&](auto mine) {
+            constexpr int MINE = decltype(mine)::value;
+            auto request = [&](int ks) {
+                const int s = eff(ks);
+                const bool cut = s == nk - 1 && lane_past;
+                const uint32_t at = lds0 + (uint32_t)((ks & 3) * kStageB + swave * 1024);
 #pragma unroll
-            for (int kk = 0; kk < kTK / 16; ++kk) {
-                bf16x8_t af[WM], bf[WN];
+                for (int i = 0; i + 1 < MINE; i += 2)
+                    bring<kPass * 128>(src_b[i], src_b[i + 1], cut, cut, buf_b, (int64_t)s * 128, at + (uint32_t)(i * kPass * 128));
+                if constexpr (MINE % 2 == 1)
+                    bring(src_b[MINE - 1], cut, buf_b, (int64_t)s * 128, at + (uint32_t)((MINE - 1) * kPass * 128));
 #pragma unroll
-                for (int m = 0; m < WM; ++m)
-                    af[m] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + (fa0 ^ (kk * 32)) + 32 * m * 128));
+                for (int i = 0; i < LA; ++i)
+                    bring(src_a[i], cut, buf_a, (int64_t)s * 128, at + (uint32_t)(TN * 128 + i * kPass * 128));
+            };
+            request(0);
+            request(1);
+            request(2);
+            for (int ks = 0; ks < nk; ++ks) {
+                // (lgkmcnt: this wavefront's own reads of slice ks - 1 are back too -- nothing else keeps the MFMAs that consume
+                // them, and with them their wait, in front of this barrier)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (LA + MINE)) : "memory");
+                request(ks + 3);
+                if (none) continue;                          // uniform; the same barriers
+                const unsigned char* base = smem + (size_t)(ks & 3) * kStageB;
 #pragma unroll
-                for (int n = 0; n < WN; ++n)
-                    bf[n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + (fb0 ^ (kk * 32)) + 32 * n * 128));
+                for (int kk = 0; kk < kTK / 16; ++kk) {
+                    bf16x8_t af[WM], bf[WN];
 #pragma unroll
-                for (int m = 0; m < WM; ++m)
+                    for (int m = 0; m < WM; ++m)
+                        af[m] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + (fa0 ^ (kk * 32)) + 32 * m * 128));
 #pragma unroll
                     for (int n = 0; n < WN; ++n)
-                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m], bf[n], acc[m][n], 0, 0, 0);
+                        bf[n] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(base + (fb0 ^ (kk * 32)) + 32 * n * 128));
+#pragma unroll
+                    for (int m = 0; m < WM; ++m)
+#pragma unroll
+                        for (int n = 0; n < WN; ++n)
+                            acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m], bf[n], acc[m][n], 0, 0, 0);
+                }
             }
+        };
+        if constexpr (kNarrow) {
+            static_assert(LB == 4, "0 to 4 requests per wavefront");
+            const int live = ((int)tn - 8 * swave + kPass - 1) / kPass;          // 0 .. 4
+            if (live >= 4) walk(std::integral_constant<int, 4>{});
+            else if (live == 3) walk(std::integral_constant<int, 3>{});
+            else if (live == 2) walk(std::integral_constant<int, 2>{});
+            else if (live == 1) walk(std::integral_constant<int, 1>{});
+            else walk(std::integral_constant<int, 0>{});
+        } else {
+            walk(std::integral_constant<int, LB>{});
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (slices past the end: requested, never read)
     } else if constexpr (PIPE == LOOP_TURNS) {

@@ -120,6 +120,22 @@ def test_list_into_a_matrix_past_four_gigabytes(rows, d, k):
     assert torch.equal(sv.subset_logits(h, U, idx).double(), ref)
 
 
+# unions of so many tokens that a tile of 256 is as wide as its share of the chip makes it: one 32 of it, an odd number, seven of
+# eight, all, and a second round, a token less and more each; requests of a wavefront that are partly, or all, past the width
+@pytest.mark.parametrize("rows,d,n", [(rows, d, n + by) for rows, d, n in ((33, 72, 8192), (64, 136, 24576), (40, 1096, 40960), (60, 264, 57344),
+                                                                          (48, 200, 65536)) for by in (-1, 0, 1)] + [(40, 2056, 5200), (64, 2304, 16385)])
+def test_union_of_a_size(rows, d, n):
+    V = 70001
+    gen, h, U, ref = _inputs(rows, d, V, rows + n)
+    step = n // rows
+    k = max(n - (rows - 1) * step, 513)                                              # the last row's reaches the end
+    at = (torch.arange(rows, device="cuda")[:, None] * step + torch.arange(k, device="cuda")) % n
+    tokens = torch.randperm(V, device="cuda", generator=gen)[:n].to(torch.int32)
+    idx = tokens[at].contiguous()
+    assert torch.unique(idx).numel() == n
+    assert torch.equal(sv.subset_logits(h, U, idx).double(), ref.gather(1, idx.long()))
+
+
 def test_lists_of_their_own_into_a_matrix_past_four_gigabytes():
     gen = torch.Generator(device="cuda")
     gen.manual_seed(2)
