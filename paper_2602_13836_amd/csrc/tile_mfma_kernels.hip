@@ -467,40 +467,82 @@ __global__ __launch_bounds__(64 * GM * GN) void tile_mfma_kernel(const GemvArgs 
     const int row0 = rt * TM + wr * 32 * WM + 4 * (lane >> 5);
     if constexpr (EPI == EPI_PICK) {
         // Band by band (the 32 GM rows that the wavefronts hold in the same accumulator group) the product goes
-        // to LDS as a [32 GM x TN] tile; then 8 (4) threads per row walk the entries of the row's index list that
+        // to LDS as a [32 GM x TN] tile; then 8 threads per row walk the entries of the row's index list that
         // fall into this item tile -- places pk.off[r, it] .. pk.off[r, it + 1] of the list (ascending, or a copy
         // grouped by tile: all that matters here is that a tile's entries are contiguous) -- and store the asked
         // entries at the same places of the output.
+        //   The tiles of the likeliest tokens bound it: rows that draw from a skewed distribution want all 256 items of
+        // them, where most tiles have a dozen entries per row.  Walked an entry at a time, 32 loads one after the other in
+        // each of four bands, such a tile took up to 60 us more than the others, all of it past the end of a launch of one
+        // round of workgroups.  So a thread has eight entries on their way and asks for the next ones, the next band's
+        // included, before it stores these.  Lists with Zipf's distribution, a whole step: 200 rows x 600 / 40000 items
+        // of 4 KB 77 -> 53 us, x 5768 / 128256 of 8 KB 319 -> 249, 100 rows x 11540 218 -> 198, 512 rows x 6260 487 -> 472;
+        // evenly drawn ones within 2 % or better.
         constexpr int kBandRows = 32 * GM;
         constexpr int kPerRow = kThreads / kBandRows;
-        static_assert((size_t)kBandRows * TN * 4 <= tile_lds_bytes<GM, GN, WM, WN, PIPE>(), "the band tile reuses the operand buffers");
+        constexpr int kBandW = TN + 8;                     // (eight rows of a wavefront's threads on banks of their own)
+        constexpr int kAhead = 8;                          // entries per thread on their way
+        static_assert((size_t)kBandRows * kBandW * 4 <= tile_lds_bytes<GM, GN, WM, WN, PIPE>(), "the band tile reuses the operand buffers");
         float* s_band = reinterpret_cast<float*>(smem);
         const int br = tid / kPerRow, sub = tid % kPerRow;                // this thread's row of the band
-        const int tile_row0 = (br / 32) * 32 * WM + (br % 32);            // + 32 m: its row of the tile
+        const int tile_row0 = rt * TM + (br / 32) * 32 * WM + (br % 32);  // + 32 m: its row
+        // the slices' bounds of all bands, and a band's first entries while the one before is stored
+        uint32_t first[WM], end[WM];
 #pragma unroll
         for (int m = 0; m < WM; ++m) {
-            const int r = rt * TM + tile_row0 + 32 * m;
-            // the slice bounds are requested before the barrier: their latency overlaps the copy to LDS
-            uint32_t ja = 0u, jb = 0u;
+            const int r = tile_row0 + 32 * m;
+            first[m] = end[m] = 0u;
             if (r < a.rows) {
-                ja = pk.off[(int64_t)r * pk.off_stride + it];
-                jb = pk.off[(int64_t)r * pk.off_stride + it + 1];
-                if (jb > (uint32_t)pk.k) jb = (uint32_t)pk.k;             // (a table built from an unsorted list: stay in bounds)
+                first[m] = pk.off[(int64_t)r * pk.off_stride + it] + sub;
+                end[m] = min(pk.off[(int64_t)r * pk.off_stride + it + 1], (uint32_t)pk.k);   // (a table built from an unsorted list: stay in bounds)
             }
+        }
+        auto ask = [&](int m, uint32_t j, int32_t (&q)[kAhead]) {
+            const int32_t* list = pk.idx + (int64_t)min(tile_row0 + 32 * m, a.rows - 1) * pk.k;
+            const uint32_t last = end[m] > 0u ? end[m] - 1u : 0u;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const uint32_t ju = j + (uint32_t)(u * kPerRow);
+                if (__builtin_amdgcn_ballot_w64(ju < end[m]) == 0ull) break;      // (most slices have one or two entries per thread)
+                q[u] = list[min(ju, last)];
+            }
+        };
+        int32_t next[kAhead] = {};
+        ask(0, first[0], next);
+#pragma unroll
+        for (int m = 0; m < WM; ++m) {
             __syncthreads();                               // the band tile (or, first, the operand buffers) is free
 #pragma unroll
             for (int n = 0; n < WN; ++n)
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
-                    s_band[(wr * 32 + 8 * (e >> 2) + (e & 3) + 4 * (lane >> 5)) * TN + wc * 32 * WN + 32 * n + (lane & 31)] =
+                    s_band[(wr * 32 + 8 * (e >> 2) + (e & 3) + 4 * (lane >> 5)) * kBandW + wc * 32 * WN + 32 * n + (lane & 31)] =
                         acc[m][n][e];
             __syncthreads();
-            const int32_t* list = pk.idx + (int64_t)r * pk.k;
-            float* o = pk.out + (int64_t)r * pk.k;
-            for (uint32_t j = ja + sub; j < jb; j += kPerRow) {
-                const uint32_t col = (uint32_t)(list[j] - (int32_t)(it * TN));
-                if (col < (uint32_t)TN) o[j] = s_band[br * TN + col];     // always true for a consistent table
+            float* o = pk.out + (int64_t)(tile_row0 + 32 * m) * pk.k;
+            const float* band = s_band + br * kBandW;
+            int32_t now[kAhead];
+            uint32_t j = first[m];
+            auto put = [&]() {
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const uint32_t ju = j + (uint32_t)(u * kPerRow), col = (uint32_t)(now[u] - (int32_t)(it * TN));
+                    if (ju < end[m] && col < (uint32_t)TN) o[ju] = band[col];    // (the latter always for a consistent table)
+                }
+                j += (uint32_t)(kAhead * kPerRow);
+            };
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) now[u] = next[u];
+            if (j + (uint32_t)(kAhead * kPerRow) < end[m]) {     // a long slice: the next entries are asked for before these are stored
+                do {
+                    ask(m, j + (uint32_t)(kAhead * kPerRow), next);
+                    put();
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) now[u] = next[u];
+                } while (j + (uint32_t)(kAhead * kPerRow) < end[m]);
             }
+            if (m + 1 < WM) ask(m + 1, first[m + 1], next);
+            if (j < end[m]) put();
         }
         return;
     }

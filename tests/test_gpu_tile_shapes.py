@@ -69,6 +69,19 @@ def test_list_per_row(rows, d, V, k, ascending):
     assert torch.equal(got.double(), ref.gather(1, idx.long()))
 
 
+# lists that crowd into a few item tiles: slices around eight and sixteen entries for each of a row's eight threads, whole tiles
+# (of 256 items), none in the next, on tiles of 128 and of 256 hidden rows
+@pytest.mark.parametrize("rows,d,V", [(70, 72, 1100), (128, 520, 1100), (200, 136, 1100), (513, 200, 1100)])
+@pytest.mark.parametrize("ascending", [True, False])
+def test_list_per_row_in_crowded_tiles(rows, d, V, ascending):
+    gen, h, U, ref = _inputs(rows, d, V, rows + V)
+    for at, n in ((0, 63), (256, 64), (512, 65), (256, 127), (0, 129), (768, 191), (0, 256), (200, 800), (844, 256)):
+        idx = at + torch.rand((rows, n), device="cuda", generator=gen).argsort(dim=1).to(torch.int32)
+        idx = idx.sort(dim=1).values if ascending else idx
+        got = sv.subset_logits(h, U, idx.contiguous(), sorted_lists=ascending)
+        assert torch.equal(got.double(), ref.gather(1, idx.long())), (at, n)
+
+
 # several float32 rows over one set of rows of M, large enough that M is read once for all of them: rows of M of one to sixteen
 # KB with ragged ends, more hidden rows than LDS holds at a time, more than a wavefront has lanes, items that do not divide;
 # few items, which make smaller groups of hidden rows (of eight, of a last group of one, of uneven numbers)
