@@ -82,6 +82,29 @@ def test_list_per_row_in_crowded_tiles(rows, d, V, ascending):
         assert torch.equal(got.double(), ref.gather(1, idx.long())), (at, n)
 
 
+# large products on either side of the lines between the union of the lists and all of the matrix; with room for the latter alone
+# (a table of slices) a call takes that form, and with less it is refused
+@pytest.mark.parametrize("rows,d,V,k", [(129, 4096, 80000, 1801), (129, 4096, 80000, 1900), (260, 2048, 76000, 1160), (260, 2048, 76000, 1180)])
+def test_list_per_row_of_a_large_product(rows, d, V, k):
+    gen, h, U, ref = _inputs(rows, d, V, k)
+    race = torch.empty((rows, V), device="cuda").exponential_(1.0, generator=gen) * torch.arange(1, V + 1, device="cuda") ** 1.1
+    idx = race.topk(k, dim=1, largest=False).indices.to(torch.int32)
+    want = ref.gather(1, idx.long())
+    assert torch.equal(sv.subset_logits(h, U, idx).double(), want)
+    idx, order = idx.sort(dim=1)
+    want = want.gather(1, order)
+    table = (rows * (-(-V // 256) + 1) + 3) // 4 * 16
+    room, out = torch.empty(table, dtype=torch.uint8, device="cuda"), torch.empty((rows, k), dtype=torch.float32, device="cuda")
+
+    def within(nbytes):
+        return sv.load_library().specvocab_subset_logits(h.data_ptr(), rows, d, d, U.data_ptr(), V, d, sv.SV_BF16, idx.data_ptr(), k,
+                                                         sv.SV_IDX_PER_ROW | sv.SV_IDX_SORTED, out.data_ptr(), room.data_ptr(), nbytes, None)
+    torch.cuda.synchronize()
+    assert within(table - 16) == 5 and within(table) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out.double(), want)
+
+
 # several float32 rows over one set of rows of M, large enough that M is read once for all of them: rows of M of one to sixteen
 # KB with ragged ends, more hidden rows than LDS holds at a time, more than a wavefront has lanes, items that do not divide;
 # few items, which make smaller groups of hidden rows (of eight, of a last group of one, of uneven numbers)
