@@ -301,11 +301,12 @@ bool pick_path_served(int dt, const GemvArgs& a, int64_t V, bool sorted) {
 //   512 rows  457 / 235   456 / 346   460 / 390   460 / 468      (all equally likely: 462 / 455   462 / 496   453 / 510)
 //   300 rows  396 / 207   397 / 289   397 / 359   400 / 412      (406 / 394   405 / 429   401 / 433)
 //   200 rows  248 / 145   250 / 225   250 / 245   253 / 265      (246 / 250   245 / 276)
-// The line lies where real lists, which overlap, still gain a third or more (300 and 512 rows) or a quarter: evenly drawn ones, at their
-// worst 20 % slower there (160 rows x 2 V / 151936 of 5 KB 192 / 236; Zipf's law 193 / 151), are what no selection yields.  Beyond it what
-// one distribution gains the other loses, and the form stays that does not depend on the overlap.  Up to 128 rows the product is bound by the pass over U and the union's tiles, made for any length, lose
-// more where it is nearly all of U (100 rows x 3 V 194 / 198, all equally likely 190 / 237); small products have nothing to save
-// (40000 tokens of 4 KB, 300 rows x 3 V 72 / 76; 512 rows x 3.9 V 106 / 74).
+// The line lies where real lists, which overlap, still gain a third or more (300 and 512 rows) or a quarter.  Evenly drawn ones, which no
+// selection yields, lose 4 to 23 % there (at their worst, 160 rows x 2 V / 151936 of 5 KB, 192 / 236; Zipf's law 193 / 151).  Beyond it
+// what one distribution gains the other loses, and the form stays that does not depend on the overlap.  Up to 128 rows the product
+// is bound by the pass over U, and the union's tiles, made for any length, lose more where it is nearly all of U (100 rows x 3 V
+// 194 / 198, evenly drawn 190 / 237); small products have nothing to save (40000 tokens of 4 KB, 300 rows x 3 V 72 / 76; 512 rows x
+// 3.9 V 106 / 74).
 bool pick_path_wanted(int dt, const GemvArgs& a, int64_t V, bool sorted) {
     if (!pick_path_served(dt, a, V, sorted)) return false;
     const bool large = a.rows > 128 && (double)a.rows * (double)V * (double)a.chunks * 8.0 >= 4e10 &&
