@@ -814,8 +814,9 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
     //     against 43.6 on 32 x 64 tiles of the plain loop, 65536 96 against 98); in between those (49152: 78 against 73), and
     //     for short reductions, the plain loop's;
     //   33 to 64 rows: 64 x 256 (eight wavefronts, one workgroup per CU) when the list fills its last round of 256 x CUs
-    //     items, or more than half of it (128256 items 188 us against 192 on the tiles below, 49152 75 against 82) -- and
-    //     for a count on the device, which a tree step has --, of a width that then fills whole rounds; otherwise 64 x 64
+    //     items, or more than half of it (128256 items 188 us against 192 on the tiles below, 49152 75 against 82), or few of
+    //     one beyond the first -- and for a count on the device, which a tree step has --, of a width that then fills whole
+    //     rounds; otherwise 64 x 64
     //     (four wavefronts, two workgroups per CU) up to 64 x CUs items and 64 x 128 (eight wavefronts of 32 x 32) beyond:
     //     64 rows of 4096 elements x 9000 / 16384 items from HBM 25.6 / 28.7 us against 33.0 / 36.9 on 64 x 128 tiles, of
     //     4104 elements 36.4 / 41.0 against 51.3 / 55.3; 60 rows x 24576 / 32768 / 98304 items 42 / 50 / 149 on those.
@@ -831,7 +832,12 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
         const int64_t round_items = (int64_t)256 * di.cus, last = a.n_items % round_items;
         // (with a count on the device a.n_items is its upper bound: at most half a round, and the list is short for sure)
         const bool unknown = a.n_items_dev != nullptr && 2 * a.n_items > round_items;
-        if (unknown || last == 0 || 2 * last > round_items) {
+        // (beyond a round, up to three eighths of the last one too: narrower tiles in all of them, where a second or third round of
+        // a few whole ones takes as long as the others.  66000 / 81920 / 135000 / 200000 items, 60-odd rows of 8 KB, us: 122 / 131 / 220 /
+        // 316 on the tiles below, 108 / 125 / 208 / 312 here, of 8208 bytes 168 / 177 / 293 / 413 and 144 / 158 / 261 / 383; 98304 151 / 150,
+        // 160000 by 33 rows 229 / 230 and of 7600 bytes 257 / 262.)
+        const bool few = a.n_items > round_items && 8 * last <= 3 * round_items;
+        if (unknown || few || last == 0 || 2 * last > round_items) {
             // (40960 items: 80 against 87 us with a width that fills whole rounds; unions of 30940 and 44831 rows: a tree
             // step in 82 and 104 us against 88 and 109)
             GemvArgs b = a;

@@ -30,6 +30,7 @@ def _inputs(rows, d, V, seed):
     # the ring of four stages (17 to 64 rows): fewer slices than stages, ragged ones, 32 x 64 to 64 x 256 tiles,
     # rows of M on cache lines (multiples of 64 elements) and off them
     (17, 520, 129), (32, 1032, 300), (24, 584, 57345), (33, 8, 127), (40, 72, 129), (60, 136, 1000), (64, 200, 32769), (48, 1096, 65537),
+    (33, 136, 65567), (64, 1096, 90112), (40, 264, 90113), (50, 72, 131073), (64, 72, 155648), (48, 200, 155649),
     (60, 2056, 70000), (34, 264, 40001),
     (17, 576, 129), (32, 1088, 300), (24, 1048, 65), (20, 576, 20001), (32, 584, 20001), (24, 576, 57345), (33, 64, 16384), (64, 1024, 16383), (40, 1088, 257), (40, 1096, 20001), (64, 136, 30000),
     (130, 72, 33000), (128, 328, 70001), (256, 64, 66000), (400, 200, 66049), (520, 1032, 40003), (700, 136, 50000)])
