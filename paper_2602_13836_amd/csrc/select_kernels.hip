@@ -170,11 +170,13 @@ __device__ __forceinline__ void locate_bin_w(const uint32_t (&c)[PER], uint32_t 
 // HIST: the scores are counted as well (scratch zeroed by an earlier launch).  DOWN: every workgroup makes h' itself, from a
 // W_down of up to kDownUnits 16-byte units (a launch of 4 us for 1 us of work where d' is a handful of rows of a small model).
 constexpr int kDownUnits = 4096, kDownRowUnits = 128;
+template <bool DOWN>
+using scores_args = std::conditional_t<DOWN, ScoresArgs, ScoresOfHidden>;
 template <int DT, int G, int UNR, bool FULL, bool HIST, bool DOWN>
 __global__ __launch_bounds__(kScoreThreads) void scores_hist_kernel(const char* __restrict__ hp_base,
                                                                     const char* __restrict__ wv_base, const int64_t V,
                                                                     float* __restrict__ s_base, const int chunks,
-                                                                    const ScoresArgs a, uint32_t* scratch) {
+                                                                    const scores_args<DOWN> a, uint32_t* scratch) {
     constexpr int RPW = 64 / G;                       // vocabulary rows per wave-wide load
     constexpr int64_t kWindow = (int64_t)RPW * UNR;   // rows per wavefront and iteration
     __shared__ uint32_t lh[HIST ? kHistBins : 1];
@@ -332,12 +334,13 @@ hipError_t launch_scores_g(const ScoresArgs& a, uint32_t* scratch, int cus, hipS
     int64_t cap = ((int64_t)cus + a.rows - 1) / a.rows;         // one long-lived block per CU
     if (cap < 1) cap = 1;
     if (bx > cap) bx = cap;
+    const scores_args<DOWN>& used = a;
     if (a.chunks == G)
         hipLaunchKernelGGL((scores_hist_kernel<DT, G, UNR, true, HIST, DOWN>), dim3((unsigned)bx, (unsigned)a.rows),
-                           dim3(kScoreThreads), 0, stream, a.hp, a.Wv, a.V, a.s, a.chunks, a, scratch);
+                           dim3(kScoreThreads), 0, stream, a.hp, a.Wv, a.V, a.s, a.chunks, used, scratch);
     else
         hipLaunchKernelGGL((scores_hist_kernel<DT, G, UNR, false, HIST, DOWN>), dim3((unsigned)bx, (unsigned)a.rows),
-                           dim3(kScoreThreads), 0, stream, a.hp, a.Wv, a.V, a.s, a.chunks, a, scratch);
+                           dim3(kScoreThreads), 0, stream, a.hp, a.Wv, a.V, a.s, a.chunks, used, scratch);
     return hipGetLastError();
 }
 
