@@ -835,8 +835,9 @@ hipError_t launch_tile_mfma(const GemvArgs& a, hipStream_t stream) {
         // (beyond a round, up to three eighths of the last one too: narrower tiles in all of them, where a second or third round of
         // a few whole ones takes as long as the others.  66000 / 81920 / 135000 / 200000 items, 60-odd rows of 8 KB, us: 122 / 131 / 220 /
         // 316 on the tiles below, 108 / 125 / 208 / 312 here, of 8208 bytes 168 / 177 / 293 / 413 and 144 / 158 / 261 / 383; 98304 151 / 150,
-        // 160000 by 33 rows 229 / 230 and of 7600 bytes 257 / 262.)
-        const bool few = a.n_items > round_items && 8 * last <= 3 * round_items;
+        // 160000 by 33 rows 229 / 230 and of 7600 bytes 257 / 262.  Rows of less than 2 KB, where a tile is mostly its start: up to an
+        // eighth, 64 rows of 512 bytes x 66000 / 90000 15.7 / 17.1 on the tiles below, 14.9 / 18.5 here.)
+        const bool few = a.n_items > round_items && 8 * last <= (a.chunks >= 128 ? 3 : 1) * round_items;
         if (unknown || few || last == 0 || 2 * last > round_items) {
             // (40960 items: 80 against 87 us with a width that fills whole rounds; unions of 30940 and 44831 rows: a tree
             // step in 82 and 104 us against 88 and 109)
