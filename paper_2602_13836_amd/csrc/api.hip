@@ -219,12 +219,7 @@ int launch_gather(int dt, const void* h, int64_t rows, int64_t d, int64_t ldh, c
     // checked here, before the first launch
     const bool copy = padded && padded_needs_copy(dt, g0);
     const size_t pb = copy ? pad_ws_bytes(rows, k, idx_mode, dt, g0) : 0;
-    size_t need = pb + product_ws_bytes(dt, g0, rows, V, k, idx_mode);
-    bool pick = sv::pick_path_wanted(dt, g0, V, is_sorted(idx_mode));
-    if (!pick && ws_bytes < need && sv::pick_path_served(dt, g0, V, is_sorted(idx_mode))) {
-        pick = true;                              // (no room for the union's product: the form that needs next to none)
-        need = pb + sv::pick_ws_bytes(rows, V, k, is_sorted(idx_mode));
-    }
+    const size_t need = pb + product_ws_bytes(dt, g0, rows, V, k, idx_mode);
     if (need) {
         if (!ws || ws_bytes < need) return SV_ERR_WORKSPACE;
         if (!aligned16(ws)) return SV_ERR_ALIGN;
@@ -244,7 +239,7 @@ int launch_gather(int dt, const void* h, int64_t rows, int64_t d, int64_t ldh, c
         rest_bytes -= pb;
     }
     const sv::GemvArgs g = gather_args(h, rows, d, ldh, U, V, ldu, dt, use, k, idx_mode, logits_out);
-    if (pick)
+    if (sv::pick_path_wanted(dt, g, V, is_sorted(idx_mode)))
         st = sv::launch_pick_logits(g, V, is_sorted(idx_mode), rest, s) == hipSuccess ? SV_OK : SV_ERR_HIP;
     else
         st = launch_rows_product(dt, g, V, rest_bytes ? rest : nullptr, rest_bytes, s, copy ? nullptr : defer);

@@ -191,8 +191,6 @@ hipError_t launch_pad_mask(const int32_t* idx, int64_t idx_row_stride, int rows,
 // cores, and each (row, j) picks its logit out of that product.
 // Many hidden rows with their own lists that together are likely to cover the vocabulary: the product over all
 // rows of M with the pick epilogue (sorted: the caller declared the lists ascending); ws: pick_ws_bytes
-// (served: it can do this call; wanted: it is expected to be the faster form)
-bool pick_path_served(int dt, const GemvArgs& a, int64_t V, bool sorted);
 bool pick_path_wanted(int dt, const GemvArgs& a, int64_t V, bool sorted);
 size_t pick_ws_bytes(int64_t rows, int64_t V, int64_t k, bool sorted);
 hipError_t launch_pick_logits(const GemvArgs& a, int64_t V, bool sorted, void* ws, hipStream_t stream);

@@ -290,28 +290,21 @@ hipError_t configure_union_lds() {
 // no more than reading the union: the product over all of U whose epilogue stores only the asked entries.  Lists
 // declared ascending need only the table of slices; lists in any order are grouped by tile first, which needs
 // the tile counters of a row in LDS.
+//   The line lies where this form stops losing on any lists.  How much of the vocabulary they cover is not known here: lists of
+// 2 / 3 / 4 V entries cover 0.87 / 0.95 / 0.98 of it where all tokens are equally likely, as the sets of a selector with random
+// weights do (0.85 / 0.93 / 0.97), and 0.42-0.49 / 0.52-0.60 / 0.62-0.65 where they are drawn by Zipf's law.  A whole step, us, by the
+// union / by all of U, 128256 tokens of 8 KB:
+//                  equally likely          random selector         Zipf's law
+//   512 rows  2 V  490 / 453               482 / 448               262 / 458
+//             3 V  489 / 444               478 / 450               325 / 446
+//   200 rows  2 V  253 / 235               250 / 238               153 / 238
+//             3 V  268 / 237               264 / 234               222 / 246
+//   160 rows  2 V  234 / 194 (151936 of 5 KB)                      150 / 191
+// All of U takes the same time whatever the lists are, and next to no workspace (512 rows 1 MB; the union's product 250 MB).
 static int64_t pick_tiles(int64_t V) { return (V + kKeepTileItems - 1) / kKeepTileItems; }
-bool pick_path_served(int dt, const GemvArgs& a, int64_t V, bool sorted) {
+bool pick_path_wanted(int dt, const GemvArgs& a, int64_t V, bool sorted) {
     return dt == DT_BF16 && a.rows > 64 && a.idx != nullptr && a.idx_row_stride != 0 && a.out_bf16 == nullptr &&
            (int64_t)a.rows * a.n_items >= 2 * V && (sorted || pick_tiles(V) <= kBucketMaxTiles);
-}
-// How much of the vocabulary the sets cover is not known here: rows k = 2 / 4 / 6 / 9 V cover 0.41-0.46 / 0.63-0.69 / 0.76-0.82 /
-// 0.87-0.92 of it where tokens are drawn by Zipf's law, less where the rows share some, and 0.87 / 0.98 / 1 / 1 where all are equally
-// likely.  A whole step by all of U / by the union, us, 128256 tokens of 8 KB, Zipf's law:
-//   512 rows  457 / 235   456 / 346   460 / 390   460 / 468      (all equally likely: 462 / 455   462 / 496   453 / 510)
-//   300 rows  396 / 207   397 / 289   397 / 359   400 / 412      (406 / 394   405 / 429   401 / 433)
-//   200 rows  248 / 145   250 / 225   250 / 245   253 / 265      (246 / 250   245 / 276)
-// The line lies where real lists, which overlap, still gain a third or more (300 and 512 rows) or a quarter.  Evenly drawn ones, which no
-// selection yields, lose 4 to 23 % there (at their worst, 160 rows x 2 V / 151936 of 5 KB, 192 / 236; Zipf's law 193 / 151).  Beyond it
-// what one distribution gains the other loses, and the form stays that does not depend on the overlap.  Up to 128 rows the product
-// is bound by the pass over U, and the union's tiles, made for any length, lose more where it is nearly all of U (100 rows x 3 V
-// 194 / 198, evenly drawn 190 / 237); small products have nothing to save (40000 tokens of 4 KB, 300 rows x 3 V 72 / 76; 512 rows x
-// 3.9 V 106 / 74).
-bool pick_path_wanted(int dt, const GemvArgs& a, int64_t V, bool sorted) {
-    if (!pick_path_served(dt, a, V, sorted)) return false;
-    const bool large = a.rows > 128 && (double)a.rows * (double)V * (double)a.chunks * 8.0 >= 4e10 &&
-                       (int64_t)a.rows * V <= (int64_t)1 << 27;              // (512 MB of products)
-    return !large || (int64_t)a.rows * a.n_items >= (a.rows > 256 ? 4 : 3) * V;
 }
 static size_t pick_table_words(int64_t rows, int64_t V) {
     return ((size_t)rows * (size_t)(pick_tiles(V) + 1) + 3) & ~(size_t)3;

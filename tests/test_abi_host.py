@@ -60,6 +60,13 @@ def test_workspace_bytes(lib):
                                 (65, 16385, 16385, 512), (512, 151936, 8192, 256), (4099, 32771, 9, 64)):
         by = {dt: sv.workspace_bytes(sv.SV_OP_SELECT, rows, 4096, V, k, d_prime, 0, dt) for dt in (sv.SV_BF16, sv.SV_F32)}
         assert by[sv.SV_BF16] <= by[sv.SV_F32], (rows, V)
+    # lists with at least twice as many entries as there are tokens need a table of slices (a word per row and 256 tokens) and, in any
+    # order, three words per entry
+    for rows, V, k in ((65, 128256, 4000), (129, 80000, 1500), (512, 128256, 513), (512, 128256, 1002), (300, 262144, 1748)):
+        for op in (sv.SV_OP_SUBSET_LOGITS, sv.SV_OP_DRAFT_STEP):
+            table = (rows * (-(-V // 256) + 1) + 3) // 4 * 16
+            assert sv.workspace_bytes(op, rows, 4096, V, k, kd=10, idx_mode=sv.SV_IDX_SORTED) == table
+            assert sv.workspace_bytes(op, rows, 4096, V, k, kd=10) == table + 12 * rows * k
 
 
 # fake, never dereferenced device addresses: every call below must fail validation on the host

@@ -83,8 +83,8 @@ def test_list_per_row_in_crowded_tiles(rows, d, V, ascending):
         assert torch.equal(got.double(), ref.gather(1, idx.long())), (at, n)
 
 
-# large products on either side of the lines between the union of the lists and all of the matrix; with room for the latter alone
-# (a table of slices) a call takes that form, and with less it is refused
+# large products whose lists have a little more than twice, or three or four times, as many entries as the matrix has rows: all of the
+# matrix is multiplied, which takes room for a table of slices; with less the call is refused
 @pytest.mark.parametrize("rows,d,V,k", [(129, 4096, 80000, 1801), (129, 4096, 80000, 1900), (260, 2048, 76000, 1160), (260, 2048, 76000, 1180)])
 def test_list_per_row_of_a_large_product(rows, d, V, k):
     gen, h, U, ref = _inputs(rows, d, V, k)
@@ -95,6 +95,7 @@ def test_list_per_row_of_a_large_product(rows, d, V, k):
     idx, order = idx.sort(dim=1)
     want = want.gather(1, order)
     table = (rows * (-(-V // 256) + 1) + 3) // 4 * 16
+    assert table == sv.workspace_bytes(sv.SV_OP_SUBSET_LOGITS, rows, d, V, k, idx_mode=sv.SV_IDX_SORTED)
     room, out = torch.empty(table, dtype=torch.uint8, device="cuda"), torch.empty((rows, k), dtype=torch.float32, device="cuda")
 
     def within(nbytes):
