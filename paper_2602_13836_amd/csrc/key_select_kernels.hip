@@ -2,9 +2,9 @@
 // the product as TWO BYTES each, and four launches do it all (the down-projection's among them).
 //   keys      the product on the matrix cores, whose epilogue stores every score's half precision (rounded towards zero, after a
 //             power of two per hidden row that brings its largest element to [1, 2)) as an unsigned number that orders like the
-//             scores (panel_mfma_kernels.hip);
-//   bracket   8192 of a row's keys say where its k-th lies, give or take; one pass turns the keys above that into bits and lists
-//             those in between (one to four per cent) with their place in the bracket, one of 2048;
+//             scores, and some keys of every unit of 32 tokens once more on their own, as a sample (panel_mfma_kernels.hip);
+//   bracket   keys of every 32 tokens say where the row's k-th lies, give or take; one pass turns the keys above that into bits and lists
+//             those in between (2 to 7 per cent, of short rows up to 10) with their place in the bracket, one of 2048;
 //   emit      the histogram of a row's lists names the place C that holds the k-th score.  Everything above C is selected; the
 //             scores of C itself -- a dozen tokens, as a rule of one and the same key -- are computed once more, by the same matrix
 //             instructions in the same order, and ranked by (score, smaller id first); the ids leave in ascending order.
@@ -17,11 +17,17 @@
 // are monotone: a sample that misleads costs its row a walk by one workgroup over all of its keys, poor keys (scores that all lie next to each
 // other) more tokens at C.
 //
-// Measured (60 rows x 128256, d' = 256, k = 4096; kernels under a profiler): h' 6.2 us, keys 17.5, bracket 9.4, emit 9.7; the whole
-// selection 45.5 -> 41.2 us.  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's product and a
-// map in front of the codes (6 and 4 us, each mostly a launch) and read the codes with one workgroup per row (17).  Two thirds of
+// The sample has tokens of every unit.  Neighbours that resemble each other, as the scripts, the numbers or the unused ids of a real vocabulary do, are in it
+// as often as they are in the row, and it says more about the row than one of independent tokens.  (A sample of 256 whole units missed where they
+// share half of their variance, in one call out of two of 60 rows x 128256, k = 16384; a missed row took 120 us more.)  Only scores that
+// depend on the token id modulo 32 mislead it: one such row of 60 x 128256 takes 31 us more, of 64 x 262144 80, all rows 36 to 41 and 86.
+//
+// Measured (60 rows x 128256, d' = 256, k = 4096; kernels under a profiler): h' 6.2 us, keys 17.6, bracket 9.2, emit 9.7; the whole
+// selection 44.4 -> 40.8 us.  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's
+// product and a map in front of the codes (6 and 4 us, each mostly a launch) and read the codes with one workgroup per row (17).  Two thirds of
 // bracket and emit are their start and six round trips to memory.  Not used: this pass by one workgroup per row, 22.7 us
-// (9.5 of them for the keys); a sample of 16 bytes per thread from lines of their own (as many bytes as the part: bracket 11.7).
+// (9.5 of them for the keys); a sample gathered from the keys, 16 bytes per thread from lines of their own (as many bytes as the part: bracket
+// 11.7); sampled words stored one by one as they are made (keys 18.6 to 18.9).
 #include "sv_device.h"
 #include "sv_launch.h"
 
@@ -38,9 +44,9 @@ namespace {
 constexpr int kThreads = 1024, kWaves = kThreads / 64;
 constexpr int kBinBits = 11, kBins = 1 << kBinBits;      // two per thread
 constexpr int kBinShift = 16 - kBinBits;                 // keys per bin of the sample's histogram, as a power of two
-constexpr int64_t kSample = 8 * kThreads;
 constexpr int64_t kMaxVocab = 262144 + 131072;           // a bit per token in LDS (48 KB)
 constexpr int64_t kMinVocab = 16384;          // (shorter rows: row_select_kernel)
+constexpr int kSampleLoads = (int)(kMaxVocab / 32 / (4 * kThreads));     // of 16 bytes per thread
 static_assert(kBins == 2 * kThreads && kMaxVocab < ((int64_t)1 << (32 - kBinBits)), "an entry is an id and a bin");
 
 constexpr int kPart = 32 * kThreads;                     // tokens of a part: a unit per thread
@@ -49,19 +55,23 @@ __host__ __device__ inline int parts_of(int64_t V) { return (int)((V + kPart - 1
 
 struct KeyLayout {
     int64_t stride;          // bytes between rows of keys: an odd multiple of 256, off the memory channels' period
-    // offsets in bytes from the scratch base (multiples of 8; the keys' of 256)
-    size_t keys, parts, bits, list, ties, total;
+    int sample_words;        // words of a unit (two keys each) that are sampled: 4096 keys of a row or more, and room for 24576 is in the registers
+    // offsets in bytes from the scratch base (multiples of 8; the keys' of 256, the sample's of 16)
+    size_t keys, parts, bits, list, ties, sample, total;
 };
 inline KeyLayout key_layout(int64_t V, int64_t rows) {
     KeyLayout L;
-    const int64_t parts = parts_of(V);
-    L.stride = ((V + 31) / 32 * 64 + 255) / 256 * 256 | 256;
+    const int64_t parts = parts_of(V), units = (V + 31) / 32;
+    L.stride = (units * 64 + 255) / 256 * 256 | 256;
+    L.sample_words = V <= 49152 ? 4 : V <= 98304 ? 2 : 1;
     size_t o = 0;
     L.keys = o;   o += (size_t)rows * (size_t)L.stride;
     L.parts = o;  o += (size_t)rows * (size_t)parts * 8;                         // {scores above the bracket, scores in it}
     L.bits = o;   o += (size_t)rows * (size_t)parts * kThreads * 4;
     L.list = o;   o += (size_t)rows * (size_t)parts * kSegment * 4;
-    L.ties = o;   o += (size_t)rows * (size_t)V * 8;
+    o = (o + 15) & ~(size_t)15;
+    L.sample = o;                                        // (has been read when there are ties)
+    L.ties = o;   o += (size_t)rows * (size_t)V * 8;     // (the sample takes 3 of 8 at most)
     L.total = o;
     return L;
 }
@@ -119,8 +129,9 @@ __device__ __forceinline__ uint32_t key_of(const unsigned char* key_row, uint32_
 
 // A workgroup has some parts of a row: the bracket, from a sample of the whole row (all of the row's workgroups make the same one), and what
 // of its parts lies above it (a bit each) and in it (id and bin of the bracket, in a list per part).
-__global__ __launch_bounds__(kThreads) void key_bracket_kernel(const unsigned char* keys, int64_t stride, int64_t V, int parts, int per, uint32_t rank_hi,
-                                                               uint32_t rank_lo, uint2* part_counts, uint32_t* bits, uint32_t* list) {
+__global__ __launch_bounds__(kThreads) void key_bracket_kernel(const unsigned char* keys, int64_t stride, int64_t V, int parts, int per,
+                                                               const u32x4* sample, int sample_units, uint32_t rank_hi, uint32_t rank_lo,
+                                                               uint2* part_counts, uint32_t* bits, uint32_t* list) {
     __shared__ uint32_t s_samp[kBins];
     __shared__ uint32_t s_list[kSegment];
     __shared__ uint32_t s_w[kWaves], s_w2[kWaves];
@@ -129,9 +140,11 @@ __global__ __launch_bounds__(kThreads) void key_bracket_kernel(const unsigned ch
     const int units = (int)((V + 31) / 32);
     const unsigned char* const key_row = keys + (int64_t)blockIdx.y * stride;
     const u32x4* const row = reinterpret_cast<const u32x4*>(key_row);
-    // the sample: 256 whole units (a thread's 16 bytes each from a line of its own cost as much as a part itself)
-    const int su = (int)(((int64_t)(tid >> 2) * units) >> 8);
-    const u32x4 samp = row[4 * su + (tid & 3)];
+    // the sample: keys of every unit, so that tokens which lie together and have something in common are in it as often as they are there
+    u32x4 samp[kSampleLoads];
+#pragma unroll
+    for (int i = 0; i < kSampleLoads; ++i)
+        samp[i] = i * kThreads + tid < sample_units ? sample[(int64_t)blockIdx.y * sample_units + i * kThreads + tid] : zero16();
     int part = (int)blockIdx.x * per;
     const int end = min(part + per, parts);
     u32x4 q[4];
@@ -148,10 +161,13 @@ __global__ __launch_bounds__(kThreads) void key_bracket_kernel(const unsigned ch
     }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        atomicAdd(&s_samp[(samp[w] & 0xFFFFu) >> kBinShift], 1u);
-        atomicAdd(&s_samp[samp[w] >> (16 + kBinShift)], 1u);
-    }
+    for (int i = 0; i < kSampleLoads; ++i)
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (samp[i][w] != 0u) {                           // (zeros: nothing there)
+                atomicAdd(&s_samp[(samp[i][w] & 0xFFFFu) >> kBinShift], 1u);
+                atomicAdd(&s_samp[samp[i][w] >> (16 + kBinShift)], 1u);
+            }
     __syncthreads();
     with_bins(s_samp, s_w, [&](uint32_t bin, uint32_t above, uint32_t c) {
         if (above < rank_hi && rank_hi <= above + c) s_out[0] = (bin << kBinShift) | ((1u << kBinShift) - 1u);
@@ -295,13 +311,15 @@ __global__ __launch_bounds__(kThreads) void key_emit_kernel(const unsigned char*
         // all keys by their upper bits, then those of the bin that holds the k-th by their lower ones
         uint32_t top = 0u, base = 0u;
         for (int level = 0; level < 2; ++level) {
-            for_each_unit([&](int u, const u32x4 (&)[4]) {
+            for_each_unit([&](int u, const u32x4 (&q)[4]) {
                 const uint32_t valid = u < units ? (uint32_t)min((int64_t)32, V - 32 * (int64_t)u) : 0u;
                 uint32_t bin = kBins, run = 0u;               // (equal ones in a row together)
-                for (uint32_t p = 0; p < valid; ++p) {
-                    const uint32_t x = key_of(key_row, 32u * (uint32_t)u + p);
-                    if (level == 1 && (x >> kBinShift) != top) continue;
+#pragma unroll
+                for (int i = 0; i < 32; ++i) {                // word i % 16 = 8 h + 4 g + c, its lower half or its upper
+                    const int w = i & 15;
+                    const uint32_t x = i < 16 ? q[w >> 2][w & 3] & 0xFFFFu : q[w >> 2][w & 3] >> 16;
                     const uint32_t b = level == 0 ? x >> kBinShift : x & ((1u << kBinShift) - 1u);
+                    if ((uint32_t)(8 * ((w >> 2) & 1) + 4 * (w >> 3) + (w & 3) + (i & 16)) >= valid || (level == 1 && (x >> kBinShift) != top)) continue;
                     if (b != bin) {
                         if (run) atomicAdd(&s_hist[bin], run);
                         bin = b;
@@ -558,13 +576,17 @@ hipError_t launch_key_select(const CodeSelectArgs& a, hipStream_t stream) {
     p.rows = a.rows;
     p.codes = reinterpret_cast<uint8_t*>(a.scratch + L.keys);
     p.code_stride = L.stride;
+    p.samples = reinterpret_cast<uint32_t*>(a.scratch + L.sample);
+    p.sample_stride = panel_key_sample_bytes(a.chunks, a.rows, a.V, L.sample_words);
+    p.sample_words = L.sample_words;
+    if (p.sample_stride > kSampleLoads * kThreads * 16 || p.sample_stride > 8 * a.V) return hipErrorInvalidValue;     // (never)
     hipError_t e = launch_panel_keys(p, stream);
     if (e != hipSuccess) return e;
-    // The number of sampled tokens among the row's k best is hypergeometric with mean m k / V, if neighbours in the vocabulary have
-    // nothing to do with each other: its rank range, 6 standard deviations and 8 more on either side
-    const double share = (double)a.k / (double)a.V, mean = (double)kSample * share;
-    const double reach = 6.0 * sqrt((double)kSample * share * (1.0 - share)) + 8.0;
-    const double rank_hi = fmax(floor(mean - reach), 0.0), rank_lo = fmin(ceil(mean + reach), (double)kSample + 1.0);   // (0, kSample + 1: none)
+    // The number of sampled tokens among the row's k best is hypergeometric with mean m k / V if the scores have nothing to do with the tokens'
+    // places, and varies less if neighbours resemble each other: its rank range, 6 standard deviations and 8 more on either side
+    const double m = (double)((a.V + 31) / 32 * 2 * L.sample_words), share = (double)a.k / (double)a.V, mean = m * share;
+    const double reach = 6.0 * sqrt(m * share * (1.0 - share)) + 8.0;
+    const double rank_hi = fmax(floor(mean - reach), 0.0), rank_lo = fmin(ceil(mean + reach), m + 1.0);     // (0, m + 1: none)
     // as many workgroups per row as make one round on the chip
     DeviceInfo di;
     e = device_info(&di);
@@ -576,8 +598,8 @@ hipError_t launch_key_select(const CodeSelectArgs& a, hipStream_t stream) {
     uint2* counts = reinterpret_cast<uint2*>(a.scratch + L.parts);
     uint32_t* bits = reinterpret_cast<uint32_t*>(a.scratch + L.bits);
     uint32_t* list = reinterpret_cast<uint32_t*>(a.scratch + L.list);
-    hipLaunchKernelGGL(key_bracket_kernel, grid, dim3(kThreads), 0, stream, keys, L.stride, a.V, parts, per, (uint32_t)rank_hi, (uint32_t)rank_lo, counts,
-                       bits, list);
+    hipLaunchKernelGGL(key_bracket_kernel, grid, dim3(kThreads), 0, stream, keys, L.stride, a.V, parts, per,
+                       reinterpret_cast<const u32x4*>(p.samples), (int)(p.sample_stride / 16), (uint32_t)rank_hi, (uint32_t)rank_lo, counts, bits, list);
     hipLaunchKernelGGL(key_emit_kernel, grid, dim3(kThreads), sel_bytes(a.V) + kStageBytes, stream, keys, L.stride, a.V, a.k, a.hp, a.Wv,
                        a.chunks, parts, per, counts, bits, list, reinterpret_cast<uint64_t*>(a.scratch + L.ties), a.idx_out);
     return hipGetLastError();

@@ -94,6 +94,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     // stores of a wavefront per step whose rows are all there
     constexpr int kStores = EPI == EPI_LSE ? 0 : EPI == EPI_CODES ? SUB * WM : EPI == EPI_KEYS ? SUB * WM * 2 : SUB * WM * 16;
     static_assert(kPieces % kWaves == 0 && kTI % (32 * GI) == 0 && kUnits <= 64 && kUnits >= 16, "whole pieces, whole sub-tiles");
+    static_assert(EPI != EPI_KEYS || SUB == 1, "a unit per wavefront and step");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [NS][kTI][kRowB], then the epilogue's
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     const int row_w = panel * TM + gm * 32 * WM;         // first hidden row of the wavefront
     bf16x8_t fx[WM][KS];
     {
-        constexpr int kRows = fill_rows<KS, GM>();       // rows per round
+        constexpr int kRows = fill_rows<KS, GM>();  // rows per round
         constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows;
         unsigned char* s_fill = smem + early_steps<KS, GM>() * stage_bytes<KS, GM>() + (size_t)wave * kRows * kRowB;
         auto fetch = [&](int round, u32x4 (&v)[kLoads]) {
@@ -187,9 +188,11 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     unsigned char* s_epi = smem + NS * stage_bytes<KS, GM>();
     [[maybe_unused]] float* s_sub = reinterpret_cast<float*>(s_epi);          // EPI_LOGP: [TM]
     const int half = lane >> 5;
-    // EPI_CODES, of hidden row row_w + 32 m + lane % 32: what makes a score a code, and where the lane's codes go
+    // EPI_CODES and EPI_KEYS, of hidden row row_w + 32 m + lane % 32: what makes a score a code or key, and where the lane's go
     [[maybe_unused]] float map_scale[WM], map_bias[WM];
     [[maybe_unused]] char* code_row[WM];
+    [[maybe_unused]] uint32_t sample_at[WM];             // EPI_KEYS: where the row's sample goes that this wavefront has ...
+    [[maybe_unused]] u32x4 kept[WM];                     // ... 16 bytes at a time
     if constexpr (EPI == EPI_CODES) {
 #pragma unroll
         for (int m = 0; m < WM; ++m) {
@@ -219,6 +222,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             e = umax32(e, (uint32_t)__shfl_xor((int)e, 32));
             e = e < 1u ? 1u : e > 253u ? 253u : e;
             map_scale[m] = __uint_as_float((254u - e) << 23);
+            sample_at[m] = (uint32_t)row * (uint32_t)a.sample_stride + (uint32_t)((run * GI + gi) * a.sample_groups) * 16u;
         }
     }
     if constexpr (EPI == EPI_LOGP) {
@@ -271,6 +275,8 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     // first row of M of the wavefront's sub-tile s of step t
     auto item_of = [&](int t, int s) { return i0 + t * kTI + (gi * SUB + s) * 32; };
 
+    // EPI_KEYS: a step's sample leaves with the last of so many steps (less one)
+    [[maybe_unused]] const int sample_mask = a.sample_words == 4 ? 0 : a.sample_words == 2 ? 1 : 3;
     auto epilogue = [&](int t, int s) {
         const int j0 = item_of(t, s);
         if constexpr (EPI == EPI_SAMPLE || EPI == EPI_LOGP) {
@@ -383,6 +389,20 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                     o[0] = w[0];
                     o[1] = w[1];
                 }
+                // the unit's part of the sample, from the lower half of the lanes; what a unit past the run has is zeros
+                if (a.sample_words == 4) kept[m] = u32x4{w[0][0], w[0][2], w[1][0], w[1][2]};
+                else if (a.sample_words == 2) {
+                    if ((t & 1) == 0) kept[m] = u32x4{w[0][0], w[1][2], 0u, 0u};
+                    else kept[m][2] = w[0][0], kept[m][3] = w[1][2];
+                } else {
+                    if ((t & 3) == 0) kept[m] = u32x4{w[0][0], 0u, 0u, 0u};
+                    else if ((t & 3) == 1) kept[m][1] = w[0][0];
+                    else if ((t & 3) == 2) kept[m][2] = w[0][0];
+                    else kept[m][3] = w[0][0];
+                }
+                if ((t & sample_mask) == sample_mask || t + 1 == nt)
+                    if (half == 0 && row_w + 32 * m + lane < a.rows)
+                        *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(a.samples) + (sample_at[m] + (uint32_t)t / (uint32_t)(sample_mask + 1) * 16u)) = kept[m];
             }
         }
     };
@@ -390,15 +410,19 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     // A step ends when the next one's pieces are there: all but the requests and stores that came after them (the counter
     // holds 63).  Then the barrier: everybody has read this step's stage.
     const bool all_rows = row_w + 32 * WM <= a.rows;
-    auto step_ends = [&](bool requested) {
-        constexpr int kSt = kStores < 63 - LR ? kStores : 63 - LR;
-        if (NS > 2 && requested) {
-            if (all_rows) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LR + kSt) : "memory");
-            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LR) : "memory");
-        } else {
-            if (all_rows) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kSt) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
+    auto step_ends = [&](bool requested, bool more_stores) {
+        auto wait = [&](auto stores) {
+            constexpr int kAll = decltype(stores)::value, kSt = kAll < 63 - LR ? kAll : 63 - LR;
+            if (NS > 2 && requested) {
+                if (all_rows) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LR + kSt) : "memory");
+                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LR) : "memory");
+            } else {
+                if (all_rows) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kSt) : "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+        };
+        if (EPI == EPI_KEYS && more_stores) wait(std::integral_constant<int, kStores + WM>{});
+        else wait(std::integral_constant<int, kStores>{});
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
 #pragma unroll
@@ -414,10 +438,17 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             multiply(stage, s);
             epilogue(t, s);
         }
-        if (t + 1 < nt) step_ends(more);
+        if (t + 1 < nt) step_ends(more, EPI == EPI_KEYS && (t & sample_mask) == sample_mask);
         stage = stage == NS - 1 ? 0 : stage + 1;
     }
 
+    if constexpr (EPI == EPI_KEYS) {                     // the places of the steps that a shorter last run does not have
+        for (int g = (nt + sample_mask) / (sample_mask + 1); g < a.sample_groups; ++g)
+#pragma unroll
+            for (int m = 0; m < WM; ++m)
+                if (half == 0 && row_w + 32 * m + lane < a.rows)
+                    *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(a.samples) + (sample_at[m] + (uint32_t)g * 16u)) = zero16();
+    }
     if constexpr (EPI == EPI_LSE) {
         // lanes l and l + 32 hold the same hidden row; one pair per hidden row, run and wavefront along the rows of M
 #pragma unroll
@@ -467,11 +498,16 @@ inline int shape_of(int chunks, int rows) {
 constexpr int kSampleShape = 2, kSampleShapeShort = 6;     // the ones that launch_panel_sample uses (and 3)
 template <int EPI, typename F>
 hipError_t with_shape(int shape, F&& f) {
-    if constexpr (EPI != EPI_SAMPLE) {
+    if constexpr (EPI != EPI_SAMPLE && EPI != EPI_KEYS) {
         switch (shape) {
             case 0: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-            case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
             case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+            default: break;
+        }
+    }
+    if constexpr (EPI != EPI_SAMPLE) {
+        switch (shape) {
+            case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
             case 5: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
             default: break;
         }
@@ -545,6 +581,7 @@ template <int EPI>
 hipError_t opt_in_epi() {
     for (int shape = 0; shape < kNShapes; ++shape) {
         if (EPI != EPI_KEYS && shape >= 7) continue;
+        if (EPI == EPI_KEYS && (shape == 0 || shape == 4)) continue;
         if (EPI == EPI_SAMPLE && shape != 3 && shape != kSampleShape && shape != kSampleShapeShort) continue;
         const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
             constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
@@ -569,14 +606,30 @@ hipError_t configure_panel_lds() {
 }
 
 bool panel_keys_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
-    return dt == DT_BF16 && rows >= 1 && chunks >= 1 && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
+    return dt == DT_BF16 && rows >= 1 && rows <= 256 && chunks >= 1 && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
 }
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);
 }
 
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_SAMPLE>(a, stream); }
-hipError_t launch_panel_keys(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_KEYS>(a, stream); }
+// (16 bytes of a row's sample from four units of a run, a wavefront's in its steps one after the other, or from two units or one)
+static int key_sample_groups(int shape, const PanelRuns& pr, int words) {
+    const int ti = shape == 3 ? 32 : kShapes[shape].gi < 4 ? 64 : 128, per = 4 / words;
+    const int steps = (int)((pr.items + ti - 1) / ti);
+    return (steps + per - 1) / per;
+}
+int64_t panel_key_sample_bytes(int chunks, int64_t rows, int64_t V, int words) {
+    const int shape = shape_of(chunks, (int)rows);
+    const PanelRuns pr = runs_of(shape, rows, V);
+    return pr.runs * kShapes[shape].gi * key_sample_groups(shape, pr, words) * 16;
+}
+hipError_t launch_panel_keys(const PanelArgs& a0, hipStream_t stream) {
+    PanelArgs a = a0;
+    const int shape = shape_of(a.chunks, a.rows);
+    a.sample_groups = key_sample_groups(shape, runs_of(shape, a.rows, a.n_items), a.sample_words);
+    return launch_epi<EPI_KEYS>(a, stream);
+}
 hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream) { return launch_epi<EPI_CODES>(a, stream); }
 
 // (maximum, sum) pairs of a hidden row

@@ -162,15 +162,21 @@ struct PanelArgs {
     // are not written, items past the last get code 0
     // launch_panel_keys: a number of 16 bits that orders like the product among those of its row; those of items j % 32 = 8 g + 4 h + c and
     // 16 more (g < 2, h < 2, c < 4) in the halves of word 8 h + 4 g + c of the 64-byte unit j / 32; items past the last get 0, others more
-    // (unless they are no number)
+    // (unless they are no number).  Of every unit the word 0; 0 and 6; or 0, 2, 4 and 6 (sample_words 1, 2, 4) also in row r of samples
+    // (sample_stride bytes apart, a multiple of 16 and at least panel_key_sample_bytes; all rows within 4 GB), in no special order, with zeros in between
     const float* code_map;
     uint8_t* codes;
     int64_t code_stride;
+    uint32_t* samples;
+    int64_t sample_stride;
+    int sample_words;
+    int sample_groups;       // (set by launch_panel_keys)
 };
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
 hipError_t launch_panel_codes(const PanelArgs& a, hipStream_t stream);
 bool panel_keys_supported(int dt, int chunks, int64_t rows, int64_t n_items);      // launch_panel_keys (the others: panel_supported)
+int64_t panel_key_sample_bytes(int chunks, int64_t rows, int64_t V, int words);
 hipError_t launch_panel_keys(const PanelArgs& a, hipStream_t stream);
 // out[r, :] = log softmax of the products of row r; ws: panel_log_softmax_ws_floats floats
 size_t panel_log_softmax_ws_floats(int chunks, int64_t rows, int64_t V);

@@ -33,7 +33,7 @@ def _check(h, Wd, Wv, k, scale=1.0):
 
 
 # a part, one token more or less, several parts a workgroup, the largest vocabulary; panels of 64, 128 and 256 hidden rows
-@pytest.mark.parametrize("rows,V,d_prime,k", [(9, 16384, 256, 4), (16, PART, 128, 900), (33, PART + 1, 40, PART + 1), (64, 2 * PART - 1, 8, 20000),
+@pytest.mark.parametrize("rows,V,d_prime,k", [(65, 16384, 256, 4), (16, PART, 128, 900), (33, PART + 1, 40, PART + 1), (64, 2 * PART - 1, 8, 20000),
                                               (24, 2 * PART + 33, 256, 30000), (64, 8 * PART, 128, 6000), (50, 12 * PART, 64, 90000),
                                               (64, 11 * PART + 7, 256, 1), (2, 16385, 128, 2000), (8, 131072, 16, 16384),
                                               (65, PART, 256, 5000), (128, 65536, 200, 8000), (200, 20000, 64, 3000), (70, 100001, 512, 2500),
@@ -42,10 +42,51 @@ def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
 
 
-@pytest.mark.parametrize("V,k", [(40000, 200), (40000, 9000), (150001, 4000)])
+def _sampled(V):
+    """Ids of the sampled tokens: of every 32 the same two, four or eight."""
+    places = np.array([0, 2, 8, 10] if V <= 49152 else [0, 10] if V <= 98304 else [0])
+    ids = np.arange(0, V, 32)[:, None] + np.concatenate((places, places + 16))
+    return ids[ids < V]
+
+
+def _records(ws, rows, V, d_prime):
+    """What a call leaves in its workspace: the rows' keys, and how many scores were above their bracket and in it."""
+    units, parts = (V + 31) // 32, (V + PART - 1) // PART
+    at, stride = (rows * d_prime * 2 + 255) // 256 * 256, (units * 64 + 255) // 256 * 256 | 256
+    keys = ws[at: at + rows * stride].view(rows, stride)[:, : units * 64].cpu().numpy().view(np.uint16)
+    at += rows * stride
+    return keys, ws[at: at + rows * parts * 8].cpu().numpy().view(np.uint32).reshape(rows, parts, 2).sum(1)
+
+
+def _ids_and_records(h, Wd, Wv, k):
+    (rows, d), (V, d_prime) = h.shape, Wv.shape
+    ws = torch.empty(sv.workspace_bytes(sv.SV_OP_SELECT, rows, d, V, k, d_prime, 0, sv.SV_BF16, 0), dtype=torch.uint8, device="cuda")
+    idx, _ = sv.select(h, Wd, Wv, k, ws=ws)
+    records = _records(ws, rows, V, d_prime)
+    assert torch.equal(idx, sv.select(h, Wd, Wv, k, want_scores=True)[0])      # (the scores in memory)
+    return records
+
+
+@pytest.mark.parametrize("rows,V,d_prime,k", [(60, 128256, 256, 16384), (20, 32768, 64, 3000), (70, 50000, 64, 6000), (9, 262144, 128, 9000),
+                                              (3, 70001, 48, 8000)])
+@pytest.mark.parametrize("together", [1, 32, 700])
+def test_neighbours_with_much_in_common(rows, V, d_prime, k, together):
+    """Seven tenths of a score's variance is shared by `together` neighbouring tokens: the bracket has the k-th score of every row all
+    the same (within 6 standard deviations of a sample of independent ones)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(together)
+    randn = lambda *n: torch.randn(n, generator=gen, device="cuda")
+    Wv = randn(V, d_prime)
+    if together > 1:
+        Wv = 0.3 ** 0.5 * Wv + 0.7 ** 0.5 * randn(V // together + 1, d_prime).repeat_interleave(together, 0)[:V]
+    _, counts = _ids_and_records(randn(rows, 512).bfloat16(), randn(d_prime, 512).bfloat16(), Wv.bfloat16(), k)
+    assert ((counts[:, 0] < k) & (k <= counts.sum(1))).all()
+
+
+@pytest.mark.parametrize("V,k", [(20000, 900), (40000, 200), (40000, 9000), (150001, 4000)])
 @pytest.mark.parametrize("best", [True, False])
 def test_samples_that_mislead(V, k, best):
-    """The tokens of the sampled units are the best of all, or the worst: the k-th score lies outside of the bracket."""
+    """The sampled tokens are the best of all, or the worst: the k-th score lies outside of the bracket."""
     rows, d_prime = 20, 32
     h, Wd, Wv = _inputs(rows, V, d_prime, k)
     h[:, 1] = 1
@@ -53,9 +94,7 @@ def test_samples_that_mislead(V, k, best):
     Wd[0, :] = 0
     Wd[0, 1] = 1                                       # h'[0] = 1 in every row
     Wv[:, 0] = 0
-    units = (V + 31) // 32
-    sampled = (np.arange(256) * units // 256)[:, None] * 32 + np.arange(32)
-    Wv[sampled[sampled < V], 0] = 64.0 if best else -64.0
+    Wv[_sampled(V), 0] = 64.0 if best else -64.0
     _check(h, Wd, Wv, k)
 
 
