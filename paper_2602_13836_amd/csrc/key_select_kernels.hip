@@ -1,8 +1,9 @@
 // Candidate-vocabulary selection (Section 3.3, Steps 1 and 2) for the rows of a tree, without the score matrix: the scores leave
 // the product as TWO BYTES each, and four launches do it all (the down-projection's among them).
-//   keys      the product on the matrix cores, whose epilogue stores every score's half precision (rounded towards zero, after a
-//             power of two per hidden row that brings its largest element to [1, 2)) as an unsigned number that orders like the
-//             scores, and some keys of every unit of 32 tokens once more on their own, as a sample (panel_mfma_kernels.hip);
+//   keys      the product on the matrix cores, whose epilogue stores the half precision (rounded towards zero) of every score's distance
+//             from about the row's median, after a power of two per hidden row that brings its largest element to [1, 2), as an
+//             unsigned number that orders like the scores, and some keys of every unit of 32 tokens once more on their own, as a sample
+//             (panel_mfma_kernels.hip);
 //   bracket   keys of every 32 tokens say where the row's k-th lies, give or take; one pass turns the keys above that into bits and lists
 //             those in between (2 to 7 per cent, of short rows up to 10) with their place in the bracket, one of 2048;
 //   emit      the histogram of a row's lists names the place C that holds the k-th score.  Everything above C is selected; the
@@ -15,15 +16,15 @@
 // products in ascending order from zero (v_mfma_f32_16x16x32_bf16 adds its 32 as two 16s), and wider selectors come here from 65
 // rows on, where the tiled kernel does too.  The result is exact with respect to those scores whatever they are, because the keys
 // are monotone: a sample that misleads costs its row a walk by one workgroup over all of its keys, poor keys (scores that all lie next to each
-// other) more tokens at C.
+// other in few places) more tokens at C.
 //
 // The sample has tokens of every unit.  Neighbours that resemble each other, as the scripts, the numbers or the unused ids of a real vocabulary do, are in it
 // as often as they are in the row, and it says more about the row than one of independent tokens.  (A sample of 256 whole units missed where they
 // share half of their variance, in one call out of two of 60 rows x 128256, k = 16384; a missed row took 120 us more.)  Only scores that
 // depend on the token id modulo 32 mislead it: one such row of 60 x 128256 takes 31 us more, of 64 x 262144 80, all rows 36 to 41 and 86.
 //
-// Measured (60 rows x 128256, d' = 256, k = 4096; kernels under a profiler): h' 6.2 us, keys 17.6, bracket 9.2, emit 9.7; the whole
-// selection 44.4 -> 40.8 us.  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's
+// Measured (60 rows x 128256, d' = 256, k = 4096; kernels under a profiler): h' 6.2 us, keys 17.6, bracket 9.2, emit 9.7 to 10.5; the whole
+// selection 44.4 -> 40.8 us (as a case with the caller's part 46.5 -> 44).  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's
 // product and a map in front of the codes (6 and 4 us, each mostly a launch) and read the codes with one workgroup per row (17).  Two thirds of
 // bracket and emit are their start and six round trips to memory.  Not used: this pass by one workgroup per row, 22.7 us
 // (9.5 of them for the keys); a sample gathered from the keys, 16 bytes per thread from lines of their own (as many bytes as the part: bracket
@@ -76,9 +77,11 @@ inline KeyLayout key_layout(int64_t V, int64_t rows) {
     return L;
 }
 
-// the list's histogram, the ties' keys from the end on downwards; later up to 64 rows of W_vocab
-constexpr int kStageBytes = 34 * 1024;
-constexpr uint32_t kTiesInLds = (kStageBytes - 4 * kBins) / 8;
+// the list's histogram, the ties' keys from the end on downwards; later up to 64 rows of W_vocab and their keys
+constexpr uint32_t kFew = 64;
+__host__ __device__ constexpr uint32_t few_bytes(int chunks) { return kFew * ((uint32_t)(chunks + 1) * 16u + 8u); }
+__host__ __device__ constexpr uint32_t stage_bytes(int chunks) { return few_bytes(chunks) > 34 * 1024 ? few_bytes(chunks) : 34 * 1024; }
+constexpr uint32_t kTiesInLds = (34 * 1024 - 4 * kBins) / 8;
 
 struct ResolveSmem {
     uint32_t w[kWaves], w2[kWaves];
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(kThreads) void key_emit_kernel(const unsigned char*
     extern __shared__ __attribute__((aligned(16))) uint32_t s_sel[];
     unsigned char* const s_stage = reinterpret_cast<unsigned char*>(s_sel) + sel_bytes(V);
     uint32_t* const s_hist = reinterpret_cast<uint32_t*>(s_stage);
-    uint64_t* const s_ties = reinterpret_cast<uint64_t*>(s_hist + kBins);
+    uint64_t* const s_ties = reinterpret_cast<uint64_t*>(s_stage + stage_bytes(chunks)) - kTiesInLds;
     __shared__ ResolveSmem sm;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -418,7 +421,7 @@ __global__ __launch_bounds__(kThreads) void key_emit_kernel(const unsigned char*
                     }
                 }
             };
-            if (LDS && n <= 64u && n * ((uint32_t)(chunks + 1) * 16u + 8u) <= (uint32_t)kStageBytes) {
+            if (LDS && n <= kFew) {
                 // The usual handful: all threads bring the rows of W_vocab, in one round trip, and two wavefronts multiply.
                 // Ranked by counting (keys are unique: they end in the id)
                 u32x4* const s_rows = reinterpret_cast<u32x4*>(s_stage);
@@ -559,7 +562,7 @@ bool key_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k
 // (more than 64 KB of LDS: an opt-in)
 hipError_t configure_key_select_lds() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&key_emit_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(sel_bytes(kMaxVocab) + kStageBytes));
+                               (int)(sel_bytes(kMaxVocab) + stage_bytes(64)));
 }
 
 size_t key_select_scratch_bytes(int64_t rows, int64_t V) { return key_layout(V, rows).total; }
@@ -600,7 +603,7 @@ hipError_t launch_key_select(const CodeSelectArgs& a, hipStream_t stream) {
     uint32_t* list = reinterpret_cast<uint32_t*>(a.scratch + L.list);
     hipLaunchKernelGGL(key_bracket_kernel, grid, dim3(kThreads), 0, stream, keys, L.stride, a.V, parts, per,
                        reinterpret_cast<const u32x4*>(p.samples), (int)(p.sample_stride / 16), (uint32_t)rank_hi, (uint32_t)rank_lo, counts, bits, list);
-    hipLaunchKernelGGL(key_emit_kernel, grid, dim3(kThreads), sel_bytes(a.V) + kStageBytes, stream, keys, L.stride, a.V, a.k, a.hp, a.Wv,
+    hipLaunchKernelGGL(key_emit_kernel, grid, dim3(kThreads), sel_bytes(a.V) + stage_bytes(a.chunks), stream, keys, L.stride, a.V, a.k, a.hp, a.Wv,
                        a.chunks, parts, per, counts, bits, list, reinterpret_cast<uint64_t*>(a.scratch + L.ties), a.idx_out);
     return hipGetLastError();
 }

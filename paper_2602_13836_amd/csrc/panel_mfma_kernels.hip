@@ -48,7 +48,7 @@ constexpr int kRunUnit = 64;             // a run is a multiple of this many row
 // EPI_LOGP       the product minus a value per hidden row (the normaliser of Section 3.4) is stored
 // EPI_LSE        only (maximum, sum of exponentials relative to it) per hidden row and run of rows of M
 // EPI_CODES      a byte per score is stored, a monotone function of the score per hidden row (the selection of a batch)
-// EPI_KEYS       two bytes per score: half precision, as a number that orders like it
+// EPI_KEYS       two bytes per score: half precision, as a number that orders like it, of its distance from the row's middle
 enum { EPI_SAMPLE = 0, EPI_LOGP = 1, EPI_LSE = 2, EPI_CODES = 3, EPI_KEYS = 4 };
 
 template <int KS, int GM>
@@ -61,13 +61,26 @@ constexpr int stages() { return stage_bytes<KS, GM>() > 32 * 1024 ? 2 : 3; }
 template <int KS, int GM>
 constexpr int early_steps() { return KS > 8 ? 1 : stages<KS, GM>() - 1; }
 // ... and so many hidden rows per wavefront at a time
-template <int KS, int GM>
-constexpr int fill_rows() { return KS > 16 || stages<KS, GM>() == 2 ? 16 : 32; }
+// (keys, up to 256 elements: fewer, which leaves room for the tokens of the middle)
+template <int KS, int GM, int EPI>
+constexpr int fill_rows() { return EPI == EPI_KEYS && KS <= 16 ? (KS > 8 ? 16 : 32) : KS > 16 || stages<KS, GM>() == 2 ? 16 : 32; }
+template <int KS, int GM, int EPI>
+constexpr size_t fill_bytes() { return early_steps<KS, GM>() * stage_bytes<KS, GM>() + (size_t)kWaves * fill_rows<KS, GM, EPI>() * KS * 32; }
+// The tokens that say where the middle of a row's scores lies, and where they are: behind the ring and the hidden rows on their way, or,
+// more than 256 elements, in the last stage before its first step is.
+template <int KS>
+constexpr int middle_tokens() { return KS > 16 ? 16 : 32; }
+template <int KS, int GM, int EPI>
+constexpr size_t middle_at() {
+    const size_t n = stages<KS, GM>() * stage_bytes<KS, GM>(), fill = fill_bytes<KS, GM, EPI>();
+    return KS > 16 ? n - stage_bytes<KS, GM>() : n > fill ? n : fill;
+}
 template <int KS, int WM, int GM, int EPI>
 constexpr size_t panel_lds_bytes() {
     size_t n = stages<KS, GM>() * stage_bytes<KS, GM>();
     if (EPI == EPI_LOGP) n += (size_t)32 * WM * GM * 4;
-    const size_t fill = early_steps<KS, GM>() * stage_bytes<KS, GM>() + (size_t)kWaves * fill_rows<KS, GM>() * KS * 32;
+    if (EPI == EPI_KEYS && KS <= 16) n = middle_at<KS, GM, EPI>() + (size_t)middle_tokens<KS>() * KS * 32;
+    const size_t fill = fill_bytes<KS, GM, EPI>();
     return n > fill ? n : fill;
 }
 
@@ -94,7 +107,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     // stores of a wavefront per step whose rows are all there
     constexpr int kStores = EPI == EPI_LSE ? 0 : EPI == EPI_CODES ? SUB * WM : EPI == EPI_KEYS ? SUB * WM * 2 : SUB * WM * 16;
     static_assert(kPieces % kWaves == 0 && kTI % (32 * GI) == 0 && kUnits <= 64 && kUnits >= 16, "whole pieces, whole sub-tiles");
-    static_assert(EPI != EPI_KEYS || SUB == 1, "a unit per wavefront and step");
+    static_assert(EPI != EPI_KEYS || (SUB == 1 && middle_tokens<KS>() * kRowB / 1024 % kWaves == 0), "a unit per wavefront and step; whole pieces");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];     // [NS][kTI][kRowB], then the epilogue's
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -137,13 +150,26 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
         }
     };
 
+    [[maybe_unused]] auto request_middle = [&]() {       // tokens from all of M, laid out like a step
+        const i32x4_t whole = buffer_of(a.M);
+#pragma unroll
+        for (int i = 0; i < middle_tokens<KS>() * kRowB / 1024 / kWaves; ++i) {
+            const int piece = i * kWaves + wave;
+            const int r = piece * (64 / kUnits) + lane / kUnits;
+            const uint32_t u = (uint32_t)((lane % kUnits) ^ (r & 15));
+            // (spread over what lies between, so that they are not all multiples of something)
+            const uint32_t row = min((uint32_t)(2 * r + 1) * (uint32_t)n_items / (uint32_t)(2 * middle_tokens<KS>()) + (uint32_t)(11 * r % 32), (uint32_t)n_items - 1u);
+            memory_to_lds((int)u < C ? row * m_row_bytes + u * 16u : kOutside, whole, 0u, lds0 + (uint32_t)middle_at<KS, GM, EPI>() + (uint32_t)(piece * 1024));
+        }
+    };
+
     // This wavefront's hidden rows: lane = (row within a group of 32, k-group), like every operand of the MFMA.  They come
     // through LDS (a part of all of it per wavefront, before the first stage is filled): whole rows per load instruction,
     // where the operand's own shape, 32 bytes of 32 rows, took 15 us for the 256 KB of a panel.
     const int row_w = panel * TM + gm * 32 * WM;         // first hidden row of the wavefront
     bf16x8_t fx[WM][KS];
     {
-        constexpr int kRows = fill_rows<KS, GM>();  // rows per round
+        constexpr int kRows = fill_rows<KS, GM, EPI>();  // rows per round
         constexpr int kLoads = kRows * kUnits / 64, kRounds = WM * 32 / kRows;
         unsigned char* s_fill = smem + early_steps<KS, GM>() * stage_bytes<KS, GM>() + (size_t)wave * kRows * kRowB;
         auto fetch = [&](int round, u32x4 (&v)[kLoads]) {
@@ -156,6 +182,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
         };
         u32x4 v[kLoads];
         fetch(0, v);                                     // (in front of M's requests: loads come back in order)
+        if constexpr (EPI == EPI_KEYS && KS <= 16) request_middle();
 #pragma unroll
         for (int t = 0; t < early_steps<KS, GM>(); ++t)
             if (t < nt) request(t, t);
@@ -171,12 +198,12 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             // (a wavefront's own LDS accesses stay in order in the hardware; the fences keep the compiler from moving a
             // lane's reads in front of the other lanes' writes, or the next round's writes in front of these reads)
             wavefront_fence();
-            if (32 / kRows == 1 || ((lane >> 4) & 1) == part) {
+            if (32 / kRows == 1 || (lane & 31) / kRows == part) {
                 const unsigned char* mine = s_fill + ((lane & 31) % kRows) * kRowB;
 #pragma unroll
                 for (int kk = 0; kk < KS; ++kk)
                     fx[m][kk] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
-                                                                 mine + (((2 * kk + (lane >> 5)) ^ (lane & 15)) * 16)));
+                                                                 mine + (((2 * kk + (lane >> 5)) ^ ((lane & 31) % kRows & 15)) * 16)));
             }
             wavefront_fence();
         }
@@ -224,6 +251,46 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             map_scale[m] = __uint_as_float((254u - e) << 23);
             sample_at[m] = (uint32_t)row * (uint32_t)a.sample_stride + (uint32_t)((run * GI + gi) * a.sample_groups) * 16u;
         }
+        // The middle of a row's scores: about the median of those of 32 (16) tokens from all of M, the same in every workgroup.  Without it
+        // half precision keeps of scores with a common offset what the offset leaves: at 20 standard deviations 60 to 180 of 128256
+        // tokens have the k-th one's key (k = 4096), at some hundreds thousands (60 rows, d' = 256, the whole selection: 49 us at 10
+        // standard deviations, 56 at 20, 190 at 100, for the 41 of none).
+        if constexpr (KS > 16) {
+            request_middle();
+            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        }
+        const unsigned char* s_mid = smem + middle_at<KS, GM, EPI>() + (lane & (middle_tokens<KS>() - 1)) * kRowB;
+#pragma unroll
+        for (int m = 0; m < WM; ++m) {
+            f32x16_t mid;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mid[e] = 0.f;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk)
+                mid = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(s_mid + (((2 * kk + half) ^ (lane & 15)) * 16))),
+                    fx[m][kk], mid, 0, 0, 0);
+            // Five medians of three of the lane's 16 tokens (or of its 8, twice), as many of lane + 32's, and the fifth smallest of the ten: a
+            // score that is there, and not a mean of two groups of tokens that have little in common
+            float t[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) t[i] = __builtin_amdgcn_fmed3f(mid[3 * i], mid[3 * i + 1], mid[3 * i + 2]);
+            auto order = [&](int i, int j) {
+                const float x = t[i];
+                t[i] = fminf(x, t[j]);
+                t[j] = fmaxf(x, t[j]);
+            };
+            order(0, 1), order(3, 4), order(2, 4), order(2, 3), order(1, 4), order(0, 3), order(0, 2), order(1, 3), order(1, 2);
+            float middle = INFINITY;
+#pragma unroll
+            for (int i = 0; i <= 5; ++i) {               // i from here and 5 - i from there
+                const float there = i < 5 ? __shfl_xor(t[4 - i], 32) : -INFINITY;
+                middle = fminf(middle, i > 0 ? fmaxf(t[i - 1], there) : there);
+            }
+            const float bias = 0.0f - middle * map_scale[m];
+            map_bias[m] = fabsf(bias) <= 1e30f ? bias : 0.0f;                 // (infinite scores, and those that are no number)
+        }
+        if constexpr (KS > 16) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the stage is free
     }
     if constexpr (EPI == EPI_LOGP) {
         for (int t = tid; t < TM; t += kThreads) s_sub[t] = panel * TM + t < a.rows ? a.row_sub[panel * TM + t] : 0.0f;
@@ -368,9 +435,9 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                 for (int g = 0; g < 2; ++g)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        // (plus zero: -0 and 0 are the same score)
-                        const auto p = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf(acc[m][4 * g + c], map_scale[m], 0.0f),
-                                                                  __builtin_fmaf(acc[m][4 * g + 8 + c], map_scale[m], 0.0f));
+                        // (-0 and 0 are the same score: the bias is never -0)
+                        const auto p = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf(acc[m][4 * g + c], map_scale[m], map_bias[m]),
+                                                                  __builtin_fmaf(acc[m][4 * g + 8 + c], map_scale[m], map_bias[m]));
                         const i16x2_t x = __builtin_bit_cast(i16x2_t, p);
                         const i16x2_t sign = x >> (short)15;
                         w[g][c] = __builtin_bit_cast(uint32_t, x) ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u);

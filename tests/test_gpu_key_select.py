@@ -36,7 +36,7 @@ def _check(h, Wd, Wv, k, scale=1.0):
 @pytest.mark.parametrize("rows,V,d_prime,k", [(65, 16384, 256, 4), (16, PART, 128, 900), (33, PART + 1, 40, PART + 1), (64, 2 * PART - 1, 8, 20000),
                                               (24, 2 * PART + 33, 256, 30000), (64, 8 * PART, 128, 6000), (50, 12 * PART, 64, 90000),
                                               (64, 11 * PART + 7, 256, 1), (2, 16385, 128, 2000), (8, 131072, 16, 16384),
-                                              (65, PART, 256, 5000), (128, 65536, 200, 8000), (200, 20000, 64, 3000), (70, 100001, 512, 2500),
+                                              (65, PART, 256, 5000), (128, 65536, 200, 8000), (200, 20000, 264, 3000), (70, 100001, 512, 2500),
                                               (130, 70000, 264, 69999)])
 def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
@@ -81,6 +81,25 @@ def test_neighbours_with_much_in_common(rows, V, d_prime, k, together):
         Wv = 0.3 ** 0.5 * Wv + 0.7 ** 0.5 * randn(V // together + 1, d_prime).repeat_interleave(together, 0)[:V]
     _, counts = _ids_and_records(randn(rows, 512).bfloat16(), randn(d_prime, 512).bfloat16(), Wv.bfloat16(), k)
     assert ((counts[:, 0] < k) & (k <= counts.sum(1))).all()
+
+
+@pytest.mark.parametrize("rows,V,d_prime,k", [(60, 128256, 256, 4096), (20, 32768, 64, 3000), (3, 70001, 40, 8000), (100, 40000, 256, 1500),
+                                              (150, 20000, 304, 700), (66, 100000, 512, 3000)])
+@pytest.mark.parametrize("offset", [-30.0, 0.0, 30.0, 1000.0])
+def test_scores_with_a_common_offset(rows, V, d_prime, k, offset):
+    """All scores of a row lie `offset` standard deviations from zero.  A key says where a score lies among those of its row, so few share
+    the k-th one's (half precision has 2048 numbers between one and three deviations)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    randn = lambda *n: torch.randn(n, generator=gen, device="cuda")
+    h, Wd, Wv = randn(rows, 512), randn(d_prime, 512) / 16, randn(V, d_prime)
+    h[:, 0] = 8.0
+    Wd[:, 0] = 0.0
+    Wd[0, 0] = 1.0                                     # h'[0] = 8 and nothing else in every row, against sums of 512 / 256 in the others
+    Wv[:, 0] = offset * (2.0 * d_prime) ** 0.5 / 8
+    keys, _ = _ids_and_records(h.bfloat16(), Wd.bfloat16(), Wv.bfloat16(), k)
+    kth = -np.partition(-keys.astype(np.int32), k - 1, axis=1)[:, k - 1: k]
+    assert (keys == kth).sum(1).max() <= 64            # (what the quick choice among them takes)
 
 
 @pytest.mark.parametrize("V,k", [(20000, 900), (40000, 200), (40000, 9000), (150001, 4000)])
