@@ -541,22 +541,23 @@ __global__ __launch_bounds__(kThreads) void key_emit_kernel(const unsigned char*
 
 }  // namespace
 
-// From how many rows on, and to how many.  us, the alternative / keys:
-//   few rows    the alternative is the scores in memory.  From 9 rows on theirs is the longer chain: d' = 256, 16500 to 262144 tokens, k = V / 32:
-//               9 rows 26 to 51 / 23 to 46, 16 rows 28 to 57 / 26 to 50; only many ids of few rows, which there leave by more workgroups, tie
-//               or lose (k = V / 2: 12 rows x 128256 38.2 / 41.5, x 32768 29.4 / 29.5, 24 rows 46.0 / 44.6).  Up to 8 rows: d' = 128 and
-//               64, k up to V / 8: 2 rows x 128256 29.3 / 25.7, x 16500 22.0 / 20.5, k = V / 8 29.7 / 28.6, k = V / 3 25.2 / 28.2;
-//               d' = 256 (where the product on panels, made for many rows, loses 3 us): 8 rows 31.3 / 33.1.
-//   many rows   the alternative is a byte per score, half of what keys write and read: by the number of scores.  d' = 256:
-//               100 x 50000 35.4 / 33.6, 65 x 128256 45.7 / 43.9, 100 x 128256 46.8 / 47.2; more than 128 rows (panels of 256): 200 x 17000
-//               37.9 / 36.2, 160 x 50000 41.0 / 42.9.  d' = 128: 128 x 17000 29.3 / 27.8, 100 x 50000 31.3 / 31.3, 128 x 50000 31.9 / 32.5.
-//               d' = 512: 128 x 128256 74.8 / 70.0, 256 x 50000 54.4 / 53.5, 160 x 128256 77.0 / 78.5, 65 x 262144 111.5 / 114.7.
+// From how many rows on, and to how many.  us, the alternative / keys (runs differ by 2 to 4 %):
+//   few rows    the alternative is the scores in memory.  From 9 rows on theirs is the longer chain: d' = 256, k = V / 32: 9 rows x 33000 to 262144
+//               29.1 to 51.5 / 27.3 to 48.2, 16 rows 30.8 to 54.3 / 27.3 to 49.4; only many ids of few rows, which there leave by more
+//               workgroups, tie or lose (k = V / 2: 16 rows x 128256 41.1 / 42 and more; V / 4: 16 x 66000 36.1 / 34.0, 9 x 128256 39.0 / 40.9, 9 x
+//               262144 54.5 / 56.7; 24 rows x 128256, V / 2 45.4 / 44.2).  Up to 8 rows: d' = 128 and 64, k up to V / 8: 2 rows x 128256 31.5 /
+//               28.5, x 16500 24.6 / 21.8, k = V / 8 32.1 / 31.1; x 262144 V / 32 40.4 / 36.7, V / 8 40.9 / 42.2 (8 rows 49.6 / 43.4); d' = 256
+//               (where the product on panels, made for many rows, loses 3 us): 8 rows 31.3 / 33.1.
+//   many rows   the alternative is a byte per score, half of what keys write and read.  d' = 256: as long as every workgroup of bracket and emit
+//               has one part, 65 x 80000 39.6 / 37.0, 128 x 50000 36.0 / 36.1; two parts 100 x 66000 39.0 / 42.8, 65 x 100000 42.2 / 43.4; more
+//               than 128 rows (panels of 256) tie: 160 x 16385 35.6 / 35.0, 200 x 17000 37.7 / 38.3; so does all of d' = 128: 128 x 17000
+//               26.7 / 26.8, 65 x 50000 29.9 / 30.1.  d' = 512: 65 x 80000 61.1 / 51.0, 128 x 128256 76.6 / 75, 65 x 262144 110 / 114; 160 x
+//               50000 61.7 / 60.6, 256 x 33000 57.8 / 57.1; d' = 264, 160 x 80000 60.3 / 62.9.
 bool key_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
     if (!panel_keys_supported(dt, chunks, rows, V) || V < kMinVocab || V > kMaxVocab || row_select_preferred(chunks, rows, V)) return false;
-    if (rows > 256) return false;                             // (more than one round of workgroups: 300 rows x 16384, d' = 512 49.5 / 49.5, 1024 82 / 89)
-    if (rows > 64) return rows * V <= (chunks > 32 ? 16800000 : chunks > 16 && rows <= 128 ? 8400000 : 4400000);
-    if (rows > 8) return chunks <= 16 || rows >= 24 || 4 * k <= V;
-    return rows > 1 && chunks <= 16 && 8 * k <= V;
+    if (rows > 64) return chunks > 32 ? rows * V <= (rows <= 128 ? 16800000 : 10000000) : rows * parts_of(V) <= 256;
+    if (rows > 8) return chunks <= 16 || rows >= 24 || (4 * k <= V && (V <= 98304 || 8 * k <= V));
+    return rows > 1 && chunks <= 16 && 8 * k <= V && (rows > 4 || V <= 196608 || 16 * k <= V);
 }
 
 // (more than 64 KB of LDS: an opt-in)

@@ -568,13 +568,8 @@ hipError_t with_shape(int shape, F&& f) {
     if constexpr (EPI != EPI_SAMPLE && EPI != EPI_KEYS) {
         switch (shape) {
             case 0: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-            case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-            default: break;
-        }
-    }
-    if constexpr (EPI != EPI_SAMPLE) {
-        switch (shape) {
             case 1: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+            case 4: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
             case 5: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
             default: break;
         }
@@ -586,9 +581,11 @@ hipError_t with_shape(int shape, F&& f) {
             default: break;
         }
     }
+    if constexpr (EPI != EPI_KEYS) {
+        if (shape == 6) return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    }
     switch (shape) {
         case 2: return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
-        case 6: return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
         case 3: return f(std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
         default: return hipErrorInvalidValue;
     }
@@ -648,7 +645,7 @@ template <int EPI>
 hipError_t opt_in_epi() {
     for (int shape = 0; shape < kNShapes; ++shape) {
         if (EPI != EPI_KEYS && shape >= 7) continue;
-        if (EPI == EPI_KEYS && (shape == 0 || shape == 4)) continue;
+        if (EPI == EPI_KEYS && shape != 2 && shape != 3 && shape < 7) continue;
         if (EPI == EPI_SAMPLE && shape != 3 && shape != kSampleShape && shape != kSampleShapeShort) continue;
         const hipError_t e = with_shape<EPI>(shape, [&](auto ks, auto wm, auto gm) {
             constexpr int KS = decltype(ks)::value, WM = decltype(wm)::value, GM = decltype(gm)::value;
@@ -673,7 +670,7 @@ hipError_t configure_panel_lds() {
 }
 
 bool panel_keys_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
-    return dt == DT_BF16 && rows >= 1 && rows <= 256 && chunks >= 1 && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
+    return dt == DT_BF16 && rows >= 1 && rows <= 256 && chunks > (rows <= 64 ? 0 : rows <= 128 ? 16 : 32) && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
 }
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);

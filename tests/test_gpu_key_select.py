@@ -67,7 +67,7 @@ def _ids_and_records(h, Wd, Wv, k):
     return records
 
 
-@pytest.mark.parametrize("rows,V,d_prime,k", [(60, 128256, 256, 16384), (20, 32768, 64, 3000), (70, 50000, 64, 6000), (9, 262144, 128, 9000),
+@pytest.mark.parametrize("rows,V,d_prime,k", [(60, 128256, 256, 16384), (20, 32768, 64, 3000), (70, 50000, 136, 6000), (9, 262144, 128, 9000),
                                               (3, 70001, 48, 8000)])
 @pytest.mark.parametrize("together", [1, 32, 700])
 def test_neighbours_with_much_in_common(rows, V, d_prime, k, together):
