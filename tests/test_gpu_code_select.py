@@ -20,6 +20,14 @@ def _inputs(rows, V, d_prime, seed, d=64):
     return (rng.integers(-1, 2, (rows, d)), rng.integers(-1, 2, (d_prime, d)), rng.integers(-2, 3, (V, d_prime)) / 64.0)
 
 
+# for inputs that are hard on codes: rows, V, d'; panels of 128, of 512, and selectors of more than 256 elements
+HARD = [(70, 50000, 64), (300, 33000, 256), (258, 40000, 512)]
+EDGES = [(65, 16384, 128, 100), (65, 32768, 64, 1), (66, 32769, 8, 32769), (90, 98303, 256, 9000), (129, 65536, 256, 64), (70, 65537, 40, 3000),
+         (257, 16384, 512, 300), (300, 65537, 512, 40000), (65, 262144, 512, 500), (512, 24576, 200, 2000)]
+LONG_LISTS = [(300, 200000, 256, 100000), (65, 393216, 256, 196608)]
+ONE_SUM = [(70, 40000, 128), (140, 60000, 256), (100, 70000, 200), (257, 33000, 512)]
+
+
 def _check(h, Wd, Wv, k):
     h, Wd, Wv = _bf16(h), _bf16(Wd), _bf16(Wv)
     idx, _ = sv.select(h, Wd, Wv, k)
@@ -42,6 +50,11 @@ def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
 
 
+@pytest.mark.parametrize("rows,V,d_prime,k", EDGES)
+def test_edges_of_codes(rows, V, d_prime, k):
+    _check(*_inputs(rows, V, d_prime, rows + k), k)
+
+
 def test_static_scratch_nearly_full():
     """20 rows of 33500 tokens: what the library's static scratch just holds.  The sums of real numbers round, so equal ids also say
     that both calls ran the same kernels."""
@@ -56,15 +69,15 @@ def test_static_scratch_nearly_full():
 
 
 # a list of entries that is longer than its LDS (wide intervals: half of the tokens are wanted), more rows than CUs among them
-@pytest.mark.parametrize("rows,V", [(300, 200000), (65, 393216)])
-def test_lists_longer_than_lds(rows, V):
-    _check(*_inputs(rows, V, 256, rows), V // 2)
+@pytest.mark.parametrize("rows,V,d_prime,k", LONG_LISTS)
+def test_lists_longer_than_lds(rows, V, d_prime, k):
+    _check(*_inputs(rows, V, d_prime, rows), k)
 
 
-def test_rows_of_zeros_and_plateaus():
+@pytest.mark.parametrize("rows,V,d_prime", HARD)
+def test_rows_of_zeros_and_plateaus(rows, V, d_prime):
     """Rows without any difference between tokens; rows with two, three or a few different scores, so that tens of thousands
     share the code that decides."""
-    rows, V, d_prime = 70, 50000, 64
     h, Wd, Wv = _inputs(rows, V, d_prime, 3)
     h[10] = 0
     h[69] = 0
@@ -73,16 +86,16 @@ def test_rows_of_zeros_and_plateaus():
     Wd[:, 0] = 0
     Wd[0, 0] = 1                                   # rows 20 to 29 see only the first column of W_vocab
     Wv[:, 0] = np.sign(Wv[:, 0]) / 64.0
-    for k in (1, 100, 16000, 33000, 50000):
+    for k in (1, 100, 16000, 33000, V):
         _check(h, Wd, Wv, k)
 
 
 @pytest.mark.parametrize("share", [1.0, 0.9, 0.55])
 @pytest.mark.parametrize("k", [1, 9000, 20000, 39999])
-def test_lists_longer_than_their_memory(share, k):
+@pytest.mark.parametrize("rows,V,d_prime", [(68, 40000, 32), HARD[2]])
+def test_lists_longer_than_their_memory(rows, V, d_prime, share, k):
     """More than half of the tokens share a score that the map has an interval for, and most of their codes do not fit the list; some
     rows select among them, some have them above or below the k-th score.  Nothing past the workspace is written."""
-    rows, V, d_prime = 68, 40000, 32
     h, Wd, Wv = _inputs(rows, V, d_prime, k)
     h[:, 1:] = 0
     h[:, 0] = np.arange(rows) % 5 - 2              # h' = (h[0], 0, ...)
@@ -99,9 +112,9 @@ def test_lists_longer_than_their_memory(share, k):
 
 @pytest.mark.parametrize("k", [200, 5000, 20000])
 @pytest.mark.parametrize("best", [True, False])
-def test_samples_that_mislead(k, best):
+@pytest.mark.parametrize("rows,V,d_prime", [(66, 40000, 32)] + HARD[1:])
+def test_samples_that_mislead(rows, V, d_prime, k, best):
     """The sampled tokens are the best of all, or the worst: the k-th score lies outside of what the sample says."""
-    rows, V, d_prime = 66, 40000, 32
     h, Wd, Wv = _inputs(rows, V, d_prime, k)
     h[:, 1] = 1
     Wd[:, 1] = 0
@@ -114,10 +127,10 @@ def test_samples_that_mislead(k, best):
 
 @pytest.mark.parametrize("far", [2.0 ** 6, 2.0 ** 20, 2.0 ** 50])
 @pytest.mark.parametrize("k", [300, 4000])
-def test_scores_far_from_all_others(k, far):
+@pytest.mark.parametrize("rows,V,d_prime", [(65, 33000, 64)] + HARD[1:])
+def test_scores_far_from_all_others(rows, V, d_prime, k, far):
     """A few tokens of every row score far above and far below the rest, sampled ones among them: one step of the map's first
     histogram holds nearly the whole sample.  (Their own scores round; all of those above are selected, none of those below.)"""
-    rows, V, d_prime = 65, 33000, 64
     h, Wd, Wv = _inputs(rows, V, d_prime, k)
     h[:, 1] = 1
     Wd[:, 1] = 0
@@ -129,13 +142,13 @@ def test_scores_far_from_all_others(k, far):
     _check(h, Wd, Wv, k)
 
 
-@pytest.mark.parametrize("rows", [12, 40, 70])
+# (12 and 40 rows: two bytes per score)
+@pytest.mark.parametrize("rows,V,d_prime", [(12, 33000, 64), (40, 33000, 64), (70, 33000, 64), HARD[2]])
 @pytest.mark.parametrize("up,down,none", [(1009, 2003, 3001), (2, 2003, 3001), (1009, 2, 3001), (1009, 2003, 4), (1, 2003, 3001)])
 @pytest.mark.parametrize("k", [20, 300, 20000])
-def test_scores_that_are_infinite(rows, up, down, none, k):
+def test_scores_that_are_infinite(rows, V, d_prime, up, down, none, k):
     """Every `up`-th token scores infinity, every `down`-th minus infinity, every `none`-th no number, which is never selected (as where
     the scores go through memory) as long as there are k others."""
-    V, d_prime = 33000, 64
     h, Wd, Wv = _inputs(rows, V, d_prime, k)
     h[:, 1] = 1
     Wd[:, 1] = 0
@@ -177,7 +190,7 @@ def test_replays_of_a_captured_call(rows):
 
 
 @pytest.mark.parametrize("rows,V,d_prime", [(9, 32768, 256), (16, 40000, 128), (17, 16384, 256), (24, 60000, 200), (32, 90112, 128), (20, 90113, 64),
-                                            (32, 128256, 256), (33, 100000, 256), (60, 33000, 248), (65, 20000, 512), (130, 40000, 512)])
+                                            (32, 128256, 256), (33, 100000, 256), (60, 33000, 248), (65, 20000, 512), (130, 40000, 512)] + ONE_SUM)
 def test_one_sum_per_score(rows, V, d_prime):
     """A call adds a score's products the same way whether or not it is asked for the scores.  All rows of W_vocab hold the same numbers in
     different orders and h' is one number d' times, so all scores are equal but for their rounding, which decides what is selected."""
@@ -189,5 +202,6 @@ def test_one_sum_per_score(rows, V, d_prime):
     k = V // 20
     idx, _ = sv.select(h, Wd, Wv, k)
     with_scores, sc = sv.select(h, Wd, Wv, k, want_scores=True)
-    assert len(sc.unique()) > rows                 # (they do round differently)
+    # (they do round differently, by more than h' does: rows whose h' is the same have the same scores)
+    assert len(sc.unique()) > len((h.double() @ Wd.double().t())[:, 0].bfloat16().unique())
     assert torch.equal(idx, with_scores)

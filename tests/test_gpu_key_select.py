@@ -10,6 +10,16 @@ sv = pytest.importorskip("paper_2602_13836_amd")
 pytestmark = pytest.mark.gpu
 
 PART = 32768
+# a part, one token more or less, several parts a workgroup, the largest vocabulary; panels of 64, 128 and 256 hidden rows
+EDGES = [(65, 16384, 256, 4), (16, PART, 128, 900), (33, PART + 1, 40, PART + 1), (64, 2 * PART - 1, 8, 20000),
+         (24, 2 * PART + 33, 256, 30000), (64, 8 * PART, 128, 6000), (50, 12 * PART, 64, 90000), (64, 11 * PART + 7, 256, 1),
+         (2, 16385, 128, 2000), (8, 131072, 16, 16384), (65, PART, 256, 5000), (128, 65536, 200, 8000), (200, 20000, 264, 3000),
+         (70, 100001, 512, 2500), (130, 70000, 264, 69999)]
+TOGETHER = [(60, 128256, 256, 16384), (20, 32768, 64, 3000), (70, 50000, 136, 6000), (9, 262144, 128, 9000), (3, 70001, 48, 8000)]
+OFFSET = [(60, 128256, 256, 4096), (20, 32768, 64, 3000), (3, 70001, 40, 8000), (100, 40000, 256, 1500), (150, 20000, 304, 700),
+          (66, 100000, 512, 3000)]
+MISLED = [(20000, 900), (40000, 200), (40000, 9000), (150001, 4000)]
+ONE_SUM = [(2, 40000, 128), (8, 128256, 64), (9, 32768, 256), (64, 50000, 200), (66, 60000, 256), (130, 40000, 512)]
 
 
 def _bf16(a):
@@ -32,12 +42,7 @@ def _check(h, Wd, Wv, k, scale=1.0):
     assert bool((ws[need:] == 0x5A).all())             # nothing past the workspace is written
 
 
-# a part, one token more or less, several parts a workgroup, the largest vocabulary; panels of 64, 128 and 256 hidden rows
-@pytest.mark.parametrize("rows,V,d_prime,k", [(65, 16384, 256, 4), (16, PART, 128, 900), (33, PART + 1, 40, PART + 1), (64, 2 * PART - 1, 8, 20000),
-                                              (24, 2 * PART + 33, 256, 30000), (64, 8 * PART, 128, 6000), (50, 12 * PART, 64, 90000),
-                                              (64, 11 * PART + 7, 256, 1), (2, 16385, 128, 2000), (8, 131072, 16, 16384),
-                                              (65, PART, 256, 5000), (128, 65536, 200, 8000), (200, 20000, 264, 3000), (70, 100001, 512, 2500),
-                                              (130, 70000, 264, 69999)])
+@pytest.mark.parametrize("rows,V,d_prime,k", EDGES)
 def test_edges(rows, V, d_prime, k):
     _check(*_inputs(rows, V, d_prime, rows + k), k)
 
@@ -67,8 +72,7 @@ def _ids_and_records(h, Wd, Wv, k):
     return records
 
 
-@pytest.mark.parametrize("rows,V,d_prime,k", [(60, 128256, 256, 16384), (20, 32768, 64, 3000), (70, 50000, 136, 6000), (9, 262144, 128, 9000),
-                                              (3, 70001, 48, 8000)])
+@pytest.mark.parametrize("rows,V,d_prime,k", TOGETHER)
 @pytest.mark.parametrize("together", [1, 32, 700])
 def test_neighbours_with_much_in_common(rows, V, d_prime, k, together):
     """Seven tenths of a score's variance is shared by `together` neighbouring tokens: the bracket has the k-th score of every row all
@@ -83,8 +87,7 @@ def test_neighbours_with_much_in_common(rows, V, d_prime, k, together):
     assert ((counts[:, 0] < k) & (k <= counts.sum(1))).all()
 
 
-@pytest.mark.parametrize("rows,V,d_prime,k", [(60, 128256, 256, 4096), (20, 32768, 64, 3000), (3, 70001, 40, 8000), (100, 40000, 256, 1500),
-                                              (150, 20000, 304, 700), (66, 100000, 512, 3000)])
+@pytest.mark.parametrize("rows,V,d_prime,k", OFFSET)
 @pytest.mark.parametrize("offset", [-30.0, 0.0, 30.0, 1000.0])
 def test_scores_with_a_common_offset(rows, V, d_prime, k, offset):
     """All scores of a row lie `offset` standard deviations from zero.  A key says where a score lies among those of its row, so few share
@@ -102,7 +105,7 @@ def test_scores_with_a_common_offset(rows, V, d_prime, k, offset):
     assert (keys == kth).sum(1).max() <= 64            # (what the quick choice among them takes)
 
 
-@pytest.mark.parametrize("V,k", [(20000, 900), (40000, 200), (40000, 9000), (150001, 4000)])
+@pytest.mark.parametrize("V,k", MISLED)
 @pytest.mark.parametrize("best", [True, False])
 def test_samples_that_mislead(V, k, best):
     """The sampled tokens are the best of all, or the worst: the k-th score lies outside of the bracket."""
@@ -143,3 +146,13 @@ def test_hidden_rows_of_any_size():
     rows, V, d_prime, k = 40, 50000, 128, 1500
     h, Wd, Wv = _inputs(rows, V, d_prime, 7)
     _check(h * 2.0 ** np.linspace(-60, 60, rows).astype(int)[:, None], Wd, Wv, k)
+
+
+@pytest.mark.parametrize("rows,V,d_prime", ONE_SUM)
+def test_one_sum_per_score(rows, V, d_prime):
+    """All rows of W_vocab hold the same numbers in different orders and h' is one number d' times, so all scores are equal but for their
+    rounding, which decides what is selected: the same, whether or not the scores go through memory."""
+    rng = np.random.default_rng(rows + V)
+    Wv = _bf16(rng.permuted(np.tile(rng.normal(size=d_prime) + 1.0, (V, 1)), axis=1))
+    h, Wd = _bf16(rng.normal(size=(rows, 64)) + 2.0), _bf16(np.full((d_prime, 64), 1 / 64))
+    _ids_and_records(h, Wd, Wv, V // 20)

@@ -804,7 +804,7 @@ def test_exact_selector_reduces_to_dense_topk():
 
 # ---------------------------------------------------------------- selection for a batch without the score matrix
 BATCH_SELECT_SHAPES = [
-    # rows, d,  d',  V,     k        (bf16, 65 rows or more, d' <= 512, V >= 16384, no scores output: the selection by one-byte codes)
+    # rows, d,  d',  V,     k        (bf16, d' <= 512, V >= 16384, no scores output: the selections by one or two bytes per score)
     (65, 256, 32, 32768, 100),       # a panel of 128 rows, half empty
     (70, 256, 32, 33000, 500),
     (100, 1024, 256, 50001, 4096),   # ragged last run
@@ -815,13 +815,14 @@ BATCH_SELECT_SHAPES = [
     (257, 256, 128, 70001, 70001),   # k = V: everything is selected
     (90, 256, 24, 45000, 44999),     # k = V - 1
     (66, 256, 32, 140000, 8192),     # several rounds of codes per thread
-    (8, 512, 64, 40000, 3000),       # few rows: the path that materialises the scores (a control)
+    (8, 512, 64, 40000, 3000),       # few rows
+    (8, 512, 64, 40000, 6000),       # ... and many ids of them: the path that materialises the scores (a control)
 ]
 
 
 @pytest.mark.parametrize("rows,d,dp,V,k", BATCH_SELECT_SHAPES)
 def test_select_batch_without_score_matrix(rows, d, dp, V, k):
-    """65 or more bf16 rows and no scores output: the selection that never writes s.  Checked against the
+    """bf16 rows and no scores output: the selections that never write s.  Checked against the
     oracle (band rule) and bit for bit against the path that materialises s (asking for the scores selects it;
     both add a score's products in the same order there)."""
     say(f"batch select rows={rows} d={d} d'={dp} V={V} k={k}")
@@ -850,7 +851,10 @@ def _adversarial_selector(rng, V, dp, sign):
     return f32_to_bf16_bits(Wv), sampled
 
 
-@pytest.mark.parametrize("rows,V,k", [(65, 40000, 2000), (70, 65536, 8192), (130, 33001, 33001)])
+USELESS_SAMPLE = [(65, 40000, 2000), (70, 65536, 8192), (130, 33001, 33001)]
+
+
+@pytest.mark.parametrize("rows,V,k", USELESS_SAMPLE)
 def test_select_batch_with_a_useless_sample(rows, V, k):
     """Inputs built to defeat the sample: every sampled token scores 0, every other token scores high, so far
     more than k scores lie above every row's interval, share its top code and are computed again.
