@@ -126,7 +126,7 @@ SelectWs select_ws(int64_t rows, int64_t V, int64_t d_prime, int64_t k, int dt) 
     w.total = w.radix_off + round256(sv::select_scratch_words(rows, V) * sizeof(uint32_t));
     w.bracket_off = w.s_off;
     w.keys = sv::key_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
-    w.codes = !w.keys && sv::code_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
+    w.codes = sv::code_select_supported(dt, (int)(d_prime * esize_of(dt) / 16), rows, V, k);
     size_t t = 0;
     if (w.keys) t = w.bracket_off + sv::key_select_scratch_bytes(rows, V);
     else if (w.codes) t = w.bracket_off + sv::code_select_scratch_bytes(rows, V);         // (less than the scores and their lists take)

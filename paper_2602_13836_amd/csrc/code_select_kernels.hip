@@ -570,16 +570,11 @@ __global__ __launch_bounds__(kThreads, GROUP > 3 ? 4 : 8) void code_resolve_kern
 
 }  // namespace
 
-// From 65 rows on, where two bytes per score are not the shorter way (key_select_kernels.hip).  d' > 256: vocabularies below the
-// bracketed selection's, whose alternative is the scores in memory, from as many rows as fill the chip (us, scores / codes): d' = 512, 32767: 65
-// rows 41.8 / 42.6, 100 rows 53.2 / 49.5; 20000: 128 rows 45.1 / 45.0, 160 rows 56.7 / 51.2; half of 25000 wanted: 128 rows 47.0 / 48.8, 160 rows
-// 56.8 / 53.9.
-inline int64_t min_rows(int chunks, int64_t V, int64_t k) {
-    if (chunks > 32) return V >= 32768 ? 65 : 8 * k > V ? 129 : 2600000 / V + 1 > 65 ? 2600000 / V + 1 : 65;
-    return 65;
-}
+// From 65 rows on (panel_supported), where two bytes per score are not the shorter way and short rows not that of row_select_kernel: both have
+// their lines, with figures, beside key_select_supported and row_select_preferred.
 bool code_select_supported(int dt, int chunks, int64_t rows, int64_t V, int64_t k) {
-    return panel_supported(dt, chunks, rows, V) && rows >= min_rows(chunks, V, k) && V >= kMinVocab && V <= kMaxVocab && !row_select_preferred(chunks, rows, V);
+    return panel_supported(dt, chunks, rows, V) && V >= kMinVocab && V <= kMaxVocab && !key_select_supported(dt, chunks, rows, V, k) &&
+           !row_select_preferred(chunks, rows, V);
 }
 
 // (more than 64 KB of LDS: an opt-in)
