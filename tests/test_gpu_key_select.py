@@ -49,7 +49,7 @@ def test_edges(rows, V, d_prime, k):
 
 def _sampled(V):
     """Ids of the sampled tokens: of every 32 the same two, four or eight."""
-    places = np.array([0, 2, 8, 10] if V <= 49152 else [0, 10] if V <= 98304 else [0])
+    places = np.array([0, 2, 8, 10] if V <= 32768 else [0, 10] if V <= 65536 else [0])
     ids = np.arange(0, V, 32)[:, None] + np.concatenate((places, places + 16))
     return ids[ids < V]
 
