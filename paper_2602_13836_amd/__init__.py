@@ -26,7 +26,7 @@ SV_IDX_PADDED = 4        # OR into idx_mode: the list may hold padding slots (-1
 SV_IDX_SORTED = 8        # OR into idx_mode: every list is sorted by ascending id (what select emits)
 MAX_KD = 64
 SELECT_SAMPLE = 8192     # sampled tokens of a batch's selection, d' > 512: ids floor(j * V / SELECT_SAMPLE)
-SELECT_CODE_SAMPLE = 4096            # ... d' <= 512: floor(j * V / SELECT_CODE_SAMPLE), every second one of those
+SELECT_CODE_SAMPLE = 4096            # ... with one byte per score in memory: floor(j * V / SELECT_CODE_SAMPLE), every second one of those
 
 EXPORTS = (
     "specvocab_version",

@@ -21,7 +21,7 @@
 // The sample has tokens of every unit.  Neighbours that resemble each other, as the scripts, the numbers or the unused ids of a real vocabulary do, are in it
 // as often as they are in the row, and it says more about the row than one of independent tokens.  (A sample of 256 whole units missed where they
 // share half of their variance, in one call out of two of 60 rows x 128256, k = 16384; a missed row took 120 us more.)  Only scores that
-// depend on the token id modulo 32 mislead it: one such row of 60 x 128256 takes 31 us more, of 64 x 262144 80, all rows 36 to 41 and 86.
+// depend on the token id modulo 32 mislead it: one such row of 60 x 128256 takes 27 to 34 us more, of 64 x 262144 57, all rows 36 to 41 and 68.
 //
 // Measured (60 rows x 128256, d' = 256, k = 4096; kernels under a profiler): h' 6.2 us, keys 17.6, bracket 9.2, emit 9.7 to 10.5; the whole
 // selection 44.4 -> 40.8 us (as a case with the caller's part 46.5 -> 44).  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's

@@ -1,6 +1,6 @@
 // Products with a SHORT reduction for many hidden rows (the selector's W_vocab h', Section 3.3 Step 1, for a batch,
 // and Section 3.4's distribution over the whole vocabulary):
-//     s[r, j] = < M[row(j), :], x[r, :] >      r < rows (more than 64; codes also for fewer), rows of M of at most 512 elements, bf16
+//     s[r, j] = < M[row(j), :], x[r, :] >      r < rows (more than 64; keys also for fewer), rows of M of at most 512 elements, bf16
 //
 // What bounds it.  With d' = 256 a 256 x 256 output tile is four 64-element slices of main loop: the tiled kernel spends
 // more time filling its pipeline, and in its epilogue, than multiplying (512 rows x 151936: 45 us of product of which
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
     // never used.  (Through registers, the compiler waited for the last step's stores in front of every write to LDS: it
     // cannot know how many there were.)
     // A run is a whole number of 32 KB of M, the memory channels' period: runs that walked in step would all be at the same
-    // channels, so every run starts its steps at another piece (60 rows x 128256, codes: 17.6 -> 15.6 us).
+    // channels, so every run starts its steps at another piece (60 rows x 128256, a byte per score: 17.6 -> 15.6 us).
     const char* m_base = EPI == EPI_SAMPLE ? a.M : a.M + (int64_t)i0 * a.m_row_bytes;
     const i32x4_t m_buf = buffer_of(m_base);
     const uint32_t m_row_bytes = (uint32_t)a.m_row_bytes;                    // n_items * m_row_bytes < 2^32: panel_supported

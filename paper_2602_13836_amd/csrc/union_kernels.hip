@@ -290,17 +290,18 @@ hipError_t configure_union_lds() {
 // no more than reading the union: the product over all of U whose epilogue stores only the asked entries.  Lists
 // declared ascending need only the table of slices; lists in any order are grouped by tile first, which needs
 // the tile counters of a row in LDS.
-//   The line lies where this form stops losing on any lists.  How much of the vocabulary they cover is not known here: lists of
-// 2 / 3 / 4 V entries cover 0.87 / 0.95 / 0.98 of it where all tokens are equally likely, as the sets of a selector with random
-// weights do (0.85 / 0.93 / 0.97), and 0.42-0.49 / 0.52-0.60 / 0.62-0.65 where they are drawn by Zipf's law.  A whole step, us, by the
-// union / by all of U, 128256 tokens of 8 KB:
-//                  equally likely          random selector         Zipf's law
-//   512 rows  2 V  490 / 453               482 / 448               262 / 458
-//             3 V  489 / 444               478 / 450               325 / 446
-//   200 rows  2 V  253 / 235               250 / 238               153 / 238
-//             3 V  268 / 237               264 / 234               222 / 246
-//   160 rows  2 V  234 / 194 (151936 of 5 KB)                      150 / 191
-// All of U takes the same time whatever the lists are, and next to no workspace (512 rows 1 MB; the union's product 250 MB).
+//   The line lies where this form stops losing on lists that do not overlap more than chance has it.  How much of the vocabulary lists cover is not
+// known here: lists of 2 / 2.5 / 3 V entries cover 0.87 / 0.92 / 0.95 of it where all tokens are equally likely, the sets of a selector with random
+// weights 0.81-0.85 / 0.87-0.91 / 0.91-0.94, lists drawn by Zipf's law 0.41-0.48 / 0.47-0.56 / 0.53-0.62.  A whole step, us, by the union / by all of U:
+//                                equally likely                     random selector                    Zipf's law
+//                                2 V       2.5 V     3 V            2 V       2.5 V     3 V            2 V       2.5 V     3 V
+//   512 rows x 128256 of 8 KB    464 / 457 480 / 457 496 / 455      450 / 448 467 / 450 481 / 452      235 / 451 257 / 453 331 / 454
+//   300 rows x 128256            394 / 402 412 / 402 422 / 402      365 / 396 403 / 393 410 / 397      211 / 398 229 / 397 273 / 398
+//   512 rows x 151936 of 5 KB    386 / 359 404 / 363 417 / 363      336 / 356 392 / 357 404 / 358      178 / 361 233 / 357 240 / 359
+//   200 rows x 128256            247 / 237 261 / 236                241 / 233 254 / 235                142 / 234 211 / 238
+//   160 rows x 151936            235 / 191 240 / 191                192 / 192 239 / 191                149 / 192 160 / 193
+// All of U takes the same time whatever the lists are, and next to no workspace (512 rows 1 MB; the union's product 250 MB); sets that overlap
+// as much as the last columns' pay for that.
 static int64_t pick_tiles(int64_t V) { return (V + kKeepTileItems - 1) / kKeepTileItems; }
 bool pick_path_wanted(int dt, const GemvArgs& a, int64_t V, bool sorted) {
     return dt == DT_BF16 && a.rows > 64 && a.idx != nullptr && a.idx_row_stride != 0 && a.out_bf16 == nullptr &&
