@@ -585,6 +585,7 @@ hipError_t launch_key_select(const CodeSelectArgs& a, hipStream_t stream) {
     p.samples = reinterpret_cast<uint32_t*>(a.scratch + L.sample);
     p.sample_stride = panel_key_sample_bytes(a.chunks, a.rows, a.V, L.sample_words);
     p.sample_words = L.sample_words;
+    p.upper_wanted = 8 * a.k <= 3 * a.V;
     if (p.sample_stride > kSampleLoads * kThreads * 16 || p.sample_stride > 8 * a.V) return hipErrorInvalidValue;     // (never)
     hipError_t e = launch_panel_keys(p, stream);
     if (e != hipSuccess) return e;

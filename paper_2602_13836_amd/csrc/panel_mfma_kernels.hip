@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             map_scale[m] = __uint_as_float((254u - e) << 23);
             sample_at[m] = (uint32_t)row * (uint32_t)a.sample_stride + (uint32_t)((run * GI + gi) * a.sample_groups) * 16u;
         }
-        // The middle of a row's scores: about the median of those of 32 (16) tokens from all of M, the same in every workgroup.  Without it
+        // The middle of a row's scores: near the median of those of 32 (16) tokens from all of M, the same in every workgroup.  Without it
         // half precision keeps of scores with a common offset what the offset leaves: at 20 standard deviations 60 to 180 of 128256
         // tokens have the k-th one's key (k = 4096), at some hundreds thousands (60 rows, d' = 256, the whole selection: 49 us at 10
         // standard deviations, 56 at 20, 190 at 100, for the 41 of none).
@@ -270,23 +270,15 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
                 mid = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(s_mid + (((2 * kk + half) ^ (lane & 15)) * 16))),
                     fx[m][kk], mid, 0, 0, 0);
-            // Five medians of three of the lane's 16 tokens (or of its 8, twice), as many of lane + 32's, and the fifth smallest of the ten: a
-            // score that is there, and not a mean of two groups of tokens that have little in common
-            float t[5];
+            // Of nine of the lane's tokens the median of three medians, or of three maxima where the upper tokens are wanted, and the smaller of this
+            // and lane + 32's: a score that is there, and not a mean of two groups of tokens that have little in common
+            float t[3];
 #pragma unroll
-            for (int i = 0; i < 5; ++i) t[i] = __builtin_amdgcn_fmed3f(mid[3 * i], mid[3 * i + 1], mid[3 * i + 2]);
-            auto order = [&](int i, int j) {
-                const float x = t[i];
-                t[i] = fminf(x, t[j]);
-                t[j] = fmaxf(x, t[j]);
-            };
-            order(0, 1), order(3, 4), order(2, 4), order(2, 3), order(1, 4), order(0, 3), order(0, 2), order(1, 3), order(1, 2);
-            float middle = INFINITY;
-#pragma unroll
-            for (int i = 0; i <= 5; ++i) {               // i from here and 5 - i from there
-                const float there = i < 5 ? __shfl_xor(t[4 - i], 32) : -INFINITY;
-                middle = fminf(middle, i > 0 ? fmaxf(t[i - 1], there) : there);
-            }
+            for (int i = 0; i < 3; ++i)
+                t[i] = a.upper_wanted ? fmaxf(fmaxf(mid[3 * i], mid[3 * i + 1]), mid[3 * i + 2])
+                                      : __builtin_amdgcn_fmed3f(mid[3 * i], mid[3 * i + 1], mid[3 * i + 2]);
+            t[0] = __builtin_amdgcn_fmed3f(t[0], t[1], t[2]);
+            const float middle = fminf(t[0], __shfl_xor(t[0], 32));
             const float bias = 0.0f - middle * map_scale[m];
             map_bias[m] = fabsf(bias) <= 1e30f ? bias : 0.0f;                 // (infinite scores, and those that are no number)
         }

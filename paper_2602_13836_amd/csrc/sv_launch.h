@@ -171,6 +171,7 @@ struct PanelArgs {
     int64_t sample_stride;
     int sample_words;
     int sample_groups;       // (set by launch_panel_keys)
+    bool upper_wanted;       // keys are finest about a score a little above the row's median, else about the median
 };
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items);
 hipError_t launch_panel_sample(const PanelArgs& a, hipStream_t stream);
