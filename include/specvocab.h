@@ -144,9 +144,9 @@ int specvocab_workspace_bytes(int op, int64_t rows, int64_t d, int64_t V, int64_
  *   V / 8 (up to 4 rows and V > 196608: V / 16); 128 < d_prime <= 256, 65 to 128 rows, rows * ceil(V / 32768) <= 256; d_prime > 256, 65 to 128 rows, up to 16.8 million
  *   scores, to 256 rows up to 10 million.  A sample of the scores brackets each row's k-th: of every 32 tokens those whose id modulo 32 is 0 or 16, V <= 65536 also 10
  *   or 26, V <= 32768 also 2, 8, 18 or 24.  Likeness of neighbouring tokens does not mislead it, and chance one row in hundreds of millions; scores that
- *   depend on the id modulo 32 do.  Such a row takes up to 11 us more at 40000 tokens, 34 at 128256, 57 at 262144 (all rows of 64: 68), and the call as long as its
- *   slowest row.  The two bytes hold a score's distance from about the row's median in 11 bits, and the tokens that share the k-th one's (a dozen) are computed again:
- *   more of them where a row's scores lie in groups far apart against their width (groups 200 standard deviations apart: 30 to 100 us more).
+ *   depend on the id modulo 32 do.  Such a row takes up to 20 us more at 40000 tokens, 37 at 128256, 57 at 262144 (all rows of 64: 66), and the call as long as its
+ *   slowest row.  The two bytes hold a score's distance from a score near the row's median in 11 bits, and the tokens that share the k-th one's (a dozen) are computed again:
+ *   more of them where a row's scores lie in groups far apart against their width and the k-th in the one that the median is not in (200 standard deviations apart: 30 to 100 us more).
  *   One byte per score: every other shape of 65 rows and more.  The scores of 4096 evenly spaced tokens (ids floor(j V / 4096)) decide how a row's
  *   scores map to bytes, and those that share the k-th one's are computed again.  Where the sample misleads (about 1e-5 of rows on scores that do not
  *   depend on the token id modulo the sampling stride; certain for inputs built so that the sampled tokens score unlike all others) a row takes tens of

@@ -1,7 +1,7 @@
 // Candidate-vocabulary selection (Section 3.3, Steps 1 and 2) for the rows of a tree, without the score matrix: the scores leave
 // the product as TWO BYTES each, and four launches do it all (the down-projection's among them).
 //   keys      the product on the matrix cores, whose epilogue stores the half precision (rounded towards zero) of every score's distance
-//             from about the row's median, after a power of two per hidden row that brings its largest element to [1, 2), as an
+//             from a score near the row's median, after a power of two per hidden row that brings its largest element to [1, 2), as an
 //             unsigned number that orders like the scores, and some keys of every unit of 32 tokens once more on their own, as a sample
 //             (panel_mfma_kernels.hip);
 //   bracket   keys of every 32 tokens say where the row's k-th lies, give or take; one pass turns the keys above that into bits and lists
@@ -21,10 +21,10 @@
 // The sample has tokens of every unit.  Neighbours that resemble each other, as the scripts, the numbers or the unused ids of a real vocabulary do, are in it
 // as often as they are in the row, and it says more about the row than one of independent tokens.  (A sample of 256 whole units missed where they
 // share half of their variance, in one call out of two of 60 rows x 128256, k = 16384; a missed row took 120 us more.)  Only scores that
-// depend on the token id modulo 32 mislead it: one such row of 60 x 128256 takes 27 to 34 us more, of 64 x 262144 57, all rows 36 to 41 and 68.
+// depend on the token id modulo 32 mislead it: one such row of 60 x 128256 takes 28 to 34 us more, of 64 x 262144 57, all rows 34 to 45 and 66.
 //
 // Measured (60 rows x 128256, d' = 256, k = 4096; kernels under a profiler): h' 6.2 us, keys 17.6, bracket 9.2, emit 9.7 to 10.5; the whole
-// selection 44.4 -> 40.8 us (as a case with the caller's part 46.5 -> 44).  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's
+// selection 44.5 -> 40.3 us (as a case with the caller's part 46.5 -> 43.5).  The form it replaces (one byte per score: code_select_kernels.hip) had a sample's
 // product and a map in front of the codes (6 and 4 us, each mostly a launch) and read the codes with one workgroup per row (17).  Two thirds of
 // bracket and emit are their start and six round trips to memory.  Not used: this pass by one workgroup per row, 22.7 us
 // (9.5 of them for the keys); a sample gathered from the keys, 16 bytes per thread from lines of their own (as many bytes as the part: bracket
