@@ -137,23 +137,30 @@ int specvocab_workspace_bytes(int op, int64_t rows, int64_t d, int64_t V, int64_
  * h: device [rows x d], row stride ldh.  idx_out: device [rows x k] int32.
  * scores_out: device [rows x k] float32 receiving s[r, idx_out[r, j]], or NULL.
  * Requires 1 <= k <= V, 1 <= d_prime, rows >= 1; V above 4194304 is SV_ERR_UNSUPPORTED.
- * Cost.  Rows of up to 16384 tokens: s lies in the workspace, and one launch selects from it (of exactly 16384, only up to 64 rows, up to 256 with
- * d_prime > 256).  With bf16, scores_out == NULL, no threshold, d_prime <= 512 and 16384 <= V <= 393216, a call of more than a handful of hidden rows keeps
- * less than s in memory; the result is the same exact top-k.
- *   Two bytes per score: d_prime <= 256 and 9 to 64 rows (d_prime > 128 and less than 24 rows: k <= V / 4, V > 98304: V / 8); d_prime <= 128, 2 to 8 rows, k <=
- *   V / 8 (up to 4 rows and V > 196608: V / 16); 128 < d_prime <= 256, 65 to 128 rows, rows * ceil(V / 32768) <= 256; d_prime > 256, 65 to 128 rows, up to 16.8 million
- *   scores, to 256 rows up to 10 million.  A sample of the scores brackets each row's k-th: of every 32 tokens those whose id modulo 32 is 0 or 16, V <= 65536 also 10
- *   or 26, V <= 32768 also 2, 8, 18 or 24.  Likeness of neighbouring tokens does not mislead it, and chance one row in hundreds of millions; scores that
- *   depend on the id modulo 32 do.  Such a row takes up to 20 us more at 40000 tokens, 37 at 128256, 57 at 262144 (all rows of 64: 66), and the call as long as its
- *   slowest row.  The two bytes hold a score's distance from a score near the row's median in 11 bits, and the tokens that share the k-th one's (a dozen) are computed again:
- *   more of them where a row's scores lie in groups far apart against their width and the k-th in the one that the median is not in (200 standard deviations apart: 30 to 100 us more).
- *   One byte per score: every other shape of 65 rows and more.  The scores of 4096 evenly spaced tokens (ids floor(j V / 4096)) decide how a row's
- *   scores map to bytes, and those that share the k-th one's are computed again.  Where the sample misleads (about 1e-5 of rows on scores that do not
- *   depend on the token id modulo the sampling stride; certain for inputs built so that the sampled tokens score unlike all others) a row takes tens of
- *   microseconds more, up to a few milliseconds.
- * From 65 hidden rows and 32768 tokens on wider selectors keep only the few per cent of scores inside a bracket from 8192 sampled tokens (ids floor(j V /
- * 8192)); a row whose bracket misses is recomputed by a slow exact path, about a millisecond per such row.  Every other shape, every call with scores_out and
- * every threshold materialises s in the workspace, which is the same size either way: 12 bytes per score and some kilobytes per row. */
+ * Cost.  Rows of up to 16384 tokens: s lies in the workspace, and one launch selects from it (bf16, exactly 16384:
+ * up to 64 rows, up to 256 with d_prime > 256).  With bf16, scores_out == NULL, no threshold, d_prime <= 512 and
+ * 16384 <= V <= 393216, a call of more than a handful of hidden rows keeps less than s in memory; the result is the
+ * same exact top-k.
+ *   Two bytes per score: d_prime <= 256 and 9 to 64 rows (d_prime > 128 and less than 24 rows: k <= V / 4, V > 98304:
+ *   V / 8); d_prime <= 128, 2 to 8 rows, k <= V / 8 (up to 4 rows and V > 196608: V / 16); 128 < d_prime <= 256, 65
+ *   to 128 rows, rows * ceil(V / 32768) <= 256; d_prime > 256, 65 to 128 rows, up to 16.8 million scores, to 256 rows
+ *   up to 10 million.  A sample of the scores brackets each row's k-th: of every 32 tokens those whose id modulo 32
+ *   is 0 or 16, V <= 65536 also 10 or 26, V <= 32768 also 2, 8, 18 or 24.  Likeness of neighbouring tokens does not
+ *   mislead it, and chance one row in hundreds of millions; scores that depend on the id modulo 32 do.  Such a row
+ *   takes up to 20 us more at 40000 tokens, 37 at 128256, 57 at 262144 (all rows of 64: 66), and the call as long as
+ *   its slowest row.  The two bytes hold a score's distance from a score near the row's median in 11 bits, and the
+ *   tokens that share the k-th one's (a dozen) are computed again: more of them where a row's scores lie in groups
+ *   far apart against their width and the k-th in the one that the median is not in (200 standard deviations apart:
+ *   30 to 100 us more).
+ *   One byte per score: every other shape of 65 rows and more.  The scores of 4096 evenly spaced tokens (ids floor(j
+ *   V / 4096)) decide how a row's scores map to bytes, and those that share the k-th one's are computed again.  Where
+ *   the sample misleads (about 1e-5 of rows on scores that do not depend on the token id modulo the sampling stride;
+ *   certain for inputs built so that the sampled tokens score unlike all others) a row takes tens of microseconds
+ *   more, up to a few milliseconds.
+ * From 65 hidden rows and 32768 tokens on wider selectors keep only the few per cent of scores inside a bracket from
+ * 8192 sampled tokens (ids floor(j V / 8192)); a row whose bracket misses is recomputed by a slow exact path, about a
+ * millisecond per such row.  Every other shape, every call with scores_out and every threshold materialises s in the
+ * workspace, which is the same size either way: 12 bytes per score and some kilobytes per row. */
 int specvocab_select(const void* h, int64_t rows, int64_t d, int64_t ldh,
                      const void* W_down, int64_t d_prime,
                      const void* W_vocab, int64_t V,

@@ -158,7 +158,8 @@ __global__ __launch_bounds__(kThreads) void panel_mfma_kernel(const PanelArgs a)
             const int r = piece * (64 / kUnits) + lane / kUnits;
             const uint32_t u = (uint32_t)((lane % kUnits) ^ (r & 15));
             // (spread over what lies between, so that they are not all multiples of something)
-            const uint32_t row = min((uint32_t)(2 * r + 1) * (uint32_t)n_items / (uint32_t)(2 * middle_tokens<KS>()) + (uint32_t)(11 * r % 32), (uint32_t)n_items - 1u);
+            const uint32_t row = min((uint32_t)(2 * r + 1) * (uint32_t)n_items / (uint32_t)(2 * middle_tokens<KS>()) + (uint32_t)(11 * r % 32),
+                                     (uint32_t)n_items - 1u);
             memory_to_lds((int)u < C ? row * m_row_bytes + u * 16u : kOutside, whole, 0u, lds0 + (uint32_t)middle_at<KS, GM, EPI>() + (uint32_t)(piece * 1024));
         }
     };
@@ -662,7 +663,8 @@ hipError_t configure_panel_lds() {
 }
 
 bool panel_keys_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
-    return dt == DT_BF16 && rows >= 1 && rows <= 256 && chunks > (rows <= 64 ? 0 : rows <= 128 ? 16 : 32) && chunks <= (rows <= 64 ? 32 : 64) && n_items < ((int64_t)1 << 22);
+    return dt == DT_BF16 && rows >= 1 && rows <= 256 && chunks > (rows <= 64 ? 0 : rows <= 128 ? 16 : 32) && chunks <= (rows <= 64 ? 32 : 64) &&
+           n_items < ((int64_t)1 << 22);
 }
 bool panel_supported(int dt, int chunks, int64_t rows, int64_t n_items) {
     return dt == DT_BF16 && rows > 64 && chunks >= 1 && chunks <= 64 && n_items < ((int64_t)1 << 22);

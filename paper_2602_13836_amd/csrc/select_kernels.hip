@@ -371,7 +371,8 @@ hipError_t launch_scores_dt(const ScoresArgs& a, uint32_t* scratch, int cus, hip
 // equal to it and among the first of those -- and where it goes.
 // What bounds it is the chain of barriers and the LDS atomics of the histogram, not the row: 8192 scores 6.8 us where collect and
 // emit take 5.7 and 5.3 (and up to three launches more from two rows on); the selection of one float32 row of d = 256 over 8192 tokens 19.8
-// -> 15.0 us, and 11.8 with h' made by the scores' launch (16384 tokens 21.3 -> 16.4 -> 14.9), 40 bf16 rows, d' = 256, over 10000 tokens 30.8 -> 21.3, 256 rows over 16384 35 -> 33.
+// -> 15.0 us, and 11.8 with h' made by the scores' launch (16384 tokens 21.3 -> 16.4 -> 14.9), 40 bf16 rows, d' = 256, over 10000 tokens
+// 30.8 -> 21.3, 256 rows over 16384 35 -> 33.
 // Not used: eight groups of 4096 (30000 scores: 21.6 us, the registers spill).
 constexpr int kRowFew = 256;
 template <int J>
